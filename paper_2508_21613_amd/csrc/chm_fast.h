@@ -1,29 +1,38 @@
 // Shape-specialised search kernels (chm_fast.hip): interface to the host part.
 #ifndef CHM_FAST_H
 #define CHM_FAST_H
+#include <hip/hip_runtime.h>
+
 #include "chm_dev.h"
 #include "chm_pool.h"
 #include <vector>
 
 enum {
-  FAST_MAX_P = 8,            // peers per affected stage the specialised sweeps are instantiated for
-  FAST_FUSED_R = 4096,       // up to this many reroute vectors (all stages) the sweep runs inside the search kernel
-  FAST_SPLIT_R = 1 << 23,    // up to this many per stage the vectors are tabulated and swept by a kernel of their own
-  FAST_SUB = 1 << 20,        // partitions per pass of the split and scoring paths (bounds their scratch memory: 152 MB;
+  BLOCK = 256,               // workgroup of the search kernels
+  FAST_MAX_P = 15,           // peers a stage that lost nodes can have (DEV_MAX_D - 1)
+  ROWS_MAX_P = 8,            // peers and
+  ROWS_MAX_R = 1 << 23,      // reroute vectors per stage up to which the vectors are tabulated for the cost store of plan indices
+  FAST_FUSED_R = 4096,       // more vectors than this (all stages): a large reroute space (see FastState::large_reroute)
+  FAST_SUB = 1 << 20,        // partitions per pass of the cost store of plan indices (bounds its scratch memory: 136 MB;
                              // the scratch is sized for the passes actually asked for and grows when needed)
   LIST_SUB = 1 << 24,        // list entries per filter + search pass of explicit lists (scratch: 336 MB when a list is that long)
-  LIST_FIRST = 1 << 16       // entries of the first pass of a bounded list search
+  LIST_FIRST = 1 << 16,      // entries of the first pass of a bounded list search
+  FILTER_TILES = 16,         // tiles of BLOCK list entries per workgroup = rounds of the search kernel per region
+  FILTER_TILES_BOUNDED = 4   // a bounded search keeps few entries: shorter regions, more workgroups to filter with
 };
 
 // One pipeline class in the form the specialised kernels read (all int32).
 struct FastClass {
   int32_t n, M;
-  int32_t dead0, dead1;           // partition stages missing from the chain (>= stages: none)
+  uint32_t dead;                  // bit s: partition stage s has no node in this chain (strategy 0)
   int32_t unit;                   // 1: every node of the chain runs at nominal speed (no scaling)
   uint32_t q_min;                 // smallest speed factor along the chain (lower bound of the step time)
   int32_t lb_slack;               // what rounding can take from that bound when q_min scales it (0 at nominal speed)
   int32_t comm_total;             // (n-1) * comm
-  uint32_t q[DEV_MAX_S];
+  // per partition stage: speed factor of its node, nodes of the chain behind it, and micro-batches - nodes + position
+  // (see pipeline_time; a stage without a node: factor 65536 and -1)
+  uint32_t q_stage[DEV_MAX_S];
+  int32_t after[DEV_MAX_S], steady[DEV_MAX_S];
   int32_t wlo[DEV_MAX_S], whi[DEV_MAX_S];   // memory prefix at the bounds of the fault-free stage of node j
 };
 
@@ -38,6 +47,7 @@ struct FastFamily {
   int32_t allreduce;              // time of one round of gradient communication (0: not modelled)
   int32_t fixed_layers;           // strategy 1: layers of the largest stage on a node of an untouched pipeline, else 0
   uint32_t node_exists;           // strategy 0: bit s = some pipeline still has its node of stage s
+  int32_t time24;                 // 1: (doubled, scaled) stage times and their sums stay below 2^24
   int32_t lb_prefix;              // 1: the sharper lower bound (24-bit multiplies are safe for these times)
   FastClass cls[DEV_MAX_CLS];
 };
@@ -48,20 +58,8 @@ struct FastTables {
   // 4 (up to 4 peers) or 8 dwords, and the row count is padded to a multiple of 4
   uint32_t vec_off[DEV_MAX_AFF];  // offset (in uint32) of stage a's rows in vecs[]
   uint32_t vec_rows[DEV_MAX_AFF]; // rows including the padding
-  // the same vectors as runs: all vectors that share their first P-2 entries are consecutive in
-  // rank order, the entry before last counts up from `lo` and the last one down.  A run is 8
-  // dwords: [0..5] the shared entries, [6] = lo | (sum of the last two entries << 16), [7] = length
-  uint32_t run_off[DEV_MAX_AFF];  // offset (in uint32) of stage a's runs in runs[]
-  uint32_t run_count[DEV_MAX_AFF];
-  // and as groups (three or more peers, at most 8 or 16 micro-batches per peer: see k_sweep_groups): all vectors that
-  // share their first P-3 entries.  A group is 8 dwords: [0..4] the shared entries, [5] = first value of the entry
-  // before the last two, [6] = how many consecutive values it takes, [7] = what the last three entries add up to
-  uint32_t grp_off[DEV_MAX_AFF];  // offset (in uint32) of stage a's groups in runs[]
-  uint32_t grp_count[DEV_MAX_AFF];
-  uint32_t grp_cap[DEV_MAX_AFF];  // 0: stage a has no group table; else the entry limit (8 or 16) its sweep is compiled for
-  // small uncapped reroute spaces have a sweep unrolled at compile time (see sweep_products):
-  // peers * 256 + orphaned micro-batches when such a sweep exists for stage a, else 0
-  uint32_t unrolled_shape[DEV_MAX_AFF];
+  // peers of stage a all of one speed: the extra micro-batches of the fullest peer when they share evenly; else 0
+  uint32_t even_share[DEV_MAX_AFF];
   // lower bound of stage a's reroute penalty: some peer takes at least lb_mult[a] = ceil(orphans / peers)
   // micro-batches (0 when a cap below that leaves this unclear), each at a stage time scaled by at least lb_q[a]
   uint32_t lb_mult[DEV_MAX_AFF], lb_q[DEV_MAX_AFF];
@@ -69,11 +67,11 @@ struct FastTables {
 
 struct FastState {
   bool usable[3] = {false, false, false};   // per strategy: a specialised kernel covers this scenario
-  bool split = false;                       // rerouting: vectors swept by k_sweep instead of inside the search kernel
-  bool mul24_reroute = false;               // peer stage times stay below 2^24: the reroute sweeps may use 24-bit multiplies
-  // bounded search on the split path: the least penalty of a stage is found from the peers' capacities
-  // (k_least_penalty) instead of sweeping every reroute vector; set by the caller per search
-  bool penalty_by_capacity = false;
+  // rerouting: at most 8 peers and 2^23 vectors per stage, and more than FAST_FUSED_R vectors over all stages.
+  // (chm_search_best_static does not take such a family, see chm.h.)
+  bool large_reroute = false;
+  bool rows_ok = false;                     // the vectors of every stage can be tabulated (cost store of plan indices)
+  bool mul24_reroute = false;               // peer stage times stay below 2^24: what least_penalty needs
   // Range search of strategies 0 and 1: share of the partitions that pass the memory filter, estimated at load
   // from FIT_SAMPLES seeded random partitions; below QUEUE_BELOW_SHARE the search compacts the partitions that
   // fit through a ring per wave (k_fast_search, QUEUED).  queue_mode: -1 = by that estimate, 0 = never, 1 = always.
@@ -89,19 +87,13 @@ struct FastState {
   FastTables h_tables;
   FastTables *d_tables = nullptr;
   uint32_t *d_vecs = nullptr;
-  uint32_t *d_runs = nullptr;
-  // scratch of the split and scoring paths, FAST_SUB partitions at a time; allocated when first needed
+  // scratch of the cost store of plan indices, FAST_SUB partitions at a time; allocated when first needed
   uint64_t *d_base = nullptr;               // cost without penalties, ~0 for a partition that does not fit
   uint32_t *d_weights = nullptr;            // [partition][affected stage][8] peer stage times
-  uint32_t *d_pen = nullptr;                // [partition][4] best penalty per affected stage
-  uint64_t *d_rowkey = nullptr;             // [4] (penalty << 32 | row) of the winning partition
-  uint32_t *d_fit_list = nullptr;           // [partition] the partitions of the pass that fit in memory, in no particular order
-  uint32_t *d_fit_count = nullptr;          // how many of them
-  uint32_t scratch_parts = 0;               // partitions d_base, d_weights, d_pen and d_fit_list have room for
-  // The run and vector tables of a rerouting family whose vectors are swept by kernels of their own (split) are
-  // large (tens of MB, milliseconds to enumerate) and a bounded search never reads them: they are built when an
-  // exhaustive search, a cost store or the recovery of a winner's vectors first asks for them.
-  bool reroute_tables_ready = false;
+  uint64_t *d_unread = nullptr;             // 16 words the base pass reports to, not read
+  uint32_t scratch_parts = 0;               // partitions d_base and d_weights have room for
+  // The rank-ordered vector table only serves the cost store of plan indices (up to 76 MB where the vectors are many)
+  // and is decoded when one first asks for it.
   bool vecs_ready = false;                  // the rank-ordered vector table (d_vecs) has been decoded
   size_t vec_words = 0;                     // size of the vector table
   const DevScenario *d_scn = nullptr;       // the handle's device tables (for that later build)
@@ -123,6 +115,42 @@ struct FastState {
   uint8_t *h_cand_stage = nullptr;          // pinned staging of the two tables on their way to the device
   size_t cand_stage_capacity = 0;
   void *cand_copied = nullptr;              // hipEvent_t: the last copy out of the staging buffer is done
+};
+
+struct FastLaunch {
+  SearchLaunch s;
+  const FastTables *tab;
+  uint32_t per_lane;            // consecutive partition ranks per lane
+  // cost store of rerouting plan indices: the kernel leaves the penalties out and stores, per partition, the cost
+  // without them and the peer stage times (null: otherwise)
+  uint64_t *base_out;
+  uint32_t *weights_out;
+  // compacted list mode: workgroup b owns slots [b * per_lane * BLOCK, ...) of cut_list / cut_pos, of which the
+  // first cut_count[b] are filled (by k_list_filter, with the list entries that fit in memory).  In round `it`
+  // lane t evaluates slot it * BLOCK + t: the partition whose cut positions are the bytes of cut_list[slot],
+  // reported under list position cut_pos[slot].  Every lane of every wave has work except in a workgroup's
+  // last round (null: other modes)
+  const uint4 *cut_list;
+  const uint32_t *cut_pos;
+  const uint32_t *cut_count;
+};
+
+struct ListFilter {
+  const DevScenario *scn;
+  const FastTables *tab;
+  const uint64_t *ranks;        // list entries of this pass, as partition ranks, or (ranks null)
+  const uint8_t *cuts;          // as rows of stages - 1 cut positions
+  uint32_t n;                   // entries in this pass
+  uint32_t pos_base;            // list position (chunk-local) of entry 0 of this pass
+  int64_t *costs_out;           // chunk-local cost array (nullable)
+  int32_t tiles;                // tiles of BLOCK entries per workgroup
+  uint4 *cut_list;              // [workgroup][tiles * BLOCK]
+  uint32_t *cut_pos;            // likewise
+  uint32_t *cut_count;          // [workgroup] filled slots
+  // bounded search (no cost store): entries whose lower bound of the cost lies above *incumbent (the lowest cost
+  // the passes before this one have evaluated) are dropped like those that do not fit; null = keep all that fit
+  const uint64_t *incumbent;
+  uint64_t incumbent0;          // a cost known before the call (see SearchLaunch::incumbent0)
 };
 
 // Bounded search, candidate path.  Every term of the lower bound of a plan's cost belongs to one stage
@@ -149,7 +177,7 @@ enum {
 };
 
 // Counts the candidates of a strategy against an incumbent cost (host).  Returns false when the strategy has no
-// specialised kernel, is swept by the split rerouting path, or the tables are out of the candidate path's limits.
+// specialised kernel or the tables are out of the candidate path's limits.
 bool fast_candidates_build(const FastState *f, const DevScenario &h, int strategy, uint64_t incumbent, CandidateSet *out);
 // Enumerates the candidates on the device and runs the search kernel over them; the key written to a.result
 // carries the candidate's index.  Same return convention as fast_search.
@@ -169,9 +197,16 @@ int fast_prepare(FastState *f, const DevScenario &h, bool int32_ok, const DevSce
 // value when the strategy is not covered (the caller then uses the generic kernel), or a
 // negative value on a HIP error.
 int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void *stream);
-// Whether fast_search would run this launch as a bounded search if a.incumbent were set (a range search of a
-// covered strategy without cost store whose reroute vectors, if any, are swept inside the search kernel).
-bool fast_can_bound(const FastState *f, const SearchLaunch &a);
+// Whether fast_search would run this launch as a bounded search if a.incumbent were set (a search of a covered
+// strategy of at most 16 stages without cost store).
+bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch &a);
+// Kernel launchers by strategy (chm_search_s0/1/2.hip): 1 = no instance for this number of stages, else 0.
+int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
+int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
+int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
+int chmk_list_filter_s0(int sp, const ListFilter &a, uint32_t blocks, void *stream);
+int chmk_list_filter_s1(int sp, const ListFilter &a, uint32_t blocks, void *stream);
+int chmk_list_filter_s2(int sp, const ListFilter &a, uint32_t blocks, void *stream);
 // Sampled share of partitions of a strategy that pass the memory filter (1.0 where no sample applies).
 float fast_fit_share(FastState *f, const DevScenario &h, int strategy);
 // Scores plan indices [local_first, local_first+count) of the rerouting family (indices local to

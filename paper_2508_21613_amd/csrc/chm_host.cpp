@@ -663,7 +663,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
         if (fast_candidates_search(&s->fast, s->h, a, *j.cand, j.stride, st)) return CHM_ERR_HIP;
         continue;
       }
-      if (bounded && fast_can_bound(&s->fast, a)) {
+      if (bounded && fast_can_bound(&s->fast, s->h, a)) {
         a.incumbent = d_incumbent;
         a.evaluated = j.seed ? d_seed_count : d_evaluated + (size_t)j.strategy * c.chunk_words;
         c.bounded_used[j.strategy] = !(j.ranks || j.cuts);   // lists: what passes their filter is evaluated and counted as fitting
@@ -689,7 +689,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
     memset(&f, 0, sizeof(f));
     f.scn = s->d_scn; f.slots = d_keys; f.counters = d_count;
     f.n_slots = (uint32_t)c.slots.size(); f.ways = c.ways; f.stride = c.stride; f.idx_bits = s->idx_bits;
-    f.sweep_winner = light ? 0 : ((s->fast.split && s->fast.usable[2]) ? 2 : 1);
+    f.reroute_winner = light ? 0 : 1;
     f.comp = s->d_comp;
     for (size_t i = 0; i < FINISH_MAX_SLOTS; ++i) f.jump_at[i] = 0xffffffffu;
     f.cand_slot = cand_jobs == 1 ? cand_slot : -1;
@@ -817,8 +817,7 @@ int collect_jobs(chm_scenario *s, chm_best *out, uint64_t *position, hipStream_t
   // synchronisation; its step time follows from cost = horizon x step + transition
   const bool rerouted = best_strategy == 2 && s->h.n_aff > 0;
   if (rerouted) {
-    const int32_t by_capacity = (s->fast.split && s->fast.usable[2]) ? 1 : 0;     // too many vectors for a one-lane sweep
-    if (chmk_reroute_winner(s->d_scn, s->d_comp, best_part, by_capacity, s->d_winner, s->smax, st)) return CHM_ERR_HIP;
+    if (chmk_reroute_winner(s->d_scn, s->d_comp, best_part, s->d_winner, s->smax, st)) return CHM_ERR_HIP;
     HIP_TRY(hipMemcpyAsync(s->h_pinned, s->d_winner, DEV_MAX_AFF * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
   }
   if (chmk_plan_transition(s->d_scn, best_strategy, best_part, (int64_t *)s->d_xfer, s->smax, st)) return CHM_ERR_HIP;
@@ -892,7 +891,6 @@ bool any_enumerable(const chm_scenario *s, const std::vector<Job> &given) {
 }
 
 int run_search(chm_scenario *s, const std::vector<Job> &given, chm_best *out, uint64_t *position, hipStream_t st) {
-  s->fast.penalty_by_capacity = s->bounded && out != nullptr;
   if (!(s->bounded && out != nullptr)) return run_jobs(s, given, out, position, st, ~0ull, false);
   const uint64_t enumerate_from = s->bounded == 2 ? 1 : ENUMERATE_FROM;
   const std::vector<Job> seeds = make_seeds(s, given);
@@ -1081,7 +1079,7 @@ extern "C" int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection
       out->sharp_bound[k] = s->fast.usable[k] ? s->fast.h_tables.fam[k].lb_prefix : 0;
     }
     out->reroute_mul24 = s->fast.mul24_reroute ? 1 : 0;
-    out->reroute_swept_apart = s->fast.split ? 1 : 0;
+    out->reroute_swept_apart = s->fast.large_reroute ? 1 : 0;
   }
   delete s;
   return rc;
@@ -1235,7 +1233,6 @@ extern "C" int chm_search_best_batch(chm_scenario *const *handles, int32_t n, ui
     // searches that need the host between two of their passes (a bounded search that enumerates candidates) run
     // on their own; all others are launched now and collected after one wait for the whole batch
     if (s->bounded && any_enumerable(s, jobs)) { codes[i] = run_search(s, jobs, &outs[i], nullptr, stream_of(i)); continue; }
-    s->fast.penalty_by_capacity = s->bounded != 0;
     if (s->bounded) {
       std::vector<Job> all = make_seeds(s, jobs);
       all.insert(all.end(), jobs.begin(), jobs.end());
@@ -1292,8 +1289,8 @@ extern "C" int chm_search_best_static(chm_scenario *s, uint32_t strategy_mask, c
   for (int i = 0; i < s->space.n_families; ++i) {
     const chm_family &f = s->space.fam[i];
     if (!(strategy_mask & (1u << f.strategy))) continue;
-    // reroute spaces that are swept by kernels of their own need per-partition scratch (tens of MB)
-    if (f.strategy == 2 && s->fast.usable[2] && s->fast.split) { nothing_found(out); return CHM_ERR_LIMIT; }
+    // large reroute spaces are not taken here (chm.h)
+    if (f.strategy == 2 && s->fast.usable[2] && s->fast.large_reroute) { nothing_found(out); return CHM_ERR_LIMIT; }
     jobs.push_back({f.strategy, 0, f.n_part, nullptr, nullptr});
   }
   if (jobs.empty()) { nothing_found(out); return CHM_ERR_UNRECOVERABLE; }
@@ -1308,7 +1305,6 @@ extern "C" int chm_search_best_static(chm_scenario *s, uint32_t strategy_mask, c
   s->d_slots = base; s->slot_words = STATIC_KEY_WORDS;
   s->d_winner = base + STATIC_WINNER_AT;
   s->d_xfer = base + STATIC_XFER_AT;
-  s->fast.penalty_by_capacity = false;
   StreamGuard guard(s, hip_stream);
   const int rc = guard.settled(run_jobs(s, jobs, out, nullptr, (hipStream_t)hip_stream, ~0ull, false));
   s->d_slots = own_slots; s->slot_words = own_words; s->d_winner = own_winner; s->d_xfer = own_xfer;

@@ -6,14 +6,8 @@
 // (more than 16 stages, times that do not fit int32, more than 8 peers), plus the small
 // one-lane kernels around a search (fixed pipelines, the winner's terms, migration scheme).
 //
-// Pipeline time: the 1F1B dependency recurrence of the Estimator subsection
-// (eq. (transition)) is a longest path in a fixed graph, so any topological order gives
-// the same integers.  The order used here keeps ONE value per stage live: in round t
-// (t = 0 .. M+n-2) stage s runs forward t (if t < M) and then backward t-(n-1-s) (if that
-// is a valid micro-batch).  Forward t of stage s needs forward t of stage s-1 (same
-// round, swept in stage order) and the stage's previous operation; backward j of stage s
-// needs backward j of stage s+1, which stage s+1 ran in round t-1 as its last operation,
-// i.e. the value E[s+1] held before this round's forward sweep overwrote it.
+// Pipeline time: the closed form of the 1F1B dependency recurrence (Estimator subsection, eq. (transition)) that
+// chm_search_kernel.h derives at pipeline_time, here in int64 and for a number of stages known at run time.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -30,30 +24,30 @@ __device__ __forceinline__ int64_t scale_q16(int64_t x, uint32_t q) { return (x 
 
 template <int SMAX>
 __device__ __forceinline__ int64_t makespan_generic(const int64_t (&F)[SMAX], const int64_t (&B)[SMAX], int n, int M) {
-  int64_t E[SMAX];
+  int64_t P[SMAX], U[SMAX], V[SMAX];
+  int64_t p = 0, max_f = 0, max_b = 0;
 #pragma unroll
-  for (int s = 0; s < SMAX; ++s) E[s] = 0;
-  const int rounds = M + n - 1;
-  for (int t = 0; t < rounds; ++t) {
-    const bool fwd = t < M;
-    int64_t x = 0;
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) {
-      if (s < n) {
-        const int64_t old = E[s];
-        if (fwd) {
-          E[s] = imax(E[s], x) + F[s];
-          x = E[s];
-          if (s == n - 1) E[s] += B[s];          // last stage: backward t follows its own forward
-        }
-        if (s >= 1) {
-          const int j = t - n + s;               // micro-batch whose backward stage s-1 runs now
-          if (j >= 0 && j < M) E[s - 1] = imax(E[s - 1], old) + B[s - 1];
-        }
-      }
+  for (int s = 0; s < SMAX; ++s) {
+    if (s < n) {
+      p += F[s] + B[s];
+      max_f = imax(max_f, F[s]);
+      max_b = imax(max_b, B[s]);
+      P[s] = p;
+      U[s] = p + (int64_t)(n - 1 - s) * max_b;
+      V[s] = p + (int64_t)(n - 1 - s) * max_f;
     }
   }
-  return E[0];
+  int64_t su = 0, sv = 0, r = 0;
+#pragma unroll
+  for (int j = SMAX - 1; j >= 0; --j) {
+    if (j < n) {
+      su = imax(su, U[j]);
+      sv = imax(sv, V[j]);
+      const int k = M - n + j;
+      if (k >= 0) r = imax(r, su + sv - P[j] + (int64_t)k * (F[j] + B[j]));
+    }
+  }
+  return r;
 }
 
 // cut positions of one lane live in a column of LDS: c[i][tid], i = 0..stages
@@ -265,81 +259,90 @@ __device__ __forceinline__ int64_t penalty_of_rank(const DevScenario *scn, const
   return pen;
 }
 
-// Sweep of every valid reroute vector of stage a in rank order; first strict minimum.
-// The vector lives in a column of LDS.
-template <int SMAX>
-__device__ __forceinline__ void sweep_stage(const DevScenario *scn, Cuts<SMAX> cuts, int a,
-                                            int32_t (*rv)[BLOCK], int64_t *best_pen, uint64_t *best_rank) {
-  const int tid = cuts.tid;
-  const int p = scn->aff_peers[a];
-  const int total = scn->aff_total[a];
-  const int cap = scn->rcap > 0 ? scn->rcap : total;
-  int64_t w[DEV_MAX_D];
-#pragma unroll
-  for (int i = 0; i < DEV_MAX_D; ++i) w[i] = i < p ? peer_weight<SMAX>(scn, cuts, a, i) : 0;
-  // lexicographically first vector: as much as possible on the last peers
-  int rem = total;
-  for (int i = p - 1; i >= 0; --i) {
-    const int v = rem < cap ? rem : cap;
-    rv[i][tid] = v;
-    rem -= v;
-  }
-  int64_t bp = CHM_INF_COST;
-  uint64_t br = 0, rank = 0;
-  for (;;) {
-    int64_t pen = 0;
-#pragma unroll
-    for (int i = 0; i < DEV_MAX_D; ++i)
-      if (i < p) pen = imax(pen, (int64_t)rv[i][tid] * w[i]);
-    if (pen < bp) { bp = pen; br = rank; }
-    ++rank;
-    // successor: rightmost entry that can grow while something to its right can shrink
-    int suffix = rv[p - 1][tid];
-    int i = p - 2;
-    while (i >= 0 && (rv[i][tid] >= cap || suffix == 0)) { suffix += rv[i][tid]; --i; }
-    if (i < 0) break;
-    rv[i][tid] += 1;
-    int left = suffix - 1;
-    for (int j = p - 1; j > i; --j) {
-      const int v = left < cap ? left : cap;
-      rv[j][tid] = v;
-      left -= v;
-    }
-  }
-  *best_pen = bp;
-  *best_rank = br;
+// a / b for 0 <= a, 0 < b: in double precision, put right by the remainder, where a fits its 53 bits (a 64-bit integer
+// division takes some 150 instructions)
+__device__ __forceinline__ int64_t quotient(int64_t a, int64_t b) {
+  if ((a >> 52) != 0) return a / b;
+  int64_t q = (int64_t)((double)a / (double)b);
+  const int64_t r = a - q * b;
+  q -= r < 0 ? 1 : 0;
+  q += r >= b ? 1 : 0;
+  return q;
 }
 
-// Rank of the best reroute vector of stage a without a sweep, by one wavefront together (all 64 lanes call this
+// Least penalty over all valid reroute vectors of stage a under the lane's partition: the orphans-th smallest of the
+// multiples w_i, 2 w_i, ..., cap w_i of all peers taken together (see least_penalty in chm_search_kernel.h).
+template <int SMAX>
+__device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<SMAX> cuts, int a) {
+  const int p = scn->aff_peers[a];
+  const int orphans = scn->aff_total[a];
+  const int cap = scn->rcap > 0 && scn->rcap < orphans ? scn->rcap : orphans;
+  int64_t w[DEV_MAX_D], next[DEV_MAX_D];
+  double inv_sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < DEV_MAX_D; ++i) {
+    w[i] = i < p ? peer_weight<SMAX>(scn, cuts, a, i) : 0;
+    if (i < p) inv_sum += 1.0 / (double)w[i];
+  }
+  const double v0 = (double)orphans / inv_sum * (1.0 - 1e-9);
+  int taken = 0;
+#pragma unroll
+  for (int i = 0; i < DEV_MAX_D; ++i) {
+    int r = (i < p && w[i] > 0) ? (int)(v0 / (double)w[i]) : 0;
+    r = r < cap ? r : cap;
+    taken += r;
+    next[i] = i < p && r < cap ? (int64_t)(r + 1) * w[i] : CHM_INF_COST;
+  }
+  int64_t least = 0;
+  for (int guard = 0; taken < orphans && guard < 1100; ++guard) {      // (at most 4 x 256 orphans: one step takes at least one)
+    least = CHM_INF_COST;
+#pragma unroll
+    for (int i = 0; i < DEV_MAX_D; ++i) least = next[i] < least ? next[i] : least;
+#pragma unroll
+    for (int i = 0; i < DEV_MAX_D; ++i) {
+      if (next[i] == least && least != CHM_INF_COST) {
+        ++taken;
+        next[i] = (w[i] == 0 || next[i] < (int64_t)cap * w[i]) ? next[i] + w[i] : CHM_INF_COST;
+      }
+    }
+  }
+  return least;
+}
+
+// Rank of the best reroute vector of stage a, by one wavefront together (all 64 lanes call this
 // with the same cuts).  A vector stays within penalty v exactly when every peer i takes at most floor(v / w_i) extra
 // micro-batches (w_i = its forward + backward time of the stage), so the least penalty is the least v at which the
 // peers' capacities min(cap, floor(v / w_i)) cover the orphans: found by a 64-way search (each lane tries one v per
 // round).  Among the vectors within it the lowest rank is the lexicographically smallest one: every peer in turn
 // takes as little as the peers after it allow; its rank = the number of valid vectors that are lexicographically
-// smaller, read off the count table (the lanes share the additions).  Equals the first minimum of the sweep
-// (sweep_stage): same penalty, lowest rank.
+// smaller, read off the count table (the lanes share the additions).  That is the first minimum of a sweep of all
+// vectors in rank order: same penalty, lowest rank.
 template <int SMAX>
 __device__ __forceinline__ uint64_t rank_by_capacity(const DevScenario *scn, const uint64_t *comp, Cuts<SMAX> cuts, int a) {
   const int lane = threadIdx.x & 63;
   const int p = scn->aff_peers[a];
   const int64_t orphans = scn->aff_total[a];
   const int64_t cap = scn->rcap > 0 ? scn->rcap : orphans;
+  // lane i works out the time of peer i; all lanes then hold all of them
+  const int64_t mine = lane < p ? peer_weight<SMAX>(scn, cuts, a, lane) : 0;
   int64_t w[DEV_MAX_D];
   int64_t w_max = 1;
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
-    w[i] = i < p ? peer_weight<SMAX>(scn, cuts, a, i) : 0;
+    w[i] = __shfl(mine, i, 64);
     w_max = w[i] > w_max ? w[i] : w_max;
   }
-  auto room = [&](int64_t v, int i) -> int64_t {
-    const int64_t fit = w[i] == 0 ? cap : v / w[i];
+  auto room = [cap](int64_t v, int64_t weight) -> int64_t {
+    const int64_t fit = weight == 0 ? cap : quotient(v, weight);
     return fit < cap ? fit : cap;
   };
   auto covers = [&](int64_t v) -> bool {
     int64_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < DEV_MAX_D; ++i)
-      if (i < p) sum += room(v, i);
+    for (int i = 0; i < DEV_MAX_D; ++i) {
+      if (i >= p) break;                             // uniform
+      sum += room(v, w[i]);
+    }
     return sum >= orphans;
   };
   // least v in [lo, hi] with covers(v); covers(hi) holds (every peer could take all orphans, the cap permitting:
@@ -347,36 +350,34 @@ __device__ __forceinline__ uint64_t rank_by_capacity(const DevScenario *scn, con
   int64_t lo = 0, hi = orphans * w_max;
   while (lo < hi) {                                  // uniform
     const int64_t step = (hi - lo + 62) / 63;          // lane 63 reaches hi
-    int64_t mine = lo + (int64_t)lane * step;
-    mine = mine < hi ? mine : hi;
-    const uint64_t ok = __builtin_amdgcn_ballot_w64(covers(mine));      // lane 63 (or an earlier one) stands at hi
+    int64_t at = lo + (int64_t)lane * step;
+    at = at < hi ? at : hi;
+    const uint64_t ok = __builtin_amdgcn_ballot_w64(covers(at));      // lane 63 (or an earlier one) stands at hi
     if (ok == 0) { lo = hi; break; }                 // cannot happen (covers(hi) holds); keeps the loop finite regardless
     const int first = __builtin_ctzll(ok);
     const int64_t at_first = lo + (int64_t)first * step;
     hi = at_first < hi ? at_first : hi;
     lo = first == 0 ? hi : lo + (int64_t)(first - 1) * step + 1;
   }
-  const int64_t v = lo;
+  const int64_t my_room = lane < p ? room(lo, mine) : 0;
+  int64_t behind = 0;                                // capacity of the peers from the current one on
+#pragma unroll
+  for (int i = 0; i < DEV_MAX_D; ++i) behind += __shfl(my_room, i, 64);
   const uint64_t *tab = comp + scn->comp_off[a];
   const uint32_t stride = scn->comp_stride[a];
   int64_t rem = orphans;
-  uint64_t rank = 0;
+  uint64_t part = 0;                                 // this lane's share of the rank
   for (int pos = 0; pos < p; ++pos) {                // uniform
-    int64_t behind = 0;
-#pragma unroll
-    for (int i = 0; i < DEV_MAX_D; ++i)
-      if (i > pos && i < p) behind += room(v, i);
+    behind -= __shfl(my_room, pos, 64);
     const int64_t take = rem - behind > 0 ? rem - behind : 0;
     const uint32_t left = (uint32_t)(p - 1 - pos);
     // vectors whose entry at this position is smaller than `take` (and whose earlier entries agree)
-    uint64_t part = 0;
     for (int64_t t = lane; t < take; t += 64) part += tab[left * stride + (uint32_t)(rem - t)];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off, 64);
-    rank += part;
     rem -= take;
   }
-  return rank;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off, 64);
+  return part;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -511,7 +512,6 @@ __global__ void __launch_bounds__(BLOCK) k_score_ranks(const DevScenario *scn, c
 template <int SMAX>
 __global__ void __launch_bounds__(BLOCK) k_search(SearchLaunch a) {
   __shared__ int32_t cut_cols[SMAX + 2][BLOCK];
-  __shared__ int32_t rv_cols[DEV_MAX_D][BLOCK];
   const DevScenario *scn = a.scn;
   const DevFamily &fam = scn->fam[a.strategy];
   const uint32_t gid = blockIdx.x * BLOCK + threadIdx.x;
@@ -545,11 +545,7 @@ __global__ void __launch_bounds__(BLOCK) k_search(SearchLaunch a) {
     if (a.costs_out && !fits) a.costs_out[gid] = CHM_INF_COST;
     if (fits) {
       if (fam.strategy == 2) {
-        for (int st = 0; st < scn->n_aff; ++st) {
-          int64_t pen; uint64_t rk;
-          sweep_stage<SMAX>(scn, cuts, st, rv_cols, &pen, &rk);
-          t_step += pen;
-        }
+        for (int st = 0; st < scn->n_aff; ++st) t_step += least_penalty64<SMAX>(scn, cuts, st);
       }
       const uint64_t cost = (uint64_t)(scn->K * t_step + reconf);
       key = (cost << a.idx_bits) | gid;
@@ -563,30 +559,17 @@ __global__ void __launch_bounds__(BLOCK) k_search(SearchLaunch a) {
 }
 
 // ranks of the best reroute vectors of ONE partition of the rerouting family (the winner of a search), per stage
-// that lost nodes: by a sweep of all vectors (one lane per stage), or, by_capacity, from the peers' capacities
-// (one wavefront, stage after stage: for reroute spaces too large to sweep in one lane)
+// that lost nodes: one wavefront, stage after stage
 template <int SMAX>
-__global__ void __launch_bounds__(BLOCK) k_reroute_winner(const DevScenario *scn, const uint64_t *comp,
-                                                          uint64_t part_rank, int by_capacity, uint64_t *out) {
+__global__ void __launch_bounds__(64) k_reroute_winner(const DevScenario *scn, const uint64_t *comp, uint64_t part_rank, uint64_t *out) {
   __shared__ int32_t cut_cols[SMAX + 2][BLOCK];
-  __shared__ int32_t rv_cols[DEV_MAX_D][BLOCK];
   const DevFamily &fam = scn->fam[2];
   Cuts<SMAX> cuts{cut_cols, (int)threadIdx.x};
-  if (by_capacity) {
-    if (threadIdx.x >= 64) return;
-    unrank_partition<SMAX>(scn, fam.stages - 1, part_rank, cuts);     // every lane into its own column
-    for (int a = 0; a < scn->n_aff; ++a) {
-      const uint64_t rk = rank_by_capacity<SMAX>(scn, comp, cuts, a);
-      if (threadIdx.x == 0) out[a] = rk;
-    }
-    return;
+  unrank_partition<SMAX>(scn, fam.stages - 1, part_rank, cuts);       // every lane into its own column
+  for (int a = 0; a < scn->n_aff; ++a) {
+    const uint64_t rk = rank_by_capacity<SMAX>(scn, comp, cuts, a);
+    if (threadIdx.x == 0) out[a] = rk;
   }
-  const int a = threadIdx.x;                         // one lane per affected stage
-  if (a >= scn->n_aff) return;
-  unrank_partition<SMAX>(scn, fam.stages - 1, part_rank, cuts);
-  int64_t pen; uint64_t rk;
-  sweep_stage<SMAX>(scn, cuts, a, rv_cols, &pen, &rk);
-  out[a] = rk;
 }
 
 // Migration scheme of one pipeline for one partition of the re-partition strategy: which new stage
@@ -669,7 +652,6 @@ __global__ void __launch_bounds__(BLOCK) k_finish_search(FinishArgs a) {
   constexpr bool STAGED = SMAX <= 16;
   constexpr int HEAD_WORDS = (int)(offsetof(DevScenario, binom) / 8);      // 8-byte words ahead of the binomial table
   __shared__ int32_t cut_cols[SMAX + 2][BLOCK];
-  __shared__ int32_t rv_cols[DEV_MAX_D][BLOCK];
   __shared__ uint64_t keys[FINISH_MAX_SLOTS * FINISH_MAX_WAYS];
   __shared__ uint64_t counts[6 * FINISH_MAX_WAYS];
   __shared__ uint64_t win[3];                        // cost, strategy (~0: nothing found), partition rank
@@ -758,27 +740,21 @@ __global__ void __launch_bounds__(BLOCK) k_finish_search(FinishArgs a) {
           rem -= taken;
           hi = x - 1;
           if (t == 0) { cut_cols[i][0] = x + 1; }
-          if (t < DEV_MAX_AFF) cut_cols[i][64 + t] = x + 1;
+          if (t == 1) cut_cols[i][64] = x + 1;
         }
       }
     }
     if (t == 0) { cut_cols[0][0] = 0; cut_cols[k + 1][0] = L; }
-    if (t < DEV_MAX_AFF) { cut_cols[0][64 + t] = 0; cut_cols[k + 1][64 + t] = L; }
+    if (t == 1) { cut_cols[0][64] = 0; cut_cols[k + 1][64] = L; }
   }
   __syncthreads();
   Cuts<SMAX> cuts{cut_cols, (int)t};
   if (t == 0) {
     int64_t t_step = 0, reconf = 0;
     a.out[FINISH_TRANS] = (uint64_t)(eval_base<SMAX, false>(scn, fam, cuts, &t_step, &reconf) ? reconf : (int64_t)-1);
-  } else if (a.sweep_winner == 1 && strategy == 2 && t >= 64 && (int)(t - 64) < scn->n_aff) {
-    // one lane per stage that lost nodes, in the second wavefront, beside the transition time
-    const int st = (int)(t - 64);
-    int64_t pen; uint64_t rk;
-    sweep_stage<SMAX>(scn, cuts, st, rv_cols, &pen, &rk);
-    a.out[FINISH_RR + st] = rk;
-  } else if (a.sweep_winner == 2 && strategy == 2 && t >= 64 && t < 128) {
-    // reroute spaces too large for one lane: the second wavefront takes the stages one after the other, from
-    // the peers' capacities (all its lanes read the cuts of column 64)
+  } else if (a.reroute_winner && strategy == 2 && t >= 64 && t < 128) {
+    // the second wavefront takes the stages that lost nodes one after the other, beside the transition time (all its
+    // lanes read the cuts of column 64)
     Cuts<SMAX> shared_cuts{cut_cols, 64};
     for (int st = 0; st < scn->n_aff; ++st) {
       const uint64_t rk = rank_by_capacity<SMAX>(scn, a.comp, shared_cuts, st);
@@ -907,12 +883,11 @@ int chmk_finish_search(const FinishArgs &a, int32_t smax, void *stream) {
   });
 }
 
-int chmk_reroute_winner(const DevScenario *d_scn, const uint64_t *d_comp, uint64_t part_rank, int32_t by_capacity, uint64_t *d_out,
-                        int32_t smax, void *stream) {
+int chmk_reroute_winner(const DevScenario *d_scn, const uint64_t *d_comp, uint64_t part_rank, uint64_t *d_out, int32_t smax,
+                        void *stream) {
   return dispatch_smax(smax, [&](auto tag) {
     constexpr int SMAX = decltype(tag)::value;
-    hipLaunchKernelGGL(k_reroute_winner<SMAX>, dim3(1), dim3(BLOCK), 0, (hipStream_t)stream, d_scn, d_comp,
-                       part_rank, (int)by_capacity, d_out);
+    hipLaunchKernelGGL(k_reroute_winner<SMAX>, dim3(1), dim3(64), 0, (hipStream_t)stream, d_scn, d_comp, part_rank, d_out);
     return (int)hipGetLastError();
   });
 }

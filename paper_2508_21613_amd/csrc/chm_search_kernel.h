@@ -1,0 +1,928 @@
+// Shape-specialised search kernels of libchm for gfx950 (wave64, plain VALU integer work: the path is a max-plus
+// longest path, not a dense contraction, so no MFMA).  Included by one translation unit per strategy, which
+// instantiates the kernels for every number of stages.
+//
+// One lane owns a run of consecutive partition ranks.  It unranks the first one
+// (combinatorial number system), then walks to each next partition with a branch-free
+// successor step, so unranking is amortised over the run.  Everything a plan needs lives
+// in registers: the cut positions, the per-stage sums (read from one LDS table of prefix
+// sums staged once per workgroup), and the few sums and maxima the pipeline time is made of (pipeline_time).
+// All values are int32: the host only selects these kernels when its load-time bound shows
+// that no intermediate can reach 2^31, in which case the results equal the int64 ones.
+//
+// Data rerouting: after the base step time of a partition, the least penalty over all valid reroute vectors of
+// every stage that lost nodes is added (least_penalty).
+//
+// Argmin: per lane a running (cost, run position) with strict less-than, so the lowest
+// index wins inside a lane; then a DPP/shuffle wave reduction of the packed 64-bit key
+// (cost << idx_bits | chunk-local partition index), one LDS step per workgroup and one
+// 64-bit atomicMin per workgroup.
+#ifndef CHM_SEARCH_KERNEL_H
+#define CHM_SEARCH_KERNEL_H
+#include <hip/hip_runtime.h>
+
+#include "chm_fast.h"
+
+namespace {
+
+// The scenario tables are never written while a search kernel runs.  Reading them through the
+// constant address space tells the compiler so: uniform reads become scalar loads (wide
+// s_load_dwordx16 for the reroute rows) even though the kernel also stores costs to global memory.
+#define CHM_CONST __attribute__((address_space(4)))
+typedef const CHM_CONST DevScenario *ScnPtr;
+typedef const CHM_CONST FastTables *TabPtr;
+typedef const CHM_CONST FastFamily *FamPtr;
+typedef const CHM_CONST FastClass *ClsPtr;
+typedef const CHM_CONST uint32_t *RowPtr;
+template <typename T>
+__device__ __forceinline__ const CHM_CONST T *as_const(const T *p) {
+  return (const CHM_CONST T *)(uintptr_t)p;
+}
+
+__device__ __forceinline__ int imax32(int a, int b) { return a > b ? a : b; }
+__device__ __forceinline__ int imin32(int a, int b) { return a < b ? a : b; }
+// a - b, 0 when that is negative (both below 2^31 and not negative): one saturating subtract
+__device__ __forceinline__ uint32_t sub_floor(int a, int b) { return __builtin_elementwise_sub_sat((uint32_t)a, (uint32_t)b); }
+
+// (x*q + 32768) >> 16 for 0 <= x < 2^31, q <= 2^20, result < 2^31
+__device__ __forceinline__ int scale32(int x, uint32_t q) {
+  return (int)(((uint64_t)(uint32_t)x * q + 32768u) >> 16);
+}
+
+// lower bound of scale32(f, q') + scale32(b, q') for any q' >= q, given x = f + b: each rounding loses less
+// than one, so the sum is at least floor(x * q / 65536) - 1
+__device__ __forceinline__ int scale_floor(int x, uint32_t q) {
+  return q == 65536u ? x : imax32(0, (int)(((uint64_t)(uint32_t)x * q) >> 16) - 1);
+}
+
+// forward + backward time of a stage on a peer with factor q (uniform): nominal peers need no scaling
+__device__ __forceinline__ uint32_t peer_time(int f, int b, uint32_t q) {
+  return q == 65536u ? (uint32_t)(f + b) : (uint32_t)(scale32(f, q) + scale32(b, q));
+}
+
+// product of two numbers below 2^24 (low 32 bits), or of any two where the times do not fit 24 bits
+template <bool M24>
+__device__ __forceinline__ uint32_t times(uint32_t x, uint32_t y) { return M24 ? __umul24(x, y) : x * y; }
+
+// 1F1B time of N stages, M micro-batches; F = forward, C = forward + backward per stage.  The estimator's dependency
+// recurrence (eq. (transition); 2 N M cells) is the longest path of a graph so regular that its optimum is known in
+// closed form, for every N, M >= 1:
+//     T = max over j with M - N + j >= 0 of   SU[j] + SV[j] - P[j] + (M - N + j) C[j],
+//     P[s] = C[0] + ... + C[s],  SU[j] = max over s >= j of P[s] + (N-1-s) max(B[0..s]),  SV[j] likewise with F.
+// Why.  Run the rounds "forward t on every stage, then backward t-(N-1-s) on stage s" backwards in time from the end
+// of the last backward of stage 0.  A path stands on a stage and every round it crosses adds one term:
+//  - the N-1 rounds of backwards only: a round on stage k adds B[k] and the path stays or moves on to k+1; reaching
+//    stage s takes B[0..s-1] once each, the N-1-s rounds left over are best spent on the largest B[0..s] met;
+//  - the round of the last forward adds C[s] (with the forwards F[0..s-1] that lead to it: P[s] in all);
+//  - the steady rounds: a round that adds C[k] leads to stage k+1, from where any stage up to k+1 can be next, so a
+//    path climbs one stage per round, falls freely, and may stay on one stage j for as long as it likes; rounds not
+//    needed for climbing belong to the largest C met;
+//  - the warm-up mirrors the end with F in the place of B: from round N-1-s on stage s has forwards only, so a path
+//    that leaves j climbs along that edge to some s (C[j+1..s] once each) and spends the N-1-s rounds left on the
+//    largest F[0..s].
+// Both ends use N-1-s and s-j rounds whatever s they turn at, which leaves exactly M-N+j rounds for C[j], and none
+// of the choices depends on the others: hence the sum.  N maxima of N terms instead of 2 N M cells: at 8 stages and 16
+// micro-batches about 80 instead of 280 instructions, at 16 and 64 about 160 instead of 2,000.
+// A node that is left out of the pipeline (UNI: redundant computation, coefficients from the class) has F = C = 0,
+// after = nodes behind it and steady = -1; its own term is never the largest (its neighbours' cover it).
+template <int N, bool UNI, bool M24>
+__device__ __forceinline__ int pipeline_time_m(const int (&F)[N], const int (&C)[N], ClsPtr cl) {
+  const int M = cl->M;
+  uint32_t P[N], U[N], V[N];
+  uint32_t p = 0, max_f = 0, max_b = 0;
+#pragma unroll
+  for (int s = 0; s < N; ++s) {
+    const uint32_t f = (uint32_t)F[s], b = (uint32_t)(C[s] - F[s]);
+    p += (uint32_t)C[s];
+    max_f = max_f > f ? max_f : f;
+    max_b = max_b > b ? max_b : b;
+    const uint32_t after = UNI ? (uint32_t)cl->after[s] : (uint32_t)(N - 1 - s);
+    P[s] = p;
+    U[s] = times<M24>(max_b, after) + p;
+    V[s] = times<M24>(max_f, after) + p;
+  }
+  uint32_t su = 0, sv = 0, r = 0;
+  if (M >= N) {                                      // uniform
+#pragma unroll
+    for (int j = N - 1; j >= 0; --j) {
+      su = su > U[j] ? su : U[j];
+      sv = sv > V[j] ? sv : V[j];
+      const uint32_t k = UNI ? (uint32_t)cl->steady[j] : (uint32_t)(M - N + j);
+      const uint32_t t = times<M24>((uint32_t)C[j], k) + su + (sv - P[j]);
+      r = r > t ? r : t;
+    }
+  } else {
+#pragma unroll
+    for (int j = N - 1; j >= 0; --j) {
+      su = su > U[j] ? su : U[j];
+      sv = sv > V[j] ? sv : V[j];
+      const int k = UNI ? cl->steady[j] : M - N + j;
+      if (k >= 0) {                                  // uniform
+        const uint32_t t = times<M24>((uint32_t)C[j], (uint32_t)k) + su + (sv - P[j]);
+        r = r > t ? r : t;
+      }
+    }
+  }
+  return (int)r + cl->comm_total;
+}
+
+template <int N, bool UNI>
+__device__ __forceinline__ int pipeline_time(const int (&F)[N], const int (&C)[N], ClsPtr cl, int time24) {
+  return time24 ? pipeline_time_m<N, UNI, true>(F, C, cl) : pipeline_time_m<N, UNI, false>(F, C, cl);
+}
+
+// The least of max_i r_i * w_i over all valid reroute vectors (0 <= r_i <= cap, sum = orphans), w_i = the stage's
+// forward + backward time on peer i, all below 2^24.  Of the multiples w_i, 2 w_i, ..., cap w_i of all peers taken
+// together a vector whose maximum is v uses only ones up to v, at least `orphans` of them; so the minimum is the
+// orphans-th smallest multiple (equal ones counted one by one).  The multiples below orphans / sum(1 / w_i) are fewer
+// than `orphans` (floats, rounded well to the safe side), the few left are merged one at a time: about as many steps
+// as there are peers, each a minimum over the peers, whatever the number of vectors (2,380,833 for 32 micro-batches
+// over seven peers, which a sweep that shares their common entries took 318 us for; 153 for 16 over three).
+__device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[FAST_MAX_P], int peers, uint32_t orphans, uint32_t cap) {
+  float inv_sum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < FAST_MAX_P; ++i) {
+    if (i >= peers) break;                           // uniform
+    inv_sum += __builtin_amdgcn_rcpf((float)w[i]);
+  }
+  const float v0 = (float)orphans * __builtin_amdgcn_rcpf(inv_sum) * 0.99999f;
+  uint32_t next[FAST_MAX_P];                         // peer i's smallest multiple not taken yet
+  uint32_t taken = 0;
+#pragma unroll
+  for (int i = 0; i < FAST_MAX_P; ++i) {
+    if (i >= peers) break;
+    uint32_t r = (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));    // (a time of 0 makes v0 0 and this 0)
+    r = r < cap ? r : cap;
+    taken += r;
+    next[i] = r < cap ? __umul24(r + 1, w[i]) : 0xffffffffu;
+  }
+  uint32_t least = 0;
+  const bool capped = cap < orphans;
+  for (uint32_t guard = 0; taken < orphans && guard < 1100u; ++guard) {   // (at most 4 x 256 orphans: one step takes at least one)
+    least = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < FAST_MAX_P; ++i) {
+      if (i >= peers) break;
+      least = least < next[i] ? least : next[i];
+    }
+#pragma unroll
+    for (int i = 0; i < FAST_MAX_P; ++i) {
+      if (i >= peers) break;
+      const bool hit = next[i] == least;
+      taken += hit ? 1u : 0u;
+      uint32_t after = next[i] + w[i];
+      if (capped && after > __umul24(cap, w[i])) after = 0xffffffffu;
+      next[i] = hit ? after : next[i];
+    }
+  }
+  return least;
+}
+
+// least reroute penalty of affected stage `st` whose forward and backward times are f and b.  Peers of equal speed
+// share the orphans evenly: the fullest takes ceil(orphans / peers), which a cap that admits any vector admits too.
+__device__ __forceinline__ uint32_t stage_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
+  const int p = scn->aff_peers[st];
+  if (tab->even_share[st] != 0) return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);    // uniform
+  uint32_t w[FAST_MAX_P];
+#pragma unroll
+  for (int i = 0; i < FAST_MAX_P; ++i) w[i] = i < p ? peer_time(f, b, scn->aff_q[st][i]) : 0u;
+  const uint32_t orphans = (uint32_t)scn->aff_total[st];
+  return least_penalty(w, p, orphans, scn->rcap > 0 ? (uint32_t)scn->rcap : orphans);
+}
+
+__device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
+
+// 1-based position of the n-th set bit of x (1 <= n <= popcount(x)): which half holds it is decided
+// by a population count, six times
+__device__ __forceinline__ int nth_set_bit(uint64_t x, int n) {
+  const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+  int c = __popc(lo);
+  bool up = n > c;
+  uint32_t w = up ? hi : lo;
+  int r = up ? n - c : n;
+  int pos = up ? 32 : 0;
+#pragma unroll
+  for (int sh = 16; sh >= 1; sh >>= 1) {
+    const uint32_t part = w & ((1u << sh) - 1u);
+    c = __popc(part);
+    up = r > c;
+    w = up ? (w >> sh) : part;
+    r = up ? r - c : r;
+    pos += up ? sh : 0;
+  }
+  return pos + 1;
+}
+
+// Rounds of gradient communication under redundant computation (see comm_rounds in chm_kernels.hip):
+// the colour set of stage s = the n_s lowest colours not used by stage s-1 (if its node exists) nor,
+// for the last stage, by stage 0 (if the last node exists); sets are 64-bit masks, L <= 64.
+template <int SP>
+__device__ __forceinline__ int ring_rounds(const int (&c)[SP + 1], uint32_t node_exists) {
+  uint64_t prev = 0, first = 0;
+  int rounds = 0;
+#pragma unroll
+  for (int s = 0; s < SP; ++s) {
+    const int n = c[s + 1] - c[s];
+    uint64_t f = 0;
+    if (s >= 1) f |= ((node_exists >> (s - 1)) & 1u) ? prev : 0ull;
+    if (s >= 1 && s == SP - 1) f |= ((node_exists >> s) & 1u) ? first : 0ull;
+    const int p = nth_set_bit(~f, n);
+    const uint64_t low = p >= 64 ? ~0ull : ((1ull << p) - 1ull);
+    const uint64_t cur = ~f & low;
+    rounds = imax32(rounds, p);
+    if (s == 0) first = cur;
+    prev = cur;
+  }
+  return rounds;
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_min(uint64_t v) {
+  const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(v >> 32), (int)(uint32_t)(v >> 32), CTRL, 0xF, 0xF, false);
+  return umin64(v, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {
+  v = dpp_min<0xB1>(v);     // quad_perm [1,0,3,2]
+  v = dpp_min<0x4E>(v);     // quad_perm [2,3,0,1]
+  v = dpp_min<0x141>(v);    // row_half_mirror
+  v = dpp_min<0x140>(v);    // row_mirror
+  v = umin64(v, __shfl_xor(v, 16, 64));
+  v = umin64(v, __shfl_xor(v, 32, 64));
+  return v;
+}
+
+// Combinadic digits of `rem` (a partition rank): for i = K..1 the largest x with C(x, i) <= rem.
+// C(., i) grows with x, so each digit is found by a four-way search over [i-1, previous digit - 1]:
+// three independent table probes per step, the range shrinks to a quarter; all lanes take the same
+// number of steps (no divergence), `steps` = 3 for up to 64 candidates, 4 for up to 256.
+template <int K>
+__device__ __forceinline__ void unrank_digits(uint64_t rem, int L, int steps, const uint64_t *table, int (&c)[K + 2]) {
+  // table[(i-1) * DEV_MAX_L + x] = C(x, i)
+  auto column = [table](int i, int x) { return table[(i - 1) * DEV_MAX_L + x]; };
+  int hi = L - 2;
+#pragma unroll
+  for (int i = K; i >= 1; --i) {
+    int lo = i - 1;                                  // C(i-1, i) = 0 <= rem always
+    for (int s = 0; s < steps; ++s) {
+      const int q = (hi - lo + 4) >> 2;              // ceil((range size) / 4), 0 only when hi < lo
+      const int m1 = lo + q, m2 = m1 + q, m3 = m2 + q;
+      const bool a1 = m1 <= hi && column(i, m1 <= hi ? m1 : hi) <= rem;
+      const bool a2 = m2 <= hi && column(i, m2 <= hi ? m2 : hi) <= rem;
+      const bool a3 = m3 <= hi && column(i, m3 <= hi ? m3 : hi) <= rem;
+      // the answer lies in [lo, m1-1], [m1, m2-1], [m2, m3-1] or [m3, hi]
+      const int nlo = a3 ? m3 : (a2 ? m2 : (a1 ? m1 : lo));
+      const int nhi = a3 ? hi : (a2 ? m3 - 1 : (a1 ? m2 - 1 : m1 - 1));
+      lo = nlo;
+      hi = nhi < hi ? nhi : hi;
+    }
+    c[i] = lo + 1;
+    rem -= column(i, lo);
+    hi = lo - 1;
+  }
+}
+
+// largest peak memory over the nodes of a plan: static + (pipeline length - position) * activations of the
+// most demanding node of every stage (strategy 0: a node holds its stage and its ring successor's)
+template <int SP, int STRAT>
+__device__ __forceinline__ int largest_peak(FamPtr ff, const int (&ms)[SP], const int (&as)[SP]) {
+  int mmax = 0;
+  if (ff->has_act) {
+#pragma unroll
+    for (int j = 0; j < SP; ++j) {
+      const int coef = ff->mem_coef[j];
+      const int st = STRAT == 0 ? ms[j] + ms[(j + 1) % SP] : ms[j];
+      const int ac = STRAT == 0 ? as[j] + as[(j + 1) % SP] : as[j];
+      const int m = st + (int)__umul24((uint32_t)ac, (uint32_t)(coef < 0 ? 0 : coef));
+      mmax = imax32(mmax, coef < 0 ? 0 : m);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < SP; ++j) {
+      const int m = STRAT == 0 ? ms[j] + ms[(j + 1) % SP] : ms[j];
+      mmax = imax32(mmax, ff->mem_coef[j] < 0 ? 0 : m);
+    }
+  }
+  return mmax;
+}
+
+// Lower bound of a plan's cost from its cuts c[0..SP] and the forward + backward time cs[] of its stages.
+template <int SP, int STRAT>
+__device__ __forceinline__ uint64_t cost_lower_bound(ScnPtr scn, TabPtr tab, FamPtr ff, const int (&cs)[SP], const int (&c)[SP + 1]) {
+    // Lower bound of the plan's cost.  Every stage of a pipeline runs its M forwards and M backwards one
+    // after the other, so the pipeline takes at least M x the largest (forward + backward) of its chain;
+    // rounds of gradient communication: at least the layers of the largest stage; a stage that lost
+    // nodes leaves some peer with at least ceil(orphans / peers) extra micro-batches; the weight transfer
+    // is at least zero.  Above the incumbent the partition can neither win nor tie.
+    // (Sharper where the times allow 24-bit multiplies: stage s cannot start before the forwards of the
+    // stages ahead of it and is followed by their backwards: M x its own time + the times of stages 0..s-1.)
+    int lb = ff->fixed_step;
+    if (STRAT == 0) {
+      int cd[SP];
+#pragma unroll
+      for (int j = 0; j < SP; ++j) cd[j] = cs[j] + cs[(j + 1) % SP];
+      for (int ci = 0; ci < ff->n_cls; ++ci) {
+        const ClsPtr cl = &ff->cls[ci];
+        int v = 0;
+        if (ff->lb_prefix) {
+          int pre = 0;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            const int cj = ((cl->dead >> j) & 1u) ? 0 : cd[j];
+            v = imax32(v, (int)__umul24((uint32_t)cl->M, (uint32_t)cj) + pre);
+            pre += cj;
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < SP; ++j) v = imax32(v, ((cl->dead >> j) & 1u) ? 0 : cd[j]);
+          v *= cl->M;
+        }
+        lb = imax32(lb, imax32(0, scale_floor(v, cl->q_min) - cl->lb_slack) + cl->comm_total);
+      }
+    } else {
+      for (int ci = 0; ci < ff->n_cls; ++ci) {
+        const ClsPtr cl = &ff->cls[ci];
+        int v = 0;
+        if (ff->lb_prefix) {
+          int pre = 0;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            v = imax32(v, (int)__umul24((uint32_t)cl->M, (uint32_t)cs[j]) + pre);
+            pre += cs[j];
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < SP; ++j) v = imax32(v, cs[j]);
+          v *= cl->M;
+        }
+        lb = imax32(lb, imax32(0, scale_floor(v, cl->q_min) - cl->lb_slack) + cl->comm_total);
+      }
+    }
+    if (ff->allreduce > 0) {
+      int layers = STRAT == 0 ? 0 : ff->fixed_layers;
+#pragma unroll
+      for (int j = 0; j < SP; ++j) layers = imax32(layers, c[j + 1] - c[j]);
+      lb += ff->allreduce * layers;
+    }
+    if (STRAT == 2) {
+      for (int st = 0; st < scn->n_aff; ++st) {
+        const int sa = scn->aff_stage[st];
+        int c_st = cs[0];
+#pragma unroll
+        for (int j = 1; j < SP; ++j) c_st = sa == j ? cs[j] : c_st;
+        lb += (int)tab->lb_mult[st] * scale_floor(c_st, tab->lb_q[st]);
+      }
+    }
+    return (uint64_t)scn->K * (uint32_t)lb + (uint64_t)scn->reconf[STRAT];
+}
+
+// Entries of a wave's queue of partitions that fit (QUEUED kernels): a ring of twice the wave width,
+// since a round appends at most 64 entries to fewer than 64 waiting ones.
+constexpr int QCAP = 128;
+
+// Waves per SIMD the register allocator is asked to keep possible: 5 up to 5 stages (at most 96 vector registers), 4 up
+// to 9 (128), 3 up to 14 (168, up to 32 of them spilled), 2 beyond (256; from 20 stages on some are spilled).  One wave
+// more at 8 stages (96 registers, 22 spilled) took 1,299 instead of 1,099 us for the 32-card search.
+//
+// QUEUED (range search of strategies 0 and 1 without cost store): lanes whose partition fails the memory
+// filter would idle through the recurrence of their wave, and consecutive ranks share their upper cuts, so
+// whole runs of a lane fail together.  Each wave therefore first only filters: every lane takes the next
+// partition of its run, and those that fit are appended (cut positions packed into bytes, position) to a
+// ring in LDS that belongs to the wave.  Whenever 64 entries wait, the wave evaluates them, one per lane,
+// with every lane busy; what is left after the last round is evaluated by a partly filled wave.  A ring is
+// written and read by one wave only, whose LDS operations complete in order: no barrier is needed.
+// MODE 0: every lane evaluates its own partitions; 1: QUEUED; 2: QUEUED with the bounds of a bounded search (a
+// variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
+// spilled bytes per lane at 8 stages and 4 % of its time).
+template <int SP, int STRAT, int MODE = 0>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= 5 ? 5 : SP <= 9 ? 4 : SP <= 14 ? 3 : 2)))
+k_fast_search(FastLaunch a) {
+  constexpr bool QUEUED = MODE >= 1;
+  constexpr int K = SP - 1;
+  __shared__ uint4 q_cuts[QUEUED ? (BLOCK / 64) * QCAP : 1];
+  __shared__ uint32_t q_pos[QUEUED ? (BLOCK / 64) * QCAP : 1];
+  __shared__ int4 T[DEV_MAX_L + 1];            // prefix sums: forward, forward + backward, static memory, activation memory
+  __shared__ uint64_t BN[(K > 0 ? K : 1) * DEV_MAX_L];   // BN[(i-1)*128 + x] = C(x, i), i = 1..K
+  __shared__ uint64_t wave_keys[BLOCK / 64];
+  __shared__ uint32_t wave_fit[BLOCK / 64];
+  __shared__ uint32_t wave_eval[BLOCK / 64];
+  extern __shared__ int64_t cost_tile[];       // BLOCK * per_lane costs when a cost store with per_lane > 1 is asked for
+  const ScnPtr scn = as_const(a.s.scn);
+  const TabPtr tab = as_const(a.tab);
+  const FamPtr ff = &tab->fam[STRAT];
+  const int L = scn->L;
+  const bool compact = !QUEUED && a.cut_list != nullptr;
+  const uint32_t n_slots = compact ? a.cut_count[blockIdx.x] : 0u;       // filled slots of this workgroup's region
+  if (compact && n_slots == 0) return;
+  for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
+  if (!compact)                                                 // a compacted list needs no unranking
+    for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
+  __syncthreads();
+
+  const uint32_t lane_id = blockIdx.x * BLOCK + threadIdx.x;
+  const uint32_t run_first = lane_id * a.per_lane;                       // chunk-local (a chunk holds at most 2^30 partitions)
+  const uint32_t run_len = (compact || run_first >= a.s.part_count) ? 0u
+                           : (uint32_t)(a.s.part_count - run_first < a.per_lane ? a.s.part_count - run_first : a.per_lane);
+  const uint32_t region = blockIdx.x * a.per_lane * BLOCK;               // compact mode: first slot of this workgroup
+
+  // cut positions c[1..K]; c[0] = 0 and c[SP] = L are constants
+  int c[SP + 1];
+  c[0] = 0;
+  c[SP] = L;
+  bool listed_ok = true;
+  if (!compact) {
+    uint64_t rem = run_len ? a.s.part_first + run_first + (run_first >= a.s.jump_at ? a.s.jump_by : 0) : 0;   // idle lanes walk from rank 0: always valid cuts
+    if (!QUEUED && a.s.ranks != nullptr && run_len) {            // list mode (one partition per lane)
+      rem = a.s.ranks[run_first];
+      listed_ok = rem < scn->fam[STRAT].n_part;
+      if (!listed_ok) rem = 0;
+    }
+    // combinadic digits from the LDS copy of the binomial table
+    unrank_digits<K>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+  }
+
+  const int cap = (int)scn->cap;
+  uint64_t best_cost = ~0ull;
+  uint32_t best_pos = 0;        // output position (chunk-local partition index or list position) of the lane's best
+  uint32_t n_fit = 0;           // wave-uniform count of partitions that pass the memory filter
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t q_head = 0, q_tail = 0;        // wave-uniform: entries [q_head, q_tail) of the wave's ring wait
+  // bounded search: the lowest cost evaluated so far, by this wave or (as of its last look) by any other
+  const bool bounded = MODE == 2 && a.s.incumbent != nullptr;
+  uint64_t incumbent = ~0ull;
+  uint32_t n_eval = 0;                    // wave-uniform count of partitions whose recurrences were run
+  if (bounded) incumbent = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  // Bounded search, a whole run at once.  Consecutive ranks differ in their lowest cuts.  When the run of a lane
+  // stays inside the block of ranks that share the cuts above the h lowest ones (its offset among the
+  // arrangements of those h cuts, plus its length, does not exceed their number C(c[h+1]-1, h)), the stages
+  // from h+1 on are the same for every partition of the run, and so is their part of the lower bound: stage s
+  // contributes M x its time + the time of all layers ahead of it, whatever the lower cuts are.  If that
+  // alone lies above the incumbent for every lane, the wave has nothing to look at.
+  bool wave_dead = false;
+  if (bounded && K >= 2) {
+    uint64_t offset = 0;
+    int first_fixed = SP;                   // stages first_fixed.. are the same throughout the run
+#pragma unroll
+    for (int h = 1; h < K; ++h) {
+      offset += BN[(h - 1) * DEV_MAX_L + (c[h] - 1)];
+      const bool stays = offset + run_len <= BN[(h - 1) * DEV_MAX_L + (c[h + 1] - 1)];
+      first_fixed = (first_fixed == SP && stays) ? h + 1 : first_fixed;
+    }
+    int pc[SP + 1];                         // forward + backward time of the layers ahead of stage s
+#pragma unroll
+    for (int s2 = 1; s2 <= SP; ++s2) pc[s2] = T[c[s2]].y;
+    int lb = ff->fixed_step;
+    for (int ci = 0; ci < ff->n_cls; ++ci) {
+      const ClsPtr cl = &ff->cls[ci];
+      int v = 0;
+#pragma unroll
+      for (int s2 = 1; s2 < SP; ++s2) {
+        int vs;
+        if (STRAT == 0) {
+          // a node's own stage and its successor's; the pair that wraps around to stage 0 is left out
+          const int pair = s2 + 2 <= SP ? pc[s2 + 2 <= SP ? s2 + 2 : SP] - pc[s2] : 0;
+          vs = ((cl->dead >> s2) & 1u) ? 0 : cl->M * pair;
+        } else {
+          const int own = pc[s2 + 1] - pc[s2];
+          vs = ff->lb_prefix ? (int)__umul24((uint32_t)cl->M, (uint32_t)own) + pc[s2] : cl->M * own;
+        }
+        v = imax32(v, s2 >= first_fixed ? vs : 0);
+      }
+      lb = imax32(lb, imax32(0, scale_floor(v, cl->q_min) - cl->lb_slack) + cl->comm_total);
+    }
+    const uint64_t lb_cost = (uint64_t)scn->K * (uint32_t)lb + (uint64_t)scn->reconf[STRAT];
+    const bool look = run_len != 0 && !(first_fixed < SP && lb_cost > incumbent);
+    wave_dead = __builtin_amdgcn_ballot_w64(look) == 0;
+  }
+  // evaluation cuts: the lane's own cuts, or (QUEUED) those of the entry it takes from the ring
+  int ce[SP + 1];
+  ce[0] = 0;
+  ce[SP] = L;
+
+  for (uint32_t it = 0; it < (wave_dead ? 0u : a.per_lane + (QUEUED ? 1u : 0u)); ++it) {
+    bool live = it < run_len;             // this lane has a partition in this round
+    uint32_t pos = run_first + it;        // where its result is reported
+    if (QUEUED) {
+      if (it < a.per_lane) {              // uniform; the extra round only drains the ring
+        // ---- filter the lane's next partition and append it to the ring if it fits
+        int ms[SP], as[SP], cs[SP];           // cs: forward + backward time per stage
+        {
+          int lo_m = 0, lo_a = 0, lo_c = 0;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            const int4 hi = T[c[j + 1]];
+            ms[j] = hi.z - lo_m;
+            as[j] = hi.w - lo_a;
+            cs[j] = hi.y - lo_c;
+            lo_m = hi.z;
+            lo_a = hi.w;
+            lo_c = hi.y;
+          }
+        }
+        bool fits = live && largest_peak<SP, STRAT>(ff, ms, as) <= cap;
+        const uint64_t in_memory = __builtin_amdgcn_ballot_w64(fits);
+        n_fit += (uint32_t)__popcll(in_memory);
+        if (bounded && in_memory != 0) {      // uniform; nothing to bound where nothing fits
+          const uint64_t lb_cost = cost_lower_bound<SP, STRAT>(scn, tab, ff, cs, c);
+          fits = fits && lb_cost <= incumbent;
+        }
+        const uint64_t fit_mask = __builtin_amdgcn_ballot_w64(fits);
+        if (fits) {
+          const uint32_t slot = (uint32_t)wave * QCAP + ((q_tail + (uint32_t)__popcll(fit_mask & ((1ull << lane) - 1ull))) & (QCAP - 1));
+          uint32_t words[4] = {0, 0, 0, 0};
+#pragma unroll
+          for (int i = 1; i <= K; ++i) words[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+          q_cuts[slot] = make_uint4(words[0], words[1], words[2], words[3]);
+          q_pos[slot] = (uint32_t)pos;
+        }
+        q_tail += (uint32_t)__popcll(fit_mask);
+        // next partition of the run
+        bool done = false;
+#pragma unroll
+        for (int i = 1; i <= K; ++i) {
+          const bool can = c[i] + 1 < c[i + 1];
+          c[i] = done ? c[i] : (can ? c[i] + 1 : i);
+          done = done || can;
+        }
+      }
+      const uint32_t waiting = q_tail - q_head;
+      if (waiting < 64 && !(it == a.per_lane && waiting > 0)) continue;     // uniform
+      // ---- evaluate up to 64 waiting entries, one per lane
+      const uint32_t take = waiting < 64 ? waiting : 64u;
+      live = (uint32_t)lane < take;
+      const uint32_t slot = (uint32_t)wave * QCAP + ((q_head + (uint32_t)lane) & (QCAP - 1));
+      // lanes past the end take the first partition (cuts 1..K): always valid
+      const uint4 packed = live ? q_cuts[slot] : make_uint4(0x04030201u, 0x08070605u, 0x0c0b0a09u, 0x000f0e0du);
+      const uint32_t words[4] = {packed.x, packed.y, packed.z, packed.w};
+#pragma unroll
+      for (int i = 1; i <= K; ++i) ce[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+      pos = live ? q_pos[slot] : 0;
+      q_head += take;
+    }
+    if (compact) {
+      if (it * BLOCK >= n_slots) break;   // uniform: the region is used up
+      const uint32_t slot = it * BLOCK + threadIdx.x;
+      live = slot < n_slots;
+      // lanes past the end take the first partition (cuts 1..K): always valid
+      const uint4 packed = live ? a.cut_list[region + slot] : make_uint4(0x04030201u, 0x08070605u, 0x0c0b0a09u, 0x000f0e0du);
+      const uint32_t words[4] = {packed.x, packed.y, packed.z, packed.w};
+#pragma unroll
+      for (int i = 1; i <= K; ++i) c[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+      pos = live ? a.cut_pos[region + slot] : 0;
+    }
+    if (!QUEUED) {
+#pragma unroll
+      for (int i = 1; i <= K; ++i) ce[i] = c[i];
+    }
+    // ---- stage sums from the LDS prefix table (strategy 0: of a node, which runs its stage and its ring successor's)
+    int fs[SP], cs[SP], ms[SP], as[SP];
+    int wp[SP + 1];                         // memory prefix at the cuts
+    {
+      int pf[SP + 1], pc[SP + 1], pa[SP + 1];
+      pf[0] = pc[0] = pa[0] = wp[0] = 0;
+#pragma unroll
+      for (int j = 1; j <= SP; ++j) {
+        const int4 hi = T[ce[j]];
+        pf[j] = hi.x; pc[j] = hi.y; wp[j] = hi.z; pa[j] = hi.w;
+      }
+#pragma unroll
+      for (int j = 0; j < SP; ++j) {
+        fs[j] = pf[j + 1] - pf[j];
+        cs[j] = pc[j + 1] - pc[j];
+        ms[j] = wp[j + 1] - wp[j];
+        as[j] = pa[j + 1] - pa[j];
+      }
+    }
+    // ---- memory filter
+    // (QUEUED: every entry of the ring has passed it already)
+    const bool ok = QUEUED ? live : ((largest_peak<SP, STRAT>(ff, ms, as) <= cap) && live && listed_ok);
+    uint64_t cost = (uint64_t)CHM_INF_COST;
+    const uint64_t ok_mask = __builtin_amdgcn_ballot_w64(ok);
+    if (!QUEUED) n_fit += (uint32_t)__popcll(ok_mask);
+    if (ok_mask != 0) {
+      int t_step = ff->fixed_step;
+      int missing = 0;
+      if (STRAT != 1) {
+        // weights the stage-j node must fetch: stage size minus what it already holds; prefix
+        // sums are monotone, so the prefix at max(a,a0) is the max of the two prefixes
+        uint32_t have = 0;
+#pragma unroll
+        for (int j = 0; j < SP; ++j)
+          have += sub_floor(imin32(wp[j + 1], ff->w0[j + 1]), imax32(wp[j], ff->w0[j]));
+        missing = ff->w_total - (int)have;
+      }
+      for (int ci = 0; ci < ff->n_cls; ++ci) {
+        const ClsPtr cl = &ff->cls[ci];
+        int F[SP], C[SP];
+        if (STRAT == 0) {
+          const uint32_t dead = cl->dead;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            const int keep = ((dead >> j) & 1u) ? 0 : -1;            // uniform
+            F[j] = (fs[j] + fs[(j + 1) % SP]) & keep;
+            C[j] = (cs[j] + cs[(j + 1) % SP]) & keep;
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < SP; ++j) { F[j] = fs[j]; C[j] = cs[j]; }
+        }
+        if (!cl->unit) {
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            const uint32_t q = cl->q_stage[j];
+            const int b = scale32(C[j] - F[j], q);
+            F[j] = scale32(F[j], q);
+            C[j] = F[j] + b;
+          }
+        }
+        t_step = imax32(t_step, pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24));
+        if (STRAT == 1) {
+          int have = 0;
+          if (ff->assign) {
+            // least-transfer assignment = largest total overlap of a non-crossing matching of survivors
+            // and new stages (both are in layer order, see best_overlap in chm_kernels.hip); one row of
+            // the two-index recurrence lives in registers.  A negative raw overlap needs no clamp:
+            // diag + (negative) < diag <= G[j], which is already among the operands of the max.
+            int G[SP + 1];
+#pragma unroll
+            for (int j = 0; j <= SP; ++j) G[j] = 0;
+#pragma unroll
+            for (int i = 0; i < SP; ++i) {
+              const int wlo_i = cl->wlo[i], whi_i = cl->whi[i];
+              int diag = 0;
+#pragma unroll
+              for (int j = 0; j < SP; ++j) {
+                const int above = G[j + 1];
+                const int cand = diag + (imin32(wp[j + 1], whi_i) - imax32(wp[j], wlo_i));
+                G[j + 1] = imax32(imax32(above, G[j]), cand);
+                diag = above;
+              }
+            }
+            have = G[SP];
+          } else {
+#pragma unroll
+            for (int j = 0; j < SP; ++j)
+              have += (int)sub_floor(imin32(wp[j + 1], cl->whi[j]), imax32(wp[j], cl->wlo[j]));
+          }
+          missing = imax32(missing, ff->w_total - have);
+        }
+      }
+      if (ff->allreduce > 0) {
+        // rounds of gradient communication: largest stage on any device, or the ring colouring when nodes hold two stages
+        int rounds;
+        if (STRAT == 0) {
+          rounds = ring_rounds<SP>(ce, ff->node_exists);
+        } else {
+          rounds = ff->fixed_layers;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) rounds = imax32(rounds, ce[j + 1] - ce[j]);
+        }
+        t_step += ff->allreduce * rounds;
+      }
+      if (STRAT == 2 && (QUEUED || a.base_out == nullptr)) {
+        // least penalty over the reroute vectors of every stage that lost nodes
+        for (int st = 0; st < scn->n_aff; ++st) {
+          const int sa = scn->aff_stage[st];
+          int f_st = fs[0], c_st = cs[0];
+#pragma unroll
+          for (int j = 1; j < SP; ++j) {
+            f_st = sa == j ? fs[j] : f_st;
+            c_st = sa == j ? cs[j] : c_st;
+          }
+          t_step += (int)stage_penalty(scn, tab, st, f_st, c_st - f_st);
+        }
+      }
+      if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
+        // cost store of plan indices: hand the peer stage times of this partition to the expanding kernel
+        if (ok) {
+          uint32_t *wout = a.weights_out + (size_t)(run_first + it) * (DEV_MAX_AFF * 8);
+          for (int st = 0; st < scn->n_aff; ++st) {
+            const int sa = scn->aff_stage[st];
+            int f_st = fs[0], c_st = cs[0];
+#pragma unroll
+            for (int j = 1; j < SP; ++j) {
+              f_st = sa == j ? fs[j] : f_st;
+              c_st = sa == j ? cs[j] : c_st;
+            }
+            const int p = scn->aff_peers[st];
+            for (int i = 0; i < p; ++i) {
+              const uint32_t q = scn->aff_q[st][i];
+              wout[st * 8 + i] = peer_time(f_st, c_st - f_st, q);
+            }
+          }
+        }
+      }
+      cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] + (uint64_t)scn->xfer * (uint32_t)missing;
+      // a lane meets the entries of a compacted list or of a ring in no particular order of position:
+      // there the lower position wins among equal costs; a run is walked in ascending order
+      const bool lower = (QUEUED || compact) ? (cost < best_cost || (cost == best_cost && pos < best_pos)) : cost < best_cost;
+      if (ok && lower) { best_cost = cost; best_pos = pos; }
+      if (bounded) {
+        // the round's lowest cost becomes known to every wave; what the others found is picked up in turn
+        n_eval += (uint32_t)__popcll(ok_mask);
+        const uint64_t round_best = wave_min(ok ? cost : ~0ull);
+        if (round_best < incumbent) {
+          incumbent = round_best;
+          if (lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)round_best);
+        }
+        incumbent = umin64(incumbent, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      }
+      if (!QUEUED && STRAT == 2 && a.base_out != nullptr && ok) a.base_out[run_first + it] = cost;
+    }
+    if (!QUEUED && STRAT == 2 && a.base_out != nullptr && !ok && it < run_len) a.base_out[run_first + it] = ~0ull;
+    if (!QUEUED && a.s.costs_out != nullptr) {
+      // per_lane == 1: the store is coalesced as it is; longer runs go through an LDS tile
+      // (laid out in output order) and are written out together after the loop
+      const int64_t v = ok ? (int64_t)cost : CHM_INF_COST;
+      if (a.per_lane == 1 || compact) { if (live) a.s.costs_out[pos] = v; }
+      else cost_tile[threadIdx.x * a.per_lane + it] = v;
+    }
+    // ---- next partition in rank order: bump the lowest cut that has room, reset those below
+    if (!compact && !QUEUED) {
+      bool done = false;
+#pragma unroll
+      for (int i = 1; i <= K; ++i) {
+        const bool can = c[i] + 1 < c[i + 1];
+        c[i] = done ? c[i] : (can ? c[i] + 1 : i);
+        done = done || can;
+      }
+    }
+  }
+
+  if (!QUEUED && a.s.costs_out != nullptr && a.per_lane > 1 && !compact) {
+    __syncthreads();
+    const uint64_t block_first = (uint64_t)blockIdx.x * BLOCK * a.per_lane;
+    const uint32_t n_tile = BLOCK * a.per_lane;
+    for (uint32_t i = threadIdx.x; i < n_tile; i += BLOCK)
+      if (block_first + i < a.s.part_count) a.s.costs_out[block_first + i] = cost_tile[i];
+  }
+  uint64_t key = best_cost == ~0ull ? CHM_KEY_NONE
+                                    : ((best_cost << a.s.idx_bits) | (uint64_t)best_pos);
+  if (!QUEUED && STRAT == 2 && a.base_out != nullptr) key = CHM_KEY_NONE;   // the combine kernel takes the argmin
+  key = wave_min(key);
+  if (lane == 0) { wave_keys[wave] = key; wave_fit[wave] = n_fit; wave_eval[wave] = n_eval; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    // one atomic of each kind per workgroup, spread over several words (see SearchLaunch)
+    const uint32_t slot = (blockIdx.x & a.s.slot_mask) * a.s.slot_stride;
+    uint64_t k = wave_keys[0];
+    uint32_t fit = wave_fit[0], evaluated = wave_eval[0];
+#pragma unroll
+    for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; evaluated += wave_eval[i]; }
+    if (fit) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
+    if (bounded && evaluated) atomicAdd((unsigned long long *)a.s.evaluated + slot, (unsigned long long)evaluated);
+    // a search over a list of candidates of a bounded search makes its best cost known to what follows
+    if (!QUEUED && a.s.incumbent != nullptr && k != CHM_KEY_NONE)
+      atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)(k >> a.s.idx_bits));
+    if (k != CHM_KEY_NONE) atomicMin((unsigned long long *)a.s.result + slot, (unsigned long long)k);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// explicit lists: memory filter and compaction
+// ---------------------------------------------------------------------------------------
+// One lane per list entry: cut positions (given, or unranked), stage memory sums, memory filter.  An entry
+// that does not fit (or is malformed) gets its cost (infeasible) right away; the others are appended to the
+// workgroup's own region of a compact list as (cut positions packed into 16 bytes, list position).  Slots are
+// handed out through a counter in LDS: atomics of many workgroups on one global counter would serialise (about
+// 10 ns each).  The search kernel then runs over every region with all lanes busy.
+
+template <int SP, int STRAT>
+__global__ void __launch_bounds__(BLOCK) k_list_filter(ListFilter a) {
+  constexpr int K = SP - 1;
+  __shared__ int4 T[DEV_MAX_L + 1];
+  __shared__ uint64_t BN[(K > 0 ? K : 1) * DEV_MAX_L];
+  __shared__ uint32_t filled;
+  const ScnPtr scn = as_const(a.scn);
+  const TabPtr tab = as_const(a.tab);
+  const FamPtr ff = &tab->fam[STRAT];
+  const int L = scn->L;
+  const bool bounded = a.incumbent != nullptr && a.costs_out == nullptr;
+  const uint64_t incumbent = bounded ? umin64(a.incumbent0, __hip_atomic_load(a.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : ~0ull;
+  for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
+  if (a.cuts == nullptr)
+    for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
+  if (threadIdx.x == 0) filled = 0;
+  __syncthreads();
+  const uint32_t region = blockIdx.x * ((uint32_t)a.tiles * BLOCK);
+  for (int tile = 0; tile < a.tiles; ++tile) {
+    const uint32_t gid = region + tile * BLOCK + threadIdx.x;
+    if (gid - threadIdx.x >= a.n) break;                        // uniform: this tile and the next ones are empty
+    const bool live = gid < a.n;
+    int c[SP + 1];
+    c[0] = 0;
+    c[SP] = L;
+    bool valid = live;
+    if (a.cuts != nullptr) {
+      // explicit cut positions; a row that does not increase strictly within 1..L-1 is replaced by 1..K
+      const uint8_t *row = a.cuts + (size_t)(live ? gid : 0) * K;
+      int prev = 0;
+#pragma unroll
+      for (int i = 1; i <= K; ++i) {
+        c[i] = row[i - 1];
+        valid = valid && c[i] > prev && c[i] <= L - 1;
+        prev = c[i];
+      }
+      if (!valid) {
+#pragma unroll
+        for (int i = 1; i <= K; ++i) c[i] = i;
+      }
+    } else {
+      uint64_t rem = live ? a.ranks[gid] : 0;
+      valid = live && rem < scn->fam[STRAT].n_part;
+      if (!valid) rem = 0;
+      unrank_digits<K>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+    }
+    int ms[SP], as[SP], cs[SP];
+    {
+      int lo_m = 0, lo_a = 0, lo_c = 0;
+#pragma unroll
+      for (int j = 0; j < SP; ++j) {
+        const int4 hi = T[c[j + 1]];
+        ms[j] = hi.z - lo_m;
+        as[j] = hi.w - lo_a;
+        cs[j] = hi.y - lo_c;
+        lo_m = hi.z;
+        lo_a = hi.w;
+        lo_c = hi.y;
+      }
+    }
+    bool ok = valid && largest_peak<SP, STRAT>(ff, ms, as) <= (int)scn->cap;
+    if (bounded && incumbent != ~0ull && __builtin_amdgcn_ballot_w64(ok) != 0)      // uniform
+      ok = ok && cost_lower_bound<SP, STRAT>(scn, tab, ff, cs, c) <= incumbent;
+    if (live && !ok && a.costs_out != nullptr) a.costs_out[a.pos_base + gid] = CHM_INF_COST;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
+    if (mask != 0) {
+      const int lane = threadIdx.x & 63;
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&filled, (uint32_t)__popcll(mask));
+      base = __shfl(base, 0, 64);
+      if (ok) {
+        const uint32_t slot = region + base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+        uint32_t words[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 1; i <= K; ++i) words[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+        a.cut_list[slot] = make_uint4(words[0], words[1], words[2], words[3]);
+        a.cut_pos[slot] = a.pos_base + gid;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) a.cut_count[blockIdx.x] = filled;
+}
+
+// queued: the variant that compacts the partitions that fit (and, in a bounded search, may still win) through a ring per wave
+template <int STRAT>
+int launch_by_stages(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, hipStream_t st, bool queued = false) {
+#define CHM_CASE(SPV)                                                                         \
+  case SPV:                                                                                   \
+    if (queued && (STRAT == 2 || a.s.incumbent != nullptr))                                   \
+      hipLaunchKernelGGL((k_fast_search<SPV, STRAT, 2>), dim3(blocks), dim3(BLOCK), 0, st, a); \
+    else if (queued)                                                                          \
+      hipLaunchKernelGGL((k_fast_search<SPV, STRAT, (STRAT == 2 ? 2 : 1)>), dim3(blocks), dim3(BLOCK), 0, st, a); \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_fast_search<SPV, STRAT>), dim3(blocks), dim3(BLOCK), tile_bytes, st, a); \
+    return 0;
+// (a ring or list entry holds up to 16 cuts: deeper pipelines have the plain range and rank-list kernel only)
+#define CHM_DEEP(SPV)                                                                         \
+  case SPV:                                                                                   \
+    if (queued || a.cut_list != nullptr) return 1;                                            \
+    hipLaunchKernelGGL((k_fast_search<SPV, STRAT>), dim3(blocks), dim3(BLOCK), tile_bytes, st, a); \
+    return 0;
+  switch (sp) {
+#ifdef CHM_TUNING_SUBSET        // (-DCHM_TUNING_SUBSET: only the stage counts of the 32-card shape, for quick rebuilds while tuning)
+    CHM_CASE(7) CHM_CASE(8)
+#else
+    CHM_CASE(2) CHM_CASE(3) CHM_CASE(4) CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8)
+    CHM_CASE(9) CHM_CASE(10) CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)
+    CHM_DEEP(17) CHM_DEEP(18) CHM_DEEP(19) CHM_DEEP(20) CHM_DEEP(21) CHM_DEEP(22) CHM_DEEP(23) CHM_DEEP(24) CHM_DEEP(25) CHM_DEEP(26) CHM_DEEP(27) CHM_DEEP(28) CHM_DEEP(29) CHM_DEEP(30) CHM_DEEP(31) CHM_DEEP(32)
+#endif
+    default: return 1;
+  }
+#undef CHM_DEEP
+#undef CHM_CASE
+}
+
+template <int STRAT>
+int filter_by_stages(int sp, const ListFilter &a, uint32_t blocks, hipStream_t st) {
+#define CHM_CASE(SPV)                                                                         \
+  case SPV:                                                                                   \
+    hipLaunchKernelGGL((k_list_filter<SPV, STRAT>), dim3(blocks), dim3(BLOCK), 0, st, a);      \
+    return 0;
+  switch (sp) {
+#ifdef CHM_TUNING_SUBSET        // (-DCHM_TUNING_SUBSET: only the stage counts of the 32-card shape, for quick rebuilds while tuning)
+    CHM_CASE(7) CHM_CASE(8)
+#else
+    CHM_CASE(2) CHM_CASE(3) CHM_CASE(4) CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8)
+    CHM_CASE(9) CHM_CASE(10) CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)
+#endif
+    default: return 1;
+  }
+#undef CHM_CASE
+}
+
+}  // namespace
+
+#endif
