@@ -38,6 +38,7 @@ struct FastClass {
 
 struct FastFamily {
   int32_t n_cls;
+  int32_t n_time;                 // classes that can be the slowest: the first n_time (see fast_select)
   int32_t fixed_step;             // strategy 1: step time of the untouched pipelines
   int32_t w0[DEV_MAX_S + 1];      // memory prefix at the fault-free stage bounds
   int32_t w_total;                // memory of the whole model
@@ -98,6 +99,9 @@ struct FastState {
   size_t vec_words = 0;                     // size of the vector table
   const DevScenario *d_scn = nullptr;       // the handle's device tables (for that later build)
   const uint64_t *d_comp = nullptr;
+  // search by halves, per strategy: records of the upper halves and first items (a few MB), laid out by the first search
+  uint32_t *d_upper[3] = {nullptr, nullptr, nullptr};
+  bool upper_ready[3] = {false, false, false};
   // scratch of explicit lists, LIST_SUB entries at a time; allocated when first needed
   void *d_cut_list = nullptr;               // [entry] cut positions of the entries that fit in memory, 16 bytes each
   uint32_t *d_cut_pos = nullptr;            // [entry] their list positions
@@ -153,6 +157,22 @@ struct ListFilter {
   uint64_t incumbent0;          // a cost known before the call (see SearchLaunch::incumbent0)
 };
 
+// Exhaustive search of a whole family by halves (chm_halves_kernel.h).
+struct HalvesItems {
+  int4 prefix[DEV_MAX_L + 1];   // prefix sums: forward, forward + backward, static memory, activation memory
+  uint32_t first[DEV_MAX_L];    // per last lower cut, its first wavefront item
+  uint32_t binom[DEV_MAX_S * DEV_MAX_L];    // row i - 1: C(x, i), 0 < i <= lower cuts
+};
+struct HalvesLaunch {
+  SearchLaunch s;               // result = words of the family's first chunk
+  const FastTables *tab;
+  uint32_t *upper;              // records of the upper halves
+  HalvesItems *items;
+  uint32_t n_upper, n_items;
+  uint32_t chunk;               // upper halves per item
+  uint32_t chunk_words;         // words from one chunk's argmin words to the next chunk's
+};
+
 // Bounded search, candidate path.  Every term of the lower bound of a plan's cost belongs to one stage
 // (micro-batches x its time + the time of the layers ahead of it, its memory) or, under redundant computation,
 // to one node's pair of adjacent stages, and each is monotone in where the stage (or pair) starts: with its end
@@ -204,9 +224,23 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
 int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
 int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
+int chmk_halves_s0(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s1(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s2(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_words_s0(int up, int n_cls);     // words of one upper half's record
+int chmk_halves_words_s1(int up, int n_cls);
+int chmk_halves_words_s2(int up, int n_cls);
 int chmk_list_filter_s0(int sp, const ListFilter &a, uint32_t blocks, void *stream);
 int chmk_list_filter_s1(int sp, const ListFilter &a, uint32_t blocks, void *stream);
 int chmk_list_filter_s2(int sp, const ListFilter &a, uint32_t blocks, void *stream);
+// Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
+// halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
+// search, only for what chm_halves_kernel.h says.  may_allocate = false: only with tables that are already there.  Same
+// return convention as fast_search (positive: not covered, or smaller than what the range search does as fast).
+// fast_halves_covers: whether it takes the family at all.
+bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);
+int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
+                       bool may_allocate, void *stream);
 // Sampled share of partitions of a strategy that pass the memory filter (1.0 where no sample applies).
 float fast_fit_share(FastState *f, const DevScenario &h, int strategy);
 // Scores plan indices [local_first, local_first+count) of the rerouting family (indices local to

@@ -436,9 +436,23 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
     ff.lb_prefix = (2 * (h.pf[h.L] + h.pb[h.L]) < (1ll << 24)) && ((int64_t)(h.D * h.M + h.S) * 2 * (h.pf[h.L] + h.pb[h.L]) < (1ll << 31)) ? 1 : 0;
     if (k == 0 && h.allreduce > 0 && h.L > 64) continue;     // colour masks of the specialised kernel hold 64 colours
     for (int j = 0; j <= h.S; ++j) ff.w0[j] = (int32_t)h.pw[h.p0[j]];
+    // Re-partition at nominal speed: the chains are alike and differ in their micro-batches alone, more of which never take
+    // less time (every term of pipeline_time grows with M): the class with the most goes first and is the only one timed.
+    std::vector<int> order;
+    for (int ci = 0; ci < fam.n_cls; ++ci) order.push_back(ci);
+    ff.n_time = fam.n_cls;
+    if (k == 1 && fam.n_cls > 0) {
+      bool nominal = true;
+      for (int ci = 0; ci < fam.n_cls; ++ci)
+        for (int j = 0; j < fam.cls[ci].n; ++j) nominal = nominal && fam.cls[ci].q[j] == 65536u;
+      if (nominal) {
+        std::stable_sort(order.begin(), order.end(), [&fam](int a, int b) { return fam.cls[a].M > fam.cls[b].M; });
+        ff.n_time = 1;
+      }
+    }
     uint32_t q_all = 65536;
     for (int ci = 0; ci < fam.n_cls && ok; ++ci) {
-      const DevClass &c = fam.cls[ci];
+      const DevClass &c = fam.cls[order[ci]];
       FastClass &fc = ff.cls[ci];
       fc.n = c.n; fc.M = c.M; fc.comm_total = (int32_t)((c.n - 1) * h.comm);
       fc.dead = 0;
@@ -837,6 +851,73 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
   return a.costs_out == nullptr && h.fam[a.strategy].stages <= PACKED_MAX_STAGES;
 }
 
+namespace {
+// Partitions from which a family is searched by halves.  Below, its seeds, its first search's table and the fixed cost of
+// a wavefront (its lower half, a round of 32 upper halves) weigh more than the partitions: 1.5 M partitions of 6 stages took
+// 23 + 12 us by halves and take 17 in the range kernel, 10.7 M of 7 stages 35 + 12 by halves and 70.
+constexpr uint64_t HALVES_FROM = 1ull << 21;
+// bytes a table of upper halves may take (one per strategy and handle, kept): three cuts up to here, else two
+constexpr uint64_t HALVES_TABLE = 8ull << 20;
+}  // namespace
+
+bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_t partitions) {
+  if (k < 0 || k > 2 || !f->usable[k] || partitions != h.fam[k].n_part || partitions < HALVES_FROM) return false;
+  const FastFamily &ff = f->h_tables.fam[k];
+  const int sp = h.fam[k].stages;
+  if (sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return false;
+  for (int ci = 0; ci < ff.n_cls; ++ci)
+    if (!ff.cls[ci].unit || ff.cls[ci].M < sp) return false;
+  if (ff.n_time > (k == 0 ? 3 : 1)) return false;
+  for (int s = 0; k == 2 && s < h.n_aff; ++s)
+    if (f->h_tables.even_share[s] == 0) return false;
+  return true;
+}
+
+int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
+                       bool may_allocate, void *stream) {
+  const int k = a.strategy;
+  if (!fast_halves_covers(f, h, k, partitions)) return 1;
+  const FastFamily &ff = f->h_tables.fam[k];
+  const int sp = h.fam[k].stages, L = h.L;
+  HalvesLaunch hl;
+  hl.s = a;
+  hl.tab = f->d_tables;
+  hl.chunk_words = chunk_words;
+  for (int up = 3; up >= 2; --up) {
+    const int H = sp - 1 - up;
+    const uint64_t n_upper = h.binom[up][L - 1 - H];
+    const int words = k == 0 ? chmk_halves_words_s0(up, ff.n_time) : k == 1 ? chmk_halves_words_s1(up, ff.n_time) : chmk_halves_words_s2(up, ff.n_time);
+    const uint64_t bytes = n_upper * (uint64_t)words * 4 + sizeof(HalvesItems);
+    if (bytes > HALVES_TABLE) continue;
+    // wavefront steps (64 lower halves x one upper half), cut into items of `chunk` upper halves
+    uint64_t steps = 0;
+    for (int v = H; v <= L - 1 - up; ++v) {
+      if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return 1;
+      steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
+    }
+    hl.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(512, steps / 32768));
+    uint64_t items = 0;
+    for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hl.chunk - 1) / hl.chunk);
+    if (items >= (1ull << 31)) return 1;
+    hl.n_items = (uint32_t)items;
+    hl.n_upper = (uint32_t)n_upper;
+    if (!f->d_upper[k]) {
+      if (!may_allocate) return 1;
+      if (!pool_take(f->d_upper[k], bytes)) return -1;
+    }
+    hl.upper = f->d_upper[k];
+    hl.items = (HalvesItems *)(f->d_upper[k] + n_upper * (uint64_t)words);     // (records are whole 16 bytes)
+    const bool build = !f->upper_ready[k];
+    const int rc = k == 0 ? chmk_halves_s0(sp, up, ff.n_time, hl, build, stream)
+                   : k == 1 ? chmk_halves_s1(sp, up, ff.n_time, hl, build, stream) : chmk_halves_s2(sp, up, ff.n_time, hl, build, stream);
+    if (rc) return rc;
+    if (hipGetLastError() != hipSuccess) return -1;
+    f->upper_ready[k] = true;
+    return 0;
+  }
+  return 1;
+}
+
 int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void *stream) {
   if (a.strategy < 0 || a.strategy > 2 || !f->usable[a.strategy]) return 1;
   if (a.part_count == 0) return 0;
@@ -954,6 +1035,7 @@ void fast_release(FastState *f) {
   if (f->d_weights) pool_release(f->d_weights);
   if (f->d_base) pool_release(f->d_base);
   if (f->d_vecs) pool_release(f->d_vecs);
+  for (uint32_t *&p : f->d_upper) { if (p) pool_release(p); p = nullptr; }
   if (f->d_tables) pool_release(f->d_tables);
   f->d_unread = nullptr; f->d_weights = nullptr; f->d_base = nullptr;
   f->d_vecs = nullptr;

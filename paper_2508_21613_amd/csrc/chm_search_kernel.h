@@ -257,8 +257,8 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {
 // C(., i) grows with x, so each digit is found by a four-way search over [i-1, previous digit - 1]:
 // three independent table probes per step, the range shrinks to a quarter; all lanes take the same
 // number of steps (no divergence), `steps` = 3 for up to 64 candidates, 4 for up to 256.
-template <int K>
-__device__ __forceinline__ void unrank_digits(uint64_t rem, int L, int steps, const uint64_t *table, int (&c)[K + 2]) {
+template <int K, typename Rank>
+__device__ __forceinline__ void unrank_digits(Rank rem, int L, int steps, const Rank *table, int (&c)[K + 2]) {
   // table[(i-1) * DEV_MAX_L + x] = C(x, i)
   auto column = [table](int i, int x) { return table[(i - 1) * DEV_MAX_L + x]; };
   int hi = L - 2;
@@ -305,6 +305,55 @@ __device__ __forceinline__ int largest_peak(FamPtr ff, const int (&ms)[SP], cons
     }
   }
   return mmax;
+}
+
+// Weights a plan's nodes must fetch (MiB), from the memory prefix at its cuts: stage sizes minus what their nodes already
+// hold (prefix sums are monotone, so the prefix at the larger of two positions is the larger of the two prefixes).
+// Strategy 1: the largest total over the pipelines that lost nodes, per survivor in stage order or by the
+// least-transfer assignment.
+// (The assignment's outer loop is unrolled for few stages only: 1,024 cells in a row keep the compiler busy for hours.)
+template <int SP, int STRAT>
+__device__ __forceinline__ int missing_weights(FamPtr ff, const int (&wp)[SP + 1]) {
+  if (STRAT != 1) {
+    uint32_t have = 0;
+#pragma unroll
+    for (int j = 0; j < SP; ++j) have += sub_floor(imin32(wp[j + 1], ff->w0[j + 1]), imax32(wp[j], ff->w0[j]));
+    return ff->w_total - (int)have;
+  }
+  int missing = 0;
+  for (int ci = 0; ci < ff->n_cls; ++ci) {
+    const ClsPtr cl = &ff->cls[ci];
+    int have = 0;
+    if (ff->assign) {
+      // least-transfer assignment = largest total overlap of a non-crossing matching of survivors
+      // and new stages (both are in layer order, see best_overlap in chm_kernels.hip); one row of
+      // the two-index recurrence lives in registers.  A negative raw overlap needs no clamp:
+      // diag + (negative) < diag <= G[j], which is already among the operands of the max.
+      constexpr int OUTER = SP > 8 ? 1 : SP;
+      int G[SP + 1];
+#pragma unroll
+      for (int j = 0; j <= SP; ++j) G[j] = 0;
+#pragma unroll OUTER
+      for (int i = 0; i < SP; ++i) {
+        const int wlo_i = cl->wlo[i], whi_i = cl->whi[i];
+        int diag = 0;
+#pragma unroll
+        for (int j = 0; j < SP; ++j) {
+          const int above = G[j + 1];
+          const int cand = diag + (imin32(wp[j + 1], whi_i) - imax32(wp[j], wlo_i));
+          G[j + 1] = imax32(imax32(above, G[j]), cand);
+          diag = above;
+        }
+      }
+      have = G[SP];
+    } else {
+#pragma unroll
+      for (int j = 0; j < SP; ++j)
+        have += (int)sub_floor(imin32(wp[j + 1], cl->whi[j]), imax32(wp[j], cl->wlo[j]));
+    }
+    missing = imax32(missing, ff->w_total - have);
+  }
+  return missing;
 }
 
 // Lower bound of a plan's cost from its cuts c[0..SP] and the forward + backward time cs[] of its stages.
@@ -439,7 +488,7 @@ k_fast_search(FastLaunch a) {
       if (!listed_ok) rem = 0;
     }
     // combinadic digits from the LDS copy of the binomial table
-    unrank_digits<K>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+    unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
   }
 
   const int cap = (int)scn->cap;
@@ -603,17 +652,8 @@ k_fast_search(FastLaunch a) {
     if (!QUEUED) n_fit += (uint32_t)__popcll(ok_mask);
     if (ok_mask != 0) {
       int t_step = ff->fixed_step;
-      int missing = 0;
-      if (STRAT != 1) {
-        // weights the stage-j node must fetch: stage size minus what it already holds; prefix
-        // sums are monotone, so the prefix at max(a,a0) is the max of the two prefixes
-        uint32_t have = 0;
-#pragma unroll
-        for (int j = 0; j < SP; ++j)
-          have += sub_floor(imin32(wp[j + 1], ff->w0[j + 1]), imax32(wp[j], ff->w0[j]));
-        missing = ff->w_total - (int)have;
-      }
-      for (int ci = 0; ci < ff->n_cls; ++ci) {
+      const int missing = missing_weights<SP, STRAT>(ff, wp);
+      for (int ci = 0; ci < ff->n_time; ++ci) {
         const ClsPtr cl = &ff->cls[ci];
         int F[SP], C[SP];
         if (STRAT == 0) {
@@ -638,36 +678,6 @@ k_fast_search(FastLaunch a) {
           }
         }
         t_step = imax32(t_step, pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24));
-        if (STRAT == 1) {
-          int have = 0;
-          if (ff->assign) {
-            // least-transfer assignment = largest total overlap of a non-crossing matching of survivors
-            // and new stages (both are in layer order, see best_overlap in chm_kernels.hip); one row of
-            // the two-index recurrence lives in registers.  A negative raw overlap needs no clamp:
-            // diag + (negative) < diag <= G[j], which is already among the operands of the max.
-            int G[SP + 1];
-#pragma unroll
-            for (int j = 0; j <= SP; ++j) G[j] = 0;
-#pragma unroll
-            for (int i = 0; i < SP; ++i) {
-              const int wlo_i = cl->wlo[i], whi_i = cl->whi[i];
-              int diag = 0;
-#pragma unroll
-              for (int j = 0; j < SP; ++j) {
-                const int above = G[j + 1];
-                const int cand = diag + (imin32(wp[j + 1], whi_i) - imax32(wp[j], wlo_i));
-                G[j + 1] = imax32(imax32(above, G[j]), cand);
-                diag = above;
-              }
-            }
-            have = G[SP];
-          } else {
-#pragma unroll
-            for (int j = 0; j < SP; ++j)
-              have += (int)sub_floor(imin32(wp[j + 1], cl->whi[j]), imax32(wp[j], cl->wlo[j]));
-          }
-          missing = imax32(missing, ff->w_total - have);
-        }
       }
       if (ff->allreduce > 0) {
         // rounds of gradient communication: largest stage on any device, or the ring colouring when nodes hold two stages
@@ -833,7 +843,7 @@ __global__ void __launch_bounds__(BLOCK) k_list_filter(ListFilter a) {
       uint64_t rem = live ? a.ranks[gid] : 0;
       valid = live && rem < scn->fam[STRAT].n_part;
       if (!valid) rem = 0;
-      unrank_digits<K>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+      unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
     }
     int ms[SP], as[SP], cs[SP];
     {

@@ -1,0 +1,65 @@
+"""Exhaustive search of large families by halves (from 2^21 partitions on) against the range kernel over the same space in
+two windows (which test_gpu_random.py and test_closed_forms.py hold against the oracle; test_gpu_full_space.py holds the
+search by halves itself against whole-space results of the oracle), the winner's cost against the oracle: both widths of the upper half, the smallest and largest number of stages, failed nodes that cross between the halves,
+one to three pipeline classes, every modelling option it takes, several chunks, no failure, ties.  Whole numbers,
+compared exactly."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2508_21613_amd import synth
+
+
+def _case(L, PP, DP, M, failed, cap_x=4.0, act=False, **kw):
+    fwd, bwd, mem = synth.layer_tables(17 * L + PP, L)
+    sc = synth.scenario(L, PP, DP, M, fwd, bwd, mem, failed, 150, int(cap_x * mem.sum() / PP), **kw)
+    return synth.with_activations(sc, 5, cap_scale=1.1) if act else sc
+
+
+CASES = {
+    "5 stages, long model": _case(96, 5, 2, 5, [3]),
+    "6 stages, first stage lost": _case(53, 6, 2, 7, [0], cap_x=3.0),
+    "7 stages, options": _case(39, 7, 3, 8, [10], act=True, transfer_assign=1, allreduce_us=400),
+    "8 stages, crossing node lost, three classes": _case(32, 8, 3, 9, [4, 11], transfer_assign=1),
+    "8 stages, every pipeline hit": _case(32, 8, 3, 8, [3, 12, 23], cap_x=3.0),
+    "8 stages, nothing lost": _case(32, 8, 2, 16, []),
+    "11 stages, last stage lost": _case(26, 11, 2, 12, [21], cap_x=3.0),
+    "16 stages": _case(26, 16, 2, 17, [12], cap_x=5.0),
+    "8 stages, chunks of 2^16": _case(32, 8, 2, 8, [7], horizon_steps=1 << 22),
+    "8 stages, equal layers (ties)": dict(_case(32, 8, 2, 8, [6]), fwd_us=np.full(32, 900, np.int32), bwd_us=np.full(32, 1800, np.int32),
+                                          mem_mib=np.full(32, 500, np.int32)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CASES)
+def test_search_by_halves_finds_what_the_range_kernel_finds(name):
+    from paper_2508_21613_amd import binding as B
+    sc = CASES[name]
+    o, g = O.Scenario(sc), B.Scenario(sc)
+    assert max(f["n_part"] for f in g.families) >= 1 << 21
+    g.set_timing(True)
+
+    def range_search(k, first, count):
+        got = g.search_range(k, first, count)
+        return got, g.get_timing()["feasible"][k]
+
+    each = []
+    for f in g.families:
+        k, half = f["strategy"], f["n_part"] // 2
+        (rc_a, a), fit_a = range_search(k, 0, half)
+        (rc_b, b), fit_b = range_search(k, half, f["n_part"] - half)
+        want = (rc_a, a) if rc_a == 0 and (rc_b != 0 or a["cost"] <= b["cost"]) else (rc_b, b)      # ties: the lower rank
+        assert g.search_best(1 << k) == want, k
+        assert g.get_timing()["feasible"][k] == fit_a + fit_b == g.get_timing()["evaluated"][k]
+        if want[0] == 0:
+            assert int(o.score(want[1]["index"], 1)[0]) == want[1]["cost"]
+            each.append(want)
+    best = min(each, key=lambda v: (v[1]["cost"], v[1]["index"]))
+    assert g.search_best(7) == best                      # the tables laid out by the searches before
+    assert g.search_best_static(7) == best
+    fresh = B.Scenario(sc)
+    assert fresh.search_best_static(7) == best           # nothing laid out yet: the range kernels
+    assert fresh.search_best(7) == best
+    g.close()
+    fresh.close()
