@@ -15,10 +15,7 @@ enum {
   FAST_FUSED_R = 4096,       // more vectors than this (all stages): a large reroute space (see FastState::large_reroute)
   FAST_SUB = 1 << 20,        // partitions per pass of the cost store of plan indices (bounds its scratch memory: 136 MB;
                              // the scratch is sized for the passes actually asked for and grows when needed)
-  LIST_SUB = 1 << 24,        // list entries per filter + search pass of explicit lists (scratch: 336 MB when a list is that long)
-  LIST_FIRST = 1 << 16,      // entries of the first pass of a bounded list search
-  FILTER_TILES = 16,         // tiles of BLOCK list entries per workgroup = rounds of the search kernel per region
-  FILTER_TILES_BOUNDED = 4   // a bounded search keeps few entries: shorter regions, more workgroups to filter with
+  LIST_FIRST = 1 << 16       // entries of the first launch of a bounded list search
 };
 
 // One pipeline class in the form the specialised kernels read (all int32).
@@ -102,11 +99,6 @@ struct FastState {
   // search by halves, per strategy: records of the upper halves and first items (a few MB), laid out by the first search
   uint32_t *d_upper[3] = {nullptr, nullptr, nullptr};
   bool upper_ready[3] = {false, false, false};
-  // scratch of explicit lists, LIST_SUB entries at a time; allocated when first needed
-  void *d_cut_list = nullptr;               // [entry] cut positions of the entries that fit in memory, 16 bytes each
-  uint32_t *d_cut_pos = nullptr;            // [entry] their list positions
-  uint32_t *d_cut_count = nullptr;          // [workgroup region] how many of its slots are filled
-  uint32_t list_capacity = 0;               // entries the three have room for
   // scratch of the candidate path of the bounded search; grown to what a search needs
   void *d_cand_list = nullptr;              // [candidate] cut positions, 16 bytes each
   uint32_t *d_cand_pos = nullptr;           // [candidate] its index
@@ -121,6 +113,7 @@ struct FastState {
   void *cand_copied = nullptr;              // hipEvent_t: the last copy out of the staging buffer is done
 };
 
+enum SearchVariant { SEARCH_PLAIN, SEARCH_QUEUED, SEARCH_LIST };
 struct FastLaunch {
   SearchLaunch s;
   const FastTables *tab;
@@ -129,32 +122,13 @@ struct FastLaunch {
   // without them and the peer stage times (null: otherwise)
   uint64_t *base_out;
   uint32_t *weights_out;
-  // compacted list mode: workgroup b owns slots [b * per_lane * BLOCK, ...) of cut_list / cut_pos, of which the
-  // first cut_count[b] are filled (by k_list_filter, with the list entries that fit in memory).  In round `it`
-  // lane t evaluates slot it * BLOCK + t: the partition whose cut positions are the bytes of cut_list[slot],
-  // reported under list position cut_pos[slot].  Every lane of every wave has work except in a workgroup's
-  // last round (null: other modes)
+  uint32_t pos_base = 0;        // list mode: list position (chunk-local) of entry 0 of this launch
+  // candidate mode (bounded search): workgroup b owns slots [b * per_lane * BLOCK, ...) of cut_list / cut_pos, of which the
+  // first cut_count[b] are filled.  In round `it` lane t evaluates slot it * BLOCK + t: the partition whose cut positions
+  // are the bytes of cut_list[slot], reported as number cut_pos[slot] (null: other modes)
   const uint4 *cut_list;
   const uint32_t *cut_pos;
   const uint32_t *cut_count;
-};
-
-struct ListFilter {
-  const DevScenario *scn;
-  const FastTables *tab;
-  const uint64_t *ranks;        // list entries of this pass, as partition ranks, or (ranks null)
-  const uint8_t *cuts;          // as rows of stages - 1 cut positions
-  uint32_t n;                   // entries in this pass
-  uint32_t pos_base;            // list position (chunk-local) of entry 0 of this pass
-  int64_t *costs_out;           // chunk-local cost array (nullable)
-  int32_t tiles;                // tiles of BLOCK entries per workgroup
-  uint4 *cut_list;              // [workgroup][tiles * BLOCK]
-  uint32_t *cut_pos;            // likewise
-  uint32_t *cut_count;          // [workgroup] filled slots
-  // bounded search (no cost store): entries whose lower bound of the cost lies above *incumbent (the lowest cost
-  // the passes before this one have evaluated) are dropped like those that do not fit; null = keep all that fit
-  const uint64_t *incumbent;
-  uint64_t incumbent0;          // a cost known before the call (see SearchLaunch::incumbent0)
 };
 
 // Exhaustive search of a whole family by halves (chm_halves_kernel.h).
@@ -221,18 +195,15 @@ int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void 
 // strategy of at most 16 stages without cost store).
 bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch &a);
 // Kernel launchers by strategy (chm_search_s0/1/2.hip): 1 = no instance for this number of stages, else 0.
-int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
-int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
-int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued);
+int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
+int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
+int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_halves_s0(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
 int chmk_halves_s1(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
 int chmk_halves_s2(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
 int chmk_halves_words_s0(int up, int n_cls);     // words of one upper half's record
 int chmk_halves_words_s1(int up, int n_cls);
 int chmk_halves_words_s2(int up, int n_cls);
-int chmk_list_filter_s0(int sp, const ListFilter &a, uint32_t blocks, void *stream);
-int chmk_list_filter_s1(int sp, const ListFilter &a, uint32_t blocks, void *stream);
-int chmk_list_filter_s2(int sp, const ListFilter &a, uint32_t blocks, void *stream);
 // Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
 // halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
 // search, only for what chm_halves_kernel.h says.  may_allocate = false: only with tables that are already there.  Same

@@ -327,14 +327,15 @@ __global__ void __launch_bounds__(BLOCK) k_expand32_lds(ExpandArgs32 a, uint32_t
   }
 }
 
-int launch_by_strategy(int strategy, int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, hipStream_t st, bool queued = false) {
-  return strategy == 0 ? chmk_fast_search_s0(sp, a, blocks, tile_bytes, st, queued)
-         : strategy == 1 ? chmk_fast_search_s1(sp, a, blocks, tile_bytes, st, queued)
-                         : chmk_fast_search_s2(sp, a, blocks, tile_bytes, st, queued);
+int launch_by_strategy(int strategy, int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, hipStream_t st, SearchVariant variant = SEARCH_PLAIN) {
+  return strategy == 0 ? chmk_fast_search_s0(sp, a, blocks, tile_bytes, st, variant)
+         : strategy == 1 ? chmk_fast_search_s1(sp, a, blocks, tile_bytes, st, variant)
+                         : chmk_fast_search_s2(sp, a, blocks, tile_bytes, st, variant);
 }
 
 // most stages the kernels are instantiated for: any search, and one that packs its cuts (bounded, cut lists)
 constexpr int PACKED_MAX_STAGES = 16;
+constexpr uint32_t LIST_TILES = 16;
 bool stages_covered(int sp) { return sp >= 2 && sp <= DEV_MAX_S; }
 
 // Share of uniformly drawn partitions into `sp` stages whose largest per-node peak memory stays within the cap
@@ -545,60 +546,32 @@ bool ensure_scratch(FastState *f, uint64_t parts) {
   return ok;
 }
 
-// scratch of one pass over an explicit list of `entries` entries (at most LIST_SUB); grows when a longer pass comes
-bool ensure_list_scratch(FastState *f, uint32_t entries) {
-  uint32_t need = 1u << 16;
-  while (need < entries) need <<= 1;
-  if (f->d_cut_list && f->d_cut_pos && f->d_cut_count && f->list_capacity >= need) return true;
-  fast_quiesce(f);                                           // what is replaced may still be read by an asynchronous call
-  if (f->d_cut_count) pool_release(f->d_cut_count);
-  if (f->d_cut_pos) pool_release(f->d_cut_pos);
-  if (f->d_cut_list) pool_release(f->d_cut_list);
-  f->d_cut_count = nullptr; f->d_cut_pos = nullptr; f->d_cut_list = nullptr; f->list_capacity = 0;
-  bool ok = pool_take(f->d_cut_list, (size_t)need * sizeof(uint4));
-  ok = ok && pool_take(f->d_cut_pos, (size_t)need * sizeof(uint32_t));
-  ok = ok && pool_take(f->d_cut_count, (size_t)(need / (BLOCK * FILTER_TILES_BOUNDED) + 1) * sizeof(uint32_t));
-  if (ok) f->list_capacity = need;
-  return ok;
-}
-
-// Explicit list of partition ranks: per pass of LIST_SUB entries, filter + compaction, then the search kernel
-// over the entries that fit.
+// Explicit list of partition ranks or cut positions.
 int launch_list(FastState *f, const DevScenario &h, const SearchLaunch &a, hipStream_t st) {
-  if (!ensure_list_scratch(f, std::min<uint32_t>(a.part_count, LIST_SUB))) return -1;
   const int sp = h.fam[a.strategy].stages;
-  // a bounded search prunes the later passes against the best cost of the earlier ones: a short first pass
-  // makes one known early
+  // a bounded search prunes against the best cost evaluated so far: a short first launch makes one known early
   const bool bounded = a.incumbent != nullptr && a.costs_out == nullptr;
   for (uint32_t done = 0; done < a.part_count;) {
-    const uint32_t n = std::min<uint32_t>(bounded && done == 0 ? LIST_FIRST : LIST_SUB, a.part_count - done);
-    const uint32_t tiles = bounded ? FILTER_TILES_BOUNDED : FILTER_TILES;
-    const uint32_t blocks = (n + BLOCK * tiles - 1) / (BLOCK * tiles);   // one workgroup per region, both kernels
-    ListFilter lf;
-    lf.tiles = (int32_t)tiles;
-    lf.incumbent = bounded ? a.incumbent : nullptr;
-    lf.incumbent0 = a.incumbent0;
-    lf.scn = a.scn; lf.tab = f->d_tables; lf.n = n; lf.pos_base = done;
-    lf.ranks = a.ranks ? a.ranks + done : nullptr;
-    lf.cuts = a.cuts ? a.cuts + (size_t)done * (size_t)(sp - 1) : nullptr;
-    lf.costs_out = a.costs_out; lf.cut_list = (uint4 *)f->d_cut_list; lf.cut_pos = f->d_cut_pos; lf.cut_count = f->d_cut_count;
-    int rc = a.strategy == 0 ? chmk_list_filter_s0(sp, lf, blocks, st)
-             : a.strategy == 1 ? chmk_list_filter_s1(sp, lf, blocks, st) : chmk_list_filter_s2(sp, lf, blocks, st);
-    if (rc) return rc;
+    const uint32_t n = bounded && done == 0 ? std::min<uint32_t>(LIST_FIRST, a.part_count) : a.part_count - done;
     FastLaunch fl;
     fl.s = a;
-    fl.s.ranks = nullptr;
-    fl.s.cuts = nullptr;
     fl.s.part_first = 0;
     fl.s.part_count = n;
+    fl.s.ranks = a.ranks ? a.ranks + done : nullptr;
+    fl.s.cuts = a.cuts ? a.cuts + (size_t)done * (size_t)(sp - 1) : nullptr;
+    if (!bounded) fl.s.incumbent = nullptr;
+    fl.pos_base = done;
     fl.tab = f->d_tables;
-    fl.per_lane = tiles;                  // rounds per region
+    // rounds of 64 entries per wavefront: as many as leave eight workgroups to every compute unit, up to LIST_TILES (the ring
+    // is drained once per wavefront, by a wave that is filled in part)
+    fl.per_lane = std::max<uint32_t>(1, std::min<uint32_t>(LIST_TILES, n / (BLOCK * 256 * 8)));
     fl.base_out = nullptr;
     fl.weights_out = nullptr;
-    fl.cut_list = (const uint4 *)f->d_cut_list;
-    fl.cut_pos = f->d_cut_pos;
-    fl.cut_count = f->d_cut_count;
-    rc = launch_by_strategy(a.strategy, sp, fl, blocks, 0, st);
+    fl.cut_list = nullptr;
+    fl.cut_pos = nullptr;
+    fl.cut_count = nullptr;
+    const uint32_t blocks = (n + BLOCK * fl.per_lane - 1) / (BLOCK * fl.per_lane);
+    const int rc = launch_by_strategy(a.strategy, sp, fl, blocks, 0, st, SEARCH_LIST);
     if (rc) return rc;
     if (hipGetLastError() != hipSuccess) return -1;
     done += n;
@@ -626,7 +599,7 @@ int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uin
   uint64_t per = a.part_count / lanes_balanced;
   if (per < 4) per = std::min<uint64_t>(4, a.part_count / lanes_resident);
   per = std::max<uint64_t>(1, std::min<uint64_t>(per, 32));
-  if (a.ranks != nullptr || a.jump_at != 0xffffffffu) per = 1;   // a list has no successor to walk to; a run must not straddle two windows
+  if (a.jump_at != 0xffffffffu) per = 1;               // a run must not straddle two windows
   else if (a.costs_out != nullptr) per = std::min<uint64_t>(per, 8);   // bounds the LDS tile of the cost store
   fl.per_lane = (uint32_t)per;
   const uint32_t tile_bytes = (a.costs_out != nullptr && per > 1) ? (uint32_t)(BLOCK * per * sizeof(int64_t)) : 0u;
@@ -635,12 +608,12 @@ int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uin
   const int sp = h.fam[a.strategy].stages;
   // pure range search of a family in which a good share of the partitions fails the memory filter
   // (a bounded search needs the ring: only there a wave decides what to evaluate before it evaluates)
-  const bool pure_range = a.ranks == nullptr && a.costs_out == nullptr && base_out == nullptr;
+  const bool pure_range = a.costs_out == nullptr && base_out == nullptr;
   const bool queued = pure_range && sp <= PACKED_MAX_STAGES && (a.incumbent != nullptr ||
                                      (a.strategy != 2 && f->queue_mode != 0 &&
                                       (f->queue_mode > 0 || fast_fit_share(f, h, a.strategy) < QUEUE_BELOW_SHARE)));
   if (!queued) { fl.s.incumbent = nullptr; fl.s.evaluated = nullptr; }
-  const int rc = launch_by_strategy(a.strategy, sp, fl, blocks, tile_bytes, st, queued);
+  const int rc = launch_by_strategy(a.strategy, sp, fl, blocks, tile_bytes, st, queued ? SEARCH_QUEUED : SEARCH_PLAIN);
   if (rc) return rc;
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1027,10 +1000,6 @@ void fast_release(FastState *f) {
   if (f->d_cand_list) pool_release(f->d_cand_list);
   f->d_cand_low = nullptr; f->d_cand_ways = nullptr; f->d_cand_count = nullptr; f->d_cand_pos = nullptr; f->d_cand_list = nullptr;
   f->cand_capacity = 0; f->cand_ways_capacity = 0;
-  if (f->d_cut_count) pool_release(f->d_cut_count);
-  if (f->d_cut_pos) pool_release(f->d_cut_pos);
-  if (f->d_cut_list) pool_release(f->d_cut_list);
-  f->d_cut_count = nullptr; f->d_cut_pos = nullptr; f->d_cut_list = nullptr; f->list_capacity = 0;
   if (f->d_unread) pool_release(f->d_unread);
   if (f->d_weights) pool_release(f->d_weights);
   if (f->d_base) pool_release(f->d_base);

@@ -88,8 +88,8 @@ __device__ __forceinline__ uint32_t times(uint32_t x, uint32_t y) { return M24 ?
 template <int N, bool UNI, bool M24>
 __device__ __forceinline__ int pipeline_time_m(const int (&F)[N], const int (&C)[N], ClsPtr cl) {
   const int M = cl->M;
-  uint32_t P[N], U[N], V[N];
-  uint32_t p = 0, max_f = 0, max_b = 0;
+  uint32_t U[N], V[N];
+  uint32_t p = 0, max_f = 0, max_b = 0;              // p = P[s] on the way up, P[j] on the way down
 #pragma unroll
   for (int s = 0; s < N; ++s) {
     const uint32_t f = (uint32_t)F[s], b = (uint32_t)(C[s] - F[s]);
@@ -97,7 +97,6 @@ __device__ __forceinline__ int pipeline_time_m(const int (&F)[N], const int (&C)
     max_f = max_f > f ? max_f : f;
     max_b = max_b > b ? max_b : b;
     const uint32_t after = UNI ? (uint32_t)cl->after[s] : (uint32_t)(N - 1 - s);
-    P[s] = p;
     U[s] = times<M24>(max_b, after) + p;
     V[s] = times<M24>(max_f, after) + p;
   }
@@ -108,8 +107,9 @@ __device__ __forceinline__ int pipeline_time_m(const int (&F)[N], const int (&C)
       su = su > U[j] ? su : U[j];
       sv = sv > V[j] ? sv : V[j];
       const uint32_t k = UNI ? (uint32_t)cl->steady[j] : (uint32_t)(M - N + j);
-      const uint32_t t = times<M24>((uint32_t)C[j], k) + su + (sv - P[j]);
+      const uint32_t t = times<M24>((uint32_t)C[j], k) + su + (sv - p);
       r = r > t ? r : t;
+      p -= (uint32_t)C[j];
     }
   } else {
 #pragma unroll
@@ -118,9 +118,10 @@ __device__ __forceinline__ int pipeline_time_m(const int (&F)[N], const int (&C)
       sv = sv > V[j] ? sv : V[j];
       const int k = UNI ? cl->steady[j] : M - N + j;
       if (k >= 0) {                                  // uniform
-        const uint32_t t = times<M24>((uint32_t)C[j], (uint32_t)k) + su + (sv - P[j]);
+        const uint32_t t = times<M24>((uint32_t)C[j], (uint32_t)k) + su + (sv - p);
         r = r > t ? r : t;
       }
+      p -= (uint32_t)C[j];
     }
   }
   return (int)r + cl->comm_total;
@@ -142,19 +143,20 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[FAST_MAX_P
   float inv_sum = 0.0f;
 #pragma unroll
   for (int i = 0; i < FAST_MAX_P; ++i) {
-    if (i >= peers) break;                           // uniform
-    inv_sum += __builtin_amdgcn_rcpf((float)w[i]);
+    if (i < peers) inv_sum += __builtin_amdgcn_rcpf((float)w[i]);      // uniform
   }
   const float v0 = (float)orphans * __builtin_amdgcn_rcpf(inv_sum) * 0.99999f;
   uint32_t next[FAST_MAX_P];                         // peer i's smallest multiple not taken yet
   uint32_t taken = 0;
 #pragma unroll
   for (int i = 0; i < FAST_MAX_P; ++i) {
-    if (i >= peers) break;
-    uint32_t r = (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));    // (a time of 0 makes v0 0 and this 0)
-    r = r < cap ? r : cap;
-    taken += r;
-    next[i] = r < cap ? __umul24(r + 1, w[i]) : 0xffffffffu;
+    next[i] = 0xffffffffu;
+    if (i < peers) {
+      uint32_t r = (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));  // (a time of 0 makes v0 0 and this 0)
+      r = r < cap ? r : cap;
+      taken += r;
+      next[i] = r < cap ? __umul24(r + 1, w[i]) : 0xffffffffu;
+    }
   }
   uint32_t least = 0;
   const bool capped = cap < orphans;
@@ -162,17 +164,17 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[FAST_MAX_P
     least = 0xffffffffu;
 #pragma unroll
     for (int i = 0; i < FAST_MAX_P; ++i) {
-      if (i >= peers) break;
-      least = least < next[i] ? least : next[i];
+      if (i < peers) least = least < next[i] ? least : next[i];
     }
 #pragma unroll
     for (int i = 0; i < FAST_MAX_P; ++i) {
-      if (i >= peers) break;
-      const bool hit = next[i] == least;
-      taken += hit ? 1u : 0u;
-      uint32_t after = next[i] + w[i];
-      if (capped && after > __umul24(cap, w[i])) after = 0xffffffffu;
-      next[i] = hit ? after : next[i];
+      if (i < peers) {
+        const bool hit = next[i] == least;
+        taken += hit ? 1u : 0u;
+        uint32_t after = next[i] + w[i];
+        if (capped && after > __umul24(cap, w[i])) after = 0xffffffffu;
+        next[i] = hit ? after : next[i];
+      }
     }
   }
   return least;
@@ -286,21 +288,31 @@ __device__ __forceinline__ void unrank_digits(Rank rem, int L, int steps, const 
 // largest peak memory over the nodes of a plan: static + (pipeline length - position) * activations of the
 // most demanding node of every stage (strategy 0: a node holds its stage and its ring successor's)
 template <int SP, int STRAT>
-__device__ __forceinline__ int largest_peak(FamPtr ff, const int (&ms)[SP], const int (&as)[SP]) {
+__device__ __forceinline__ int largest_peak(FamPtr ff, const int (&c)[SP + 1], const int *pw, const int *pa) {
   int mmax = 0;
+  int at[SP + 1];
+  at[0] = 0;
+#pragma unroll
+  for (int j = 1; j <= SP; ++j) at[j] = pw[c[j]];
+  // strategy 0: [c[j], c[j+2]) is two stages; the last node's second one is stage 0
   if (ff->has_act) {
+    int ac[SP + 1];
+    ac[0] = 0;
+#pragma unroll
+    for (int j = 1; j <= SP; ++j) ac[j] = pa[c[j]];
 #pragma unroll
     for (int j = 0; j < SP; ++j) {
       const int coef = ff->mem_coef[j];
-      const int st = STRAT == 0 ? ms[j] + ms[(j + 1) % SP] : ms[j];
-      const int ac = STRAT == 0 ? as[j] + as[(j + 1) % SP] : as[j];
-      const int m = st + (int)__umul24((uint32_t)ac, (uint32_t)(coef < 0 ? 0 : coef));
+      const int e = STRAT == 0 ? (j + 2 <= SP ? j + 2 : SP) : j + 1;
+      const int w = at[e] - at[j] + (STRAT == 0 && j == SP - 1 ? at[1] : 0), a = ac[e] - ac[j] + (STRAT == 0 && j == SP - 1 ? ac[1] : 0);
+      const int m = w + (int)__umul24((uint32_t)a, (uint32_t)(coef < 0 ? 0 : coef));
       mmax = imax32(mmax, coef < 0 ? 0 : m);
     }
   } else {
 #pragma unroll
     for (int j = 0; j < SP; ++j) {
-      const int m = STRAT == 0 ? ms[j] + ms[(j + 1) % SP] : ms[j];
+      const int e = STRAT == 0 ? (j + 2 <= SP ? j + 2 : SP) : j + 1;
+      const int m = at[e] - at[j] + (STRAT == 0 && j == SP - 1 ? at[1] : 0);
       mmax = imax32(mmax, ff->mem_coef[j] < 0 ? 0 : m);
     }
   }
@@ -426,6 +438,19 @@ __device__ __forceinline__ uint64_t cost_lower_bound(ScnPtr scn, TabPtr tab, Fam
     return (uint64_t)scn->K * (uint32_t)lb + (uint64_t)scn->reconf[STRAT];
 }
 
+// forward and forward + backward time of stage `sa` (uniform)
+template <int SP>
+__device__ __forceinline__ int2 stage_times(const int2 *tc, const int (&c)[SP + 1], int sa) {
+  int lo = c[0], hi = c[1];
+#pragma unroll
+  for (int j = 1; j < SP; ++j) {
+    lo = sa == j ? c[j] : lo;
+    hi = sa == j ? c[j + 1] : hi;
+  }
+  const int2 a = tc[lo], b = tc[hi];
+  return make_int2(b.x - a.x, b.y - a.y);
+}
+
 // Entries of a wave's queue of partitions that fit (QUEUED kernels): a ring of twice the wave width,
 // since a round appends at most 64 entries to fewer than 64 waiting ones.
 constexpr int QCAP = 128;
@@ -445,13 +470,15 @@ constexpr int QCAP = 128;
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
 // spilled bytes per lane at 8 stages and 4 % of its time).
 template <int SP, int STRAT, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= 5 ? 5 : SP <= 9 ? 4 : SP <= 14 ? 3 : 2)))
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= 5 ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : 2)))
 k_fast_search(FastLaunch a) {
-  constexpr bool QUEUED = MODE >= 1;
+  constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
   __shared__ uint4 q_cuts[QUEUED ? (BLOCK / 64) * QCAP : 1];
   __shared__ uint32_t q_pos[QUEUED ? (BLOCK / 64) * QCAP : 1];
-  __shared__ int4 T[DEV_MAX_L + 1];            // prefix sums: forward, forward + backward, static memory, activation memory
+  // prefix sums: forward and forward + backward; static memory; activation memory
+  __shared__ int2 TC[DEV_MAX_L + 1];
+  __shared__ int PW[DEV_MAX_L + 1], PA[DEV_MAX_L + 1];
   __shared__ uint64_t BN[(K > 0 ? K : 1) * DEV_MAX_L];   // BN[(i-1)*128 + x] = C(x, i), i = 1..K
   __shared__ uint64_t wave_keys[BLOCK / 64];
   __shared__ uint32_t wave_fit[BLOCK / 64];
@@ -464,14 +491,18 @@ k_fast_search(FastLaunch a) {
   const bool compact = !QUEUED && a.cut_list != nullptr;
   const uint32_t n_slots = compact ? a.cut_count[blockIdx.x] : 0u;       // filled slots of this workgroup's region
   if (compact && n_slots == 0) return;
-  for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
-  if (!compact)                                                 // a compacted list needs no unranking
+  for (int i = threadIdx.x; i <= L; i += BLOCK) {
+    TC[i] = make_int2((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]));
+    PW[i] = (int)scn->pw[i];
+    PA[i] = (int)scn->pa[i];
+  }
+  if (!compact && !(LIST && a.s.cuts != nullptr))               // positions given as cuts need no unranking
     for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
   __syncthreads();
 
   const uint32_t lane_id = blockIdx.x * BLOCK + threadIdx.x;
   const uint32_t run_first = lane_id * a.per_lane;                       // chunk-local (a chunk holds at most 2^30 partitions)
-  const uint32_t run_len = (compact || run_first >= a.s.part_count) ? 0u
+  const uint32_t run_len = (LIST || compact || run_first >= a.s.part_count) ? 0u
                            : (uint32_t)(a.s.part_count - run_first < a.per_lane ? a.s.part_count - run_first : a.per_lane);
   const uint32_t region = blockIdx.x * a.per_lane * BLOCK;               // compact mode: first slot of this workgroup
 
@@ -479,14 +510,8 @@ k_fast_search(FastLaunch a) {
   int c[SP + 1];
   c[0] = 0;
   c[SP] = L;
-  bool listed_ok = true;
-  if (!compact) {
+  if (!compact && !LIST) {
     uint64_t rem = run_len ? a.s.part_first + run_first + (run_first >= a.s.jump_at ? a.s.jump_by : 0) : 0;   // idle lanes walk from rank 0: always valid cuts
-    if (!QUEUED && a.s.ranks != nullptr && run_len) {            // list mode (one partition per lane)
-      rem = a.s.ranks[run_first];
-      listed_ok = rem < scn->fam[STRAT].n_part;
-      if (!listed_ok) rem = 0;
-    }
     // combinadic digits from the LDS copy of the binomial table
     unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
   }
@@ -499,7 +524,7 @@ k_fast_search(FastLaunch a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t q_head = 0, q_tail = 0;        // wave-uniform: entries [q_head, q_tail) of the wave's ring wait
   // bounded search: the lowest cost evaluated so far, by this wave or (as of its last look) by any other
-  const bool bounded = MODE == 2 && a.s.incumbent != nullptr;
+  const bool bounded = MODE >= 2 && a.s.incumbent != nullptr;
   uint64_t incumbent = ~0ull;
   uint32_t n_eval = 0;                    // wave-uniform count of partitions whose recurrences were run
   if (bounded) incumbent = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -510,7 +535,7 @@ k_fast_search(FastLaunch a) {
   // contributes M x its time + the time of all layers ahead of it, whatever the lower cuts are.  If that
   // alone lies above the incumbent for every lane, the wave has nothing to look at.
   bool wave_dead = false;
-  if (bounded && K >= 2) {
+  if (MODE == 2 && bounded && K >= 2) {
     uint64_t offset = 0;
     int first_fixed = SP;                   // stages first_fixed.. are the same throughout the run
 #pragma unroll
@@ -521,7 +546,7 @@ k_fast_search(FastLaunch a) {
     }
     int pc[SP + 1];                         // forward + backward time of the layers ahead of stage s
 #pragma unroll
-    for (int s2 = 1; s2 <= SP; ++s2) pc[s2] = T[c[s2]].y;
+    for (int s2 = 1; s2 <= SP; ++s2) pc[s2] = TC[c[s2]].y;
     int lb = ff->fixed_step;
     for (int ci = 0; ci < ff->n_cls; ++ci) {
       const ClsPtr cl = &ff->cls[ci];
@@ -556,41 +581,78 @@ k_fast_search(FastLaunch a) {
     if (QUEUED) {
       if (it < a.per_lane) {              // uniform; the extra round only drains the ring
         // ---- filter the lane's next partition and append it to the ring if it fits
-        int ms[SP], as[SP], cs[SP];           // cs: forward + backward time per stage
-        {
-          int lo_m = 0, lo_a = 0, lo_c = 0;
+        uint32_t words[4] = {0, 0, 0, 0};     // its cut positions, a byte each
+        bool valid = true;
+        if (LIST) {
+          // tile `it` of this workgroup's part of the list: neighbouring lanes read neighbouring entries
+          const uint32_t entry = (blockIdx.x * a.per_lane + it) * BLOCK + threadIdx.x;
+          live = entry < a.s.part_count;
+          pos = a.pos_base + entry;
+          if (a.s.cuts != nullptr) {
+            const uint64_t at = (uint64_t)(live ? entry : 0) * K;
+            if (at + 16 <= (uint64_t)a.s.part_count * K) {
+              __builtin_memcpy(words, a.s.cuts + at, 16);          // (unaligned; bytes behind the row are not looked at)
+            } else {
+              for (int i = 0; i < K; ++i) {
+                const uint32_t b = (uint32_t)a.s.cuts[at + i] << (8 * (i & 3));
+                words[0] |= i < 4 ? b : 0; words[1] |= (i >> 2) == 1 ? b : 0; words[2] |= (i >> 2) == 2 ? b : 0; words[3] |= (i >> 2) == 3 ? b : 0;
+              }
+            }
+            // a row that does not increase strictly within 1..L-1 does not fit; 1..K stands in for it
+            int prev = 0;
 #pragma unroll
-          for (int j = 0; j < SP; ++j) {
-            const int4 hi = T[c[j + 1]];
-            ms[j] = hi.z - lo_m;
-            as[j] = hi.w - lo_a;
-            cs[j] = hi.y - lo_c;
-            lo_m = hi.z;
-            lo_a = hi.w;
-            lo_c = hi.y;
+            for (int i = 1; i <= K; ++i) {
+              const int ci = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+              valid = valid && ci > prev;
+              prev = ci;
+            }
+            valid = valid && prev <= L - 1;
+            const uint32_t first[4] = {0x04030201u, 0x08070605u, 0x0c0b0a09u, 0x000f0e0du};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) words[w] = valid ? words[w] : first[w];
+#pragma unroll
+            for (int i = 1; i <= K; ++i) c[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+          } else {
+            uint64_t rem = live ? a.s.ranks[entry] : 0;
+            valid = rem < scn->fam[STRAT].n_part;
+            if (!valid) rem = 0;
+            unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
           }
         }
-        bool fits = live && largest_peak<SP, STRAT>(ff, ms, as) <= cap;
+        bool fits = live && valid && largest_peak<SP, STRAT>(ff, c, PW, PA) <= cap;
         const uint64_t in_memory = __builtin_amdgcn_ballot_w64(fits);
-        n_fit += (uint32_t)__popcll(in_memory);
+        if (!LIST) n_fit += (uint32_t)__popcll(in_memory);
         if (bounded && in_memory != 0) {      // uniform; nothing to bound where nothing fits
+          int cs[SP];                           // forward + backward time per stage
+          int before = 0;
+#pragma unroll
+          for (int j = 0; j < SP; ++j) {
+            const int behind = TC[c[j + 1]].y;
+            cs[j] = behind - before;
+            before = behind;
+          }
           const uint64_t lb_cost = cost_lower_bound<SP, STRAT>(scn, tab, ff, cs, c);
           fits = fits && lb_cost <= incumbent;
         }
         const uint64_t fit_mask = __builtin_amdgcn_ballot_w64(fits);
+        if (LIST) {
+          n_fit += (uint32_t)__popcll(fit_mask);      // (of a bounded search: those that pass the bound too)
+          if (a.s.costs_out != nullptr && live && !fits) a.s.costs_out[pos] = CHM_INF_COST;
+        }
         if (fits) {
           const uint32_t slot = (uint32_t)wave * QCAP + ((q_tail + (uint32_t)__popcll(fit_mask & ((1ull << lane) - 1ull))) & (QCAP - 1));
-          uint32_t words[4] = {0, 0, 0, 0};
+          if (!LIST || a.s.cuts == nullptr) {
 #pragma unroll
-          for (int i = 1; i <= K; ++i) words[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+            for (int i = 1; i <= K; ++i) words[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+          }
           q_cuts[slot] = make_uint4(words[0], words[1], words[2], words[3]);
           q_pos[slot] = (uint32_t)pos;
         }
         q_tail += (uint32_t)__popcll(fit_mask);
         // next partition of the run
-        bool done = false;
+        bool done = LIST;
 #pragma unroll
-        for (int i = 1; i <= K; ++i) {
+        for (int i = 1; i <= K && !LIST; ++i) {
           const bool can = c[i] + 1 < c[i + 1];
           c[i] = done ? c[i] : (can ? c[i] + 1 : i);
           done = done || can;
@@ -625,48 +687,48 @@ k_fast_search(FastLaunch a) {
 #pragma unroll
       for (int i = 1; i <= K; ++i) ce[i] = c[i];
     }
-    // ---- stage sums from the LDS prefix table (strategy 0: of a node, which runs its stage and its ring successor's)
-    int fs[SP], cs[SP], ms[SP], as[SP];
-    int wp[SP + 1];                         // memory prefix at the cuts
-    {
-      int pf[SP + 1], pc[SP + 1], pa[SP + 1];
-      pf[0] = pc[0] = pa[0] = wp[0] = 0;
-#pragma unroll
-      for (int j = 1; j <= SP; ++j) {
-        const int4 hi = T[ce[j]];
-        pf[j] = hi.x; pc[j] = hi.y; wp[j] = hi.z; pa[j] = hi.w;
-      }
-#pragma unroll
-      for (int j = 0; j < SP; ++j) {
-        fs[j] = pf[j + 1] - pf[j];
-        cs[j] = pc[j + 1] - pc[j];
-        ms[j] = wp[j + 1] - wp[j];
-        as[j] = pa[j + 1] - pa[j];
-      }
-    }
     // ---- memory filter
     // (QUEUED: every entry of the ring has passed it already)
-    const bool ok = QUEUED ? live : ((largest_peak<SP, STRAT>(ff, ms, as) <= cap) && live && listed_ok);
+    const bool ok = QUEUED ? live : (largest_peak<SP, STRAT>(ff, ce, PW, PA) <= cap && live);
     uint64_t cost = (uint64_t)CHM_INF_COST;
     const uint64_t ok_mask = __builtin_amdgcn_ballot_w64(ok);
     if (!QUEUED) n_fit += (uint32_t)__popcll(ok_mask);
     if (ok_mask != 0) {
       int t_step = ff->fixed_step;
-      const int missing = missing_weights<SP, STRAT>(ff, wp);
+      int missing;
+      {
+        int wp[SP + 1];                     // memory prefix at the cuts
+        wp[0] = 0;
+#pragma unroll
+        for (int j = 1; j <= SP; ++j) wp[j] = PW[ce[j]];
+        missing = missing_weights<SP, STRAT>(ff, wp);
+      }
+      // Times per pipeline class.  The stage sums are read from the LDS table again for every class: at 16 stages keeping them
+      // for the next class costs a wave per SIMD (two pipelines of 16 stages alike or not, 168 registers and spills).
       for (int ci = 0; ci < ff->n_time; ++ci) {
         const ClsPtr cl = &ff->cls[ci];
         int F[SP], C[SP];
-        if (STRAT == 0) {
-          const uint32_t dead = cl->dead;
+        {
+          // (the compiler is not to know that these reads are the same for every class)
+#pragma unroll
+          for (int j = 1; j <= K; ++j) asm volatile("" : "+v"(ce[j]));
+          int2 t[SP + 1];
+          t[0] = make_int2(0, 0);
+#pragma unroll
+          for (int j = 1; j <= SP; ++j) t[j] = TC[ce[j]];
+          const uint32_t dead = STRAT == 0 ? cl->dead : 0u;
 #pragma unroll
           for (int j = 0; j < SP; ++j) {
-            const int keep = ((dead >> j) & 1u) ? 0 : -1;            // uniform
-            F[j] = (fs[j] + fs[(j + 1) % SP]) & keep;
-            C[j] = (cs[j] + cs[(j + 1) % SP]) & keep;
+            const int e = STRAT == 0 ? (j + 2 <= SP ? j + 2 : SP) : j + 1;      // (strategy 0: a node runs two stages)
+            F[j] = t[e].x - t[j].x;
+            C[j] = t[e].y - t[j].y;
+            if (STRAT == 0) {
+              if (j == SP - 1) { F[j] += t[1].x; C[j] += t[1].y; }
+              const int keep = ((dead >> j) & 1u) ? 0 : -1;            // uniform
+              F[j] &= keep;
+              C[j] &= keep;
+            }
           }
-        } else {
-#pragma unroll
-          for (int j = 0; j < SP; ++j) { F[j] = fs[j]; C[j] = cs[j]; }
         }
         if (!cl->unit) {
 #pragma unroll
@@ -694,14 +756,8 @@ k_fast_search(FastLaunch a) {
       if (STRAT == 2 && (QUEUED || a.base_out == nullptr)) {
         // least penalty over the reroute vectors of every stage that lost nodes
         for (int st = 0; st < scn->n_aff; ++st) {
-          const int sa = scn->aff_stage[st];
-          int f_st = fs[0], c_st = cs[0];
-#pragma unroll
-          for (int j = 1; j < SP; ++j) {
-            f_st = sa == j ? fs[j] : f_st;
-            c_st = sa == j ? cs[j] : c_st;
-          }
-          t_step += (int)stage_penalty(scn, tab, st, f_st, c_st - f_st);
+          const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
+          t_step += (int)stage_penalty(scn, tab, st, t.x, t.y - t.x);
         }
       }
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
@@ -709,17 +765,11 @@ k_fast_search(FastLaunch a) {
         if (ok) {
           uint32_t *wout = a.weights_out + (size_t)(run_first + it) * (DEV_MAX_AFF * 8);
           for (int st = 0; st < scn->n_aff; ++st) {
-            const int sa = scn->aff_stage[st];
-            int f_st = fs[0], c_st = cs[0];
-#pragma unroll
-            for (int j = 1; j < SP; ++j) {
-              f_st = sa == j ? fs[j] : f_st;
-              c_st = sa == j ? cs[j] : c_st;
-            }
+            const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
             const int p = scn->aff_peers[st];
             for (int i = 0; i < p; ++i) {
               const uint32_t q = scn->aff_q[st][i];
-              wout[st * 8 + i] = peer_time(f_st, c_st - f_st, q);
+              wout[st * 8 + i] = peer_time(t.x, t.y - t.x, q);
             }
           }
         }
@@ -742,6 +792,7 @@ k_fast_search(FastLaunch a) {
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr && ok) a.base_out[run_first + it] = cost;
     }
     if (!QUEUED && STRAT == 2 && a.base_out != nullptr && !ok && it < run_len) a.base_out[run_first + it] = ~0ull;
+    if (LIST && a.s.costs_out != nullptr && live) a.s.costs_out[pos] = (int64_t)cost;
     if (!QUEUED && a.s.costs_out != nullptr) {
       // per_lane == 1: the store is coalesced as it is; longer runs go through an LDS tile
       // (laid out in output order) and are written out together after the loop
@@ -782,7 +833,7 @@ k_fast_search(FastLaunch a) {
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; evaluated += wave_eval[i]; }
     if (fit) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
-    if (bounded && evaluated) atomicAdd((unsigned long long *)a.s.evaluated + slot, (unsigned long long)evaluated);
+    if (MODE == 2 && bounded && evaluated) atomicAdd((unsigned long long *)a.s.evaluated + slot, (unsigned long long)evaluated);
     // a search over a list of candidates of a bounded search makes its best cost known to what follows
     if (!QUEUED && a.s.incumbent != nullptr && k != CHM_KEY_NONE)
       atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)(k >> a.s.idx_bits));
@@ -790,146 +841,41 @@ k_fast_search(FastLaunch a) {
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// explicit lists: memory filter and compaction
-// ---------------------------------------------------------------------------------------
-// One lane per list entry: cut positions (given, or unranked), stage memory sums, memory filter.  An entry
-// that does not fit (or is malformed) gets its cost (infeasible) right away; the others are appended to the
-// workgroup's own region of a compact list as (cut positions packed into 16 bytes, list position).  Slots are
-// handed out through a counter in LDS: atomics of many workgroups on one global counter would serialise (about
-// 10 ns each).  The search kernel then runs over every region with all lanes busy.
-
-template <int SP, int STRAT>
-__global__ void __launch_bounds__(BLOCK) k_list_filter(ListFilter a) {
-  constexpr int K = SP - 1;
-  __shared__ int4 T[DEV_MAX_L + 1];
-  __shared__ uint64_t BN[(K > 0 ? K : 1) * DEV_MAX_L];
-  __shared__ uint32_t filled;
-  const ScnPtr scn = as_const(a.scn);
-  const TabPtr tab = as_const(a.tab);
-  const FamPtr ff = &tab->fam[STRAT];
-  const int L = scn->L;
-  const bool bounded = a.incumbent != nullptr && a.costs_out == nullptr;
-  const uint64_t incumbent = bounded ? umin64(a.incumbent0, __hip_atomic_load(a.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : ~0ull;
-  for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
-  if (a.cuts == nullptr)
-    for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
-  if (threadIdx.x == 0) filled = 0;
-  __syncthreads();
-  const uint32_t region = blockIdx.x * ((uint32_t)a.tiles * BLOCK);
-  for (int tile = 0; tile < a.tiles; ++tile) {
-    const uint32_t gid = region + tile * BLOCK + threadIdx.x;
-    if (gid - threadIdx.x >= a.n) break;                        // uniform: this tile and the next ones are empty
-    const bool live = gid < a.n;
-    int c[SP + 1];
-    c[0] = 0;
-    c[SP] = L;
-    bool valid = live;
-    if (a.cuts != nullptr) {
-      // explicit cut positions; a row that does not increase strictly within 1..L-1 is replaced by 1..K
-      const uint8_t *row = a.cuts + (size_t)(live ? gid : 0) * K;
-      int prev = 0;
-#pragma unroll
-      for (int i = 1; i <= K; ++i) {
-        c[i] = row[i - 1];
-        valid = valid && c[i] > prev && c[i] <= L - 1;
-        prev = c[i];
-      }
-      if (!valid) {
-#pragma unroll
-        for (int i = 1; i <= K; ++i) c[i] = i;
-      }
-    } else {
-      uint64_t rem = live ? a.ranks[gid] : 0;
-      valid = live && rem < scn->fam[STRAT].n_part;
-      if (!valid) rem = 0;
-      unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
-    }
-    int ms[SP], as[SP], cs[SP];
-    {
-      int lo_m = 0, lo_a = 0, lo_c = 0;
-#pragma unroll
-      for (int j = 0; j < SP; ++j) {
-        const int4 hi = T[c[j + 1]];
-        ms[j] = hi.z - lo_m;
-        as[j] = hi.w - lo_a;
-        cs[j] = hi.y - lo_c;
-        lo_m = hi.z;
-        lo_a = hi.w;
-        lo_c = hi.y;
-      }
-    }
-    bool ok = valid && largest_peak<SP, STRAT>(ff, ms, as) <= (int)scn->cap;
-    if (bounded && incumbent != ~0ull && __builtin_amdgcn_ballot_w64(ok) != 0)      // uniform
-      ok = ok && cost_lower_bound<SP, STRAT>(scn, tab, ff, cs, c) <= incumbent;
-    if (live && !ok && a.costs_out != nullptr) a.costs_out[a.pos_base + gid] = CHM_INF_COST;
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
-    if (mask != 0) {
-      const int lane = threadIdx.x & 63;
-      uint32_t base = 0;
-      if (lane == 0) base = atomicAdd(&filled, (uint32_t)__popcll(mask));
-      base = __shfl(base, 0, 64);
-      if (ok) {
-        const uint32_t slot = region + base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-        uint32_t words[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int i = 1; i <= K; ++i) words[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
-        a.cut_list[slot] = make_uint4(words[0], words[1], words[2], words[3]);
-        a.cut_pos[slot] = a.pos_base + gid;
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) a.cut_count[blockIdx.x] = filled;
-}
-
-// queued: the variant that compacts the partitions that fit (and, in a bounded search, may still win) through a ring per wave
+// Which variant of the search kernel: every lane its own partitions; the partitions that fit (and, in a bounded search, may
+// still win) compacted through a ring per wave; the same fed from an explicit list.
 template <int STRAT>
-int launch_by_stages(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, hipStream_t st, bool queued = false) {
+int launch_by_stages(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, hipStream_t st, SearchVariant variant) {
+  // (the ring of strategy 2 exists with bounds only: without them nothing has shown a use for it)
+  const bool bounds = STRAT == 2 || a.s.incumbent != nullptr;
 #define CHM_CASE(SPV)                                                                         \
   case SPV:                                                                                   \
-    if (queued && (STRAT == 2 || a.s.incumbent != nullptr))                                   \
+    if (variant == SEARCH_LIST)                                                               \
+      hipLaunchKernelGGL((k_fast_search<SPV, STRAT, 3>), dim3(blocks), dim3(BLOCK), 0, st, a); \
+    else if (variant == SEARCH_QUEUED && bounds)                                              \
       hipLaunchKernelGGL((k_fast_search<SPV, STRAT, 2>), dim3(blocks), dim3(BLOCK), 0, st, a); \
-    else if (queued)                                                                          \
+    else if (variant == SEARCH_QUEUED)                                                        \
       hipLaunchKernelGGL((k_fast_search<SPV, STRAT, (STRAT == 2 ? 2 : 1)>), dim3(blocks), dim3(BLOCK), 0, st, a); \
     else                                                                                      \
       hipLaunchKernelGGL((k_fast_search<SPV, STRAT>), dim3(blocks), dim3(BLOCK), tile_bytes, st, a); \
     return 0;
-// (a ring or list entry holds up to 16 cuts: deeper pipelines have the plain range and rank-list kernel only)
+// (a ring or list entry holds up to 16 cuts: deeper pipelines have the plain range kernel only)
 #define CHM_DEEP(SPV)                                                                         \
   case SPV:                                                                                   \
-    if (queued || a.cut_list != nullptr) return 1;                                            \
+    if (variant != SEARCH_PLAIN || a.cut_list != nullptr) return 1;                           \
     hipLaunchKernelGGL((k_fast_search<SPV, STRAT>), dim3(blocks), dim3(BLOCK), tile_bytes, st, a); \
     return 0;
   switch (sp) {
-#ifdef CHM_TUNING_SUBSET        // (-DCHM_TUNING_SUBSET: only the stage counts of the 32-card shape, for quick rebuilds while tuning)
-    CHM_CASE(7) CHM_CASE(8)
+#ifdef CHM_TUNING_SUBSET        // (-DCHM_TUNING_SUBSET: a few stage counts, for quick rebuilds while tuning)
+    CHM_CASE(7) CHM_CASE(8) CHM_CASE(15) CHM_CASE(16)
 #else
     CHM_CASE(2) CHM_CASE(3) CHM_CASE(4) CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8)
     CHM_CASE(9) CHM_CASE(10) CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)
-    CHM_DEEP(17) CHM_DEEP(18) CHM_DEEP(19) CHM_DEEP(20) CHM_DEEP(21) CHM_DEEP(22) CHM_DEEP(23) CHM_DEEP(24) CHM_DEEP(25) CHM_DEEP(26) CHM_DEEP(27) CHM_DEEP(28) CHM_DEEP(29) CHM_DEEP(30) CHM_DEEP(31) CHM_DEEP(32)
+    CHM_DEEP(17) CHM_DEEP(18) CHM_DEEP(19) CHM_DEEP(20) CHM_DEEP(21) CHM_DEEP(22) CHM_DEEP(23) CHM_DEEP(24)
+    CHM_DEEP(25) CHM_DEEP(26) CHM_DEEP(27) CHM_DEEP(28) CHM_DEEP(29) CHM_DEEP(30) CHM_DEEP(31) CHM_DEEP(32)
 #endif
     default: return 1;
   }
 #undef CHM_DEEP
-#undef CHM_CASE
-}
-
-template <int STRAT>
-int filter_by_stages(int sp, const ListFilter &a, uint32_t blocks, hipStream_t st) {
-#define CHM_CASE(SPV)                                                                         \
-  case SPV:                                                                                   \
-    hipLaunchKernelGGL((k_list_filter<SPV, STRAT>), dim3(blocks), dim3(BLOCK), 0, st, a);      \
-    return 0;
-  switch (sp) {
-#ifdef CHM_TUNING_SUBSET        // (-DCHM_TUNING_SUBSET: only the stage counts of the 32-card shape, for quick rebuilds while tuning)
-    CHM_CASE(7) CHM_CASE(8)
-#else
-    CHM_CASE(2) CHM_CASE(3) CHM_CASE(4) CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8)
-    CHM_CASE(9) CHM_CASE(10) CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)
-#endif
-    default: return 1;
-  }
 #undef CHM_CASE
 }
 

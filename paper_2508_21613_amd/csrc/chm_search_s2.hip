@@ -1,12 +1,9 @@
-// The search and list kernels of strategy 2 (data rerouting), one instance per number of stages.
+// The search kernels of strategy 2 (data rerouting), one instance per number of stages.
 #include "chm_halves_kernel.h"
 #include "chm_search_kernel.h"
 
-int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, bool queued) {
-  return launch_by_stages<2>(sp, a, blocks, tile_bytes, (hipStream_t)stream, queued);
-}
-int chmk_list_filter_s2(int sp, const ListFilter &a, uint32_t blocks, void *stream) {
-  return filter_by_stages<2>(sp, a, blocks, (hipStream_t)stream);
+int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant) {
+  return launch_by_stages<2>(sp, a, blocks, tile_bytes, (hipStream_t)stream, variant);
 }
 int chmk_halves_s2(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream) {
   return halves_by_stages<2>(sp, up, n_cls, a, build, (hipStream_t)stream);
