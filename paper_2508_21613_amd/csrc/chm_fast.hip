@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(BLOCK) k_expand(ExpandArgs a) {
     const uint64_t r = rr - q * a.R[s];
     rr = q;
     const uint32_t *row = a.rows[s] + r * (uint64_t)a.stride[s];
-    const uint32_t *w = a.weights + pl * (DEV_MAX_AFF * 8) + s * 8;
+    const uint32_t *w = a.weights + pl * (a.n_aff * ROWS_MAX_P) + s * 8;
     uint32_t m = 0;
     for (int i = 0; i < a.peers[s]; ++i) {
       const uint32_t v = base != ~0ull ? __umul24(row[i], w[i]) : 0u;
@@ -216,7 +216,7 @@ __device__ __forceinline__ int64_t expand_one(const ExpandArgs32 &a, uint32_t gi
         r = rr - qq * a.R[s].d;
         rr = qq;
       }
-      const uint32_t *w = a.weights + (size_t)pl * (DEV_MAX_AFF * 8) + s * 8;
+      const uint32_t *w = a.weights + (size_t)pl * (a.n_aff * ROWS_MAX_P) + s * 8;
       const uint32_t *row = a.rows[s] + (size_t)r * (uint32_t)a.stride[s];
       uint32_t m = 0;
       if (a.stride[s] == 4) {
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(BLOCK) k_expand32_lds(ExpandArgs32 a, uint32_t
   for (uint32_t i = threadIdx.x; i < n_parts; i += BLOCK) {
     const uint32_t pl = a.first_part + p_first + i;
     const uint64_t b = a.base[pl];
-    const uint4 *w4 = (const uint4 *)(a.weights + (size_t)pl * (DEV_MAX_AFF * 8));
+    const uint4 *w4 = (const uint4 *)(a.weights + (size_t)pl * (a.n_aff * ROWS_MAX_P));
     rec[i * EXPAND_REC] = make_uint4((uint32_t)b, (uint32_t)(b >> 32), 0u, 0u);
     rec[i * EXPAND_REC + 1] = w4[0];
     rec[i * EXPAND_REC + 2] = w4[1];
@@ -593,11 +593,12 @@ int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uin
   // tail: 62.9 M partitions then make about 30 workgroups per compute unit, six rounds of the five that are
   // resident); spaces below 2^25 partitions get at least 16 workgroups per compute unit and correspondingly shorter
   // runs (measured on 10 to 15 M partitions: unranking once per 10 to 15 partitions costs less than the idle tail
-  // of fewer, longer workgroups; runs of 5 to 7 were 1 to 8 % slower).  Small spaces: runs of 4 as long as that
-  // still gives every resident wave slot (256 CUs x 5 workgroups x 256 lanes) a lane, then shorter.
+  // of fewer, longer workgroups; runs of 5 to 7 were 1 to 8 % slower).  Small spaces: runs of 4, or as short
+  // as lets every lane of the resident wave slots (256 CUs x 5 workgroups x 256 lanes) have one: a second round of workgroups
+  // costs more than a second partition per lane.
   const uint64_t lanes_balanced = 256ull * 16 * BLOCK, lanes_resident = 256ull * 5 * BLOCK;
   uint64_t per = a.part_count / lanes_balanced;
-  if (per < 4) per = std::min<uint64_t>(4, a.part_count / lanes_resident);
+  if (per < 4) per = std::min<uint64_t>(4, (a.part_count + lanes_resident - 1) / lanes_resident);
   per = std::max<uint64_t>(1, std::min<uint64_t>(per, 32));
   if (a.jump_at != 0xffffffffu) per = 1;               // a run must not straddle two windows
   else if (a.costs_out != nullptr) per = std::min<uint64_t>(per, 8);   // bounds the LDS tile of the cost store

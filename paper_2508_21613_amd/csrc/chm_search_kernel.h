@@ -763,14 +763,15 @@ k_fast_search(FastLaunch a) {
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
         // cost store of plan indices: hand the peer stage times of this partition to the expanding kernel
         if (ok) {
-          uint32_t *wout = a.weights_out + (size_t)(run_first + it) * (DEV_MAX_AFF * 8);
+          uint4 *wout = (uint4 *)(a.weights_out + (size_t)(run_first + it) * (scn->n_aff * ROWS_MAX_P));
           for (int st = 0; st < scn->n_aff; ++st) {
             const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
             const int p = scn->aff_peers[st];
-            for (int i = 0; i < p; ++i) {
-              const uint32_t q = scn->aff_q[st][i];
-              wout[st * 8 + i] = peer_time(t.x, t.y - t.x, q);
-            }
+            uint32_t w[ROWS_MAX_P];
+#pragma unroll
+            for (int i = 0; i < ROWS_MAX_P; ++i) w[i] = i < p ? peer_time(t.x, t.y - t.x, scn->aff_q[st][i]) : 0u;
+            wout[2 * st] = make_uint4(w[0], w[1], w[2], w[3]);
+            wout[2 * st + 1] = make_uint4(w[4], w[5], w[6], w[7]);
           }
         }
       }
