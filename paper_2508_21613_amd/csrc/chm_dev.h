@@ -110,6 +110,7 @@ enum { FINISH_COST = 0,        // winner's cost
        FINISH_TRANS = 3,       // its transition time (int64; -1: does not fit, cannot happen for a winner)
        FINISH_RR = 4,          // DEV_MAX_AFF words: rank of its best reroute vector per stage that lost nodes
        FINISH_COUNTS = 8,      // 3 sums of partitions that fit, then 3 sums of partitions evaluated, per strategy
+       FINISH_POSITION = 14,   // list search: the winner's position
        FINISH_WORDS = 16 };
 struct FinishArgs {
   const DevScenario *scn;
@@ -131,6 +132,9 @@ struct FinishArgs {
   // and the candidate's partition rank follows from its cuts.  cand_slot = -1: none.
   int32_t cand_slot, cand_k;
   const void *cand_cuts;
+  // a search over one explicit list: chunk-local indices (plus part_first) are positions in it (both null: no list)
+  const uint8_t *list_cuts;    // rows of stages - 1 cut positions
+  const uint64_t *list_ranks;
   uint64_t *out;               // FINISH_WORDS words
 };
 int chmk_finish_search(const FinishArgs &a, int32_t smax, void *stream);

@@ -626,14 +626,14 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
   if (s->timing) HIP_TRY(hipEventRecord(s->ev[0], st));
   size_t si = 0;
   int ev_i = 1;
-  bool plain = true;                         // range jobs only: the device can pick the winner
+  bool plain = true;                         // range jobs, or one list: the device can pick the winner
   // (one enumerated candidate set of a single pass is as good as a range: the finish kernel reads the winner's cuts
   // from the candidate list)
   int cand_jobs = 0, cand_slot = -1, cand_strategy = -1;
   {
     int slot_at = 0;
     for (const Job &j : jobs) {
-      plain = plain && !j.ranks && !j.cuts;
+      plain = plain && (jobs.size() == 1 || (!j.ranks && !j.cuts));       // (one explicit list is as good, too)
       if (j.cand) {
         ++cand_jobs;
         cand_slot = slot_at; cand_strategy = j.strategy;
@@ -717,6 +717,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
       f.strategy[i] = c.slots[i].strategy; f.part_first[i] = c.slots[i].part_first;
       f.jump_at[i] = c.slots[i].jump_at; f.jump_by[i] = c.slots[i].jump_by;
     }
+    f.list_cuts = jobs[0].cuts; f.list_ranks = jobs[0].ranks;
     f.out = s->d_result;                       // pinned host memory: no copy behind the kernel
     f.reset = spread ? 1 : 0;
     if (chmk_finish_search(f, s->smax, st)) return CHM_ERR_HIP;
@@ -768,6 +769,7 @@ int collect_jobs(chm_scenario *s, chm_best *out, uint64_t *position, hipStream_t
     best_cost = (int64_t)rec[FINISH_COST];
     best_strategy = (int)rec[FINISH_STRATEGY];
     best_part = rec[FINISH_PART];
+    if (position && (c.jobs[0].ranks || c.jobs[0].cuts)) *position = rec[FINISH_POSITION];
     if (light) {
       fill_plan(s, find_family(s, best_strategy), best_part, rr, best_cost, out);
       return CHM_OK;

@@ -51,9 +51,9 @@ __device__ __forceinline__ int64_t makespan_generic(const int64_t (&F)[SMAX], co
 }
 
 // cut positions of one lane live in a column of LDS: c[i][tid], i = 0..stages
-template <int SMAX>
+template <int SMAX, int COLS = BLOCK>
 struct Cuts {
-  int32_t (*c)[BLOCK];
+  int32_t (*c)[COLS];
   int tid;
   __device__ __forceinline__ int get(int i) const { return c[i][tid]; }
   __device__ __forceinline__ void set(int i, int v) { c[i][tid] = v; }
@@ -88,8 +88,8 @@ __device__ __forceinline__ int64_t missing_interval(const DevScenario *scn, int 
 // disjoint, so two pairs with a non-zero overlap never cross; pairs without overlap can complete
 // any matching.  The optimum is therefore the best non-crossing matching, a two-index recurrence:
 // G[i][j] = max(G[i-1][j], G[i][j-1], G[i-1][j-1] + overlap(node i-1, stage j-1)), kept as one row.
-template <int SMAX>
-__device__ __forceinline__ int64_t best_overlap(const DevScenario *scn, const DevClass &cls, Cuts<SMAX> cuts) {
+template <int SMAX, int COLS>
+__device__ __forceinline__ int64_t best_overlap(const DevScenario *scn, const DevClass &cls, Cuts<SMAX, COLS> cuts) {
   int64_t G[SMAX + 1];
 #pragma unroll
   for (int j = 0; j <= SMAX; ++j) G[j] = 0;
@@ -214,7 +214,7 @@ __device__ __forceinline__ bool eval_base(const DevScenario *scn, const DevFamil
         }
       }
     }
-    if (fam.strategy == 1 && scn->assign) miss = scn->pw[scn->L] - best_overlap<SMAX>(scn, cls, cuts);
+    if (fam.strategy == 1 && scn->assign) miss = scn->pw[scn->L] - best_overlap(scn, cls, cuts);
     if (WITH_TIME) {
       const int64_t T = makespan_generic<SMAX>(F, B, cls.n, cls.M) + (int64_t)(cls.n - 1) * scn->comm;
       t_step = imax(t_step, T);
@@ -228,8 +228,8 @@ __device__ __forceinline__ bool eval_base(const DevScenario *scn, const DevFamil
 }
 
 // forward+backward time of affected stage a on its peer i under the lane's partition
-template <int SMAX>
-__device__ __forceinline__ int64_t peer_weight(const DevScenario *scn, Cuts<SMAX> cuts, int a, int i) {
+template <int SMAX, int COLS>
+__device__ __forceinline__ int64_t peer_weight(const DevScenario *scn, Cuts<SMAX, COLS> cuts, int a, int i) {
   const int st = scn->aff_stage[a];
   const int lo = cuts.get(st), hi = cuts.get(st + 1);
   const uint32_t q = scn->aff_q[a][i];
@@ -254,7 +254,7 @@ __device__ __forceinline__ int64_t penalty_of_rank(const DevScenario *scn, const
       rank -= cnt;
     }
     rem -= v;   // a valid rank is always found at a v within [0, min(rem, cap)]
-    pen = imax(pen, (int64_t)v * peer_weight<SMAX>(scn, cuts, a, pos));
+    pen = imax(pen, (int64_t)v * peer_weight(scn, cuts, a, pos));
   }
   return pen;
 }
@@ -281,7 +281,7 @@ __device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<
   double inv_sum = 0.0;
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
-    w[i] = i < p ? peer_weight<SMAX>(scn, cuts, a, i) : 0;
+    w[i] = i < p ? peer_weight(scn, cuts, a, i) : 0;
     if (i < p) inv_sum += 1.0 / (double)w[i];
   }
   const double v0 = (double)orphans / inv_sum * (1.0 - 1e-9);
@@ -317,14 +317,14 @@ __device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<
 // takes as little as the peers after it allow; its rank = the number of valid vectors that are lexicographically
 // smaller, read off the count table (the lanes share the additions).  That is the first minimum of a sweep of all
 // vectors in rank order: same penalty, lowest rank.
-template <int SMAX>
-__device__ __forceinline__ uint64_t rank_by_capacity(const DevScenario *scn, const uint64_t *comp, Cuts<SMAX> cuts, int a) {
+template <int SMAX, int COLS>
+__device__ __forceinline__ uint64_t rank_by_capacity(const DevScenario *scn, const uint64_t *comp, Cuts<SMAX, COLS> cuts, int a) {
   const int lane = threadIdx.x & 63;
   const int p = scn->aff_peers[a];
   const int64_t orphans = scn->aff_total[a];
   const int64_t cap = scn->rcap > 0 ? scn->rcap : orphans;
   // lane i works out the time of peer i; all lanes then hold all of them
-  const int64_t mine = lane < p ? peer_weight<SMAX>(scn, cuts, a, lane) : 0;
+  const int64_t mine = lane < p ? peer_weight(scn, cuts, a, lane) : 0;
   int64_t w[DEV_MAX_D];
   int64_t w_max = 1;
 #pragma unroll
@@ -567,7 +567,7 @@ __global__ void __launch_bounds__(64) k_reroute_winner(const DevScenario *scn, c
   Cuts<SMAX> cuts{cut_cols, (int)threadIdx.x};
   unrank_partition<SMAX>(scn, fam.stages - 1, part_rank, cuts);       // every lane into its own column
   for (int a = 0; a < scn->n_aff; ++a) {
-    const uint64_t rk = rank_by_capacity<SMAX>(scn, comp, cuts, a);
+    const uint64_t rk = rank_by_capacity(scn, comp, cuts, a);
     if (threadIdx.x == 0) out[a] = rk;
   }
 }
@@ -638,36 +638,77 @@ __global__ void __launch_bounds__(BLOCK) k_plan_transition(const DevScenario *sc
   out[0] = eval_base<SMAX, false>(scn, fam, cuts, &t_step, &reconf) ? reconf : -1;
 }
 
+// MiB a plan's nodes must fetch, by one wavefront together (all lanes read the same column of cuts): stage by stage, lane
+// by lane, or, with the least-transfer assignment, by every lane alike.
+template <int SMAX, int COLS>
+__device__ __forceinline__ int64_t missing_by_wave(const DevScenario *scn, const DevFamily &fam, Cuts<SMAX, COLS> cuts) {
+  const int lane = threadIdx.x & 63;
+  auto sum_over_stages = [&](auto first_of) {
+    int64_t v = 0;
+    if (lane < fam.stages) {
+      const int h = first_of(lane);                  // fault-free stage whose layers the node of stage `lane` holds
+      v = missing_interval(scn, cuts.get(lane), cuts.get(lane + 1), scn->p0[h], scn->p0[h + 1]);
+    }
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor((long long)v, off, 64);
+    return (int64_t)__shfl((long long)v, 0, 64);     // (at most 32 stages: the lower half wave holds them all)
+  };
+  if (fam.strategy != 1) return sum_over_stages([](int j) { return j; });
+  int64_t missing = 0;
+  for (int ci = 0; ci < fam.n_cls; ++ci) {           // uniform
+    const DevClass &cls = fam.cls[ci];
+    const int64_t miss = scn->assign ? scn->pw[scn->L] - best_overlap(scn, cls, cuts)
+                                     : sum_over_stages([&cls](int j) { return (int)cls.host[j]; });
+    missing = imax(missing, miss);
+  }
+  return missing;
+}
+
 // End of a search on the device: the winner among the argmin words of all launched chunks (lowest cost; among
-// equal costs the lowest strategy, then the lowest partition rank: the lowest plan index), the sums of the
-// feasibility counters, the winner's transition time and, for data rerouting, the ranks of its best reroute
+// equal costs the lowest strategy, then the lowest partition rank: the lowest plan index; in a list the lowest position),
+// the sums of the feasibility counters, the winner's transition time and, for data rerouting, the ranks of its best reroute
 // vectors, gathered into one record (written straight to pinned host memory when the caller passes such a
-// pointer).  One workgroup.  The kernel sits on the critical path of every search, and a single lane chasing
-// table entries through global memory pays a microsecond per dependent load, so: all lanes first copy the part of
-// the scenario ahead of the binomial table into LDS (SMAX <= 16; the one-lane steps then read LDS), and the
-// winner's partition is unranked by the first wavefront together, one table column per digit held across the
-// lanes (all columns loaded up front, the digit found with a ballot).
+// pointer).  One workgroup.  The kernel sits on the critical path of every search and is all latency, so: everything that
+// does not depend on the winner is loaded at once (argmin words, counters, the part of the scenario ahead of the binomial
+// table into LDS, and, up to 16 stages, the binomial columns), words and counters are combined by their 16 lanes each,
+// the winner's partition is unranked by the first wavefront together (a digit is found with a ballot), and its transition
+// time is summed over the lanes while the second wavefront works out the reroute vectors.
 template <int SMAX>
 __global__ void __launch_bounds__(BLOCK) k_finish_search(FinishArgs a) {
   constexpr bool STAGED = SMAX <= 16;
   constexpr int HEAD_WORDS = (int)(offsetof(DevScenario, binom) / 8);      // 8-byte words ahead of the binomial table
-  __shared__ int32_t cut_cols[SMAX + 2][BLOCK];
-  __shared__ uint64_t keys[FINISH_MAX_SLOTS * FINISH_MAX_WAYS];
-  __shared__ uint64_t counts[6 * FINISH_MAX_WAYS];
-  __shared__ uint64_t win[3];                        // cost, strategy (~0: nothing found), partition rank
+  constexpr int AHEAD = STAGED ? SMAX - 1 : 8;       // digits whose binomial columns are held at a time
+  __shared__ int32_t cut_cols[SMAX + 2][1];          // the winner's cuts
+  __shared__ uint64_t keys[FINISH_MAX_SLOTS];
+  __shared__ uint64_t win[4];                        // cost, strategy (~0: nothing found), partition rank, list position
   __shared__ uint64_t head[STAGED ? HEAD_WORDS : 1];
   const uint32_t chunk_words = a.ways * a.stride;
   const uint32_t t = threadIdx.x;
-  if (t < a.n_slots * a.ways) keys[t] = a.slots[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride];
-  if (t < 6 * a.ways) counts[t] = a.counters[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride];
+  const uint32_t n_keys = a.n_slots * a.ways, n_counts = 6 * a.ways;
+  uint64_t key = t < n_keys ? a.slots[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride] : CHM_KEY_NONE;
+  uint64_t count = t < n_counts ? a.counters[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride] : 0;
+  uint64_t lo_col[AHEAD], hi_col[AHEAD];             // lane x of the first wavefront: C(x, i) and C(x + 64, i), i = 1..AHEAD
+  if (STAGED && t < 64) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) { lo_col[u] = a.scn->binom[u + 1][t]; hi_col[u] = a.scn->binom[u + 1][t + 64]; }
+  }
   if (STAGED) {
     const uint64_t *src = (const uint64_t *)a.scn;
     for (int i = (int)t; i < HEAD_WORDS; i += BLOCK) head[i] = src[i];
   }
+  if (a.ways > 1) {                                  // 16 words each, 16 neighbouring lanes
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+      key = umin64(key, __shfl_xor(key, off, 64));
+      count += __shfl_xor(count, off, 64);
+    }
+  }
+  if (t < n_keys && t % a.ways == 0) keys[t / a.ways] = key;
+  if (t < n_counts && t % a.ways == 0) a.out[FINISH_COUNTS + t / a.ways] = count;
   if (a.reset) {
     // every word is rewritten by the lane that has just read it (the seventh counter and the incumbent are not read here)
     uint64_t *slots = const_cast<uint64_t *>(a.slots), *counters = const_cast<uint64_t *>(a.counters);
-    if (t < a.n_slots * a.ways) slots[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride] = CHM_KEY_NONE;
+    if (t < n_keys) slots[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride] = CHM_KEY_NONE;
     if (t < 7 * a.ways) counters[(size_t)(t / a.ways) * chunk_words + (size_t)(t % a.ways) * a.stride] = 0;
     if (t == 0) counters[(size_t)7 * chunk_words] = ~0ull;
   }
@@ -676,12 +717,11 @@ __global__ void __launch_bounds__(BLOCK) k_finish_search(FinishArgs a) {
     uint64_t best_cost = ~0ull, best_part = 0;
     int best_strategy = -1;
     for (uint32_t i = 0; i < a.n_slots; ++i) {
-      uint64_t key = CHM_KEY_NONE;
-      for (uint32_t w = 0; w < a.ways; ++w) key = umin64(key, keys[i * a.ways + w]);
-      if (key == CHM_KEY_NONE) continue;
-      const uint64_t cost = key >> a.idx_bits;
-      const uint64_t local = key & ((1ull << a.idx_bits) - 1ull);
-      uint64_t part = a.part_first[i] + local + (local >= a.jump_at[i] ? a.jump_by[i] : 0);
+      const uint64_t word = keys[i];
+      if (word == CHM_KEY_NONE) continue;
+      const uint64_t cost = word >> a.idx_bits;
+      const uint64_t local = word & ((1ull << a.idx_bits) - 1ull);
+      uint64_t part = a.part_first[i] + local + (local >= a.jump_at[i] ? a.jump_by[i] : 0);     // (a list: the position)
       if ((int)i == a.cand_slot) {
         // a candidate's index: its partition rank = sum of C(c_i - 1, i) over its cut positions
         const uint4 packed = ((const uint4 *)a.cand_cuts)[local];
@@ -698,66 +738,74 @@ __global__ void __launch_bounds__(BLOCK) k_finish_search(FinishArgs a) {
         best_cost = cost; best_strategy = strategy; best_part = part;
       }
     }
-    win[0] = best_cost; win[1] = best_strategy < 0 ? ~0ull : (uint64_t)best_strategy; win[2] = best_part;
+    const uint64_t position = best_part;
+    if (best_strategy >= 0 && a.list_ranks != nullptr) best_part = a.list_ranks[position];
+    win[0] = best_cost; win[1] = best_strategy < 0 ? ~0ull : (uint64_t)best_strategy; win[2] = best_part; win[3] = position;
     a.out[FINISH_COST] = best_cost;
     a.out[FINISH_STRATEGY] = win[1];
-    a.out[FINISH_PART] = best_part;
-    for (int k = 0; k < 6; ++k) {
-      uint64_t sum = 0;
-      for (uint32_t w = 0; w < a.ways; ++w) sum += counts[k * a.ways + w];
-      a.out[FINISH_COUNTS + k] = sum;
-    }
+    a.out[FINISH_POSITION] = position;
+    if (a.list_cuts == nullptr) a.out[FINISH_PART] = best_part;
   }
   __syncthreads();
   if (win[1] == ~0ull) return;
   const int strategy = (int)win[1];
-  const uint64_t part = win[2];
-  // what the one-lane steps read: the LDS copy (everything they touch lies ahead of the binomial table), else global
+  // what the steps below read: the LDS copy (everything they touch lies ahead of the binomial table), else global
   const DevScenario *scn = STAGED ? (const DevScenario *)head : a.scn;
   const DevFamily &fam = scn->fam[strategy];
   const int k = fam.stages - 1, L = scn->L;
-  // ---- unranking by the first wavefront: lane x holds C(x, i) and C(x + 64, i) of every digit i
-  if (t < 64) {
-    uint64_t rem = part;
-    int hi = L - 2;                                  // the digit is the largest x <= hi with C(x, i) <= rem
-    for (int i0 = k; i0 >= 1; i0 -= 8) {             // eight digits' columns at a time: their loads are in flight together
-      uint64_t lo_col[8], hi_col[8];
+  if (t < 64 && a.list_cuts != nullptr) {
+    // a list of cut positions: lane i takes cut i + 1; their ranks add up to the partition's
+    uint64_t rank = 0;
+    if ((int)t < k) {
+      const int c = a.list_cuts[(size_t)win[3] * (size_t)k + t];
+      cut_cols[t + 1][0] = c;
+      rank = a.scn->binom[t + 1][c - 1];
+    }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 - u;
-        lo_col[u] = i >= 1 ? a.scn->binom[i][t] : 0;
-        hi_col[u] = i >= 1 ? a.scn->binom[i][t + 64] : 0;
-      }
+    for (int off = 16; off >= 1; off >>= 1) rank += __shfl_xor(rank, off, 64);
+    if (t == 0) a.out[FINISH_PART] = rank;
+  } else if (t < 64) {
+    // ---- unranking by the first wavefront: the digit is the largest x <= hi with C(x, i) <= rem
+    uint64_t rem = win[2];
+    int hi = L - 2;
+    auto digit = [&](int i, uint64_t lo_c, uint64_t hi_c) {
+      const uint64_t m_hi = __builtin_amdgcn_ballot_w64(hi_c <= rem && (int)t + 64 <= hi);
+      const uint64_t m_lo = __builtin_amdgcn_ballot_w64(lo_c <= rem && (int)t <= hi);
+      // C(i - 1, i) = 0 <= rem and i - 1 <= hi always: some lane answers
+      const int x = m_hi ? 127 - __builtin_clzll(m_hi) : 63 - __builtin_clzll(m_lo);
+      const uint64_t taken = m_hi ? __shfl(hi_c, x - 64, 64) : __shfl(lo_c, x, 64);
+      rem -= taken;
+      hi = x - 1;
+      if (t == 0) cut_cols[i][0] = x + 1;
+    };
+    if (STAGED) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 - u;
-        if (i >= 1) {                                // uniform
-          const uint64_t m_hi = __builtin_amdgcn_ballot_w64(hi_col[u] <= rem && (int)t + 64 <= hi);
-          const uint64_t m_lo = __builtin_amdgcn_ballot_w64(lo_col[u] <= rem && (int)t <= hi);
-          // C(i - 1, i) = 0 <= rem and i - 1 <= hi always: some lane answers
-          const int x = m_hi ? 127 - __builtin_clzll(m_hi) : 63 - __builtin_clzll(m_lo);
-          const uint64_t taken = m_hi ? __shfl(hi_col[u], x - 64, 64) : __shfl(lo_col[u], x, 64);
-          rem -= taken;
-          hi = x - 1;
-          if (t == 0) { cut_cols[i][0] = x + 1; }
-          if (t == 1) cut_cols[i][64] = x + 1;
+      for (int i = AHEAD; i >= 1; --i)
+        if (i <= k) digit(i, lo_col[i - 1], hi_col[i - 1]);               // uniform
+    } else {
+      for (int i0 = k; i0 >= 1; i0 -= AHEAD) {       // eight digits' columns at a time: their loads are in flight together
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+          const int i = i0 - u;
+          lo_col[u] = i >= 1 ? a.scn->binom[i][t] : 0;
+          hi_col[u] = i >= 1 ? a.scn->binom[i][t + 64] : 0;
         }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+          if (i0 - u >= 1) digit(i0 - u, lo_col[u], hi_col[u]);
       }
     }
-    if (t == 0) { cut_cols[0][0] = 0; cut_cols[k + 1][0] = L; }
-    if (t == 1) { cut_cols[0][64] = 0; cut_cols[k + 1][64] = L; }
   }
+  if (t == 0) { cut_cols[0][0] = 0; cut_cols[k + 1][0] = L; }
   __syncthreads();
-  Cuts<SMAX> cuts{cut_cols, (int)t};
-  if (t == 0) {
-    int64_t t_step = 0, reconf = 0;
-    a.out[FINISH_TRANS] = (uint64_t)(eval_base<SMAX, false>(scn, fam, cuts, &t_step, &reconf) ? reconf : (int64_t)-1);
-  } else if (a.reroute_winner && strategy == 2 && t >= 64 && t < 128) {
-    // the second wavefront takes the stages that lost nodes one after the other, beside the transition time (all its
-    // lanes read the cuts of column 64)
-    Cuts<SMAX> shared_cuts{cut_cols, 64};
+  Cuts<SMAX, 1> cuts{cut_cols, 0};
+  if (t < 64) {
+    const int64_t missing = missing_by_wave(scn, fam, cuts);
+    if (t == 0) a.out[FINISH_TRANS] = (uint64_t)(scn->reconf[strategy] + scn->xfer * missing);
+  } else if (a.reroute_winner && strategy == 2 && t < 128) {
+    // the second wavefront takes the stages that lost nodes one after the other
     for (int st = 0; st < scn->n_aff; ++st) {
-      const uint64_t rk = rank_by_capacity<SMAX>(scn, a.comp, shared_cuts, st);
+      const uint64_t rk = rank_by_capacity(scn, a.comp, cuts, st);
       if (t == 64) a.out[FINISH_RR + st] = rk;
     }
   }
