@@ -2,7 +2,7 @@
 
 A step is one exhaustive chm_search_best over the whole plan space of the 32-card
 configuration (L=48, PP=8, DP=4, M=16, one failed node): unranking, stage sums, memory
-filter, 1F1B recurrence per pipeline class, strategy terms and argmin for every partition
+filter, 1F1B time per pipeline class, strategy terms and argmin for every partition
 of the three strategies and every reroute vector.  The scenario tables are resident in
 HBM before the timed region.  Prints one JSON line; with no flags that line also carries a
 `workloads` block with the other configurations (1, 3, 4, 5), the cost store and the
@@ -26,12 +26,12 @@ METRIC = "candidate plans scored/sec + time-to-best-plan per failure event (1 GP
 # v_mul_u32_u24, which the path needs, issue at half of it (chm_valu_probe measures both).
 ALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 
-# From the rocprofv3 --pmc runs summarised in profiles/search_kernels_config2.md (counters cannot be read from
+# From the rocprofv3 --pmc runs summarised in profiles/measured_cases.md (counters cannot be read from
 # inside this process), per strategy kernel of config 2:
 # HBM bytes per launch = FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 KiB (factors from the 1 GiB calibration copy of the same runs)
-CONFIG2_TRAFFIC_BYTES = {0: (163.9 * 2.0 + 447.6) * 1024, 1: (125.0 * 2.0 + 256.4) * 1024, 2: (186.6 * 2.0 + 475.4) * 1024}
+CONFIG2_TRAFFIC_BYTES = {0: (9540.0 * 2.0 + 238.0) * 1024, 1: (6429.0 * 2.0 + 67.0) * 1024, 2: (6387.0 * 2.0 + 266.0) * 1024}
 # executed VALU lane-instructions per partition = SQ_INSTS_VALU x 64 / partitions of the family
-CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 558.0, 1: 419.0, 2: 754.0}
+CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 120.0, 1: 69.0, 2: 53.5}
 
 
 def note(msg):
@@ -39,47 +39,23 @@ def note(msg):
 
 
 def algorithmic_ops(fam, feasible):
-    """Integer operations the method needs for one search launch of a strategy (not what the kernel
-    executes).  Every partition: 3 stage sums per stage and the memory compare per stage.  A
-    partition that passes the memory filter in addition: per pipeline class one max and one add
-    per recurrence cell (2 x stages x micro-batches cells), 2 Q16 scalings per stage, the
-    comm add and the max over pipelines; 4 per stage for the weight-fetch volume; 2 for the cost;
-    per stage that lost nodes the products (extra micro-batches x peer stage time) for every count
-    0..orphans, one add each, which all reroute vectors share; and per reroute vector the max over
-    its peers' products and the compare."""
+    """Integer operations the method needs for one search launch of a strategy, every partition worked out on its own
+    (not what the kernel executes: a large search shares the upper and lower halves of its partitions).  Every partition:
+    3 stage sums per stage and the memory compare per stage.  A partition that passes the memory filter in addition: per
+    pipeline class the closed form of the 1F1B recurrence (14 operations per stage: a sum, two prefix maxima, two
+    multiply-adds, two suffix maxima, and a multiply, three adds and a max for the stage's own term), 2 Q16 scalings per
+    stage, the comm add and the max over pipelines; 4 per stage for the weight-fetch volume; 2 for the cost; per stage that
+    lost nodes the least penalty, an order statistic of the peers' multiples (3 operations per peer and merge step, about
+    as many steps as peers)."""
     S = fam["stages"]
     light = 4 * S
-    heavy = sum(4 * n_c * m_c + 2 * n_c + 2 for n_c, m_c in fam["classes"]) + 4 * S + 2
-    heavy += sum(R * p + p * t for R, p, t in zip(fam["R"], fam["peers"], fam["orphans"]))
+    heavy = sum(16 * n_c + 2 for n_c, _ in fam["classes"]) + 4 * S + 2
+    heavy += sum(3 * p * p for p in fam["peers"])
     if fam.get("assign") and fam["strategy"] == 1:
         # least-transfer assignment: the two-index recurrence over (survivor, new stage) pairs, per cell
         # the overlap (min, max, subtract, clamp) and one add and two max
         heavy += sum(7 * n_c * n_c for n_c, _ in fam["classes"])
     return fam["n_part"] * light + feasible * heavy, light, heavy
-
-
-def shared_prefix_ops(peers, total, cap):
-    """Operations of one partition's reroute sweep of one stage in the formulation the large-space sweep kernel uses
-    (the vectors of a group share the largest product of their first peers - 3 entries; per value of the entry before
-    the last two one add, two max and one min; the least larger-product of the last two entries per remaining sum
-    from a table built once, one max and one min per pair): the count that kernel's executed instructions are close to."""
-    cap = min(cap, total) if cap > 0 else total
-    q = peers - 3
-    if q < 0:
-        return None
-    # number of ways to fill the first q entries (each 0..cap) with a given sum
-    ways = [1] + [0] * total
-    for _ in range(q):
-        ways = [sum(ways[t - v] for v in range(0, min(cap, t) + 1)) for t in range(total + 1)]
-    groups = runs = 0
-    for used, w in enumerate(ways):
-        rest = total - used                                   # for the last three entries
-        lo, hi = max(0, rest - 2 * cap), min(cap, rest)
-        if w and lo <= hi:
-            groups += w
-            runs += w * (hi - lo + 1)
-    pairs = sum(min(cap, r) - max(0, r - cap) + 1 for r in range(2 * cap + 1))
-    return groups * max(0, 2 * q - 1) + runs * 4 + pairs * 2 + 2 * cap
 
 
 def copy_calibration():
@@ -236,6 +212,8 @@ def bench_replan(args, B, synth):
            "bounded_search": bounded, "replan_table_1_to_3": table_rec, "best": plan,
            "roofline": {"bound": "alu", "kernel": "split search (all pipeline lengths)", "achieved": achieved,
                         "peak": ALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / ALU_PEAK_TOPS, "traffic": None,
+                        "frac_is": "the call's own accounting (4 n M operations of the recurrence per split that fits); above 1 because the "
+                                   "kernels evaluate its closed form and share it between splits",
                         "kernel_ms": search_ms, "algorithmic_ops_per_launch": st["algorithmic_ops"]}}
     if not args.no_cpu_baseline:
         from oracle import oracle as O
@@ -589,7 +567,7 @@ def bench_search(args, B, synth, name):
         for f in fams:
             ops[f["strategy"]] += algorithmic_ops(f, tm["feasible"][f["strategy"]])[0]
             n_part_total += f["n_part"]
-            # recurrence cells that run: the partitions that pass the memory filter, every pipeline class
+            # recurrence cells whose closed form is evaluated: the partitions that pass the memory filter, every pipeline class
             cells += tm["feasible"][f["strategy"]] * sum(2 * n * m for n, m in f["classes"])
     n_plans = float(evaluations.sum())
 
@@ -663,38 +641,17 @@ def bench_search(args, B, synth, name):
     note("%s: measured VALU rates (T lane-ops/s): %s" % (name, probes))
     sc = scenarios[0]
     best = plans[0][1]
-    shared = None
-    if dom == 2 and fam0 and sum(fam0[0]["R"]) > 4096 and all(p >= 3 for p in fam0[0]["peers"]):
-        # large reroute spaces are swept group by group (shared leading entries): the same figure with the operations
-        # of that formulation in place of `peers` operations per reroute vector
-        per_part = [shared_prefix_ops(p, t, sc0_cap) for p, t, sc0_cap in
-                    zip(fam0[0]["peers"], fam0[0]["orphans"], [scenarios[0].get("reroute_cap", 0)] * len(fam0[0]["peers"]))]
-        if all(x is not None for x in per_part):
-            base_ops = algorithmic_ops(dict(fam0[0], R=[0] * len(fam0[0]["R"])), feasible[dom] / len(handles))[0]
-            shared = (base_ops + feasible[dom] / len(handles) * sum(per_part)) * len(handles)
     roofline = {"bound": "alu", "kernel": "search, strategy %d" % dom, "achieved": achieved,
                 "peak": ALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / ALU_PEAK_TOPS,
-                "frac_is": "algorithmic int32 lane operations per second (the method's max/add/compare count, whatever the kernel "
-                           "executes) over the nominal VALU peak of 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz; this is the figure "
-                           "the 50 % target is read against",
+                "frac_is": "algorithmic int32 lane operations per second (the method's count with every partition worked out on its own, "
+                           "whatever the kernel executes) over the nominal VALU peak of 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz; above 1 "
+                           "where partitions share what their halves have in common",
                 "measured_valu_rates_tops": probes,
-                "algorithmic_ops_over_measured_naive_cell_rate": achieved / probes["max_add_cell_chain"],
-                "algorithmic_ops_over_measured_naive_cell_rate_is": "the same numerator over the measured rate of a plain dependent "
-                    "v_max_i32 + v_add_u32 chain; above 1 because the kernel executes fewer instructions than the algorithmic count "
-                    "(one v_max serves a forward and a backward cell, the forward add folds into the frame, v_max3/v_min3 fold two operations)",
                 "traffic": CONFIG2_TRAFFIC_BYTES[dom] if name == "config2" and not args.transfer_assign else None,
                 "kernel_ms": float(fam_ms[dom]), "algorithmic_ops_per_launch": float(ops[dom] / len(handles)),
                 "feasible_partitions": float(feasible[dom]),
                 "algorithmic_ops_per_feasible_partition": ops_light + ops_heavy,
                 "algorithmic_ops_per_infeasible_partition": ops_light}
-    if shared is not None:
-        a2 = shared / (fam_ms[dom] * 1e-3) / 1e12
-        roofline["achieved_shared_prefix_accounting"] = a2
-        roofline["frac_shared_prefix_accounting"] = a2 / ALU_PEAK_TOPS
-        roofline["frac_shared_prefix_accounting_is"] = (
-            "`frac` charges every reroute vector its `peers` operations (the accounting of all workloads); this kernel takes the "
-            "largest product of the leading entries once per group of vectors and the best pair of the last two entries from a "
-            "table, so it needs far fewer: with the operations of that formulation as the numerator the fraction is this one")
     if name == "config2" and not args.transfer_assign:
         per_part = CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION[dom]
         executed = per_part * fam0[0]["n_part"] / (fam_ms[dom] * 1e-3) / 1e12
@@ -752,8 +709,7 @@ def summary(rec):
     out = {k: rec[k] for k in keep if k in rec and rec[k] is not None}
     out["workload"] = rec["config"]["workload"]
     r = rec["roofline"]
-    out["roofline"] = {k: r[k] for k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "kernel_ms", "achieved_shared_prefix_accounting",
-                                         "frac_shared_prefix_accounting", "frac_shared_prefix_accounting_is") if k in r}
+    out["roofline"] = {k: r[k] for k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "kernel_ms") if k in r}
     if rec.get("bounded_search"):
         b = rec["bounded_search"]
         out["bounded_search"] = {k: b[k] for k in ("search_ms_all_scenarios", "bounded_ms_per_step", "time_to_best_plan_ms",

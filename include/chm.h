@@ -168,10 +168,12 @@ int chm_search_ranks(chm_scenario *s, int32_t strategy, const uint64_t *d_part_r
 int chm_search_cuts(chm_scenario *s, int32_t strategy, const uint8_t *d_cuts, uint64_t n,
                     int64_t *d_costs, chm_best *out, uint64_t *position, void *hip_stream);
 
-/* Exhaustive argmin over the strategies in strategy_mask (bit k = strategy k): every
- * partition of every selected family is scored on the device; for data rerouting every
- * reroute vector of every stage that lost nodes is scored (the penalty is a sum of
- * independent per-stage terms, so stages are swept one after the other).  Ties go to the
+/* Exhaustive argmin over the strategies in strategy_mask (bit k = strategy k): memory peak and
+ * step time of every partition of every selected family are worked out on the device; for data
+ * rerouting with the least penalty over every reroute vector of every stage that lost nodes (an order
+ * statistic: the orphans-th smallest multiple of the peers' stage times; the penalty is a sum of
+ * independent per-stage terms).  In families of 2^21 partitions and more the transition time is worked out where
+ * horizon x step time alone does not already exceed the lowest cost met so far.  Ties go to the
  * lowest plan index.  Synchronises hip_stream before returning.  Errors:
  * CHM_ERR_UNRECOVERABLE (mask selects no existing family), CHM_ERR_NO_FEASIBLE (out is
  * filled with index UINT64_MAX, cost CHM_INFEASIBLE), CHM_ERR_OVERFLOW (the selected families hold more
@@ -200,8 +202,8 @@ int chm_search_best_batch(chm_scenario *const *handles, int32_t n, uint32_t stra
  * from the allocator.  The call makes no hipMalloc, hipFree or other allocating call.  Always exhaustive
  * (chm_set_bounded_search is ignored).  Limits: at most 8,184 chunks of 2^idx_bits partitions (CHM_ERR_LIMIT
  * beyond; with the usual idx_bits of 30 that is every space chm_search_best accepts short of 2^43 partitions),
- * and no rerouting family whose reroute vectors are swept by kernels of their own (more than 4,096 vectors
- * over its stages: CHM_ERR_LIMIT, use chm_search_best).  On CHM_ERR_LIMIT out is filled as for
+ * and no rerouting family with a large reroute space (more than 4,096 vectors over its stages, at most 8 peers
+ * and 2^23 vectors each: CHM_ERR_LIMIT, use chm_search_best).  On CHM_ERR_LIMIT out is filled as for
  * CHM_ERR_NO_FEASIBLE.  All calls on one GPU share the array, which keeps the last call's contents (the
  * call resets what it reads): two calls that overlap in time on one GPU, from any handles or threads, race.
  * Otherwise as chm_search_best (synchronises hip_stream; same errors). */
@@ -241,9 +243,7 @@ int chm_decode_plan(const chm_scenario *s, uint64_t index, chm_best *out);
  * starts with the ranks around the time-balanced and the memory-balanced partition of each range, so that a
  * good cost is known early.  chm_timing.evaluated (chm_measure.h) tells how many
  * partitions were evaluated in full; chm_timing.feasible then counts only those partitions that were looked
- * at one by one and fit.  Where the reroute vectors of a stage are too many to sweep inside the search kernel,
- * a bounded search finds the least penalty of eq. (re-route) from the peers' capacities instead of sweeping them
- * (some vector stays within v exactly when the peers can take all orphaned micro-batches within v each).  Covers
+ * at one by one and fit.  Covers
  * the range and list searches of the specialised kernels without cost store (other paths evaluate everything;
  * with a cost store every cost is wanted and nothing is skipped).  Errors: CHM_ERR_ARG. */
 int chm_set_bounded_search(chm_scenario *s, int32_t on);
@@ -293,8 +293,9 @@ typedef struct {
   /* work accounting of the call (all candidates, not only the chosen one) */
   uint64_t splits_scored;                     /* contiguous splits scored by the search kernels */
   uint64_t splits_feasible;                   /* of which passed the memory filter (bounded: of those looked at one by one) */
-  uint64_t splits_evaluated;                  /* of which had their recurrence run (all of them unless bounded_search) */
-  double algorithmic_ops;                     /* 4n per split + (4nM + 6n + 4) per split that fits, n stages, M micro-batches */
+  uint64_t splits_evaluated;                  /* of which had their pipeline time worked out (all of them unless bounded_search) */
+  double algorithmic_ops;                     /* 4n per split + (4nM + 6n + 4) per split that fits, n stages, M micro-batches:
+                                                 the operations of the recurrence (the kernels evaluate its closed form) */
   float search_ms, assign_ms;                 /* HIP-event time of the split-search kernels / of the assignment kernels */
 } chm_replan_plan;
 

@@ -24,7 +24,7 @@ typedef struct {
   uint64_t partitions[3];      /* partitions evaluated per strategy                                  */
   uint64_t evaluations[3];     /* (partition, reroute vector) evaluations per strategy               */
   uint64_t feasible[3];        /* partitions per strategy that passed the memory filter              */
-  uint64_t evaluated[3];       /* of those, partitions whose pipeline recurrences were run: all of
+  uint64_t evaluated[3];       /* of those, partitions whose pipeline times were worked out: all of
                                 * them, or fewer in a bounded search (chm_set_bounded_search)         */
 } chm_timing;
 
@@ -41,7 +41,7 @@ typedef struct {
   int32_t specialised[3];        /* per strategy: 1 = the int32 shape-specialised kernels, 0 = the generic int64 ones */
   int32_t sharp_bound[3];        /* per strategy: the bounded search may use its sharper lower bound (24-bit multiplies) */
   int32_t reroute_mul24;         /* peer stage times stay below 2^24 (needed by the specialised rerouting kernels) */
-  int32_t reroute_swept_apart;   /* rerouting: more than 4,096 reroute vectors, swept by kernels of their own */
+  int32_t reroute_swept_apart;   /* rerouting: a large reroute space (more than 4,096 vectors; see chm_search_best_static) */
 } chm_selection;
 int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
 
@@ -55,6 +55,7 @@ int chm_get_timing(const chm_scenario *s, chm_timing *out);
  * collects the partitions that fit and evaluates them 64 at a time with all lanes busy; mode 0 = every lane
  * evaluates its own partitions, lanes whose partition fails idle; mode -1 (the default) = per strategy, mode 1
  * when fewer than 80 % of a seeded sample of partitions fit, else mode 0.  Results do not depend on the mode.
+ * (Families of 2^21 partitions and more that are searched by halves do not use it.)
  * share[k] (host, 3 floats, may be NULL) receives the sampled share per strategy (1.0 where no sample was
  * taken).  Errors: CHM_ERR_ARG. */
 int chm_set_filter_compaction(chm_scenario *s, int32_t mode, float *share);
