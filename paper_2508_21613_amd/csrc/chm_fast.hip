@@ -410,7 +410,7 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
   // memory side of the int32 kernels: doubled static sums plus the largest activation term stay below
   // 2^31, and the (doubled) activation sums fit the 24-bit multiply
   if (2 * h.pw[h.L] + 2 * h.pa[h.L] * (int64_t)DEV_MAX_S >= (1ll << 31) || 2 * h.pa[h.L] >= (1ll << 24)) return;
-  // 24-bit multiplies in the reroute sweep need peer stage times below 2^24
+  // 24-bit multiplies in least_penalty need peer stage times below 2^24
   uint32_t q_aff = 65536;
   for (int a = 0; a < h.n_aff; ++a)
     for (int i = 0; i < h.aff_peers[a]; ++i) q_aff = std::max(q_aff, h.aff_q[a][i]);
@@ -828,7 +828,7 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
 namespace {
 // Partitions from which a family is searched by halves.  Below, its seeds, its first search's table and the fixed cost of
 // a wavefront (its lower half, a round of 32 upper halves) weigh more than the partitions: 1.5 M partitions of 6 stages took
-// 23 + 12 us by halves and take 17 in the range kernel, 10.7 M of 7 stages 35 + 12 by halves and 70.
+// 23 + 12 us by halves and take 17 in the range kernel, 10.7 M of 7 stages 35 + 12 by halves and 79.
 constexpr uint64_t HALVES_FROM = 1ull << 21;
 // bytes a table of upper halves may take (one per strategy and handle, kept): three cuts up to here, else two
 constexpr uint64_t HALVES_TABLE = 8ull << 20;

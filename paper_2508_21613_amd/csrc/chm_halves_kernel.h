@@ -7,7 +7,7 @@
 // a list of upper halves whose share was worked out once for all lower halves (k_upper_halves) and arrives through
 // scalar loads.  Bound by VALU issue: a partition costs 45 instructions (strategies 1 and 2; 100 with the two pipeline classes
 // of strategy 0) at any depth, where working it out on its own costs over 200 at 8 stages and 300 at 11.  62.9 M
-// partitions of 8 stages: 0.12 ms (0.5 ms one by one), of 5.2 G of 11 stages: 6.4 ms (49).  64 VGPRs or fewer at one class: 8
+// partitions of 8 stages: 0.12 ms (0.48 ms one by one in the range kernel), 5.2 G of 11 stages: 6.4 ms (51).  64 VGPRs or fewer at one class: 8
 // waves per SIMD, which hide the scalar loads.  All lanes of a wavefront have the same last lower cut v, and the list is ordered by its
 // first cut, descending: the upper halves that go with v are the first C(L-1-v, UP) of the list, for every v.
 //
