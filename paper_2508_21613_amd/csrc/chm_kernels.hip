@@ -279,19 +279,21 @@ __device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<
   const int cap = scn->rcap > 0 && scn->rcap < orphans ? scn->rcap : orphans;
   int64_t w[DEV_MAX_D], next[DEV_MAX_D];
   double inv_sum = 0.0;
+  int taken = 0;                                     // (peers whose time is 0 first: up to the cap each, for nothing)
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
     w[i] = i < p ? peer_weight(scn, cuts, a, i) : 0;
-    if (i < p) inv_sum += 1.0 / (double)w[i];
+    if (i < p && w[i] != 0) inv_sum += 1.0 / (double)w[i];
+    if (i < p && w[i] == 0) taken += cap;
   }
-  const double v0 = (double)orphans / inv_sum * (1.0 - 1e-9);
-  int taken = 0;
+  const double v0 = taken < orphans ? (double)(orphans - taken) / inv_sum * (1.0 - 1e-9) : 0.0;
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
-    int r = (i < p && w[i] > 0) ? (int)(v0 / (double)w[i]) : 0;
+    const bool busy = i < p && w[i] != 0;
+    int r = busy ? (int)(v0 / (double)w[i]) : 0;
     r = r < cap ? r : cap;
     taken += r;
-    next[i] = i < p && r < cap ? (int64_t)(r + 1) * w[i] : CHM_INF_COST;
+    next[i] = busy && r < cap ? (int64_t)(r + 1) * w[i] : CHM_INF_COST;
   }
   int64_t least = 0;
   for (int guard = 0; taken < orphans && guard < 1100; ++guard) {      // (at most 4 x 256 orphans: one step takes at least one)
@@ -302,7 +304,7 @@ __device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<
     for (int i = 0; i < DEV_MAX_D; ++i) {
       if (next[i] == least && least != CHM_INF_COST) {
         ++taken;
-        next[i] = (w[i] == 0 || next[i] < (int64_t)cap * w[i]) ? next[i] + w[i] : CHM_INF_COST;
+        next[i] = next[i] < (int64_t)cap * w[i] ? next[i] + w[i] : CHM_INF_COST;
       }
     }
   }

@@ -135,31 +135,39 @@ __device__ __forceinline__ int pipeline_time(const int (&F)[N], const int (&C)[N
 // The least of max_i r_i * w_i over all valid reroute vectors (0 <= r_i <= cap, sum = orphans), w_i = the stage's
 // forward + backward time on peer i, all below 2^24.  Of the multiples w_i, 2 w_i, ..., cap w_i of all peers taken
 // together a vector whose maximum is v uses only ones up to v, at least `orphans` of them; so the minimum is the
-// orphans-th smallest multiple (equal ones counted one by one).  The multiples below orphans / sum(1 / w_i) are fewer
-// than `orphans` (floats, rounded well to the safe side), the few left are merged one at a time: about as many steps
-// as there are peers, each a minimum over the peers, whatever the number of vectors (2,380,833 for 32 micro-batches
-// over seven peers, which a sweep that shares their common entries took 318 us for; 153 for 16 over three).
+// orphans-th smallest multiple (equal ones counted one by one).  A peer whose time is 0 (a small factor rounds it down)
+// has cap multiples of 0: they are taken first, and the peer takes no more.  Of the others' multiples those below
+// (orphans left) / sum(1 / w_i) are fewer than the orphans left (floats, rounded well to the safe side), the few left are
+// merged one at a time: about as many steps as there are peers, each a minimum over the peers, whatever the number of
+// vectors (2,380,833 for 32 micro-batches over seven peers, which a sweep that shares their common entries took 318 us
+// for; 153 for 16 over three).
 __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[FAST_MAX_P], int peers, uint32_t orphans, uint32_t cap) {
+  const uint32_t most = cap < orphans ? cap : orphans;    // a peer can take this many
   float inv_sum = 0.0f;
+  uint32_t taken = 0;
 #pragma unroll
   for (int i = 0; i < FAST_MAX_P; ++i) {
-    if (i < peers) inv_sum += __builtin_amdgcn_rcpf((float)w[i]);      // uniform
+    if (i < peers) {                                 // uniform
+      const float inv = __builtin_amdgcn_rcpf((float)w[i]);
+      inv_sum += w[i] ? inv : 0.0f;
+      taken += w[i] ? 0u : most;
+    }
   }
-  const float v0 = (float)orphans * __builtin_amdgcn_rcpf(inv_sum) * 0.99999f;
+  // (all times 0: the peers can take all orphans, and inv_sum is not looked at)
+  const float v0 = taken < orphans ? (float)(orphans - taken) * __builtin_amdgcn_rcpf(inv_sum) * 0.99999f : 0.0f;
   uint32_t next[FAST_MAX_P];                         // peer i's smallest multiple not taken yet
-  uint32_t taken = 0;
 #pragma unroll
   for (int i = 0; i < FAST_MAX_P; ++i) {
     next[i] = 0xffffffffu;
     if (i < peers) {
-      uint32_t r = (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));  // (a time of 0 makes v0 0 and this 0)
-      r = r < cap ? r : cap;
+      const bool idle = w[i] == 0;
+      uint32_t r = idle ? 0u : (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));
+      r = r < most ? r : most;
       taken += r;
-      next[i] = r < cap ? __umul24(r + 1, w[i]) : 0xffffffffu;
+      next[i] = !idle && r < most ? __umul24(r + 1, w[i]) : 0xffffffffu;
     }
   }
   uint32_t least = 0;
-  const bool capped = cap < orphans;
   for (uint32_t guard = 0; taken < orphans && guard < 1100u; ++guard) {   // (at most 4 x 256 orphans: one step takes at least one)
     least = 0xffffffffu;
 #pragma unroll
@@ -172,7 +180,7 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[FAST_MAX_P
         const bool hit = next[i] == least;
         taken += hit ? 1u : 0u;
         uint32_t after = next[i] + w[i];
-        if (capped && after > __umul24(cap, w[i])) after = 0xffffffffu;
+        if (most < orphans && after > __umul24(most, w[i])) after = 0xffffffffu;
         next[i] = hit ? after : next[i];
       }
     }
