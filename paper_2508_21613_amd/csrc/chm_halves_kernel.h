@@ -30,6 +30,9 @@ __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st,
   return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);
 }
 constexpr int HALVES_NEVER = -(1 << 30);   // a term of a maximum that does not exist
+// memory peak of a lane without a lower half: above every cap (the peaks of plans stay below it by the bound that selects
+// these kernels, so a cap of 2^31 - 1, "no limit", can be taken as one less)
+constexpr int IDLE_PEAK = 0x7fffffff;
 
 // Words of an upper half's record.  UP cuts c[H+1..K]; the stages behind the crossing one, s = H+1..N-1, have UP nodes
 // of which the last has no waiting behind it.  (Strategy 0: node s runs stages s and s+1, the last node also stage 0.)
@@ -236,7 +239,7 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
     t[0] = make_int4(0, 0, 0, 0);
 #pragma unroll
     for (int i = 1; i <= H; ++i) t[i] = T[c[i]];
-    int peak_low = active ? 0 : 0x7fffffff, layers_low = ff->fixed_layers;
+    int peak_low = active ? 0 : IDLE_PEAK, layers_low = ff->fixed_layers;
     int F[LOW > 0 ? LOW : 1], C[LOW > 0 ? LOW : 1];
 #pragma unroll
     for (int s = 0; s < LOW; ++s) {
@@ -315,7 +318,7 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
     const int4 tv = t[H], tw = t[STRAT == 0 ? H - 1 : H], t1 = t[1];
 
     // ---- the upper halves
-    const int cap = (int)scn->cap;
+    const int cap = imin32((int)scn->cap, IDLE_PEAK - 1);
     const int fixed_step = in_vector(ff->fixed_step);
     const double per_step = 1.0 / (double)scn->K;
     auto limit_of = [&](uint64_t cost) -> int {       // no step time above this can reach `cost` (rounded up)

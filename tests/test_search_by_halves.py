@@ -1,7 +1,7 @@
 """Exhaustive search of large families by halves (from 2^21 partitions on) against the range kernel over the same space in
 two windows (which test_gpu_random.py and test_closed_forms.py hold against the oracle; test_gpu_full_space.py holds the
 search by halves itself against whole-space results of the oracle), the winner's cost against the oracle: both widths of the upper half, the smallest and largest number of stages, failed nodes that cross between the halves,
-one to three pipeline classes, every modelling option it takes, several chunks, no failure, ties.  Whole numbers,
+one to three pipeline classes, every modelling option it takes, several chunks, no failure, no memory limit, ties.  Whole numbers,
 compared exactly."""
 import numpy as np
 import pytest
@@ -26,6 +26,8 @@ CASES = {
     "11 stages, last stage lost": _case(26, 11, 2, 12, [21], cap_x=3.0),
     "16 stages": _case(26, 16, 2, 17, [12], cap_x=5.0),
     "8 stages, chunks of 2^16": _case(32, 8, 2, 8, [7], horizon_steps=1 << 22),
+    "6 stages, no memory limit": dict(_case(53, 6, 2, 7, [2]), mem_cap_mib=2 ** 31 - 1),
+    "8 stages, no memory limit, chunks of 2^16": dict(_case(32, 8, 2, 8, [7], horizon_steps=1 << 22), mem_cap_mib=2 ** 31 - 1),
     "8 stages, equal layers (ties)": dict(_case(32, 8, 2, 8, [6]), fwd_us=np.full(32, 900, np.int32), bwd_us=np.full(32, 1800, np.int32),
                                           mem_mib=np.full(32, 500, np.int32)),
 }
