@@ -45,6 +45,13 @@ typedef struct {
 } chm_selection;
 int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
 
+/* Whether chm_search_best takes a strategy's family by halves (a partition = a lower half that a lane keeps and an
+ * upper half that its wavefront walks over; large families at nominal speed): *upper_cuts = cuts of an upper half, 0 = it
+ * goes through the kernels that take partitions one by one; *wave_steps = steps of 64 lanes, one upper half each (partitions /
+ * (64 x wave_steps) = share of the lanes at work).  Host only; the decision chm_load_scenario takes.  Errors: CHM_ERR_ARG,
+ * CHM_ERR_OVERFLOW. */
+int chm_halves_selection(const chm_scenario_desc *desc, int32_t strategy, int32_t *upper_cuts, uint64_t *wave_steps);
+
 /* Switches event timing of chm_search_best / chm_search_range on or off for a handle,
  * and reads the timings of the last such call. */
 int chm_set_timing(chm_scenario *s, int32_t on);
@@ -55,7 +62,7 @@ int chm_get_timing(const chm_scenario *s, chm_timing *out);
  * collects the partitions that fit and evaluates them 64 at a time with all lanes busy; mode 0 = every lane
  * evaluates its own partitions, lanes whose partition fails idle; mode -1 (the default) = per strategy, mode 1
  * when fewer than 80 % of a seeded sample of partitions fit, else mode 0.  Results do not depend on the mode.
- * (Families of 2^21 partitions and more that are searched by halves do not use it.)
+ * (Families searched by halves do not use it: chm_halves_selection.)
  * share[k] (host, 3 floats, may be NULL) receives the sampled share per strategy (1.0 where no sample was
  * taken).  Errors: CHM_ERR_ARG. */
 int chm_set_filter_compaction(chm_scenario *s, int32_t mode, float *share);

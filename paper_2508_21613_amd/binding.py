@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(_HERE, "libchm_san.so" if os.environ.get("CHM_SANITIZE",
 OK, ERR_ARG, ERR_RANGE, ERR_OVERFLOW, ERR_UNRECOVERABLE, ERR_NO_FEASIBLE, ERR_HIP, ERR_LIMIT = 0, -1, -2, -3, -4, -5, -6, -7
 INFEASIBLE = (1 << 63) - 1
 
-SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection",
+SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection", "chm_halves_selection",
            "chm_search_range", "chm_search_ranks", "chm_search_cuts", "chm_rank_partitions", "chm_decode_plan", "chm_set_timing", "chm_set_filter_compaction", "chm_set_bounded_search", "chm_get_timing", "chm_family_classes",
            "chm_reroute_shape", "chm_transfer_plan", "chm_replan", "chm_replan_table", "chm_compare_objective", "chm_valu_probe", "chm_free_scenario",
            "chm_strerror"]
@@ -111,6 +111,7 @@ def lib():
         vp = C.c_void_p
         L.chm_load_scenario.argtypes = [C.POINTER(Desc), C.POINTER(vp)]
         L.chm_kernel_selection.argtypes = [C.POINTER(Desc), C.POINTER(Selection)]
+        L.chm_halves_selection.argtypes = [C.POINTER(Desc), C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_uint64)]
         L.chm_plan_space.argtypes = [vp, C.POINTER(Space)]
         L.chm_score_plans.argtypes = [vp, C.c_uint64, C.c_uint64, vp, vp]
         L.chm_score_ranks.argtypes = [vp, C.c_int32, vp, C.c_uint64, vp, vp]
@@ -291,6 +292,14 @@ def kernel_selection(sc):
             "present": [bool(x) for x in out.present], "specialised": [bool(x) for x in out.specialised],
             "sharp_bound": [bool(x) for x in out.sharp_bound], "reroute_mul24": bool(out.reroute_mul24),
             "reroute_swept_apart": bool(out.reroute_swept_apart)}
+
+
+def halves_selection(sc, strategy):
+    """chm_halves_selection: (cuts of an upper half, steps of a wavefront) of a strategy's exhaustive search; 0 cuts = not by halves (host only)"""
+    d, keep = _desc(sc)
+    up, steps = C.c_int32(), C.c_uint64()
+    _check(lib().chm_halves_selection(C.byref(d), strategy, C.byref(up), C.byref(steps)))
+    return int(up.value), int(steps.value)
 
 
 def search_best_batch(scenarios, mask=7, stream=None):

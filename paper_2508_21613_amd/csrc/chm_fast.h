@@ -63,6 +63,15 @@ struct FastTables {
   uint32_t lb_mult[DEV_MAX_AFF], lb_q[DEV_MAX_AFF];
 };
 
+// How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
+struct HalvesShape {
+  int up = 0;                   // cuts of an upper half
+  uint32_t n_upper = 0;         // upper halves
+  uint32_t n_items = 0;         // wavefronts of the search
+  uint32_t chunk = 0;           // upper halves per item
+  uint64_t steps = 0;           // 64 lower halves x one upper half
+};
+
 struct FastState {
   bool usable[3] = {false, false, false};   // per strategy: a specialised kernel covers this scenario
   // rerouting: at most 8 peers and 2^23 vectors per stage, and more than FAST_FUSED_R vectors over all stages.
@@ -99,6 +108,7 @@ struct FastState {
   // search by halves, per strategy: records of the upper halves and first items (a few MB), laid out by the first search
   uint32_t *d_upper[3] = {nullptr, nullptr, nullptr};
   bool upper_ready[3] = {false, false, false};
+  HalvesShape halves[3];
   // scratch of the candidate path of the bounded search; grown to what a search needs
   void *d_cand_list = nullptr;              // [candidate] cut positions, 16 bytes each
   uint32_t *d_cand_pos = nullptr;           // [candidate] its index

@@ -382,6 +382,77 @@ float estimate_fit_share(const DevScenario &h, const FastFamily &ff, int strat, 
   return (float)fit / (float)FIT_SAMPLES;
 }
 
+// Search by halves (chm_halves_kernel.h): which families, and how many cuts the upper half takes.
+//
+// Partitions from which a family is looked at: below, its seeds, its first search's table and the fixed cost of
+// a wavefront (its lower half, a round of 32 upper halves) weigh more than the partitions (1.6 M of 7 stages, us, range
+// kernel / by halves: 28 / 34).
+constexpr uint64_t HALVES_FROM = 1ull << 21;
+// What halves must save: a partition costs the range kernel about `stages` units, a lane's step one unit per pipeline
+// class, whether the lane has a lower half or not, and the fixed cost is about 7 M units.  (A unit is a nanosecond over
+// 1,000 of them.)  Decides for families whose lower halves leave most lanes idle, us, range kernel / by halves: 5 stages,
+// 2.1 M partitions (a third of the lanes at work) 29 / 33 and, of two classes, 29 / 40; 3.0 M 36 / 35 and 34 / 44; 3.8 M
+// (whole searches) 68 / 64; 5.6 M 53 / 41 and 50 / 55; 6 stages, 2.9 M (78 % at work) 36 / 36 and 38 / 33.
+constexpr int64_t HALVES_SAVES = 7ll << 20;
+// Bytes a table of upper halves may take (one per strategy and handle, kept).
+constexpr uint64_t HALVES_TABLE = 8ull << 20;
+// Upper halves of three cuts fall into longer lists than those of two (fewer wavefronts, each of which works out its
+// lower half), but a lower half that is a cut shorter may be one of few: the 64 lanes of a wavefront share the last lower
+// cut.  Three cuts are taken unless their wavefront steps exceed those of two by a quarter.  us, two cuts / three, strategies
+// 2 and 0, with the ratio of the steps: 6 stages, 7.0 M partitions (4.3) 44 / 80, 47 / 113; 7 stages, 3.3 M (1.75) 35 / 39,
+// 37 / 44, and 45 M (1.32) 97 / 128, 134 / 185; 8 stages, 15 M (1.13) 62 / 56, 65 / 79; 10 stages, 39 M (1.02) 128 / 110,
+// 160 / 142; 16 stages, 7.7 M (1.01) 126 / 93, 164 / 110.
+constexpr uint64_t WIDER_BY = 4;
+
+int halves_record_words(int k, int up, int n_time) {
+  return k == 0 ? chmk_halves_words_s0(up, n_time) : k == 1 ? chmk_halves_words_s1(up, n_time) : chmk_halves_words_s2(up, n_time);
+}
+
+// wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts; steps = 0: not
+// within the kernel's 32-bit ranks of lower halves
+HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
+  const int H = sp - 1 - up, L = h.L;
+  HalvesShape hs;
+  uint64_t steps = 0, items = 0;
+  if (L - 1 - H < up) return hs;
+  for (int v = H; v <= L - 1 - up; ++v) {
+    if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return hs;
+    steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
+  }
+  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(512, steps / 32768));
+  for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hs.chunk - 1) / hs.chunk);
+  if (items >= (1ull << 31)) return hs;
+  hs.up = up;
+  hs.steps = steps;
+  hs.n_items = (uint32_t)items;
+  hs.n_upper = (uint32_t)h.binom[up][L - 1 - H];
+  return hs;
+}
+
+HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
+  const FastFamily &ff = t->fam[k];
+  const int sp = h.fam[k].stages;
+  const uint64_t partitions = h.fam[k].n_part;
+  const HalvesShape none;
+  if (partitions < HALVES_FROM || sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return none;
+  for (int ci = 0; ci < ff.n_cls; ++ci)
+    if (!ff.cls[ci].unit || ff.cls[ci].M < sp) return none;
+  if (ff.n_time > (k == 0 ? 3 : 1)) return none;
+  for (int s = 0; k == 2 && s < h.n_aff; ++s)
+    if (t->even_share[s] == 0) return none;
+  auto in_table = [&](const HalvesShape &hs) {
+    return hs.up != 0 && (uint64_t)hs.n_upper * (uint64_t)halves_record_words(k, hs.up, ff.n_time) * 4 + sizeof(HalvesItems) <= HALVES_TABLE;
+  };
+  const HalvesShape two = halves_of_width(h, sp, 2);
+  HalvesShape taken = in_table(two) ? two : none;
+  if (sp >= 7) {                          // (5 and 6 stages: never worth it, and no instance)
+    const HalvesShape three = halves_of_width(h, sp, 3);
+    if (in_table(three) && (taken.up == 0 || three.steps <= two.steps + two.steps / WIDER_BY)) taken = three;
+  }
+  const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
+  return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)ff.n_time + (unsigned)HALVES_SAVES ? taken : none;
+}
+
 }  // namespace
 
 static void fast_quiesce(FastState *f) {
@@ -402,6 +473,7 @@ static bool build_vector_rows(FastState *f, const DevScenario &h, hipStream_t st
 
 void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
   for (bool &u : f->usable) u = false;
+  for (HalvesShape &hs : f->halves) hs = HalvesShape();
   f->large_reroute = f->rows_ok = false;
   f->mul24_reroute = false;
   f->vec_words = 16;
@@ -510,6 +582,7 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
       f->large_reroute = ok && f->rows_ok && r_sum > FAST_FUSED_R;
     }
     f->usable[k] = ok;
+    if (ok) f->halves[k] = halves_shape(t, h, k);
     f->fit_share[k] = (ok && k != 2) ? -1.0f : 1.0f;      // sampled on first need
   }
   f->vec_words = vec_words;
@@ -825,71 +898,37 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
   return a.costs_out == nullptr && h.fam[a.strategy].stages <= PACKED_MAX_STAGES;
 }
 
-namespace {
-// Partitions from which a family is searched by halves.  Below, its seeds, its first search's table and the fixed cost of
-// a wavefront (its lower half, a round of 32 upper halves) weigh more than the partitions: 1.5 M partitions of 6 stages took
-// 23 + 12 us by halves and take 17 in the range kernel, 10.7 M of 7 stages 35 + 12 by halves and 79.
-constexpr uint64_t HALVES_FROM = 1ull << 21;
-// bytes a table of upper halves may take (one per strategy and handle, kept): three cuts up to here, else two
-constexpr uint64_t HALVES_TABLE = 8ull << 20;
-}  // namespace
-
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_t partitions) {
-  if (k < 0 || k > 2 || !f->usable[k] || partitions != h.fam[k].n_part || partitions < HALVES_FROM) return false;
-  const FastFamily &ff = f->h_tables.fam[k];
-  const int sp = h.fam[k].stages;
-  if (sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return false;
-  for (int ci = 0; ci < ff.n_cls; ++ci)
-    if (!ff.cls[ci].unit || ff.cls[ci].M < sp) return false;
-  if (ff.n_time > (k == 0 ? 3 : 1)) return false;
-  for (int s = 0; k == 2 && s < h.n_aff; ++s)
-    if (f->h_tables.even_share[s] == 0) return false;
-  return true;
+  return k >= 0 && k <= 2 && f->halves[k].up != 0 && partitions == h.fam[k].n_part;
 }
 
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, void *stream) {
   const int k = a.strategy;
   if (!fast_halves_covers(f, h, k, partitions)) return 1;
-  const FastFamily &ff = f->h_tables.fam[k];
-  const int sp = h.fam[k].stages, L = h.L;
+  const HalvesShape &hs = f->halves[k];
+  const int sp = h.fam[k].stages, n_time = f->h_tables.fam[k].n_time;
+  const size_t records = (size_t)hs.n_upper * (size_t)halves_record_words(k, hs.up, n_time);
+  if (!f->d_upper[k]) {
+    if (!may_allocate) return 1;
+    if (!pool_take(f->d_upper[k], records * sizeof(uint32_t) + sizeof(HalvesItems))) return -1;
+  }
   HalvesLaunch hl;
   hl.s = a;
   hl.tab = f->d_tables;
   hl.chunk_words = chunk_words;
-  for (int up = 3; up >= 2; --up) {
-    const int H = sp - 1 - up;
-    const uint64_t n_upper = h.binom[up][L - 1 - H];
-    const int words = k == 0 ? chmk_halves_words_s0(up, ff.n_time) : k == 1 ? chmk_halves_words_s1(up, ff.n_time) : chmk_halves_words_s2(up, ff.n_time);
-    const uint64_t bytes = n_upper * (uint64_t)words * 4 + sizeof(HalvesItems);
-    if (bytes > HALVES_TABLE) continue;
-    // wavefront steps (64 lower halves x one upper half), cut into items of `chunk` upper halves
-    uint64_t steps = 0;
-    for (int v = H; v <= L - 1 - up; ++v) {
-      if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return 1;
-      steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
-    }
-    hl.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(512, steps / 32768));
-    uint64_t items = 0;
-    for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hl.chunk - 1) / hl.chunk);
-    if (items >= (1ull << 31)) return 1;
-    hl.n_items = (uint32_t)items;
-    hl.n_upper = (uint32_t)n_upper;
-    if (!f->d_upper[k]) {
-      if (!may_allocate) return 1;
-      if (!pool_take(f->d_upper[k], bytes)) return -1;
-    }
-    hl.upper = f->d_upper[k];
-    hl.items = (HalvesItems *)(f->d_upper[k] + n_upper * (uint64_t)words);     // (records are whole 16 bytes)
-    const bool build = !f->upper_ready[k];
-    const int rc = k == 0 ? chmk_halves_s0(sp, up, ff.n_time, hl, build, stream)
-                   : k == 1 ? chmk_halves_s1(sp, up, ff.n_time, hl, build, stream) : chmk_halves_s2(sp, up, ff.n_time, hl, build, stream);
-    if (rc) return rc;
-    if (hipGetLastError() != hipSuccess) return -1;
-    f->upper_ready[k] = true;
-    return 0;
-  }
-  return 1;
+  hl.chunk = hs.chunk;
+  hl.n_items = hs.n_items;
+  hl.n_upper = hs.n_upper;
+  hl.upper = f->d_upper[k];
+  hl.items = (HalvesItems *)(f->d_upper[k] + records);       // (records are whole 16 bytes)
+  const bool build = !f->upper_ready[k];
+  const int rc = k == 0 ? chmk_halves_s0(sp, hs.up, n_time, hl, build, stream)
+                 : k == 1 ? chmk_halves_s1(sp, hs.up, n_time, hl, build, stream) : chmk_halves_s2(sp, hs.up, n_time, hl, build, stream);
+  if (rc) return rc;
+  if (hipGetLastError() != hipSuccess) return -1;
+  f->upper_ready[k] = true;
+  return 0;
 }
 
 int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void *stream) {

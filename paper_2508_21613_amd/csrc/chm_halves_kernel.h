@@ -497,8 +497,10 @@ void launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
 template <int STRAT, int N>
 int halves_by_shape(int up, int n_cls, const HalvesLaunch &a, bool build, hipStream_t st) {
 #define CHM_SHAPE(UPV, NCV) if (up == UPV && n_cls == NCV) { launch_halves<STRAT, N, UPV, NCV>(a, build, st); return 0; }
-  CHM_SHAPE(2, 1) CHM_SHAPE(3, 1)
-  if constexpr (STRAT == 0) { CHM_SHAPE(2, 2) CHM_SHAPE(3, 2) CHM_SHAPE(2, 3) CHM_SHAPE(3, 3) }
+  CHM_SHAPE(2, 1)
+  if constexpr (STRAT == 0) { CHM_SHAPE(2, 2) CHM_SHAPE(2, 3) }
+  if constexpr (N >= 7) { CHM_SHAPE(3, 1) }          // (fewer stages: lower halves of one or two cuts, too few for 64 lanes)
+  if constexpr (N >= 7 && STRAT == 0) { CHM_SHAPE(3, 2) CHM_SHAPE(3, 3) }
 #undef CHM_SHAPE
   return 1;
 }

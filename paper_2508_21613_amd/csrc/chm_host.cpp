@@ -1125,6 +1125,24 @@ extern "C" int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection
   return rc;
 }
 
+extern "C" int chm_halves_selection(const chm_scenario_desc *desc, int32_t strategy, int32_t *upper_cuts, uint64_t *wave_steps) {
+  if (strategy < 0 || strategy > 2 || !upper_cuts || !wave_steps) return CHM_ERR_ARG;
+  *upper_cuts = 0;
+  *wave_steps = 0;
+  int rc = validate(desc);
+  if (rc) return rc;
+  chm_scenario *s = new (std::nothrow) chm_scenario();
+  if (!s || !s->search) { delete s; return CHM_ERR_HIP; }
+  rc = build_model(desc, s);
+  if (rc == CHM_OK) {
+    fast_select(&s->fast, s->h, s->int32_ok);
+    *upper_cuts = s->fast.halves[strategy].up;
+    *wave_steps = s->fast.halves[strategy].steps;
+  }
+  delete s;
+  return rc;
+}
+
 extern "C" int chm_plan_space(const chm_scenario *s, chm_space *out) {
   if (!s || !out) return CHM_ERR_ARG;
   *out = s->space;

@@ -18,8 +18,10 @@ def _case(L, PP, DP, M, failed, cap_x=4.0, act=False, **kw):
 
 CASES = {
     "5 stages, long model": _case(96, 5, 2, 5, [3]),
+    "5 stages, longest model, nothing lost": _case(128, 5, 2, 9, []),
     "6 stages, first stage lost": _case(53, 6, 2, 7, [0], cap_x=3.0),
     "7 stages, options": _case(39, 7, 3, 8, [10], act=True, transfer_assign=1, allreduce_us=400),
+    "7 stages, long model": _case(68, 7, 2, 9, [8]),
     "8 stages, crossing node lost, three classes": _case(32, 8, 3, 9, [4, 11], transfer_assign=1),
     "8 stages, every pipeline hit": _case(32, 8, 3, 8, [3, 12, 23], cap_x=3.0),
     "8 stages, nothing lost": _case(32, 8, 2, 16, []),
@@ -31,6 +33,39 @@ CASES = {
     "8 stages, equal layers (ties)": dict(_case(32, 8, 2, 8, [6]), fwd_us=np.full(32, 900, np.int32), bwd_us=np.full(32, 1800, np.int32),
                                           mem_mib=np.full(32, 500, np.int32)),
 }
+
+
+def _large(L, PP, DP, M, failed):
+    fwd, bwd, mem = synth.layer_tables(L, L)
+    return synth.scenario(L, PP, DP, M, fwd, bwd, mem, failed, 150, int(mem.sum()))
+
+
+def test_lanes_are_at_work_in_every_family_searched_by_halves():
+    """wavefronts share the last lower cut, so a family with few lower halves per cut leaves lanes idle: such a family takes
+    shorter upper halves, or the range kernel (5 stages, where even two upper cuts leave two thirds idle)"""
+    from math import comb
+    from paper_2508_21613_amd import binding as B
+    widths = set()
+    for PP in range(5, 17):
+        for L in range(PP + 6, 129, 3):
+            sc = _large(L, PP, 3, PP + 4, [PP // 2])
+            if comb(L - 1, PP - 1) >= 1 << 36:
+                continue
+            for k, stages in ((0, PP), (1, PP - 1), (2, PP)):
+                n, (up, steps) = comb(L - 1, stages - 1), B.halves_selection(sc, k)
+                classes = 2 if k == 0 else 1
+                widths.add((stages, up))
+                if up == 0:
+                    assert n < 1 << 21 or stages < 7, (L, stages, k)
+                    continue
+                assert n >= 1 << 21 and n * stages >= 64 * steps * classes + (7 << 20), (L, stages, k)
+                by_width = {w: sum(-(-comb(v - 1, stages - 2 - w) // 64) * comb(L - 1 - v, w) for v in range(stages - 1 - w, L - w)) for w in (2, 3)}
+                assert steps == by_width[up] and 4 * steps <= 5 * by_width[2], (L, stages, k)
+                assert n / (64 * steps) > (0.3 if stages == 5 else 0.55), (L, stages, k)
+    assert {(5, 0), (5, 2), (6, 2), (7, 2), (7, 3), (8, 3), (16, 3)} <= widths
+    assert B.halves_selection(_large(90, 5, 3, 8, [3]), 0)[0] == B.halves_selection(_large(87, 5, 3, 8, [3]), 2)[0] == 0
+    assert B.halves_selection(_large(54, 6, 3, 8, [3]), 0)[0] == B.halves_selection(_large(60, 7, 3, 8, [3]), 2)[0] == 2
+    assert B.halves_selection(dict(_large(48, 8, 3, 8, [3]), speed_q16=np.full(24, 65537, np.uint32)), 2)[0] == 0
 
 
 @pytest.mark.gpu
