@@ -28,6 +28,8 @@ CASES = {
     "11 stages, last stage lost": _case(26, 11, 2, 12, [21], cap_x=3.0),
     "16 stages": _case(26, 16, 2, 17, [12], cap_x=5.0),
     "8 stages, chunks of 2^16": _case(32, 8, 2, 8, [7], horizon_steps=1 << 22),
+    "8 stages, next to nothing fits": _case(32, 8, 3, 9, [4], cap_x=2.1),
+    "8 stages, nothing of one strategy fits": _case(32, 8, 3, 9, [4], cap_x=1.5),
     "6 stages, no memory limit": dict(_case(53, 6, 2, 7, [2]), mem_cap_mib=2 ** 31 - 1),
     "8 stages, no memory limit, chunks of 2^16": dict(_case(32, 8, 2, 8, [7], horizon_steps=1 << 22), mem_cap_mib=2 ** 31 - 1),
     "8 stages, equal layers (ties)": dict(_case(32, 8, 2, 8, [6]), fwd_us=np.full(32, 900, np.int32), bwd_us=np.full(32, 1800, np.int32),
