@@ -31,6 +31,8 @@ CASES = {
     "two of three peers": (True, _case(10, 4, 4, 6, [2], (65536, 1, 1, 70000), 3)),
     "all peers": (True, _case(10, 4, 3, 6, [2], (65536, 1, 1), 3)),
     "two stages lost": (True, _case(9, 4, 3, 4, [1, 6], (65536, 1, 60000), 3)),
+    "four peers": (True, _case(8, 3, 5, 9, [1], (65536, 1, 60000, 61000, 90000), 4)),
+    "five peers": (True, _case(8, 3, 6, 9, [1], (65536, 1, 60000, 61000, 90000, 65536), 3)),
     "nine peers": (True, _case(8, 3, 10, 6, [1], (65536, 1, 2, 60000, 61000, 1, 62000, 63000, 64000, 65000), 1)),
     "generic kernel, cap binds": (False, _case(10, 8, 3, 16, [3], (65536, 1, 65536), 9, scale=8, slowest=17)),
     "generic kernel, no cap": (False, _case(10, 8, 3, 16, [3], (65536, 1, 65536), 0, scale=8, slowest=17)),
