@@ -277,8 +277,10 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {
 
 // Combinadic digits of `rem` (a partition rank): for i = K..1 the largest x with C(x, i) <= rem.
 // C(., i) grows with x, so each digit is found by a four-way search over [i-1, previous digit - 1]:
-// three independent table probes per step, the range shrinks to a quarter; all lanes take the same
-// number of steps (no divergence), `steps` = 3 for up to 64 candidates, 4 for up to 256.
+// three independent table probes per step, the range shrinks to a quarter; all lanes take the same number of steps (no
+// divergence): unrank_steps of the L - K candidates a digit has at most (the digits above and below it narrow its range).
+__device__ __forceinline__ int unrank_steps(int candidates) { return candidates <= 4 ? 1 : candidates <= 16 ? 2 : candidates <= 64 ? 3 : 4; }
+
 template <int K, typename Rank>
 __device__ __forceinline__ void unrank_digits(Rank rem, int L, int steps, const Rank *table, int (&c)[K + 2]) {
   // table[(i-1) * DEV_MAX_L + x] = C(x, i)
@@ -533,7 +535,7 @@ k_fast_search(FastLaunch a) {
   if (!compact && !LIST) {
     uint64_t rem = run_len ? a.s.part_first + run_first + (run_first >= a.s.jump_at ? a.s.jump_by : 0) : 0;   // idle lanes walk from rank 0: always valid cuts
     // combinadic digits from the LDS copy of the binomial table
-    unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+    unrank_digits<K, uint64_t>(rem, L, unrank_steps(L - K), BN, c);
   }
 
   const int cap = (int)scn->cap;
@@ -636,7 +638,7 @@ k_fast_search(FastLaunch a) {
             uint64_t rem = live ? a.s.ranks[entry] : 0;
             valid = rem < scn->fam[STRAT].n_part;
             if (!valid) rem = 0;
-            unrank_digits<K, uint64_t>(rem, L, (L - 1) <= 64 ? 3 : 4, BN, c);
+            unrank_digits<K, uint64_t>(rem, L, unrank_steps(L - K), BN, c);
           }
         }
         bool fits = live && valid && largest_peak<SP, STRAT>(ff, c, PW, PA) <= cap;
