@@ -283,17 +283,18 @@ __device__ __forceinline__ int64_t least_penalty64(const DevScenario *scn, Cuts<
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
     w[i] = i < p ? peer_weight(scn, cuts, a, i) : 0;
-    if (i < p && w[i] != 0) inv_sum += 1.0 / (double)w[i];
-    if (i < p && w[i] == 0) taken += cap;
+    if (i < p) {                                     // uniform
+      inv_sum += w[i] != 0 ? 1.0 / (double)w[i] : 0.0;
+      taken += w[i] != 0 ? 0 : cap;
+    }
   }
   const double v0 = taken < orphans ? (double)(orphans - taken) / inv_sum * (1.0 - 1e-9) : 0.0;
 #pragma unroll
   for (int i = 0; i < DEV_MAX_D; ++i) {
-    const bool busy = i < p && w[i] != 0;
-    int r = busy ? (int)(v0 / (double)w[i]) : 0;
+    int r = i < p && w[i] > 0 ? (int)(v0 / (double)w[i]) : 0;
     r = r < cap ? r : cap;
     taken += r;
-    next[i] = busy && r < cap ? (int64_t)(r + 1) * w[i] : CHM_INF_COST;
+    next[i] = i < p && r < cap && w[i] > 0 ? (int64_t)(r + 1) * w[i] : CHM_INF_COST;
   }
   int64_t least = 0;
   for (int guard = 0; taken < orphans && guard < 1100; ++guard) {      // (at most 4 x 256 orphans: one step takes at least one)

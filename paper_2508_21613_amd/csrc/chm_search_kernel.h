@@ -141,41 +141,34 @@ __device__ __forceinline__ int pipeline_time(const int (&F)[N], const int (&C)[N
 // merged one at a time: about as many steps as there are peers, each a minimum over the peers, whatever the number of
 // vectors (2,380,833 for 32 micro-batches over seven peers, which a sweep that shares their common entries took 318 us
 // for; 153 for 16 over three).
-// P: the most peers this instance takes.  Up to 4 (the usual case) everything is worked out for all four, which costs less
-// than a branch per peer: peers that are not there are entered with a time above all others and no multiples.  Two stages
-// of 2 peers and 9 vectors each, 1.6 M partitions of 8 stages: 87 us a search, 97 with the instance for 15 peers (sweeping
-// the 9 vectors 87).
+// w[i] = NO_MULTIPLES for a peer without any left to take; taken = multiples of 0 taken already; most = multiples a peer has
+// (cap, or all orphans); P = the most peers this instance takes.  Up to 4 (the usual case) everything is worked out for all
+// four, which costs less than a branch per peer: two stages of 2 peers and 9 vectors each, 1.6 M partitions of 8 stages: 87 us
+// a search, 97 with the instance for 15 peers (sweeping the 9 vectors 87).
+constexpr uint32_t NO_MULTIPLES = 0xffffffffu;
 template <int P>
-__device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[P], int peers, uint32_t orphans, uint32_t cap) {
+__device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[P], int peers, uint32_t taken, uint32_t orphans, uint32_t most) {
   constexpr bool ALL = P <= 4;
-  const uint32_t most = cap < orphans ? cap : orphans;    // a peer can take this many
-  float inv_sum = 0.0f;
-  uint32_t taken = 0;
+  float inv_sum = 0.0f;                              // (peers without multiples add next to nothing, to the safe side)
 #pragma unroll
   for (int i = 0; i < P; ++i) {
-    if (ALL || i < peers) {                          // uniform
-      const float inv = __builtin_amdgcn_rcpf((float)w[i]);
-      inv_sum += w[i] ? inv : 0.0f;
-      taken += w[i] ? 0u : most;
-    }
+    if (ALL || i < peers) inv_sum += __builtin_amdgcn_rcpf((float)w[i]);      // uniform
   }
-  // (all times 0: the peers can take all orphans, and inv_sum is not looked at)
   const float v0 = taken < orphans ? (float)(orphans - taken) * __builtin_amdgcn_rcpf(inv_sum) * 0.99999f : 0.0f;
   uint32_t next[P];                                  // peer i's smallest multiple not taken yet
 #pragma unroll
   for (int i = 0; i < P; ++i) {
-    next[i] = 0xffffffffu;
+    next[i] = NO_MULTIPLES;
     if (ALL || i < peers) {
-      const bool idle = w[i] == 0;
-      uint32_t r = idle ? 0u : (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));      // (v0 < 2^31: 0 where there is no peer)
+      uint32_t r = (uint32_t)(v0 * __builtin_amdgcn_rcpf((float)w[i]));      // (v0 < 2^31: 0 for a peer without multiples)
       r = r < most ? r : most;
       taken += r;
-      next[i] = !idle && r < most && i < peers ? __umul24(r + 1, w[i]) : 0xffffffffu;
+      next[i] = r < most && w[i] != NO_MULTIPLES ? __umul24(r + 1, w[i]) : NO_MULTIPLES;
     }
   }
   uint32_t least = 0;
   for (uint32_t guard = 0; taken < orphans && guard < 1100u; ++guard) {   // (at most 4 x 256 orphans: one step takes at least one)
-    least = 0xffffffffu;
+    least = NO_MULTIPLES;
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       if (ALL || i < peers) least = least < next[i] ? least : next[i];
@@ -186,7 +179,7 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[P], int pe
         const bool hit = next[i] == least;
         taken += hit ? 1u : 0u;
         uint32_t after = next[i] + w[i];
-        if (most < orphans && after > __umul24(most, w[i])) after = 0xffffffffu;
+        if (most < orphans && after > __umul24(most, w[i])) after = NO_MULTIPLES;
         next[i] = hit ? after : next[i];
       }
     }
@@ -199,17 +192,25 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[P], int pe
 __device__ __forceinline__ uint32_t stage_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
   const int p = scn->aff_peers[st];
   if (tab->even_share[st] != 0) return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);    // uniform
-  const uint32_t orphans = (uint32_t)scn->aff_total[st], cap = scn->rcap > 0 ? (uint32_t)scn->rcap : orphans;
+  const uint32_t orphans = (uint32_t)scn->aff_total[st];
+  const uint32_t most = scn->rcap > 0 && (uint32_t)scn->rcap < orphans ? (uint32_t)scn->rcap : orphans;
+  uint32_t taken = 0;
+  auto time_of = [&](int i) -> uint32_t {
+    if (i >= p) return NO_MULTIPLES;                 // uniform
+    const uint32_t w = peer_time(f, b, scn->aff_q[st][i]);
+    taken += w ? 0u : most;
+    return w ? w : NO_MULTIPLES;
+  };
   if (p <= 4) {                                      // uniform
     uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = i < p ? peer_time(f, b, scn->aff_q[st][i]) : 0xffffffffu;
-    return least_penalty<4>(w, p, orphans, cap);
+    for (int i = 0; i < 4; ++i) w[i] = time_of(i);
+    return least_penalty<4>(w, p, taken, orphans, most);
   }
   uint32_t w[FAST_MAX_P];
 #pragma unroll
-  for (int i = 0; i < FAST_MAX_P; ++i) w[i] = i < p ? peer_time(f, b, scn->aff_q[st][i]) : 0u;
-  return least_penalty<FAST_MAX_P>(w, p, orphans, cap);
+  for (int i = 0; i < FAST_MAX_P; ++i) w[i] = time_of(i);
+  return least_penalty<FAST_MAX_P>(w, p, taken, orphans, most);
 }
 
 __device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
@@ -477,9 +478,10 @@ __device__ __forceinline__ int2 stage_times(const int2 *tc, const int (&c)[SP + 
 // since a round appends at most 64 entries to fewer than 64 waiting ones.
 constexpr int QCAP = 128;
 
-// Waves per SIMD the register allocator is asked to keep possible: 5 up to 5 stages (at most 96 vector registers), 4 up
-// to 9 (128), 3 up to 14 (168, up to 32 of them spilled), 2 beyond (256; from 20 stages on some are spilled).  One wave
-// more at 8 stages (96 registers, 22 spilled) took 1,299 instead of 1,099 us for the 32-card search.
+// Waves per SIMD the register allocator is asked to keep possible: 5 up to 5 stages (at most 96 vector registers), 4 up to
+// 10 (128), 3 up to 16 (168), 2 beyond (256; from 27 stages on some are spilled).  Strategy 2, whose loops over the peers
+// need the most: 5 up to 8 stages, which fit 96 without spills when asked to (97 unasked: a range of 3 M partitions of 8
+// stages 69 instead of 73 us, 2.6 M of uneven speeds 201 instead of 224).
 //
 // QUEUED (range search of strategies 0 and 1 without cost store): lanes whose partition fails the memory
 // filter would idle through the recurrence of their wave, and consecutive ranks share their upper cuts, so
@@ -492,7 +494,7 @@ constexpr int QCAP = 128;
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
 // spilled bytes per lane at 8 stages and 4 % of its time).
 template <int SP, int STRAT, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= 5 ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : 2)))
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : 2)))
 k_fast_search(FastLaunch a) {
   constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
