@@ -216,7 +216,7 @@ int chmk_halves_words_s1(int up, int n_cls);
 int chmk_halves_words_s2(int up, int n_cls);
 // Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
 // halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
-// search, only for what chm_halves_kernel.h says.  may_allocate = false: only with tables that are already there.  Same
+// search, only for what chm_halves_kernel.h says.  may_allocate = false, or no memory to be had: only with tables that are already there.  Same
 // return convention as fast_search (positive: not covered, or smaller than what the range search does as fast).
 // fast_halves_covers: whether it takes the family at all.
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);

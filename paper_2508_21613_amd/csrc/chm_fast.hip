@@ -910,8 +910,8 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   const int sp = h.fam[k].stages, n_time = f->h_tables.fam[k].n_time;
   const size_t records = (size_t)hs.n_upper * (size_t)halves_record_words(k, hs.up, n_time);
   if (!f->d_upper[k]) {
-    if (!may_allocate) return 1;
-    if (!pool_take(f->d_upper[k], records * sizeof(uint32_t) + sizeof(HalvesItems))) return -1;
+    // (no memory for the table: the range kernel needs none)
+    if (!may_allocate || !pool_take(f->d_upper[k], records * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
   }
   HalvesLaunch hl;
   hl.s = a;
