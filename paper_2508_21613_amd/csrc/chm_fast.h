@@ -107,7 +107,8 @@ struct FastState {
   const uint64_t *d_comp = nullptr;
   // search by halves, per strategy: records of the upper halves and first items (a few MB), laid out by the first search
   uint32_t *d_upper[3] = {nullptr, nullptr, nullptr};
-  bool upper_ready[3] = {false, false, false};
+  bool upper_ready[3] = {false, false, false};      // the table is there: a search that filled it has been waited for
+  bool upper_queued[3] = {false, false, false};     // a launch of the current search fills it, or found it ready
   HalvesShape halves[3];
   // scratch of the candidate path of the bounded search; grown to what a search needs
   void *d_cand_list = nullptr;              // [candidate] cut positions, 16 bytes each
@@ -222,6 +223,8 @@ int chmk_halves_words_s2(int up, int n_cls);
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, void *stream);
+// The stream of the last search has been waited for: the tables its launches filled are there.
+void fast_halves_settled(FastState *f);
 // Sampled share of partitions of a strategy that pass the memory filter (1.0 where no sample applies).
 float fast_fit_share(FastState *f, const DevScenario &h, int strategy);
 // Scores plan indices [local_first, local_first+count) of the rerouting family (indices local to

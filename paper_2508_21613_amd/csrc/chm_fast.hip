@@ -927,8 +927,15 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
                  : k == 1 ? chmk_halves_s1(sp, hs.up, n_time, hl, build, stream) : chmk_halves_s2(sp, hs.up, n_time, hl, build, stream);
   if (rc) return rc;
   if (hipGetLastError() != hipSuccess) return -1;
-  f->upper_ready[k] = true;
+  f->upper_queued[k] = true;
   return 0;
+}
+
+void fast_halves_settled(FastState *f) {
+  for (int k = 0; k < 3; ++k) {
+    f->upper_ready[k] = f->upper_ready[k] || f->upper_queued[k];
+    f->upper_queued[k] = false;
+  }
 }
 
 int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void *stream) {

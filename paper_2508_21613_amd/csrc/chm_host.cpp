@@ -582,6 +582,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
   s->last = chm_timing();
   SearchCtx &c = s->search->ctx;
   c = SearchCtx();
+  for (bool &q : s->fast.upper_queued) q = false;     // (left by a call that failed before its wait)
   c.jobs = jobs;
   c.light = light;
   const uint64_t chunk = 1ull << s->idx_bits;
@@ -754,6 +755,7 @@ int collect_jobs(chm_scenario *s, chm_best *out, uint64_t *position, hipStream_t
   if (c.empty) { nothing_found(out); return CHM_ERR_NO_FEASIBLE; }
   HIP_TRY(hipSetDevice(s->device));
   if (!synced && hipStreamSynchronize(st) != hipSuccess) { s->slots_ready_for = 0; return CHM_ERR_HIP; }
+  fast_halves_settled(&s->fast);
   const bool light = c.light;
   int64_t best_cost = CHM_INFEASIBLE;
   int best_strategy = -1;

@@ -1,6 +1,7 @@
-/* A plain C caller whose device memory runs short: this program's own hipMalloc stands in front of the runtime's and refuses
- * allocations above a size while `limit` is set.  Searches a scenario of at least 2^21 partitions so, and again with memory.
- * tests/test_scarce_memory.py builds and runs it. */
+/* A plain C caller that some calls of the runtime fail: its own hipMalloc stands in front of the runtime's and refuses
+ * allocations above a size while `limit` is set, its hipStreamSynchronize waits but reports an error while `broken` is, and its
+ * hipLaunchKernel counts.  Searches a scenario of at least 2^21 partitions without memory for tables, after a search whose wait
+ * was reported as failed, and undisturbed.  tests/test_scarce_memory.py builds and runs it. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <stdio.h>
@@ -17,6 +18,23 @@ int hipMalloc(void **p, size_t bytes) {
   if (!real) *(void **)&real = dlsym(RTLD_NEXT, "hipMalloc");
   if (limit && bytes > limit) { ++refused; return 2; }          /* out of memory */
   return real(p, bytes);
+}
+
+static int broken = 0, launched = 0;
+typedef struct { unsigned x, y, z; } dim3_t;
+
+int hipStreamSynchronize(void *stream) {
+  static int (*real)(void *) = NULL;
+  if (!real) *(void **)&real = dlsym(RTLD_NEXT, "hipStreamSynchronize");
+  const int rc = real(stream);
+  return broken ? 999 : rc;                                     /* unknown error */
+}
+
+int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream) {
+  static int (*real)(const void *, dim3_t, dim3_t, void **, size_t, void *) = NULL;
+  if (!real) *(void **)&real = dlsym(RTLD_NEXT, "hipLaunchKernel");
+  ++launched;
+  return real(f, grid, block, args, lds, stream);
 }
 
 static void print_best(const char *what, int rc, const chm_best *b) {
@@ -44,6 +62,14 @@ int main(int argc, char **argv) {
     print_best("scarce", rc, &b);
   }
   printf("refused %d\n", refused);
+  for (int i = 0; i < 3; ++i) {                                 /* the first one's wait fails */
+    broken = i == 0;
+    launched = 0;
+    rc = chm_search_best(s, 7u, &b, NULL);
+    broken = 0;
+    printf("launches %d rc=%d\n", launched, rc);
+    if (i > 0) print_best("after", rc, &b);
+  }
   for (uint32_t mask = 1; mask <= 7; mask = mask == 4 ? 7 : 2 * mask) {
     rc = chm_search_best(s, mask, &b, NULL);
     print_best("plenty", rc, &b);

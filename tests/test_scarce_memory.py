@@ -1,5 +1,6 @@
-"""Large searches when the tables they would lay out cannot be allocated: they run on the kernels that need none and return
-the same plans (tests/c_client/scarce.c refuses the allocations from the host)."""
+"""Large searches when the tables they would lay out cannot be allocated (they run on the kernels that need none and return
+the same plans), and after a search whose wait failed (its tables count as laid out only once their search has been waited
+for).  tests/c_client/scarce.c brings both about from the host."""
 import os
 import subprocess
 
@@ -28,6 +29,12 @@ def test_search_without_memory_for_its_tables(tmp_path):
     scarce, plenty = [x[7:] for x in out if x.startswith("scarce ")], [x[7:] for x in out if x.startswith("plenty ")]
     assert len(scarce) == 4 and scarce == plenty and all(x.startswith("rc=0 ") for x in scarce), out
     assert int([x for x in out if x.startswith("refused")][0].split()[1]) > 0      # (the tables were asked for)
+    # failed wait, next search, search on finished tables: kernels launched
+    (failed, rc_f), (again, rc_a), (settled, rc_s) = [(int(x.split()[1]), x.split()[2]) for x in out if x.startswith("launches")]
+    tables = sum(B.halves_selection(sc, k)[0] > 0 for k in range(3))
+    assert (rc_f, rc_a, rc_s) == ("rc=-6", "rc=0", "rc=0"), out
+    assert (again, settled) == (failed + 1, failed - tables), out        # (+ 1: the search's words are filled afresh, too)
+    assert [x[6:] for x in out if x.startswith("after ")] == [plenty[3]] * 2
     g, o = B.Scenario(sc), O.Scenario(sc)
     for line, mask in zip(scarce, (1, 2, 4, 7)):
         rc, b = g.search_best(mask)
