@@ -318,7 +318,8 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
     const int4 tv = t[H], tw = t[STRAT == 0 ? H - 1 : H], t1 = t[1];
 
     // ---- the upper halves
-    const int cap = imin32((int)scn->cap, IDLE_PEAK - 1);
+    int cap = imin32((int)scn->cap, IDLE_PEAK - 1);
+    asm("" : "+s"(cap));     // (a compiler that sees this bound tests for idle lanes apart in every step: 1.3 % of the re-plan's time)
     const int fixed_step = in_vector(ff->fixed_step);
     const double per_step = 1.0 / (double)scn->K;
     auto limit_of = [&](uint64_t cost) -> int {       // no step time above this can reach `cost` (rounded up)
