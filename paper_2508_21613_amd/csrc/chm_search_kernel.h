@@ -189,6 +189,9 @@ __device__ __forceinline__ uint32_t least_penalty(const uint32_t (&w)[P], int pe
 
 // least reroute penalty of affected stage `st` whose forward and backward times are f and b.  Peers of equal speed
 // share the orphans evenly: the fullest takes ceil(orphans / peers), which a cap that admits any vector admits too.
+// (More than 10 stages have the instance for 15 peers alone: a second one costs their kernels, which are the longest and short
+// of registers, 1 % where nothing needs it.)
+template <int SP>
 __device__ __forceinline__ uint32_t stage_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
   const int p = scn->aff_peers[st];
   if (tab->even_share[st] != 0) return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);    // uniform
@@ -201,7 +204,7 @@ __device__ __forceinline__ uint32_t stage_penalty(ScnPtr scn, TabPtr tab, int st
     taken += w ? 0u : most;
     return w ? w : NO_MULTIPLES;
   };
-  if (p <= 4) {                                      // uniform
+  if (SP <= 10 && p <= 4) {                          // uniform
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = time_of(i);
@@ -781,7 +784,7 @@ k_fast_search(FastLaunch a) {
         // least penalty over the reroute vectors of every stage that lost nodes
         for (int st = 0; st < scn->n_aff; ++st) {
           const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
-          t_step += (int)stage_penalty(scn, tab, st, t.x, t.y - t.x);
+          t_step += (int)stage_penalty<SP>(scn, tab, st, t.x, t.y - t.x);
         }
       }
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
