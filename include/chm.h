@@ -178,7 +178,9 @@ int chm_search_cuts(chm_scenario *s, int32_t strategy, const uint8_t *d_cuts, ui
  * CHM_ERR_UNRECOVERABLE (mask selects no existing family), CHM_ERR_NO_FEASIBLE (out is
  * filled with index UINT64_MAX, cost CHM_INFEASIBLE), CHM_ERR_OVERFLOW (the selected families hold more
  * than 2^16 chunks of 2^idx_bits partitions, idx_bits <= 30: beyond exhaustive reach; search windows with
- * chm_search_range or lists instead), CHM_ERR_ARG, CHM_ERR_HIP. */
+ * chm_search_range or lists instead), CHM_ERR_ARG, CHM_ERR_HIP.  The first search of a large family lays out a table
+ * of at most 8 MB of device memory per strategy, which the handle keeps (where there is none to be had, the search
+ * runs on the kernels that need no table). */
 int chm_search_best(chm_scenario *s, uint32_t strategy_mask, chm_best *out, void *hip_stream);
 
 /* chm_search_best on n distinct handles of one device in one call (the plan cache of the Planner's overhead
@@ -203,7 +205,9 @@ int chm_search_best_batch(chm_scenario *const *handles, int32_t n, uint32_t stra
  * (chm_set_bounded_search is ignored).  Limits: at most 8,184 chunks of 2^idx_bits partitions (CHM_ERR_LIMIT
  * beyond; with the usual idx_bits of 30 that is every space chm_search_best accepts short of 2^43 partitions),
  * and no rerouting family with a large reroute space (more than 4,096 vectors over its stages, at most 8 peers
- * and 2^23 vectors each: CHM_ERR_LIMIT, use chm_search_best).  On CHM_ERR_LIMIT out is filled as for
+ * and 2^23 vectors each: CHM_ERR_LIMIT, use chm_search_best).  Families that chm_search_best searches by halves
+ * run so here only on a handle that it has searched before: the tables are laid out then (at most 8 MB a strategy,
+ * kept until the handle is freed); otherwise the kernels that need none take them, two to four times as long.  On CHM_ERR_LIMIT out is filled as for
  * CHM_ERR_NO_FEASIBLE.  All calls on one GPU share the array, which keeps the last call's contents (the
  * call resets what it reads): two calls that overlap in time on one GPU, from any handles or threads, race.
  * Otherwise as chm_search_best (synchronises hip_stream; same errors). */

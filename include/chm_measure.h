@@ -41,7 +41,8 @@ typedef struct {
   int32_t specialised[3];        /* per strategy: 1 = the int32 shape-specialised kernels, 0 = the generic int64 ones */
   int32_t sharp_bound[3];        /* per strategy: the bounded search may use its sharper lower bound (24-bit multiplies) */
   int32_t reroute_mul24;         /* peer stage times stay below 2^24 (needed by the specialised rerouting kernels) */
-  int32_t reroute_swept_apart;   /* rerouting: a large reroute space (more than 4,096 vectors; see chm_search_best_static) */
+  int32_t reroute_swept_apart;   /* rerouting: a large reroute space (more than 4,096 vectors over its stages, at most 8 peers
+                                  * and 2^23 vectors each), which chm_search_best_static refuses; no search sweeps it */
 } chm_selection;
 int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
 

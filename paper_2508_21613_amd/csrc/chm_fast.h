@@ -59,7 +59,7 @@ struct FastTables {
   // peers of stage a all of one speed: the extra micro-batches of the fullest peer when they share evenly; else 0
   uint32_t even_share[DEV_MAX_AFF];
   // lower bound of stage a's reroute penalty: some peer takes at least lb_mult[a] = ceil(orphans / peers)
-  // micro-batches (0 when a cap below that leaves this unclear), each at a stage time scaled by at least lb_q[a]
+  // micro-batches whatever the cap, each at a stage time scaled by at least lb_q[a]
   uint32_t lb_mult[DEV_MAX_AFF], lb_q[DEV_MAX_AFF];
 };
 
@@ -75,7 +75,7 @@ struct HalvesShape {
 struct FastState {
   bool usable[3] = {false, false, false};   // per strategy: a specialised kernel covers this scenario
   // rerouting: at most 8 peers and 2^23 vectors per stage, and more than FAST_FUSED_R vectors over all stages.
-  // (chm_search_best_static does not take such a family, see chm.h.)
+  // (chm_search_best_static refuses such a family, see chm.h; no search needs it any more.)
   bool large_reroute = false;
   bool rows_ok = false;                     // the vectors of every stage can be tabulated (cost store of plan indices)
   bool mul24_reroute = false;               // peer stage times stay below 2^24: what least_penalty needs

@@ -667,8 +667,9 @@ int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uin
   // resident); spaces below 2^25 partitions get at least 16 workgroups per compute unit and correspondingly shorter
   // runs (measured on 10 to 15 M partitions: unranking once per 10 to 15 partitions costs less than the idle tail
   // of fewer, longer workgroups; runs of 5 to 7 were 1 to 8 % slower).  Small spaces: runs of 4, or as short
-  // as lets every lane of the resident wave slots (256 CUs x 5 workgroups x 256 lanes) have one: a second round of workgroups
-  // costs more than a second partition per lane.
+  // as lets every lane of five workgroups per CU have one: a second round of workgroups costs more than a second partition per
+  // lane.  (Five are resident up to 5 stages, with strategy 2 up to 8; deeper kernels hold four, three or two, and then
+  // run further rounds.)
   const uint64_t lanes_balanced = 256ull * 16 * BLOCK, lanes_resident = 256ull * 5 * BLOCK;
   uint64_t per = a.part_count / lanes_balanced;
   if (per < 4) per = std::min<uint64_t>(4, (a.part_count + lanes_resident - 1) / lanes_resident);

@@ -5,10 +5,12 @@
 // made of (pipeline_time in chm_search_kernel.h) splits at the cut between them: maxima and sums over the stages of one
 // half alone, and a few terms of the stage that crosses.  So a lane keeps one lower half in registers, a wavefront walks
 // a list of upper halves whose share was worked out once for all lower halves (k_upper_halves) and arrives through
-// scalar loads.  Bound by VALU issue: a partition costs 45 instructions (strategies 1 and 2; 100 with the two pipeline classes
-// of strategy 0) at any depth, where working it out on its own costs over 200 at 8 stages and 300 at 11.  62.9 M
-// partitions of 8 stages: 0.12 ms (0.48 ms one by one in the range kernel), 5.2 G of 11 stages: 6.4 ms (51).  64 VGPRs or fewer at one class: 8
-// waves per SIMD, which hide the scalar loads.  All lanes of a wavefront have the same last lower cut v, and the list is ordered by its
+// scalar loads.  Bound by VALU issue: a partition costs 51 to 54 lane instructions at 7 and 8 stages (104 with the two pipeline
+// classes of strategy 0), lanes without a lower half and the wavefronts' own lower halves included, where working it out on
+// its own costs over 200 at 8 stages and 300 at 11; a step of the loop costs the same at any depth, idle lanes weigh where
+// lower halves are few (fast_select decides for which families it pays and how many cuts an upper half takes).  62.9 M partitions
+// of 8 stages: 0.12 ms (0.44 ms one by one in the range kernel), 5.2 G of 11 stages: 6.4 ms (51).  64 VGPRs or fewer at one
+// class: 8 waves per SIMD, which hide the scalar loads.  All lanes of a wavefront have the same last lower cut v, and the list is ordered by its
 // first cut, descending: the upper halves that go with v are the first C(L-1-v, UP) of the list, for every v.
 //
 // Every partition's memory peak and step time are worked out.  The weights to fetch (the transition time) only where

@@ -1,9 +1,10 @@
 // Generic scoring kernels of libchm for gfx950: any shape within the library limits,
 // int64 arithmetic throughout.  One lane evaluates one plan (scoring) or one partition
 // with all of its reroute vectors (search).  The shape-specialised kernels live in
-// chm_fast.hip and serve searching and scoring alike wherever their load-time bounds hold;
-// these are what the library falls back to for every shape and magnitude those do not cover
-// (more than 16 stages, times that do not fit int32, more than 8 peers), plus the small
+// chm_search_kernel.h and serve searching and scoring alike wherever their load-time bounds hold;
+// these are what the library falls back to for what those do not cover: times or memory that do not
+// fit int32 (peers' stage times: 24 bits), one stage, lists of more than 16 stages, rerouting plan indices with more than 8 peers or
+// 2^23 vectors a stage, communication rounds of redundant computation beyond 64 layers; plus the small
 // one-lane kernels around a search (fixed pipelines, the winner's terms, migration scheme).
 //
 // Pipeline time: the closed form of the 1F1B dependency recurrence (Estimator subsection, eq. (transition)) that
