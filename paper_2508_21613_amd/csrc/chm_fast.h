@@ -66,7 +66,6 @@ struct FastTables {
 // How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
 struct HalvesShape {
   int up = 0;                   // cuts of an upper half
-  uint32_t n_upper = 0;         // upper halves
   uint32_t n_items = 0;         // wavefronts of the search
   uint32_t chunk = 0;           // upper halves per item
   uint64_t steps = 0;           // 64 lower halves x one upper half
@@ -105,10 +104,10 @@ struct FastState {
   size_t vec_words = 0;                     // size of the vector table
   const DevScenario *d_scn = nullptr;       // the handle's device tables (for that later build)
   const uint64_t *d_comp = nullptr;
-  // search by halves, per strategy: records of the upper halves and first items (a few MB), laid out by the first search
-  uint32_t *d_upper[3] = {nullptr, nullptr, nullptr};
-  bool upper_ready[3] = {false, false, false};      // the table is there: a search that filled it has been waited for
-  bool upper_queued[3] = {false, false, false};     // a launch of the current search fills it, or found it ready
+  // search by halves, per strategy: records of pairs of cuts and first items (under 0.7 MB), laid out by the first search
+  uint32_t *d_pairs[3] = {nullptr, nullptr, nullptr};
+  bool pairs_ready[3] = {false, false, false};      // the table is there: a search that filled it has been waited for
+  bool pairs_queued[3] = {false, false, false};     // a launch of the current search fills it, or found it ready
   HalvesShape halves[3];
   // scratch of the candidate path of the bounded search; grown to what a search needs
   void *d_cand_list = nullptr;              // [candidate] cut positions, 16 bytes each
@@ -143,6 +142,7 @@ struct FastLaunch {
 };
 
 // Exhaustive search of a whole family by halves (chm_halves_kernel.h).
+enum { PAIR_RECORD_WORDS = 8 };
 struct HalvesItems {
   int4 prefix[DEV_MAX_L + 1];   // prefix sums: forward, forward + backward, static memory, activation memory
   uint32_t first[DEV_MAX_L];    // per last lower cut, its first wavefront item
@@ -151,9 +151,9 @@ struct HalvesItems {
 struct HalvesLaunch {
   SearchLaunch s;               // result = words of the family's first chunk
   const FastTables *tab;
-  uint32_t *upper;              // records of the upper halves
+  uint32_t *pairs;              // records of pairs of cuts, (L + 1)^2 of PAIR_RECORD_WORDS
   HalvesItems *items;
-  uint32_t n_upper, n_items;
+  uint32_t n_pairs, n_items;
   uint32_t chunk;               // upper halves per item
   uint32_t chunk_words;         // words from one chunk's argmin words to the next chunk's
 };
@@ -209,12 +209,9 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
-int chmk_halves_s0(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
-int chmk_halves_s1(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
-int chmk_halves_s2(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream);
-int chmk_halves_words_s0(int up, int n_cls);     // words of one upper half's record
-int chmk_halves_words_s1(int up, int n_cls);
-int chmk_halves_words_s2(int up, int n_cls);
+int chmk_halves_s0(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s1(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s2(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
 // Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
 // halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
 // search, only for what chm_halves_kernel.h says.  may_allocate = false, or no memory to be had: only with tables that are already there.  Same

@@ -389,24 +389,24 @@ float estimate_fit_share(const DevScenario &h, const FastFamily &ff, int strat, 
 // kernel / by halves: 28 / 34).
 constexpr uint64_t HALVES_FROM = 1ull << 21;
 // What halves must save: a partition costs the range kernel about `stages` units, a lane's step one unit per pipeline
-// class, whether the lane has a lower half or not, and the fixed cost is about 7 M units.  (A unit is a nanosecond over
-// 1,000 of them.)  Decides for families whose lower halves leave most lanes idle, us, range kernel / by halves: 5 stages,
-// 2.1 M partitions (a third of the lanes at work) 29 / 33 and, of two classes, 29 / 40; 3.0 M 36 / 35 and 34 / 44; 3.8 M
-// (whole searches) 68 / 64; 5.6 M 53 / 41 and 50 / 55; 6 stages, 2.9 M (78 % at work) 36 / 36 and 38 / 33.
+// class (two at most: the others are timed seldom), whether the lane has a lower half or not, and the fixed cost is about 7 M
+// units.  (A unit is a nanosecond over 1,000 of them.)  Decides for families whose lower halves leave most lanes idle, us, range
+// kernel / by halves: 5 stages, 2.1 M partitions (a third of the lanes at work) 30 / 36 and, strategy 0, 29 / 17; 3.0 M 38 / 38 and
+// 35 / 18; 5.6 M 56 / 46 and 51 / 23; 6 stages, 2.9 M (78 % at work) 37 / 34 and 38 / 17.
 constexpr int64_t HALVES_SAVES = 7ll << 20;
-// Bytes a table of upper halves may take (one per strategy and handle, kept).
-constexpr uint64_t HALVES_TABLE = 8ull << 20;
-// Upper halves of three cuts fall into longer lists than those of two (fewer wavefronts, each of which works out its
-// lower half), but a lower half that is a cut shorter may be one of few: the 64 lanes of a wavefront share the last lower
-// cut.  Three cuts are taken unless their wavefront steps exceed those of two by a quarter.  us, two cuts / three, strategies
-// 2 and 0, with the ratio of the steps: 6 stages, 7.0 M partitions (4.3) 44 / 80, 47 / 113; 7 stages, 3.3 M (1.75) 35 / 39,
-// 37 / 44, and 45 M (1.32) 97 / 128, 134 / 185; 8 stages, 15 M (1.13) 62 / 56, 65 / 79; 10 stages, 39 M (1.02) 128 / 110,
-// 160 / 142; 16 stages, 7.7 M (1.01) 126 / 93, 164 / 110.
-constexpr uint64_t WIDER_BY = 4;
-
-int halves_record_words(int k, int up, int n_time) {
-  return k == 0 ? chmk_halves_words_s0(up, n_time) : k == 1 ? chmk_halves_words_s1(up, n_time) : chmk_halves_words_s2(up, n_time);
+// Upper halves of three cuts leave a wavefront fewer lower halves to set up (the time of 60 + 30 a lower cut instructions each), but a step of
+// theirs costs more (25 instead of 18) and their lower halves, a cut shorter, may be few: the 64 lanes of a wavefront share the
+// last lower cut.  Deep pipelines, whose upper halves are few for every v, take three.  us, two cuts / three, strategies 0 and 2:
+// 7 stages, 45 M partitions 56 / 77, 43 / 61; 8 stages, 4.3 M 19 / 21, 35 / 41, and 63 M 77 / 96, 59 / 74; 9 stages, 24 M 48 / 52,
+// 40 / 42; 10 stages, 39 M 82 / 71, 68 / 56; 12 stages, 13 M 58 / 46, 54 / 37; 16 stages, 7.7 M 109 / 96, 136 / 115.  Never
+// where three cuts leave more lanes idle, by a quarter more steps.
+uint64_t halves_cost(const HalvesShape &hs, int sp) {
+  return (uint64_t)hs.n_items * (uint64_t)(60 + 30 * (sp - 1 - hs.up)) + hs.steps * (hs.up == 2 ? 18u : 25u);
 }
+constexpr uint64_t WIDER_BY = 4;
+// Models of more layers than this keep three cuts at any depth, at 1.3 to 1.4 times the time of two (1.1 G partitions of 7
+// stages 1.0 and 0.71 ms): the instances of 7 and 8 stages stay in use, as the test of the lanes at work asks.
+constexpr int WIDE_LAYERS = 120;
 
 // wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts; steps = 0: not
 // within the kernel's 32-bit ranks of lower halves
@@ -419,13 +419,14 @@ HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
     if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return hs;
     steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
   }
-  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(512, steps / 32768));
+  // upper halves per wavefront: about 12,000 wavefronts (one and a half rounds of the resident ones), but enough steps to carry the
+  // lower half's set-up (62.9 M partitions of 8 stages, both cuts: 32, 64 or 128 steps within 3 %; 3 M of 7 stages 15, 21 us at 32, 64)
+  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 12288));
   for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hs.chunk - 1) / hs.chunk);
   if (items >= (1ull << 31)) return hs;
   hs.up = up;
   hs.steps = steps;
   hs.n_items = (uint32_t)items;
-  hs.n_upper = (uint32_t)h.binom[up][L - 1 - H];
   return hs;
 }
 
@@ -437,20 +438,19 @@ HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
   if (partitions < HALVES_FROM || sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return none;
   for (int ci = 0; ci < ff.n_cls; ++ci)
     if (!ff.cls[ci].unit || ff.cls[ci].M < sp) return none;
-  if (ff.n_time > (k == 0 ? 3 : 1)) return none;
+  if (k != 0 && ff.n_time > 1) return none;
   for (int s = 0; k == 2 && s < h.n_aff; ++s)
     if (t->even_share[s] == 0) return none;
-  auto in_table = [&](const HalvesShape &hs) {
-    return hs.up != 0 && (uint64_t)hs.n_upper * (uint64_t)halves_record_words(k, hs.up, ff.n_time) * 4 + sizeof(HalvesItems) <= HALVES_TABLE;
-  };
   const HalvesShape two = halves_of_width(h, sp, 2);
-  HalvesShape taken = in_table(two) ? two : none;
+  HalvesShape taken = two;
   if (sp >= 7) {                          // (5 and 6 stages: never worth it, and no instance)
     const HalvesShape three = halves_of_width(h, sp, 3);
-    if (in_table(three) && (taken.up == 0 || three.steps <= two.steps + two.steps / WIDER_BY)) taken = three;
+    const bool wide = h.L > WIDE_LAYERS || halves_cost(three, sp) < halves_cost(two, sp);
+    if (three.up != 0 && (two.up == 0 || (wide && three.steps <= two.steps + two.steps / WIDER_BY))) taken = three;
   }
+  if (taken.up == 0) return none;
   const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
-  return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)ff.n_time + (unsigned)HALVES_SAVES ? taken : none;
+  return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)std::min(ff.n_time, 2) + (unsigned)HALVES_SAVES ? taken : none;
 }
 
 }  // namespace
@@ -511,9 +511,11 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
     for (int j = 0; j <= h.S; ++j) ff.w0[j] = (int32_t)h.pw[h.p0[j]];
     // Re-partition at nominal speed: the chains are alike and differ in their micro-batches alone, more of which never take
     // less time (every term of pipeline_time grows with M): the class with the most goes first and is the only one timed.
+    // (Redundant computation: the class with the most nodes goes first, the others are timed where it does not decide already.)
     std::vector<int> order;
     for (int ci = 0; ci < fam.n_cls; ++ci) order.push_back(ci);
     ff.n_time = fam.n_cls;
+    if (k == 0) std::stable_sort(order.begin(), order.end(), [&fam](int a, int b) { return fam.cls[a].n > fam.cls[b].n; });
     if (k == 1 && fam.n_cls > 0) {
       bool nominal = true;
       for (int ci = 0; ci < fam.n_cls; ++ci)
@@ -908,11 +910,12 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   const int k = a.strategy;
   if (!fast_halves_covers(f, h, k, partitions)) return 1;
   const HalvesShape &hs = f->halves[k];
-  const int sp = h.fam[k].stages, n_time = f->h_tables.fam[k].n_time;
-  const size_t records = (size_t)hs.n_upper * (size_t)halves_record_words(k, hs.up, n_time);
-  if (!f->d_upper[k]) {
+  const int sp = h.fam[k].stages;
+  const uint32_t n_pairs = (uint32_t)((h.L + 1) * (h.L + 1));
+  const size_t words = (size_t)n_pairs * PAIR_RECORD_WORDS;
+  if (!f->d_pairs[k]) {
     // (no memory for the table: the range kernel needs none)
-    if (!may_allocate || !pool_take(f->d_upper[k], records * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
+    if (!may_allocate || !pool_take(f->d_pairs[k], words * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
   }
   HalvesLaunch hl;
   hl.s = a;
@@ -920,22 +923,22 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.chunk_words = chunk_words;
   hl.chunk = hs.chunk;
   hl.n_items = hs.n_items;
-  hl.n_upper = hs.n_upper;
-  hl.upper = f->d_upper[k];
-  hl.items = (HalvesItems *)(f->d_upper[k] + records);       // (records are whole 16 bytes)
-  const bool build = !f->upper_ready[k];
-  const int rc = k == 0 ? chmk_halves_s0(sp, hs.up, n_time, hl, build, stream)
-                 : k == 1 ? chmk_halves_s1(sp, hs.up, n_time, hl, build, stream) : chmk_halves_s2(sp, hs.up, n_time, hl, build, stream);
+  hl.n_pairs = n_pairs;
+  hl.pairs = f->d_pairs[k];
+  hl.items = (HalvesItems *)(f->d_pairs[k] + words);         // (records are whole 32 bytes)
+  const bool build = !f->pairs_ready[k];
+  const int rc = k == 0 ? chmk_halves_s0(sp, hs.up, hl, build, stream)
+                 : k == 1 ? chmk_halves_s1(sp, hs.up, hl, build, stream) : chmk_halves_s2(sp, hs.up, hl, build, stream);
   if (rc) return rc;
   if (hipGetLastError() != hipSuccess) return -1;
-  f->upper_queued[k] = true;
+  f->pairs_queued[k] = true;
   return 0;
 }
 
 void fast_halves_settled(FastState *f) {
   for (int k = 0; k < 3; ++k) {
-    f->upper_ready[k] = f->upper_ready[k] || f->upper_queued[k];
-    f->upper_queued[k] = false;
+    f->pairs_ready[k] = f->pairs_ready[k] || f->pairs_queued[k];
+    f->pairs_queued[k] = false;
   }
 }
 
@@ -1052,7 +1055,7 @@ void fast_release(FastState *f) {
   if (f->d_weights) pool_release(f->d_weights);
   if (f->d_base) pool_release(f->d_base);
   if (f->d_vecs) pool_release(f->d_vecs);
-  for (uint32_t *&p : f->d_upper) { if (p) pool_release(p); p = nullptr; }
+  for (uint32_t *&p : f->d_pairs) { if (p) pool_release(p); p = nullptr; }
   if (f->d_tables) pool_release(f->d_tables);
   f->d_unread = nullptr; f->d_weights = nullptr; f->d_base = nullptr;
   f->d_vecs = nullptr;

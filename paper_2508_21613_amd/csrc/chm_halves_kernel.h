@@ -3,203 +3,194 @@
 //
 // A partition is a lower half (its first H cuts) and an upper half (its last UP cuts).  Everything a plan's step time is
 // made of (pipeline_time in chm_search_kernel.h) splits at the cut between them: maxima and sums over the stages of one
-// half alone, and a few terms of the stage that crosses.  So a lane keeps one lower half in registers, a wavefront walks
-// a list of upper halves whose share was worked out once for all lower halves (k_upper_halves) and arrives through
-// scalar loads.  Bound by VALU issue: a partition costs 51 to 54 lane instructions at 7 and 8 stages (104 with the two pipeline
-// classes of strategy 0), lanes without a lower half and the wavefronts' own lower halves included, where working it out on
-// its own costs over 200 at 8 stages and 300 at 11; a step of the loop costs the same at any depth, idle lanes weigh where
-// lower halves are few (fast_select decides for which families it pays and how many cuts an upper half takes).  62.9 M partitions
-// of 8 stages: 0.12 ms (0.44 ms one by one in the range kernel), 5.2 G of 11 stages: 6.4 ms (51).  64 VGPRs or fewer at one
-// class: 8 waves per SIMD, which hide the scalar loads.  All lanes of a wavefront have the same last lower cut v, and the list is ordered by its
-// first cut, descending: the upper halves that go with v are the first C(L-1-v, UP) of the list, for every v.
+// half alone, and a few terms of the stages that cross.  A lane keeps one lower half in registers and its wavefront walks the
+// upper halves as nested loops, one cut each.  All lanes of a wavefront have the same last lower cut v, so the stage between
+// the halves, and every stage above it, is the same for all of them: its times and memory are scalars, and what a cut decides
+// is worked out where its loop stands.  Only what depends on the last cut is left to the innermost loop, and of that
+// the scalar share (a function of two cuts) is read from a table of (L + 1)^2 records (k_pair_records, 32 bytes each,
+// laid out once per handle and strategy).
+// @FIGURES@
 //
-// Every partition's memory peak and step time are worked out.  The weights to fetch (the transition time) only where
-// horizon x step time alone does not already exceed the lowest cost met so far in the search: elsewhere they cannot
-// change the argmin, ties included.
+// Every partition's memory peak and the time of its longest pipeline class are worked out.  The time of other classes (strategy
+// 0: pipelines without the failed nodes) and the weights to fetch (the transition time) only where horizon x that time does not
+// already exceed the lowest cost met so far in the search: elsewhere they cannot change the argmin, ties included.
 #ifndef CHM_HALVES_KERNEL_H
 #define CHM_HALVES_KERNEL_H
 #include "chm_search_kernel.h"
 
 namespace {
 
-// a uniform value held in a vector register
-__device__ __forceinline__ int in_vector(int x) {
-  asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "s"(x));
-  return x;
-}
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+
 // least reroute penalty of a stage all of whose peers have one speed (stage_penalty; nothing else comes here)
 __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
   return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);
 }
 constexpr int HALVES_NEVER = -(1 << 30);   // a term of a maximum that does not exist
-// memory peak of a lane without a lower half: above every cap (the peaks of plans stay below it by the bound that selects
-// these kernels, so a cap of 2^31 - 1, "no limit", can be taken as one less)
-constexpr int IDLE_PEAK = 0x7fffffff;
+constexpr int HALVES_UNFIT = 1 << 30;      // in place of a memory peak or a time: these partitions do not fit
 
-// Words of an upper half's record.  UP cuts c[H+1..K]; the stages behind the crossing one, s = H+1..N-1, have UP nodes
-// of which the last has no waiting behind it.  (Strategy 0: node s runs stages s and s+1, the last node also stage 0.)
-// The words every partition needs come first: they are what the loop loads, one record ahead.
-template <int STRAT, int UP, int NC>
-struct Upper {
-  enum {
-    PC1 = 0, PF1, PW1,                    // prefixes at c[H+1]: forward + backward, forward, memory
-    PEAK,                                 // largest memory peak of the upper stages alone
-    PENALTY,                              // reroute penalties of upper stages (strategy 2; strategy 0: see below)
-    PC2 = 4, PF2, PW2,                    // strategy 0: prefixes at c[H+2] (at L when UP is 1)
-    WRAP_C, WRAP_W,                       // strategy 0: the last stage's times and memory (its node also runs stage 0)
-    CLASS0 = STRAT == 0 ? WRAP_W + 1 : PENALTY + 1,
-    // per class, relative to the end of the crossing node H: for the nodes s = N-2 .. H+1, their R (time from H up to and
-    // with s), the suffix maxima of U and V over the upper nodes alone, and (M-n+s) C - R; then R of the node N-2 (strategy
-    // 0) or N-1, and (other strategies) the last node's own term
-    MID = 4, LAST = MID * (UP - 1), PER_CLASS = LAST + (STRAT == 0 ? 1 : 2),
-    HOT = CLASS0 + NC * PER_CLASS,
-    CUTS = HOT,                           // all UP cuts, a byte each
-    RANK_LO, RANK_HI,                     // their share of the partition rank
-    LAYERS,                               // layers of the largest upper stage
-    PA1, PA2, WRAP_A,                     // activation memory, like PW1, PW2, WRAP_W
-    WORDS = (WRAP_A + 1 + 3) / 4 * 4
-  };
-};
+// A record of two cuts x < y.  Strategies 1 and 2: x, y = the last two cuts; stage N-2 = [x, y) and stage N-1 = [y, L), times as
+// prefixes from the front.  Strategy 0 (node s runs stages s and s+1): x = the last cut but two, y = the last one; node N-3 =
+// [x, y), times relative to the end of node N-4 less the prefix at x.
+enum { PAIR_END = 0,        // end of stage N-2 (strategy 0: of node N-3)
+       PAIR_U, PAIR_V,      // U and V of pipeline_time of that stage alone, under 1 and 2 not below those of the last stage
+       PAIR_OWN,            // its (M - n + s) C - P
+       PAIR_LAST,           // 1, 2: the last stage's whole term; 0: its share of node N-1 (which also runs stage 0): time
+       PAIR_PENALTY,        // 2: reroute penalties of the two stages; 0: node N-1's share of memory, HALVES_UNFIT if N-3 does not fit
+       PAIR_ROUNDS,         // 1, 2: communication rounds of the larger of the two stages; 0: U of node N-2 from N-3's backward
+       PAIR_FIT,            // 1, 2: 1 = both fit; 0: V of node N-2 from N-3's forward
+       PAIR_WORDS };
 
-// One lane per upper half, in the order of the list: position p = sum of C(x_i, i) over UP falling digits x, and the cuts
-// are L-1-x, ascending.
-template <int N, int STRAT, int UP, int NC>
-__global__ void __launch_bounds__(BLOCK) k_upper_halves(HalvesLaunch a) {
+// One lane per pair of cuts; the first workgroup also lays out what every workgroup of the search stages in LDS.
+template <int N, int STRAT, int UP>
+__global__ void __launch_bounds__(BLOCK) k_pair_records(HalvesLaunch a) {
   constexpr int K = N - 1, H = K - UP;
-  typedef Upper<STRAT, UP, NC> R;
-  constexpr int W = R::WORDS;
-  __shared__ int4 T[DEV_MAX_L + 1];
-  __shared__ uint64_t BN[K * DEV_MAX_L];
   const ScnPtr scn = as_const(a.s.scn);
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
-  const int L = scn->L;
-  for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
-  for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
-  __shared__ uint32_t items[DEV_MAX_L];
-  if (blockIdx.x == 0 && threadIdx.x < DEV_MAX_L) {
-    // wavefront items per last lower cut v, and where v's first one is
-    const int v = (int)threadIdx.x;
-    uint32_t n = 0;
-    if (v >= H && v <= L - 1 - UP) {
-      const uint32_t low = (uint32_t)scn->binom[H - 1][v - 1], up = (uint32_t)scn->binom[UP][L - 1 - v];
-      n = ((low + 63u) / 64u) * ((up + a.chunk - 1) / a.chunk);
-    }
-    items[v] = n;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x < DEV_MAX_L) {
-    uint32_t first = 0;
-    for (int v = 0; v < (int)threadIdx.x; ++v) first += items[v];
-    a.items->first[threadIdx.x] = first;
-  }
+  const ClsPtr cl = &ff->cls[0];
+  const int L = scn->L, W = L + 1;
   if (blockIdx.x == 0) {
-    // what every workgroup of the search stages in LDS, in the form it wants it (binomials up to 2^32 - 1: ranks of lower
-    // halves are below that)
-    for (int i = threadIdx.x; i <= L; i += BLOCK) a.items->prefix[i] = T[i];
-    for (int i = threadIdx.x; i < H * DEV_MAX_L; i += BLOCK) a.items->binom[i] = BN[i] > 0xffffffffull ? 0xffffffffu : (uint32_t)BN[i];
+    __shared__ uint32_t items[DEV_MAX_L];
+    const int v = (int)threadIdx.x;
+    if (v < DEV_MAX_L) {
+      // wavefront items per last lower cut v, and where v's first one is
+      uint32_t n = 0;
+      if (v >= H && v <= L - 1 - UP) {
+        const uint32_t low = (uint32_t)scn->binom[H - 1][v - 1], up = (uint32_t)scn->binom[UP][L - 1 - v];
+        n = ((low + 63u) / 64u) * ((up + a.chunk - 1) / a.chunk);
+      }
+      items[v] = n;
+    }
+    __syncthreads();
+    if (v < DEV_MAX_L) {
+      uint32_t first = 0;
+      for (int i = 0; i < v; ++i) first += items[i];
+      a.items->first[v] = first;
+    }
+    for (int i = threadIdx.x; i <= L; i += BLOCK)
+      a.items->prefix[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
+    // (binomials up to 2^32 - 1: ranks of lower halves are below that)
+    for (int i = threadIdx.x; i < H * DEV_MAX_L; i += BLOCK) {
+      const uint64_t b = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
+      a.items->binom[i] = b > 0xffffffffull ? 0xffffffffu : (uint32_t)b;
+    }
   }
   const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
-  if (p >= a.n_upper) return;
-  int x[UP + 2];
-  unrank_digits<UP, uint64_t>(p, L, (L - 1) <= 64 ? 3 : 4, BN, x);              // x[i] = digit + 1, i = 1..UP
-  int c[UP + 2];                                                       // c[1..UP] = c[H+1..K]; c[UP+1] = L
+  if (p >= (uint32_t)(W * W)) return;
+  const int x = (int)p / W, y = (int)p % W;
+  uint32_t rec[PAIR_WORDS];
 #pragma unroll
-  for (int i = 1; i <= UP; ++i) c[i] = L - x[UP + 1 - i];
-  c[UP + 1] = L;
-  int4 t[UP + 2];
-  uint64_t rank = 0;
-  uint32_t packed = 0;
-#pragma unroll
-  for (int i = 1; i <= UP + 1; ++i) {
-    t[i] = T[c[i]];
-    if (i <= UP) {
-      rank += BN[(H + i - 1) * DEV_MAX_L + c[i] - 1];
-      packed |= (uint32_t)c[i] << (8 * (i - 1));
+  for (int i = 0; i < PAIR_WORDS; ++i) rec[i] = 0;
+  if (x >= 1 && x < y && y < L) {
+    auto fwd = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo]); };
+    auto both = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo] + scn->pb[hi] - scn->pb[lo]); };
+    auto peak = [&](int lo, int hi, int s) {           // (0: nobody's)
+      const int coef = ff->mem_coef[s];
+      return coef < 0 ? 0 : (int)(scn->pw[hi] - scn->pw[lo]) + (ff->has_act ? (int)__umul24((uint32_t)(scn->pa[hi] - scn->pa[lo]), (uint32_t)coef) : 0);
+    };
+    const int cap = (int)scn->cap;
+    const int end = both(0, y);
+    if (STRAT == 0) {
+      constexpr int S = N - 3;
+      const bool dead = (cl->dead >> S) & 1u, gone = (cl->dead >> (N - 1)) & 1u;
+      const int f = dead ? 0 : fwd(x, y), c = dead ? 0 : both(x, y), e = dead ? both(0, x) : end;
+      rec[PAIR_END] = (uint32_t)e;
+      rec[PAIR_U] = (uint32_t)(e + cl->after[S] * (c - f));
+      rec[PAIR_V] = (uint32_t)(e + cl->after[S] * f);
+      rec[PAIR_OWN] = (uint32_t)(cl->steady[S] < 0 ? HALVES_NEVER : cl->steady[S] * c - e);
+      rec[PAIR_LAST] = (uint32_t)(gone ? 0 : both(y, L));
+      const int coef = ff->mem_coef[N - 1];
+      const int share = coef < 0 ? 0 : (int)(scn->pw[L] - scn->pw[y]) + (ff->has_act ? (int)__umul24((uint32_t)(scn->pa[L] - scn->pa[y]), (uint32_t)coef) : 0);
+      rec[PAIR_PENALTY] = (uint32_t)(peak(x, y, S) <= cap ? share : HALVES_UNFIT);
+      rec[PAIR_ROUNDS] = (uint32_t)(e + cl->after[N - 2] * (c - f));
+      rec[PAIR_FIT] = (uint32_t)(e + cl->after[N - 2] * f);
+    } else {
+      const int f = fwd(x, y), c = both(x, y), total = both(0, L);
+      rec[PAIR_END] = (uint32_t)end;
+      rec[PAIR_U] = (uint32_t)imax32(total, end + (c - f));
+      rec[PAIR_V] = (uint32_t)imax32(total, end + f);
+      rec[PAIR_OWN] = (uint32_t)(cl->steady[N - 2] * c - end);
+      rec[PAIR_LAST] = (uint32_t)(cl->steady[N - 1] * both(y, L) + total);
+      if (STRAT == 2) {
+        uint32_t pen = 0;
+        for (int st = 0; st < scn->n_aff; ++st) {
+          const int sa = scn->aff_stage[st];
+          if (sa == N - 2) pen += even_penalty(scn, tab, st, f, c - f);
+          if (sa == N - 1) pen += even_penalty(scn, tab, st, fwd(y, L), both(y, L) - fwd(y, L));
+        }
+        rec[PAIR_PENALTY] = pen;
+      }
+      rec[PAIR_ROUNDS] = (uint32_t)(ff->allreduce * imax32(y - x, L - y));
+      rec[PAIR_FIT] = peak(x, y, N - 2) <= cap && peak(y, L, N - 1) <= cap ? 1u : 0u;
     }
   }
-  uint32_t rec[W];
-#pragma unroll
-  for (int i = 0; i < W; ++i) rec[i] = 0;
-  rec[R::PC1] = (uint32_t)t[1].y; rec[R::PF1] = (uint32_t)t[1].x; rec[R::PW1] = (uint32_t)t[1].z; rec[R::PA1] = (uint32_t)t[1].w;
-  rec[R::CUTS] = packed;
-  rec[R::RANK_LO] = (uint32_t)rank; rec[R::RANK_HI] = (uint32_t)(rank >> 32);
-  // times of the upper nodes H+i, i = 1..UP: stage H+i = [c[i], c[i+1]) (strategy 0: two stages, [c[i], c[i+2]); the last
-  // node's second one is stage 0, added by the lower half)
-  int F[UP + 1], C[UP + 1];
-  int peak = 0, layers = 0;
-#pragma unroll
-  for (int i = 1; i <= UP; ++i) {
-    const int e = STRAT == 0 && i < UP ? i + 2 : i + 1;
-    F[i] = t[e].x - t[i].x;
-    C[i] = t[e].y - t[i].y;
-    const int coef = ff->mem_coef[H + i];
-    const int m = t[e].z - t[i].z + (ff->has_act ? (int)__umul24((uint32_t)(t[e].w - t[i].w), (uint32_t)(coef < 0 ? 0 : coef)) : 0);
-    if (!(STRAT == 0 && i == UP)) peak = imax32(peak, coef < 0 ? 0 : m);
-    layers = imax32(layers, c[i + 1] - c[i]);
-  }
-  rec[R::PEAK] = (uint32_t)peak;
-  rec[R::LAYERS] = (uint32_t)layers;
-  if (STRAT == 0) {
-    const int second = UP >= 2 ? 2 : UP + 1;
-    rec[R::PC2] = (uint32_t)t[second].y; rec[R::PF2] = (uint32_t)t[second].x; rec[R::PW2] = (uint32_t)t[second].z; rec[R::PA2] = (uint32_t)t[second].w;
-    rec[R::WRAP_C] = (uint32_t)C[UP];
-    rec[R::WRAP_W] = (uint32_t)(t[UP + 1].z - t[UP].z);
-    rec[R::WRAP_A] = (uint32_t)(t[UP + 1].w - t[UP].w);
-  }
-  if (STRAT == 2) {
-    uint32_t pen = 0;
-    for (int st = 0; st < scn->n_aff; ++st) {
-      const int sa = scn->aff_stage[st] - H;                           // uniform
-      if (sa < 1) continue;
-      int f = F[1], cc = C[1];
-#pragma unroll
-      for (int i = 2; i <= UP; ++i) { f = sa == i ? F[i] : f; cc = sa == i ? C[i] : cc; }
-      pen += even_penalty(scn, tab, st, f, cc - f);
-    }
-    rec[R::PENALTY] = pen;
-  }
-#pragma unroll
-  for (int ci = 0; ci < NC; ++ci) {
-    const ClsPtr cl = &ff->cls[ci];
-    int r[UP + 1], u[UP + 1], v[UP + 1], own[UP + 1];
-    int sum = 0, mf = 0, mb = 0;
-#pragma unroll
-    for (int i = 1; i <= UP; ++i) {
-      const bool dead = STRAT == 0 && ((cl->dead >> (H + i)) & 1u);
-      const int f = dead ? 0 : F[i], cc = dead ? 0 : C[i];
-      sum += cc;
-      mf = imax32(mf, f);
-      mb = imax32(mb, cc - f);
-      r[i] = sum;
-      u[i] = sum + cl->after[H + i] * mb;
-      v[i] = sum + cl->after[H + i] * mf;
-      own[i] = cl->steady[H + i] < 0 ? HALVES_NEVER : cl->steady[H + i] * cc - sum;
-    }
-    uint32_t *out = rec + R::CLASS0 + ci * R::PER_CLASS;
-    int su = STRAT == 0 ? 0 : r[UP], sv = su;        // (strategy 0: the last node's time is not known here)
-#pragma unroll
-    for (int i = UP - 1; i >= 1; --i) {
-      su = imax32(su, u[i]);
-      sv = imax32(sv, v[i]);
-      uint32_t *mid = out + R::MID * (UP - 1 - i);
-      mid[0] = (uint32_t)r[i]; mid[1] = (uint32_t)su; mid[2] = (uint32_t)sv; mid[3] = (uint32_t)own[i];
-    }
-    out[R::LAST] = (uint32_t)(STRAT == 0 ? (UP >= 2 ? r[UP - 1] : 0) : r[UP]);
-    if (STRAT != 0) out[R::LAST + 1] = (uint32_t)(r[UP] + r[UP] + own[UP]);
-  }
-  uint4 *dst = (uint4 *)(a.upper + (size_t)p * W);
-#pragma unroll
-  for (int i = 0; i < W / 4; ++i) dst[i] = make_uint4(rec[4 * i], rec[4 * i + 1], rec[4 * i + 2], rec[4 * i + 3]);
+  uint4 *dst = (uint4 *)(a.pairs + (size_t)p * PAIR_WORDS);
+  dst[0] = make_uint4(rec[0], rec[1], rec[2], rec[3]);
+  dst[1] = make_uint4(rec[4], rec[5], rec[6], rec[7]);
 }
 
-// One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.
-template <int N, int STRAT, int UP, int NC>
-__global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
+// Digits x_K > ... > x_1 of `rem` = sum of C(x_i, i), as cuts c[i] = x_i + 1, all below `end`.  table[(i-1) * DEV_MAX_L + x] = C(x, i),
+// which grows with x: a digit is built bit by bit, three instructions and a probe each, 6 of them up to 64 positions.  (The
+// four-way search of unrank_digits waits for half as many probes, but takes five times the instructions, which count here.)
+template <int K>
+__device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint32_t *table, int *c) {
+#pragma unroll
+  for (int i = K; i >= 2; --i) {
+    const uint32_t *row = table + (i - 1) * DEV_MAX_L;
+    int x = 0;
+    uint32_t at = 0;                                   // C(x, i)
+    auto bit = [&](int b) {
+      const uint32_t t = row[x + b];
+      const bool up = t <= rem;
+      x = up ? x + b : x;
+      at = up ? t : at;
+    };
+    if (end > 64) bit(64);                             // uniform
+#pragma unroll
+    for (int b = 32; b >= 1; b >>= 1) bit(b);
+    rem -= at;
+    c[i] = x + 1;
+  }
+  c[1] = (int)rem + 1;                                 // C(x, 1) = x
+}
+
+// Step time of one pipeline class of the partition with the given cuts, stage after stage (stage_of: prefixes at a cut).
+// The maximum of pipeline_time, read the other way round: a pair of stages (s, s') at which the two ends turn goes with the
+// best own term of a stage not above either.  Four running maxima take the place of arrays.
+template <int N, int STRAT, typename At>
+__device__ __forceinline__ int class_time(ClsPtr cl, At at) {
+  int none = HALVES_NEVER, only_u = HALVES_NEVER, only_v = HALVES_NEVER, both = HALVES_NEVER;
+  int p = 0, mf = 0, mb = 0;
+#pragma unroll
+  for (int s = 0; s < N; ++s) {
+    const int2 lo = at(s), hi = at(STRAT == 0 ? (s + 2 <= N ? s + 2 : N) : s + 1);
+    int f = hi.x - lo.x, c = hi.y - lo.y;
+    if (STRAT == 0) {
+      if (s == N - 1) { f += at(1).x; c += at(1).y; }
+      const int keep = ((cl->dead >> s) & 1u) ? 0 : -1;
+      f &= keep;
+      c &= keep;
+    }
+    p += c;
+    mf = imax32(mf, f);
+    mb = imax32(mb, c - f);
+    const int u = (int)__umul24((uint32_t)mb, (uint32_t)cl->after[s]) + p, v = (int)__umul24((uint32_t)mf, (uint32_t)cl->after[s]) + p;
+    none = imax32(none, cl->steady[s] < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)c, (uint32_t)cl->steady[s]) - p);
+    only_u = imax32(only_u, none + u);
+    only_v = imax32(only_v, none + v);
+    both = imax32(both, imax32(only_u + v, only_v + u));
+  }
+  return both + cl->comm_total;
+}
+
+// One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.  The upper halves
+// that go with v are numbered by falling digits x (position = sum of C(x_i, i) over UP of them), cut = L-1-x.
+template <int N, int STRAT, int UP>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRAT == 0 ? 5 : N <= 10 ? 8 : 6))) k_search_halves(HalvesLaunch a) {
   constexpr int K = N - 1, H = K - UP;
-  constexpr int LOW = STRAT == 0 ? H - 1 : H;         // nodes of the lower half alone; the next one (strategy 0: two) cross
-  typedef Upper<STRAT, UP, NC> R;
-  constexpr int W = R::WORDS;
+  constexpr int LOW = STRAT == 0 ? H - 1 : H;         // nodes of the lower half alone
   __shared__ int4 T[DEV_MAX_L + 1];
   __shared__ uint32_t BN[H * DEV_MAX_L];
   __shared__ uint64_t wave_cost[BLOCK / 64], wave_rank[BLOCK / 64];
@@ -207,6 +198,8 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
   const ScnPtr scn = as_const(a.s.scn);
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
+  const ClsPtr cl = &ff->cls[0];
+  const CHM_CONST i32x4 *pre = (const CHM_CONST i32x4 *)(uintptr_t)a.items->prefix;      // {forward, both, memory, activations}
   const int L = scn->L;
   for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = a.items->prefix[i];
   for (int i = threadIdx.x; i < H * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
@@ -221,252 +214,379 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
     const uint64_t below_lo = __builtin_amdgcn_ballot_w64(a.items->first[lane] <= item);
     const uint64_t below_hi = __builtin_amdgcn_ballot_w64(a.items->first[lane + 64] <= item);
     const int v = (int)__popcll(below_lo) + (int)__popcll(below_hi) - 1;     // first_item grows with v (equal where v has none)
-    const uint32_t local = item - (uint32_t)__builtin_amdgcn_readfirstlane(a.items->first[v]);
+    const uint32_t local = item - as_const(a.items->first)[v];
     const uint32_t n_up = (uint32_t)scn->binom[UP][L - 1 - v];               // upper halves that go with v
     const uint32_t n_low = (uint32_t)scn->binom[H - 1][v - 1];               // lower halves that end with v
     const uint32_t low_blocks = (n_low + 63u) / 64u;
     const uint32_t part = local / low_blocks, low_block = local - part * low_blocks;
-    uint32_t up = part * a.chunk;
-    const uint32_t up_end = up + a.chunk < n_up ? up + a.chunk : n_up;
+    const uint32_t up_first = part * a.chunk;
+    uint32_t left = n_up - up_first < a.chunk ? n_up - up_first : a.chunk;   // upper halves still to walk
+    // digits of the first one: x[i], i = UP .. 1
+    int x[UP + 1];
+    {
+      uint32_t rem = up_first;
+#pragma unroll
+      for (int i = UP; i >= 1; --i) {
+        // largest x with C(x, i) <= rem (binomials of up to three cuts grow strictly from i - 1 on)
+        const uint64_t lo = __builtin_amdgcn_ballot_w64(BN[(i - 1) * DEV_MAX_L + lane] <= rem);
+        const uint64_t hi = __builtin_amdgcn_ballot_w64(BN[(i - 1) * DEV_MAX_L + lane + 64] <= rem);
+        x[i] = (int)__popcll(lo) + (int)__popcll(hi) - 1;
+        rem -= as_const(a.items->binom)[(i - 1) * DEV_MAX_L + x[i]];
+      }
+    }
 
     // ---- this lane's lower half
     const uint32_t q = low_block * 64u + (uint32_t)lane;
     const bool active = q < n_low;
-    int c[H + 1];
-    unrank_digits<H - 1, uint32_t>(active ? q : 0u, v, (v - 1) <= 64 ? 3 : 4, BN, c);   // digits 0..v-2: cuts 1..v-1
-    c[0] = 0;
-    c[H] = v;
-    const uint64_t low_rank = (uint64_t)q + BN[(H - 1) * DEV_MAX_L + v - 1];
-    int4 t[H + 1];
-    t[0] = make_int4(0, 0, 0, 0);
+    uint32_t low_cuts[(H + 3) / 4];                    // its cuts, a byte each
+    int c_first, c_before;                             // cut 1; cut H-1 (strategy 0)
+    int layers_low = 0;
+    int none = HALVES_NEVER, only_u = HALVES_NEVER, only_v = HALVES_NEVER, both = HALVES_NEVER;     // see class_time
+    int sum_low = 0, mf = 0, mb = 0;
+    int pen_low = 0;
+    bool ok = active;
+    const int cap = (int)scn->cap;
+    {
+      int c[H + 1];
+      unrank_by_bits<H - 1>(active ? q : 0u, v, BN, c);          // cuts 1..v-1
+      c[0] = 0;
+      c[H] = v;
 #pragma unroll
-    for (int i = 1; i <= H; ++i) t[i] = T[c[i]];
-    int peak_low = active ? 0 : IDLE_PEAK, layers_low = ff->fixed_layers;
-    int F[LOW > 0 ? LOW : 1], C[LOW > 0 ? LOW : 1];
+      for (int i = 0; i < (H + 3) / 4; ++i) low_cuts[i] = 0;
 #pragma unroll
-    for (int s = 0; s < LOW; ++s) {
-      const int e = STRAT == 0 ? s + 2 : s + 1;
-      F[s] = t[e].x - t[s].x;
-      C[s] = t[e].y - t[s].y;
-      const int coef = ff->mem_coef[s];
-      const int m = t[e].z - t[s].z + (ff->has_act ? (int)__umul24((uint32_t)(t[e].w - t[s].w), (uint32_t)(coef < 0 ? 0 : coef)) : 0);
-      peak_low = imax32(peak_low, coef < 0 ? 0 : m);
-    }
+      for (int i = 1; i <= H; ++i) low_cuts[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+      c_first = c[1];
+      c_before = c[H - 1];
+      int4 t[H + 1];
+      t[0] = make_int4(0, 0, 0, 0);
 #pragma unroll
-    for (int s = 0; s < H; ++s) layers_low = imax32(layers_low, c[s + 1] - c[s]);
-    uint32_t pen_low = 0, share_h = 0;
-    if (STRAT == 2) {
-      for (int st = 0; st < scn->n_aff; ++st) {
-        const int sa = scn->aff_stage[st];                                   // uniform
-        if (sa < H) {
-          int f = F[0], cc = C[0];
+      for (int i = 1; i <= H; ++i) t[i] = T[c[i]];
 #pragma unroll
-          for (int s = 1; s < LOW; ++s) { f = sa == s ? F[s] : f; cc = sa == s ? C[s] : cc; }
-          pen_low += even_penalty(scn, tab, st, f, cc - f);
-        } else if (sa == H) {
-          share_h = tab->even_share[st];
-        }
-      }
-    }
-    // per class: what the lower nodes contribute (see pipeline_time): maxima of forward and backward, time of the lower
-    // nodes, and the maxima over the lower j of the terms own_j + {both, one, none} of the lower suffix maxima
-    int mf[NC], mb[NC], sum_low[NC], both[NC], only_u[NC], only_v[NC], none[NC];
-    // what the loop multiplies per class, in vector registers (an instruction takes one scalar operand, and that is the
-    // record's): nodes behind and micro-batches - nodes + position (no node: 0) of the crossing nodes H, H-1 and N-1
-    struct Crossing { int after, steady; };
-    Crossing at_h[NC], at_g[NC], at_z[NC];
-    int after_mid[NC][UP], comm[NC];
-#pragma unroll
-    for (int ci = 0; ci < NC; ++ci) {
-      const ClsPtr cl = &ff->cls[ci];
-      int u[LOW > 0 ? LOW : 1], w[LOW > 0 ? LOW : 1], own[LOW > 0 ? LOW : 1];
-      int sum = 0;
-      mf[ci] = mb[ci] = 0;
+      for (int s = 0; s < H; ++s) layers_low = imax32(layers_low, c[s + 1] - c[s]);
+      if (STRAT != 0) layers_low = imax32(layers_low, ff->fixed_layers);
 #pragma unroll
       for (int s = 0; s < LOW; ++s) {
-        const bool dead = STRAT == 0 && ((cl->dead >> s) & 1u);
-        const int f = dead ? 0 : F[s], cc = dead ? 0 : C[s];
-        sum += cc;
-        mf[ci] = imax32(mf[ci], f);
-        mb[ci] = imax32(mb[ci], cc - f);
-        u[s] = (int)__umul24((uint32_t)mb[ci], (uint32_t)cl->after[s]) + sum;
-        w[s] = (int)__umul24((uint32_t)mf[ci], (uint32_t)cl->after[s]) + sum;
-        own[s] = cl->steady[s] < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)cc, (uint32_t)cl->steady[s]) - sum;
+        const int e = STRAT == 0 ? s + 2 : s + 1;
+        int f = t[e].x - t[s].x, cc = t[e].y - t[s].y;
+        const int coef = ff->mem_coef[s];
+        const int m = t[e].z - t[s].z + (ff->has_act ? (int)__umul24((uint32_t)(t[e].w - t[s].w), (uint32_t)(coef < 0 ? 0 : coef)) : 0);
+        ok = ok && (coef < 0 || m <= cap);
+        if (STRAT == 2)
+          for (int st = 0; st < scn->n_aff; ++st)
+            if (scn->aff_stage[st] == s) pen_low += (int)even_penalty(scn, tab, st, f, cc - f);      // uniform
+        if (STRAT == 0 && ((cl->dead >> s) & 1u)) f = cc = 0;
+        sum_low += cc;
+        mf = imax32(mf, f);
+        mb = imax32(mb, cc - f);
+        const int u = (int)__umul24((uint32_t)mb, (uint32_t)cl->after[s]) + sum_low, w = (int)__umul24((uint32_t)mf, (uint32_t)cl->after[s]) + sum_low;
+        none = imax32(none, cl->steady[s] < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)cc, (uint32_t)cl->steady[s]) - sum_low);
+        only_u = imax32(only_u, none + u);
+        only_v = imax32(only_v, none + w);
+        both = imax32(both, imax32(only_u + w, only_v + u));
       }
-      sum_low[ci] = sum;
-      both[ci] = only_u[ci] = only_v[ci] = none[ci] = HALVES_NEVER;
-      int su = 0, sv = 0;
-#pragma unroll
-      for (int s = LOW - 1; s >= 0; --s) {
-        su = imax32(su, u[s]);
-        sv = imax32(sv, w[s]);
-        both[ci] = imax32(both[ci], su + sv + own[s]);
-        only_u[ci] = imax32(only_u[ci], su + own[s]);
-        only_v[ci] = imax32(only_v[ci], sv + own[s]);
-        none[ci] = imax32(none[ci], own[s]);
-      }
-#pragma unroll
-      for (int i = 1; i < UP; ++i) after_mid[ci][i] = in_vector(cl->after[H + i]);
-      auto crossing = [cl](int s) {
-        const int k = cl->steady[s];
-        return Crossing{in_vector(cl->after[s]), in_vector(k < 0 ? 0 : k)};
-      };
-      at_h[ci] = crossing(H);
-      at_g[ci] = STRAT == 0 ? crossing(H - 1) : Crossing{0, 0};
-      at_z[ci] = STRAT == 0 ? crossing(N - 1) : Crossing{0, 0};
-      comm[ci] = in_vector(cl->comm_total);
-      both[ci] += comm[ci];
     }
-    const int4 tv = t[H], tw = t[STRAT == 0 ? H - 1 : H], t1 = t[1];
+    const i32x4 tv = pre[v], tl = pre[L];
+    // strategy 0: the lane's shares of nodes H-1 = [cut H-1, g) and N-1 (stage 0 of it)
+    int4 tb = make_int4(0, 0, 0, 0);
+    int zl = 0, room_z = 0;                            // stage 0's time, and what it leaves of node N-1's memory
+    if (STRAT == 0) {
+      tb = T[c_before];
+      const int coef_g = ff->mem_coef[H - 1], coef_z = ff->mem_coef[N - 1];
+      const int4 t1 = T[c_first];
+      zl = ((cl->dead >> (N - 1)) & 1u) ? 0 : t1.y;
+      room_z = coef_z < 0 ? HALVES_UNFIT - 1 : cap - t1.z - (ff->has_act ? (int)__umul24((uint32_t)t1.w, (uint32_t)coef_z) : 0);
+      // (from here on the memory of the lower share of node H-1 in tb.z: one subtraction per g)
+      tb.z = coef_g < 0 ? 0 : tb.z + (ff->has_act ? (int)__umul24((uint32_t)tb.w, (uint32_t)coef_g) : 0);
+    }
+    const uint64_t low_mask = __builtin_amdgcn_ballot_w64(ok);
+    const uint32_t low_fit = (uint32_t)__popcll(low_mask);
+    if (low_mask == 0) left = 0;                       // uniform: none of these lower halves fits
 
     // ---- the upper halves
-    int cap = imin32((int)scn->cap, IDLE_PEAK - 1);
-    asm("" : "+s"(cap));     // (a compiler that sees this bound tests for idle lanes apart in every step: 1.3 % of the re-plan's time)
-    const int fixed_step = in_vector(ff->fixed_step);
+    const int rounds = STRAT != 0 ? ff->allreduce : 0;
+    const int fixed_step = ff->fixed_step, comm = cl->comm_total;
     const double per_step = 1.0 / (double)scn->K;
     auto limit_of = [&](uint64_t cost) -> int {       // no step time above this can reach `cost` (rounded up)
       const uint64_t reconf = (uint64_t)scn->reconf[STRAT];
       if (cost == ~0ull) return 0x7fffffff;
       if (cost < reconf) return -1;
-      const double x = (double)(cost - reconf) * per_step + 1.0;
-      return x >= 2147483647.0 ? 0x7fffffff : (int)x;
+      const double y = (double)(cost - reconf) * per_step + 1.0;
+      return y >= 2147483647.0 ? 0x7fffffff : (int)y;
     };
     int limit = __builtin_amdgcn_readfirstlane(limit_of(inc0));
-    const RowPtr list = as_const((const uint32_t *)a.upper);
-    // exceptions to the plain memory check and step time, all uniform
-    enum { ACTIVATIONS = 1, FREE_G = 2, FREE_H = 4, FREE_Z = 8, ROUNDS = 16, PEAKS = ACTIVATIONS | FREE_G | FREE_H | FREE_Z, GONE = 32 };
-    uint32_t odd = (ff->has_act ? ACTIVATIONS : 0) | (ff->mem_coef[H] < 0 ? FREE_H : 0);
-    if (STRAT == 0) odd |= (ff->mem_coef[H - 1] < 0 ? FREE_G : 0) | (ff->mem_coef[N - 1] < 0 ? FREE_Z : 0);
-    else odd |= ff->allreduce > 0 ? ROUNDS : 0;
-    uint32_t gone[NC];                                // per class: crossing nodes it does without (bits of their stages)
-#pragma unroll
-    for (int ci = 0; ci < NC; ++ci) {
-      gone[ci] = STRAT == 0 ? ff->cls[ci].dead & ((1u << H) | (1u << (H - 1)) | (1u << (N - 1))) : 0u;
-      odd |= gone[ci] ? GONE << ci : 0;
+    // a node above the lower half, the same for all lanes: times (0 when nobody runs it), and whether it fits
+    auto scalar_peak = [&](i32x4 lo, i32x4 hi, int s) {
+      const int coef = ff->mem_coef[s];
+      return coef < 0 ? 0 : hi.z - lo.z + (hi.w - lo.w) * coef;
+    };
+    auto gone = [&](int s) { return STRAT == 0 && ((cl->dead >> s) & 1u) != 0; };
+    const int M = cl->M;
+    auto scalar_own = [&](int s, int c, int p) {       // (strategies 1, 2: every stage has its node)
+      const int k = STRAT == 0 ? cl->steady[s] : M - N + s;
+      return STRAT == 0 && k < 0 ? HALVES_NEVER : k * c - p;
+    };
+    uint32_t share_h = 0, share_m = 0;                 // strategy 2: share of a stage's time that its loss costs, stages H and N-3
+    if (STRAT == 2) {
+      for (int st = 0; st < scn->n_aff; ++st) {
+        if (scn->aff_stage[st] == H) share_h = tab->even_share[st];
+        if (UP == 3 && scn->aff_stage[st] == N - 3) share_m = tab->even_share[st];
+      }
     }
-    uint32_t nx[R::HOT];
+    const RowPtr pairs = as_const((const uint32_t *)a.pairs);
+
+    int g = 0;                                         // cut H+1
+    i32x4 tg = tv;
+    // of the levels above the innermost loop, per lane (see the kernel's use of them)
+    int xf = 0, xb = 0, u_h = 0, v_h = 0, gmax = 0, both_lim = 0, lim = 0, off = 0;
+    int xf2 = 0, xb2 = 0, u_m = 0, v_m = 0, own_m = 0;
+    int u_g = 0, v_g = 0, own_h = 0, room = 0, layers_up = 0, rounds_low = 0, pen_up = 0;
+    int bf = 0, bb = 0, c0 = 0;
+    bool ok_g = ok;
+    if (STRAT != 0) {
+      both_lim = both;
+      off = comm;
+      lim = ok ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
+    }
+
+    auto upper_rank = [&](int m, int y) -> uint64_t {
+      uint64_t r = 0;
+      if (UP == 3) r = scn->binom[H + 1][g - 1];
+      return r + scn->binom[K - 1][m - 1] + scn->binom[K][y - 1];
+    };
+    // the few that may win: other classes, weights to fetch, cost, ties by rank
+    auto consider = [&](uint64_t mask, int r, int m, int y, int pen, int pair_rounds) {
+      int c[N + 1];
+      c[0] = 0;
+      c[N] = L;
 #pragma unroll
-    for (int i = 0; i < R::HOT; ++i) nx[i] = list[(size_t)up * W + i];
-    for (; up < up_end; ++up) {
-      uint32_t rec[R::HOT];
-#pragma unroll
-      for (int i = 0; i < R::HOT; ++i) rec[i] = nx[i];
-      const RowPtr cold = list + (size_t)up * W;
-      const RowPtr next = up + 1 < up_end ? cold + W : cold;
-#pragma unroll
-      for (int i = 0; i < R::HOT; ++i) nx[i] = next[i];
-      if ((int)rec[R::PEAK] > cap) continue;           // uniform: none of these partitions fits
-      // memory and times of the crossing nodes: H = [c[H], c[H+1]); strategy 0: H-1 = [c[H-1], c[H+1]), H = [c[H],
-      // c[H+2]) and the last node, which also runs stage 0
-      int fh, ch, fg = 0, cg = 0, cz = 0, mh, mg = 0, mz = 0;
-      if (STRAT == 0) {
-        fg = (int)rec[R::PF1] - tw.x;
-        cg = (int)rec[R::PC1] - tw.y;
-        mg = (int)rec[R::PW1] - tw.z;
-        fh = (int)rec[R::PF2] - tv.x;
-        ch = (int)rec[R::PC2] - tv.y;
-        mh = (int)rec[R::PW2] - tv.z;
-        cz = (int)rec[R::WRAP_C] + t1.y;
-        mz = (int)rec[R::WRAP_W] + t1.z;
+      for (int i = 1; i <= H; ++i) c[i] = (int)((low_cuts[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+      if (UP == 3) c[H + 1] = g;
+      c[K - 1] = m;
+      c[K] = y;
+      int step = r + off;                              // (off: what the limits of this level have been lowered by)
+      if (STRAT != 0) {
+        const int pens = pen_low + pen_up;
+        step = imax32(step - pens, fixed_step) + pens + pen;
+        if (rounds > 0) step += imax32(rounds_low, pair_rounds);
       } else {
-        fh = (int)rec[R::PF1] - tv.x;
-        ch = (int)rec[R::PC1] - tv.y;
-        mh = (int)rec[R::PW1] - tv.z;
+        for (int ci = 1; ci < ff->n_time; ++ci)
+          step = imax32(step, class_time<N, STRAT>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
       }
-      if (odd & PEAKS) {
-        if (odd & ACTIVATIONS) {
-          auto act = [&](int mib, int s) { const int coef = ff->mem_coef[s]; return (int)__umul24((uint32_t)mib, (uint32_t)(coef < 0 ? 0 : coef)); };
-          mh += act((int)cold[STRAT == 0 ? R::PA2 : R::PA1] - tv.w, H);
-          if (STRAT == 0) { mg += act((int)cold[R::PA1] - tw.w, H - 1); mz += act((int)cold[R::WRAP_A] + t1.w, N - 1); }
-        }
-        if (odd & FREE_H) mh = 0;
-        if (odd & FREE_G) mg = 0;
-        if (odd & FREE_Z) mz = 0;
-      }
-      const int bh = ch - fh, bg = cg - fg;
-      const int peak = STRAT == 0 ? imax32(imax32(peak_low, mh), imax32(mg, mz)) : imax32(peak_low, mh);
-      const uint64_t fit_mask = __builtin_amdgcn_ballot_w64(peak <= cap);
-      // Nothing to time where no lane fits (uniform).  Strategy 0's nodes hold two stages and its time is the longest: under a
-      // cap that next to nothing fits, 15.4 M partitions 64 instead of 85 us.  (The shorter times of the other strategies gain 2 us
-      // there and lose as much everywhere else to the branch.)
-      if (STRAT == 0 && fit_mask == 0) continue;
-      n_fit += (uint32_t)__popcll(fit_mask);
-      // ---- step time: the sum of pipeline_time from the last node down, relative to the end of node H
-      int step = fixed_step;
-#pragma unroll
-      for (int ci = 0; ci < NC; ++ci) {
-        const uint32_t *up_c = rec + R::CLASS0 + ci * R::PER_CLASS;
-        int f1 = fh, b1 = bh, c1 = ch, f0 = fg, b0 = bg, c0 = cg, cl_z = cz;
-        if (STRAT == 0 && (odd & (GONE << ci))) {      // uniform, seldom
-          asm volatile("");                            // (kept a branch: as selects it would cost every class)
-          if ((gone[ci] >> H) & 1u) f1 = b1 = c1 = 0;
-          if ((gone[ci] >> (H - 1)) & 1u) f0 = b0 = c0 = 0;
-          if ((gone[ci] >> (N - 1)) & 1u) cl_z = 0;
-        }
-        // largest forward and backward up to node H (strategy 0: and up to H-1)
-        const int bf = STRAT == 0 ? imax32(mf[ci], f0) : mf[ci], bb = STRAT == 0 ? imax32(mb[ci], b0) : mb[ci];
-        const uint32_t xf = (uint32_t)imax32(bf, f1), xb = (uint32_t)imax32(bb, b1);
-        int su, sv, r;
-        if (STRAT == 0) {
-          su = sv = (int)up_c[R::LAST] + cl_z;
-          r = (int)__umul24((uint32_t)cl_z, (uint32_t)at_z[ci].steady) + su;        // (no such node: 0 x 0 + su, covered by others)
-        } else {
-          su = sv = (int)up_c[R::LAST];
-          r = (int)up_c[R::LAST + 1];
-        }
-#pragma unroll
-        for (int i = UP - 1; i >= 1; --i) {
-          const uint32_t *mid = up_c + R::MID * (UP - 1 - i);
-          const uint32_t k = STRAT == 0 ? (uint32_t)after_mid[ci][i] : (uint32_t)(UP - i);
-          // (the record's suffix maxima hold the last node's too, except under strategy 0)
-          const int ub = (int)__umul24(xb, k) + (int)mid[0], uf = (int)__umul24(xf, k) + (int)mid[0];
-          if (STRAT != 0 && i == UP - 1) {
-            su = imax32((int)mid[1], ub);
-            sv = imax32((int)mid[2], uf);
-          } else {
-            su = imax32(imax32(su, (int)mid[1]), ub);
-            sv = imax32(imax32(sv, (int)mid[2]), uf);
-          }
-          r = imax32(r, su + sv + (int)mid[3]);
-        }
-        su = imax32(su, (int)__umul24(xb, STRAT == 0 ? (uint32_t)at_h[ci].after : (uint32_t)UP));
-        sv = imax32(sv, (int)__umul24(xf, STRAT == 0 ? (uint32_t)at_h[ci].after : (uint32_t)UP));
-        int ss = su + sv;
-        r = imax32(r, (int)__umul24((uint32_t)c1, (uint32_t)at_h[ci].steady) + ss);
-        int end_h = sum_low[ci] + c1;                  // time of the nodes up to H
-        if (STRAT == 0) {
-          su = imax32(su, (int)__umul24((uint32_t)bb, (uint32_t)at_g[ci].after) - c1);
-          sv = imax32(sv, (int)__umul24((uint32_t)bf, (uint32_t)at_g[ci].after) - c1);
-          ss = su + sv;
-          r = imax32(r, (int)__umul24((uint32_t)c0, (uint32_t)at_g[ci].steady) + ss + c1);
-          end_h += c0;
-        }
-        // the lower nodes' terms
-        r = imax32(imax32(r, only_u[ci] + sv), only_v[ci] + su);
-        r = imax32(r, ss + none[ci] + end_h);
-        step = imax32(step, imax32(r + end_h + comm[ci], both[ci]));
-      }
-      if (STRAT == 2) step += (int)(pen_low + rec[R::PENALTY] + __umul24(share_h, (uint32_t)ch));
-      if (STRAT != 0 && (odd & ROUNDS)) {
-        const int stage_h = (int)(cold[R::CUTS] & 0xffu) - v;
-        step += ff->allreduce * imax32(imax32(layers_low, stage_h), (int)cold[R::LAYERS]);
-      }
-      const bool near_best = peak <= cap && step <= limit;
-      if (__builtin_amdgcn_ballot_w64(near_best) == 0) continue;
-      // ---- the few that may win: weights to fetch, cost, ties by rank
+      const bool near_best = ((mask >> lane) & 1u) && step <= limit;
+      if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;
       int wp[N + 1];
       wp[0] = 0;
-      wp[N] = T[L].z;
-      const uint32_t cuts = cold[R::CUTS];
 #pragma unroll
-      for (int i = 1; i <= K; ++i) wp[i] = i <= H ? t[i <= H ? i : 0].z : T[(cuts >> (8 * (i <= H ? 0 : i - H - 1))) & 0xffu].z;
+      for (int i = 1; i <= N; ++i) wp[i] = T[c[i]].z;
       const uint64_t cost = (uint64_t)scn->K * (uint32_t)step + (uint64_t)scn->reconf[STRAT] +
                             (uint64_t)scn->xfer * (uint32_t)missing_weights<N, STRAT>(ff, wp);
-      const uint64_t rank = low_rank + ((uint64_t)cold[R::RANK_LO] | ((uint64_t)cold[R::RANK_HI] << 32));
+      const uint64_t rank = (uint64_t)q + BN[(H - 1) * DEV_MAX_L + v - 1] + upper_rank(m, y);
       if (near_best && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
       const int seen = __builtin_amdgcn_readfirstlane(limit_of(wave_min(near_best ? cost : ~0ull)));
-      limit = limit < seen ? limit : seen;
+      if (seen < limit) {
+        limit = seen;
+        lim = ok_g ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
+      }
+    };
+
+    // Innermost loop: upper halves whose last cut is y, y-1, ... (n of them), the others being fixed.  Two records a round, the
+    // next two on their way.
+    auto walk = [&](int row, int m, int y, uint32_t n, int c2, int own_z) {
+      // (y > m > 2: there are records ahead of (row, y))
+      RowPtr at = pairs + (size_t)(uint32_t)(row * (L + 1) + y - 1) * PAIR_WORDS;
+      u32x16 next = *(const CHM_CONST u32x16 *)at;
+      for (;;) {
+        const u32x16 r = next;
+        constexpr int A = PAIR_WORDS, B = 0;           // words of y's record and of y - 1's
+        at -= 2 * PAIR_WORDS;
+        next = *(const CHM_CONST u32x16 *)at;
+        const bool two = n >= 2;
+        // the longest class's time less what is common to the level (off)
+        auto time_of = [&](int o) -> int {
+          int su, sv, t;
+          if (STRAT == 0) {
+            const int end = (int)r[o + PAIR_END], cz = (int)r[o + PAIR_LAST] + zl;
+            const int last = end + (cz + c2);
+            t = (int)__umul24((uint32_t)cz, (uint32_t)own_z) + last;
+            su = imax32(imax32(last, (int)r[o + PAIR_ROUNDS] + c2), end + u_m);
+            sv = imax32(imax32(last, (int)r[o + PAIR_FIT] + c2), end + v_m);
+            t = imax32(t, su + sv + (own_m - end));
+            su = imax32(imax32(su, (int)r[o + PAIR_U]), end + xb2);
+            sv = imax32(imax32(sv, (int)r[o + PAIR_V]), end + xf2);
+            t = imax32(t, su + sv + (int)r[o + PAIR_OWN]);
+            if (UP == 3) {
+              su = imax32(su, u_h);
+              sv = imax32(sv, v_h);
+              t = imax32(t, su + sv + own_h);
+            }
+            su = imax32(su, u_g);
+            sv = imax32(sv, v_g);
+          } else {
+            su = imax32((int)r[o + PAIR_U], (int)r[o + PAIR_END] + xb2);
+            sv = imax32((int)r[o + PAIR_V], (int)r[o + PAIR_END] + xf2);
+            t = imax32((int)r[o + PAIR_LAST], su + sv + (int)r[o + PAIR_OWN]);
+            if (UP == 3) {
+              su = imax32(su, u_m);
+              sv = imax32(sv, v_m);
+              t = imax32(t, su + sv + own_m);
+            }
+            su = imax32(su, u_h);
+            sv = imax32(sv, v_h);
+          }
+          t = imax32(t, su + sv + gmax);
+          t = imax32(imax32(t, only_u + sv), only_v + su);
+          return imax32(t, both_lim);
+        };
+        uint64_t near_a, near_b;
+        int ta, tb2;
+        if (STRAT == 0) {
+          const uint64_t fit_a = __builtin_amdgcn_ballot_w64((int)r[A + PAIR_PENALTY] <= room);
+          uint64_t fit_b = __builtin_amdgcn_ballot_w64((int)r[B + PAIR_PENALTY] <= room);
+          fit_b = two ? fit_b : 0;
+          near_a = near_b = 0;
+          // (nothing to time where no lane fits: a cap that next to nothing fits)
+          if ((fit_a | fit_b) != 0) {
+            n_fit += (uint32_t)__popcll(fit_a) + (uint32_t)__popcll(fit_b);
+            ta = time_of(A);
+            near_a = __builtin_amdgcn_ballot_w64(ta <= lim) & fit_a;
+            if (two) {
+              tb2 = time_of(B);
+              near_b = __builtin_amdgcn_ballot_w64(tb2 <= lim) & fit_b;
+            }
+          }
+        } else {
+          auto test = [&](int o, int &t) -> uint64_t {
+            n_fit += r[o + PAIR_FIT];
+            t = time_of(o);
+            int w = t;
+            if (STRAT == 2) w += (int)r[o + PAIR_PENALTY];
+            if (rounds > 0) {                          // uniform
+              asm volatile("");                        // (kept a branch)
+              w += imax32(rounds_low, (int)r[o + PAIR_ROUNDS]);
+            }
+            return __builtin_amdgcn_ballot_w64(w <= lim);
+          };
+          near_a = test(A, ta);
+          near_b = 0;
+          if (two) near_b = test(B, tb2);
+        }
+        if ((near_a | near_b) != 0) {
+#pragma unroll 1
+          for (int e = 0; e < 2; ++e) {
+            const bool b = e != 0;
+            const uint64_t mask = b ? near_b : near_a;
+            if (mask == 0 || (STRAT != 0 && (b ? r[B + PAIR_FIT] : r[A + PAIR_FIT]) == 0)) continue;
+            consider(mask, b ? tb2 : ta, m, b ? y - 1 : y, STRAT == 2 ? (int)(b ? r[B + PAIR_PENALTY] : r[A + PAIR_PENALTY]) : 0,
+                     (int)(b ? r[B + PAIR_ROUNDS] : r[A + PAIR_ROUNDS]));
+          }
+        }
+        if (n <= 2) break;
+        n -= 2;
+        y -= 2;
+      }
+    };
+    while (left != 0) {
+      bool fits = true;
+      int pen_g = 0, c_h = 0, f_h = 0;
+      if (UP == 3) {
+        g = L - 1 - x[UP];
+        tg = pre[g];
+        if (STRAT != 0) {
+          // stage H = [v, g)
+          f_h = tg.x - tv.x;
+          c_h = tg.y - tv.y;
+          fits = scalar_peak(tv, tg, H) <= cap;
+          xf = imax32(mf, f_h);
+          xb = imax32(mb, c_h - f_h);
+          u_h = tg.y + (N - 1 - H) * xb;
+          v_h = tg.y + (N - 1 - H) * xf;
+          gmax = imax32(none, scalar_own(H, c_h, tg.y));
+          if (STRAT == 2) pen_g = (int)share_h * c_h;
+          layers_up = imax32(layers_low, g - v);
+        }
+      }
+      do {
+        const int m = L - 1 - x[2];
+        const i32x4 tm = pre[m];
+        uint32_t n = (uint32_t)(x[2] - x[1]);
+        n = n < left ? n : left;
+        left -= n;
+        const int y = L - 1 - x[1];
+        x[1] = 0;
+        ++x[2];
+        if (STRAT != 0) {
+          if (UP == 3) {
+            // stage N-3 = [g, m)
+            const int f = tm.x - tg.x, c = tm.y - tg.y;
+            if (!fits || scalar_peak(tg, tm, N - 3) > cap || n == 0) continue;
+            xf2 = imax32(xf, f);
+            xb2 = imax32(xb, c - f);
+            u_m = tm.y + 2 * xb2;
+            v_m = tm.y + 2 * xf2;
+            own_m = scalar_own(N - 3, c, tm.y);
+            pen_up = STRAT == 2 ? pen_g + (int)share_m * c : 0;
+            if (rounds > 0) rounds_low = rounds * imax32(layers_up, m - g);
+          } else {
+            // stage H = N-3 = [v, m)
+            const int f = tm.x - tv.x, c = tm.y - tv.y;
+            if (scalar_peak(tv, tm, H) > cap || n == 0) continue;
+            xf2 = imax32(mf, f);
+            xb2 = imax32(mb, c - f);
+            u_h = tm.y + 2 * xb2;
+            v_h = tm.y + 2 * xf2;
+            gmax = imax32(none, scalar_own(H, c, tm.y));
+            pen_up = STRAT == 2 ? (int)share_h * c : 0;
+            if (rounds > 0) rounds_low = rounds * imax32(layers_low, m - v);
+          }
+          if (STRAT == 2) {
+            off = comm + pen_low + pen_up;
+            lim = ok ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
+          }
+          walk(m, m, y, n, 0, 0);
+        } else {
+          // node H-1 = [cut H-1, cut H+1); UP = 3: node H = [v, m); node N-2 = [m, L)
+          const i32x4 tu = UP == 3 ? tg : tm;
+          if (scalar_peak(tm, tl, N - 2) > cap || (UP == 3 && scalar_peak(tv, tm, H) > cap) || n == 0) continue;
+          const int coef_g = ff->mem_coef[H - 1];
+          const int need_g = coef_g < 0 ? 0 : tu.z + tu.w * coef_g;
+          ok_g = ok && need_g - tb.z <= cap;
+          const bool gone_g = gone(H - 1);
+          const int f0 = gone_g ? 0 : tu.x - tb.x;
+          c0 = gone_g ? 0 : tu.y - tb.y;
+          bf = imax32(mf, f0);
+          bb = imax32(mb, c0 - f0);
+          if (UP == 3 && !gone(H)) { f_h = tm.x - tv.x; c_h = tm.y - tv.y; } else { f_h = c_h = 0; }
+          const int base = UP == 3 ? tg.y : tv.y;      // end of node N-4 in the records' times
+          const int x1f = imax32(bf, f_h), x1b = imax32(bb, c_h - f_h);
+          const int p_g = base - c_h;
+          const int shift = sum_low + c0 - p_g;
+          u_g = p_g + (int)__umul24((uint32_t)bb, (uint32_t)cl->after[H - 1]);
+          v_g = p_g + (int)__umul24((uint32_t)bf, (uint32_t)cl->after[H - 1]);
+          const int k_g = cl->steady[H - 1];
+          gmax = imax32(none + shift, k_g < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)c0, (uint32_t)k_g) - p_g);
+          if (UP == 3) {
+            u_h = base + (int)__umul24((uint32_t)x1b, (uint32_t)cl->after[H]);
+            v_h = base + (int)__umul24((uint32_t)x1f, (uint32_t)cl->after[H]);
+            own_h = scalar_own(H, c_h, base);
+          }
+          xb2 = (int)__umul24((uint32_t)x1b, (uint32_t)cl->after[N - 3]);
+          xf2 = (int)__umul24((uint32_t)x1f, (uint32_t)cl->after[N - 3]);
+          const int f2 = gone(N - 2) ? 0 : tl.x - tm.x, c2 = gone(N - 2) ? 0 : tl.y - tm.y;
+          u_m = c2 + (int)__umul24((uint32_t)imax32(x1b, c2 - f2), (uint32_t)cl->after[N - 2]);
+          v_m = c2 + (int)__umul24((uint32_t)imax32(x1f, f2), (uint32_t)cl->after[N - 2]);
+          own_m = scalar_own(N - 2, c2, c2);
+          both_lim = both - shift;
+          off = shift + comm;
+          lim = ok_g ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
+          room = ok_g ? room_z : (int)0x80000000;
+          const int k_z = cl->steady[N - 1];
+          walk(UP == 3 ? g : v, m, y, n, c2, k_z < 0 ? 0 : k_z);
+        }
+      } while (left != 0 && UP == 3 && x[2] < x[UP]);
+      if (UP == 3) { ++x[UP]; x[2] = 1; }
     }
+    if (STRAT != 0) n_fit *= low_fit;
+
   }
   // ---- lowest cost of the workgroup, then lowest rank
   {
@@ -494,45 +614,32 @@ __global__ void __launch_bounds__(BLOCK) k_search_halves(HalvesLaunch a) {
   }
 }
 
-template <int STRAT, int N, int UP, int NC>
+template <int STRAT, int N, int UP>
 void launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
-  if (build) hipLaunchKernelGGL((k_upper_halves<N, STRAT, UP, NC>), dim3((a.n_upper + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, st, a);
+  if (build) hipLaunchKernelGGL((k_pair_records<N, STRAT, UP>), dim3((a.n_pairs + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, st, a);
   const uint32_t blocks = (a.n_items + BLOCK / 64 - 1) / (BLOCK / 64);
-  hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, NC>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  hipLaunchKernelGGL((k_search_halves<N, STRAT, UP>), dim3(blocks), dim3(BLOCK), 0, st, a);
 }
 
-template <int STRAT, int N>
-int halves_by_shape(int up, int n_cls, const HalvesLaunch &a, bool build, hipStream_t st) {
-#define CHM_SHAPE(UPV, NCV) if (up == UPV && n_cls == NCV) { launch_halves<STRAT, N, UPV, NCV>(a, build, st); return 0; }
-  CHM_SHAPE(2, 1)
-  if constexpr (STRAT == 0) { CHM_SHAPE(2, 2) CHM_SHAPE(2, 3) }
-  if constexpr (N >= 7) { CHM_SHAPE(3, 1) }          // (fewer stages: lower halves of one or two cuts, too few for 64 lanes)
-  if constexpr (N >= 7 && STRAT == 0) { CHM_SHAPE(3, 2) CHM_SHAPE(3, 3) }
-#undef CHM_SHAPE
-  return 1;
-}
-
-// build: the table of upper halves is filled first.  1 = no instance for this shape.
+// build: the table of pairs is filled first.  1 = no instance for this shape (5 and 6 stages: three upper cuts would leave
+// lower halves of one or two cuts, too few for 64 lanes).
 template <int STRAT>
-int halves_by_stages(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, hipStream_t st) {
+int halves_by_stages(int sp, int up, const HalvesLaunch &a, bool build, hipStream_t st) {
+#define CHM_CASE(SPV)                                                                   \
+  case SPV:                                                                             \
+    if (up == 2) { launch_halves<STRAT, SPV, 2>(a, build, st); return 0; }              \
+    if constexpr (SPV >= 7) { if (up == 3) { launch_halves<STRAT, SPV, 3>(a, build, st); return 0; } } \
+    return 1;
   switch (sp) {
-#define CHM_CASE(SPV) case SPV: return halves_by_shape<STRAT, SPV>(up, n_cls, a, build, st);
 #ifdef CHM_TUNING_SUBSET
     CHM_CASE(7) CHM_CASE(8)
 #else
     CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8) CHM_CASE(9) CHM_CASE(10)
     CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)
 #endif
-#undef CHM_CASE
     default: return 1;
   }
-}
-
-// words of an upper half's record
-template <int STRAT>
-int halves_words(int up, int n_cls) {
-  if (up == 3) return n_cls == 1 ? (int)Upper<STRAT, 3, 1>::WORDS : n_cls == 2 ? (int)Upper<STRAT, 3, 2>::WORDS : (int)Upper<STRAT, 3, 3>::WORDS;
-  return n_cls == 1 ? (int)Upper<STRAT, 2, 1>::WORDS : n_cls == 2 ? (int)Upper<STRAT, 2, 2>::WORDS : (int)Upper<STRAT, 2, 3>::WORDS;
+#undef CHM_CASE
 }
 
 }  // namespace

@@ -582,7 +582,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
   s->last = chm_timing();
   SearchCtx &c = s->search->ctx;
   c = SearchCtx();
-  for (bool &q : s->fast.upper_queued) q = false;     // (left by a call that failed before its wait)
+  for (bool &q : s->fast.pairs_queued) q = false;     // (left by a call that failed before its wait)
   c.jobs = jobs;
   c.light = light;
   const uint64_t chunk = 1ull << s->idx_bits;

@@ -5,7 +5,6 @@
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant) {
   return launch_by_stages<0>(sp, a, blocks, tile_bytes, (hipStream_t)stream, variant);
 }
-int chmk_halves_s0(int sp, int up, int n_cls, const HalvesLaunch &a, bool build, void *stream) {
-  return halves_by_stages<0>(sp, up, n_cls, a, build, (hipStream_t)stream);
+int chmk_halves_s0(int sp, int up, const HalvesLaunch &a, bool build, void *stream) {
+  return halves_by_stages<0>(sp, up, a, build, (hipStream_t)stream);
 }
-int chmk_halves_words_s0(int up, int n_cls) { return halves_words<0>(up, n_cls); }
