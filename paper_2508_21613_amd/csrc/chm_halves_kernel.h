@@ -188,7 +188,7 @@ __device__ __forceinline__ int class_time(ClsPtr cl, At at) {
 // One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.  The upper halves
 // that go with v are numbered by falling digits x (position = sum of C(x_i, i) over UP of them), cut = L-1-x.
 template <int N, int STRAT, int UP>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRAT == 0 ? 5 : N <= 10 ? 8 : 6))) k_search_halves(HalvesLaunch a) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRAT == 0 ? (N <= 10 ? 5 : 4) : N <= 8 ? 7 : N <= 11 ? 6 : 5))) k_search_halves(HalvesLaunch a) {
   constexpr int K = N - 1, H = K - UP;
   constexpr int LOW = STRAT == 0 ? H - 1 : H;         // nodes of the lower half alone
   __shared__ int4 T[DEV_MAX_L + 1];
