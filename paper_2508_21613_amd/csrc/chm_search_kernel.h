@@ -296,9 +296,9 @@ __device__ __forceinline__ void unrank_digits(Rank rem, int L, int steps, const 
     for (int s = 0; s < steps; ++s) {
       const int q = (hi - lo + 4) >> 2;              // ceil((range size) / 4), 0 only when hi < lo
       const int m1 = lo + q, m2 = m1 + q, m3 = m2 + q;
-      const bool a1 = m1 <= hi && column(i, m1 <= hi ? m1 : hi) <= rem;
-      const bool a2 = m2 <= hi && column(i, m2 <= hi ? m2 : hi) <= rem;
-      const bool a3 = m3 <= hi && column(i, m3 <= hi ? m3 : hi) <= rem;
+      // (all three in flight before any is looked at: written with &&, each became a branch of its own behind the one before)
+      const Rank t1 = column(i, imin32(m1, hi)), t2 = column(i, imin32(m2, hi)), t3 = column(i, imin32(m3, hi));
+      const bool a1 = (m1 <= hi) & (t1 <= rem), a2 = (m2 <= hi) & (t2 <= rem), a3 = (m3 <= hi) & (t3 <= rem);
       // the answer lies in [lo, m1-1], [m1, m2-1], [m2, m3-1] or [m3, hi]
       const int nlo = a3 ? m3 : (a2 ? m2 : (a1 ? m1 : lo));
       const int nhi = a3 ? hi : (a2 ? m3 - 1 : (a1 ? m2 - 1 : m1 - 1));
