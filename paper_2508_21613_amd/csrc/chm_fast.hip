@@ -511,11 +511,17 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
     for (int j = 0; j <= h.S; ++j) ff.w0[j] = (int32_t)h.pw[h.p0[j]];
     // Re-partition at nominal speed: the chains are alike and differ in their micro-batches alone, more of which never take
     // less time (every term of pipeline_time grows with M): the class with the most goes first and is the only one timed.
-    // (Redundant computation: the class with the most nodes goes first, the others are timed where it does not decide already.)
     std::vector<int> order;
     for (int ci = 0; ci < fam.n_cls; ++ci) order.push_back(ci);
     ff.n_time = fam.n_cls;
-    if (k == 0) std::stable_sort(order.begin(), order.end(), [&fam](int a, int b) { return fam.cls[a].n > fam.cls[b].n; });
+    // The class with the most work (micro-batches x factors of its nodes) goes first: a search times the others only where
+    // that one does not decide already.
+    auto work = [&fam](int c) {
+      uint64_t w = 0;
+      for (int j = 0; j < fam.cls[c].n; ++j) w += fam.cls[c].q[j];
+      return w * (uint64_t)fam.cls[c].M;
+    };
+    std::stable_sort(order.begin(), order.end(), [&work](int a, int b) { return work(a) > work(b); });
     if (k == 1 && fam.n_cls > 0) {
       bool nominal = true;
       for (int ci = 0; ci < fam.n_cls; ++ci)

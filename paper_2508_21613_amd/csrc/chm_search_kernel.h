@@ -279,6 +279,11 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {
   return v;
 }
 
+// a value all lanes agree on, as a scalar
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
 // Combinadic digits of `rem` (a partition rank): for i = K..1 the largest x with C(x, i) <= rem.
 // C(., i) grows with x, so each digit is found by a four-way search over [i-1, previous digit - 1]:
 // three independent table probes per step, the range shrinks to a quarter; all lanes take the same number of steps (no
@@ -545,6 +550,7 @@ k_fast_search(FastLaunch a) {
 
   const int cap = (int)scn->cap;
   uint64_t best_cost = ~0ull;
+  uint64_t wave_low = ~0ull;    // lowest cost the wave has met (uniform)
   uint32_t best_pos = 0;        // output position (chunk-local partition index or list position) of the lane's best
   uint32_t n_fit = 0;           // wave-uniform count of partitions that pass the memory filter
 
@@ -722,17 +728,17 @@ k_fast_search(FastLaunch a) {
     if (!QUEUED) n_fit += (uint32_t)__popcll(ok_mask);
     if (ok_mask != 0) {
       int t_step = ff->fixed_step;
-      int missing;
-      {
-        int wp[SP + 1];                     // memory prefix at the cuts
-        wp[0] = 0;
-#pragma unroll
-        for (int j = 1; j <= SP; ++j) wp[j] = PW[ce[j]];
-        missing = missing_weights<SP, STRAT>(ff, wp);
-      }
+      // A search looks no further at partitions whose time already exceeds the wave's lowest cost: their other classes,
+      // penalties and weights to fetch only add to it.  (A cost store needs every term.)
+      const bool every = a.s.costs_out != nullptr || (!QUEUED && STRAT == 2 && a.base_out != nullptr);
+      auto may_win = [&]() -> bool {
+        const uint64_t least = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT];
+        return every || __builtin_amdgcn_ballot_w64(ok && least <= wave_low) != 0;
+      };
       // Times per pipeline class.  The stage sums are read from the LDS table again for every class: at 16 stages keeping them
       // for the next class costs a wave per SIMD (two pipelines of 16 stages alike or not, 168 registers and spills).
-      for (int ci = 0; ci < ff->n_time; ++ci) {
+      bool open = true;
+      for (int ci = 0; ci < ff->n_time && open; ++ci) {
         const ClsPtr cl = &ff->cls[ci];
         int F[SP], C[SP];
         {
@@ -767,55 +773,66 @@ k_fast_search(FastLaunch a) {
           }
         }
         t_step = imax32(t_step, pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24));
+        open = may_win();
       }
-      if (ff->allreduce > 0) {
-        // rounds of gradient communication: largest stage on any device, or the ring colouring when nodes hold two stages
-        int rounds;
-        if (STRAT == 0) {
-          rounds = ring_rounds<SP>(ce, ff->node_exists);
-        } else {
-          rounds = ff->fixed_layers;
+      if (open) {
+        if (ff->allreduce > 0) {
+          // rounds of gradient communication: largest stage on any device, or the ring colouring when nodes hold two stages
+          int rounds;
+          if (STRAT == 0) {
+            rounds = ring_rounds<SP>(ce, ff->node_exists);
+          } else {
+            rounds = ff->fixed_layers;
 #pragma unroll
-          for (int j = 0; j < SP; ++j) rounds = imax32(rounds, ce[j + 1] - ce[j]);
+            for (int j = 0; j < SP; ++j) rounds = imax32(rounds, ce[j + 1] - ce[j]);
+          }
+          t_step += ff->allreduce * rounds;
         }
-        t_step += ff->allreduce * rounds;
-      }
-      if (STRAT == 2 && (QUEUED || a.base_out == nullptr)) {
-        // least penalty over the reroute vectors of every stage that lost nodes
-        for (int st = 0; st < scn->n_aff; ++st) {
-          const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
-          t_step += (int)stage_penalty<SP>(scn, tab, st, t.x, t.y - t.x);
-        }
-      }
-      if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
-        // cost store of plan indices: hand the peer stage times of this partition to the expanding kernel
-        if (ok) {
-          uint4 *wout = (uint4 *)(a.weights_out + (size_t)(run_first + it) * (scn->n_aff * ROWS_MAX_P));
+        if (STRAT == 2 && (QUEUED || a.base_out == nullptr)) {
+          // least penalty over the reroute vectors of every stage that lost nodes
           for (int st = 0; st < scn->n_aff; ++st) {
             const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
-            const int p = scn->aff_peers[st];
-            uint32_t w[ROWS_MAX_P];
-#pragma unroll
-            for (int i = 0; i < ROWS_MAX_P; ++i) w[i] = i < p ? peer_time(t.x, t.y - t.x, scn->aff_q[st][i]) : 0u;
-            wout[2 * st] = make_uint4(w[0], w[1], w[2], w[3]);
-            wout[2 * st + 1] = make_uint4(w[4], w[5], w[6], w[7]);
+            t_step += (int)stage_penalty<SP>(scn, tab, st, t.x, t.y - t.x);
           }
         }
+        if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
+          // cost store of plan indices: hand the peer stage times of this partition to the expanding kernel
+          if (ok) {
+            uint4 *wout = (uint4 *)(a.weights_out + (size_t)(run_first + it) * (scn->n_aff * ROWS_MAX_P));
+            for (int st = 0; st < scn->n_aff; ++st) {
+              const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
+              const int p = scn->aff_peers[st];
+              uint32_t w[ROWS_MAX_P];
+#pragma unroll
+              for (int i = 0; i < ROWS_MAX_P; ++i) w[i] = i < p ? peer_time(t.x, t.y - t.x, scn->aff_q[st][i]) : 0u;
+              wout[2 * st] = make_uint4(w[0], w[1], w[2], w[3]);
+              wout[2 * st + 1] = make_uint4(w[4], w[5], w[6], w[7]);
+            }
+          }
+        }
+        if ((STRAT != 2 && ff->allreduce <= 0) || may_win()) {
+          int wp[SP + 1];                     // memory prefix at the cuts
+          wp[0] = 0;
+#pragma unroll
+          for (int j = 1; j <= SP; ++j) wp[j] = PW[ce[j]];
+          cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] +
+                 (uint64_t)scn->xfer * (uint32_t)missing_weights<SP, STRAT>(ff, wp);
+          // a lane meets the entries of a compacted list or of a ring in no particular order of position:
+          // there the lower position wins among equal costs; a run is walked in ascending order
+          const bool lower = (QUEUED || compact) ? (cost < best_cost || (cost == best_cost && pos < best_pos)) : cost < best_cost;
+          if (ok && lower) { best_cost = cost; best_pos = pos; }
+          if (!every) wave_low = umin64(wave_low, uniform64(wave_min(ok ? cost : ~0ull)));
+        }
       }
-      cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] + (uint64_t)scn->xfer * (uint32_t)missing;
-      // a lane meets the entries of a compacted list or of a ring in no particular order of position:
-      // there the lower position wins among equal costs; a run is walked in ascending order
-      const bool lower = (QUEUED || compact) ? (cost < best_cost || (cost == best_cost && pos < best_pos)) : cost < best_cost;
-      if (ok && lower) { best_cost = cost; best_pos = pos; }
       if (bounded) {
         // the round's lowest cost becomes known to every wave; what the others found is picked up in turn
         n_eval += (uint32_t)__popcll(ok_mask);
-        const uint64_t round_best = wave_min(ok ? cost : ~0ull);
-        if (round_best < incumbent) {
-          incumbent = round_best;
-          if (lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)round_best);
+        if (wave_low < incumbent) {
+          incumbent = wave_low;
+          if (lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)wave_low);
         }
         incumbent = umin64(incumbent, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        wave_low = umin64(wave_low, uniform64(incumbent));
       }
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr && ok) a.base_out[run_first + it] = cost;
     }
