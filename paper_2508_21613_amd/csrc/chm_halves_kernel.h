@@ -9,7 +9,10 @@
 // is worked out where its loop stands.  Only what depends on the last cut is left to the innermost loop, and of that
 // the scalar share (a function of two cuts) is read from a table of (L + 1)^2 records (k_pair_records, 32 bytes each,
 // laid out once per handle and strategy).
-// @FIGURES@
+// Bound by VALU issue: 14 to 17 instructions a partition in the innermost loop (26 under redundant computation), 20 to 28 in all;
+// working every lane's upper stages out on their own took 51 to 54 (104 with two classes of pipelines), one partition at a time
+// 200 and more.  62.9 M partitions of 8 stages: 57 us (120; one by one 434), under redundant computation 75 (209; 516), 5.2 G of
+// 11 stages 4.0 ms (6.4; 51).  Six waves per SIMD and more hide the scalar loads.
 //
 // Every partition's memory peak and the time of its longest pipeline class are worked out.  The time of other classes (strategy
 // 0: pipelines without the failed nodes) and the weights to fetch (the transition time) only where horizon x that time does not
@@ -27,7 +30,7 @@ typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
   return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);
 }
-constexpr int HALVES_NEVER = -(1 << 30);   // a term of a maximum that does not exist
+constexpr int HALVES_NEVER = TERM_NEVER;
 constexpr int HALVES_UNFIT = 1 << 30;      // in place of a memory peak or a time: these partitions do not fit
 
 // A record of two cuts x < y.  Strategies 1 and 2: x, y = the last two cuts; stage N-2 = [x, y) and stage N-1 = [y, L), times as
@@ -154,35 +157,6 @@ __device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint
     c[i] = x + 1;
   }
   c[1] = (int)rem + 1;                                 // C(x, 1) = x
-}
-
-// Step time of one pipeline class of the partition with the given cuts, stage after stage (stage_of: prefixes at a cut).
-// The maximum of pipeline_time, read the other way round: a pair of stages (s, s') at which the two ends turn goes with the
-// best own term of a stage not above either.  Four running maxima take the place of arrays.
-template <int N, int STRAT, typename At>
-__device__ __forceinline__ int class_time(ClsPtr cl, At at) {
-  int none = HALVES_NEVER, only_u = HALVES_NEVER, only_v = HALVES_NEVER, both = HALVES_NEVER;
-  int p = 0, mf = 0, mb = 0;
-#pragma unroll
-  for (int s = 0; s < N; ++s) {
-    const int2 lo = at(s), hi = at(STRAT == 0 ? (s + 2 <= N ? s + 2 : N) : s + 1);
-    int f = hi.x - lo.x, c = hi.y - lo.y;
-    if (STRAT == 0) {
-      if (s == N - 1) { f += at(1).x; c += at(1).y; }
-      const int keep = ((cl->dead >> s) & 1u) ? 0 : -1;
-      f &= keep;
-      c &= keep;
-    }
-    p += c;
-    mf = imax32(mf, f);
-    mb = imax32(mb, c - f);
-    const int u = (int)__umul24((uint32_t)mb, (uint32_t)cl->after[s]) + p, v = (int)__umul24((uint32_t)mf, (uint32_t)cl->after[s]) + p;
-    none = imax32(none, cl->steady[s] < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)c, (uint32_t)cl->steady[s]) - p);
-    only_u = imax32(only_u, none + u);
-    only_v = imax32(only_v, none + v);
-    both = imax32(both, imax32(only_u + v, only_v + u));
-  }
-  return both + cl->comm_total;
 }
 
 // One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.  The upper halves
@@ -370,7 +344,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
         if (rounds > 0) step += imax32(rounds_low, pair_rounds);
       } else {
         for (int ci = 1; ci < ff->n_time; ++ci)
-          step = imax32(step, class_time<N, STRAT>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
+          step = imax32(step, class_time<N, STRAT, true>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
       }
       const bool near_best = ((mask >> lane) & 1u) && step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;

@@ -132,6 +132,48 @@ __device__ __forceinline__ int pipeline_time(const int (&F)[N], const int (&C)[N
   return time24 ? pipeline_time_m<N, UNI, true>(F, C, cl) : pipeline_time_m<N, UNI, false>(F, C, cl);
 }
 
+constexpr int TERM_NEVER = -(1 << 30);   // a term of a maximum that does not exist
+
+// Time of one pipeline class of a partition, stage after stage (at(i): prefixes of forward and forward + backward time at cut
+// i).  The maximum of pipeline_time, read the other way round: a pair of stages (s, s') at which the two ends turn goes with
+// the best own term of a stage not above either.  Four running maxima take the place of the arrays (16 instructions a stage
+// instead of 13, but no registers that grow with the stages).
+template <int N, int STRAT, bool M24, typename At>
+__device__ __forceinline__ int class_time(ClsPtr cl, At at) {
+  const int M = cl->M;
+  int none = TERM_NEVER, only_u = TERM_NEVER, only_v = TERM_NEVER, both = TERM_NEVER;
+  int p = 0, mf = 0, mb = 0;
+#pragma unroll
+  for (int s = 0; s < N; ++s) {
+    const int2 lo = at(s), hi = at(STRAT == 0 ? (s + 2 <= N ? s + 2 : N) : s + 1);
+    int f = hi.x - lo.x, c = hi.y - lo.y;              // (strategy 0: a node runs two stages)
+    if (STRAT == 0) {
+      if (s == N - 1) { f += at(1).x; c += at(1).y; }
+      const int keep = ((cl->dead >> s) & 1u) ? 0 : -1;          // uniform
+      f &= keep;
+      c &= keep;
+    }
+    if (!cl->unit) {                                   // uniform
+      const uint32_t q = cl->q_stage[s];
+      const int b = scale32(c - f, q);
+      f = scale32(f, q);
+      c = f + b;
+    }
+    p += c;
+    mf = imax32(mf, f);
+    mb = imax32(mb, c - f);
+    const int k = STRAT == 0 ? cl->steady[s] : M - N + s;
+    if (k < 0) continue;                               // uniform: no own term, and no turn counts ahead of the first one
+    const uint32_t after = STRAT == 0 ? (uint32_t)cl->after[s] : (uint32_t)(N - 1 - s);
+    const int u = (int)(times<M24>((uint32_t)mb, after) + (uint32_t)p), v = (int)(times<M24>((uint32_t)mf, after) + (uint32_t)p);
+    none = imax32(none, (int)times<M24>((uint32_t)c, (uint32_t)k) - p);
+    only_u = imax32(only_u, none + u);
+    only_v = imax32(only_v, none + v);
+    both = imax32(imax32(both, only_u + v), only_v + u);
+  }
+  return both + cl->comm_total;
+}
+
 // The least of max_i r_i * w_i over all valid reroute vectors (0 <= r_i <= cap, sum = orphans), w_i = the stage's
 // forward + backward time on peer i, all below 2^24.  Of the multiples w_i, 2 w_i, ..., cap w_i of all peers taken
 // together a vector whose maximum is v uses only ones up to v, at least `orphans` of them; so the minimum is the
@@ -486,8 +528,13 @@ __device__ __forceinline__ int2 stage_times(const int2 *tc, const int (&c)[SP + 
 // since a round appends at most 64 entries to fewer than 64 waiting ones.
 constexpr int QCAP = 128;
 
+// More stages than this: class_time (20 stages: 112 vector registers instead of 180, four waves per SIMD instead of two, a search
+// 89 instead of 107 us); fewer: pipeline_time, whose instructions are fewer (lists of 16 stages 658 us, 734 with class_time;
+// searches of 11 stages 125 and 131, of 6 174 and 185).
+constexpr int FLOW_FROM = 16;
+
 // Waves per SIMD the register allocator is asked to keep possible: 5 up to 5 stages (at most 96 vector registers), 4 up to
-// 10 (128), 3 up to 16 (168), 2 beyond (256; from 27 stages on some are spilled).  Strategy 2, whose loops over the peers
+// 10 (128), 3 up to 16 (168), 4 up to 24 and 3 beyond, without spills (class_time).  Strategy 2, whose loops over the peers
 // need the most: 5 up to 8 stages, which fit 96 without spills when asked to (97 unasked: a range of 3 M partitions of 8
 // stages 69 instead of 73 us, 2.6 M of uneven speeds 201 instead of 224).
 //
@@ -502,7 +549,7 @@ constexpr int QCAP = 128;
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
 // spilled bytes per lane at 8 stages and 4 % of its time).
 template <int SP, int STRAT, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : 2)))
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 16 ? 3 : SP <= 24 ? 4 : 3)))
 k_fast_search(FastLaunch a) {
   constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
@@ -608,6 +655,31 @@ k_fast_search(FastLaunch a) {
   ce[0] = 0;
   ce[SP] = L;
 
+  // A list's next entry is on its way while this one is worked on (a tile waits for memory otherwise, and three wavefronts per
+  // SIMD do not hide that at 16 stages: 3 x 2^24 rows 692 us without, 658 with it).
+  auto entry_of_list = [&](uint32_t it) -> uint4 {
+    const uint32_t entry = (blockIdx.x * a.per_lane + it) * BLOCK + threadIdx.x;
+    const bool there = entry < a.s.part_count;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (a.s.cuts != nullptr) {
+      const uint64_t at = (uint64_t)(there ? entry : 0) * K;
+      if (at + 16 <= (uint64_t)a.s.part_count * K) {
+        __builtin_memcpy(w, a.s.cuts + at, 16);                // (unaligned; bytes behind the row are not looked at)
+      } else {
+        for (int i = 0; i < K; ++i) {
+          const uint32_t b = (uint32_t)a.s.cuts[at + i] << (8 * (i & 3));
+          w[0] |= i < 4 ? b : 0; w[1] |= (i >> 2) == 1 ? b : 0; w[2] |= (i >> 2) == 2 ? b : 0; w[3] |= (i >> 2) == 3 ? b : 0;
+        }
+      }
+    } else {
+      const uint64_t r = there ? a.s.ranks[entry] : 0;
+      w[0] = (uint32_t)r; w[1] = (uint32_t)(r >> 32);
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  };
+  uint4 ahead = make_uint4(0, 0, 0, 0);
+  if (LIST) ahead = entry_of_list(0);
+
   for (uint32_t it = 0; it < (wave_dead ? 0u : a.per_lane + (QUEUED ? 1u : 0u)); ++it) {
     bool live = it < run_len;             // this lane has a partition in this round
     uint32_t pos = run_first + it;        // where its result is reported
@@ -621,16 +693,10 @@ k_fast_search(FastLaunch a) {
           const uint32_t entry = (blockIdx.x * a.per_lane + it) * BLOCK + threadIdx.x;
           live = entry < a.s.part_count;
           pos = a.pos_base + entry;
+          const uint4 now = ahead;
+          if (it + 1 < a.per_lane) ahead = entry_of_list(it + 1);
           if (a.s.cuts != nullptr) {
-            const uint64_t at = (uint64_t)(live ? entry : 0) * K;
-            if (at + 16 <= (uint64_t)a.s.part_count * K) {
-              __builtin_memcpy(words, a.s.cuts + at, 16);          // (unaligned; bytes behind the row are not looked at)
-            } else {
-              for (int i = 0; i < K; ++i) {
-                const uint32_t b = (uint32_t)a.s.cuts[at + i] << (8 * (i & 3));
-                words[0] |= i < 4 ? b : 0; words[1] |= (i >> 2) == 1 ? b : 0; words[2] |= (i >> 2) == 2 ? b : 0; words[3] |= (i >> 2) == 3 ? b : 0;
-              }
-            }
+            words[0] = now.x; words[1] = now.y; words[2] = now.z; words[3] = now.w;
             // a row that does not increase strictly within 1..L-1 does not fit; 1..K stands in for it
             int prev = 0;
 #pragma unroll
@@ -646,7 +712,7 @@ k_fast_search(FastLaunch a) {
 #pragma unroll
             for (int i = 1; i <= K; ++i) c[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
           } else {
-            uint64_t rem = live ? a.s.ranks[entry] : 0;
+            uint64_t rem = live ? (uint64_t)now.x | ((uint64_t)now.y << 32) : 0;
             valid = rem < scn->fam[STRAT].n_part;
             if (!valid) rem = 0;
             unrank_digits<K, uint64_t>(rem, L, unrank_steps(L - K), BN, c);
@@ -740,11 +806,15 @@ k_fast_search(FastLaunch a) {
       bool open = true;
       for (int ci = 0; ci < ff->n_time && open; ++ci) {
         const ClsPtr cl = &ff->cls[ci];
-        int F[SP], C[SP];
-        {
-          // (the compiler is not to know that these reads are the same for every class)
+        // (the compiler is not to know that these reads are the same for every class)
 #pragma unroll
-          for (int j = 1; j <= K; ++j) asm volatile("" : "+v"(ce[j]));
+        for (int j = 1; j <= K; ++j) asm volatile("" : "+v"(ce[j]));
+        int time;
+        if constexpr (SP > FLOW_FROM) {
+          auto at = [&](int i) -> int2 { return i == 0 ? make_int2(0, 0) : TC[ce[i]]; };
+          time = ff->time24 ? class_time<SP, STRAT, true>(cl, at) : class_time<SP, STRAT, false>(cl, at);
+        } else {
+          int F[SP], C[SP];
           int2 t[SP + 1];
           t[0] = make_int2(0, 0);
 #pragma unroll
@@ -762,17 +832,18 @@ k_fast_search(FastLaunch a) {
               C[j] &= keep;
             }
           }
-        }
-        if (!cl->unit) {
+          if (!cl->unit) {
 #pragma unroll
-          for (int j = 0; j < SP; ++j) {
-            const uint32_t q = cl->q_stage[j];
-            const int b = scale32(C[j] - F[j], q);
-            F[j] = scale32(F[j], q);
-            C[j] = F[j] + b;
+            for (int j = 0; j < SP; ++j) {
+              const uint32_t q = cl->q_stage[j];
+              const int b = scale32(C[j] - F[j], q);
+              F[j] = scale32(F[j], q);
+              C[j] = F[j] + b;
+            }
           }
+          time = pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24);
         }
-        t_step = imax32(t_step, pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24));
+        t_step = imax32(t_step, time);
         open = may_win();
       }
       if (open) {
