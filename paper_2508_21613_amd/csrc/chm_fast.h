@@ -141,6 +141,12 @@ struct FastLaunch {
   const uint32_t *cut_count;
 };
 
+// The families of one call in one launch (k_search_families); family[k] with blocks[k] workgroups, 0 = not among them.
+struct FamiliesLaunch {
+  FastLaunch family[3];
+  uint32_t blocks[3];
+};
+
 // Exhaustive search of a whole family by halves (chm_halves_kernel.h).
 enum { PAIR_RECORD_WORDS = 8 };
 struct HalvesItems {
@@ -205,6 +211,15 @@ int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void 
 // Whether fast_search would run this launch as a bounded search if a.incumbent were set (a search of a covered
 // strategy of at most 16 stages without cost store).
 bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch &a);
+// The range searches of up to three families (one launch argument each, at most one per strategy) in one launch, exhaustive; an
+// incumbent word set in them is lowered by what they find.  Same return convention; positive: some family is not covered, their
+// stages have no common instance, or they are large enough to fill the device one after the other.
+int fast_search_families(FastState *f, const DevScenario &h, const SearchLaunch *a, int n, void *stream);
+// its kernels by stages (chm_families_*.hip): 1 = no instance
+int chmk_families_8(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);      // up to 8 stages
+int chmk_families_12(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);     // up to 12
+int chmk_families_16(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);
+int chmk_families_24(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);
 // Kernel launchers by strategy (chm_search_s0/1/2.hip): 1 = no instance for this number of stages, else 0.
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);

@@ -382,6 +382,12 @@ float estimate_fit_share(const DevScenario &h, const FastFamily &ff, int strat, 
   return (float)fit / (float)FIT_SAMPLES;
 }
 
+// Partitions of all families of a call up to which they are searched in one launch.  us a search, one launch after the other /
+// together: 9,455 partitions of 4 stages 39 / 31, 0.5 M of 6 stages 65 / 52, 3.6 M of 8 stages at uneven speeds 127 / 106 and, where a
+// tenth of them fits (apart, a ring per wavefront collects those that do), 100 / 80; 9.7 M 285 / 241 and 182 / 153; 18.6 M 360 / 353;
+// 34 M 572 / 592 and 430 / 410: by then each family fills the device by itself.
+constexpr uint64_t FAMILIES_UP_TO = 1ull << 24;
+
 // Search by halves (chm_halves_kernel.h): which families, and how many cuts the upper half takes.
 //
 // Partitions from which a family is looked at: below, its seeds, its first search's table and the fixed cost of
@@ -660,6 +666,21 @@ int launch_list(FastState *f, const DevScenario &h, const SearchLaunch &a, hipSt
   return 0;
 }
 
+// Run length per lane.  Runs of at most 32 partitions (longer ones leave too few workgroups to even out the
+// tail: 62.9 M partitions then make about 30 workgroups per compute unit, six rounds of the five that are
+// resident); spaces below 2^25 partitions get at least 16 workgroups per compute unit and correspondingly shorter
+// runs (measured on 10 to 15 M partitions: unranking once per 10 to 15 partitions costs less than the idle tail
+// of fewer, longer workgroups; runs of 5 to 7 were 1 to 8 % slower).  Small spaces: runs of 4, or as short
+// as lets every lane of five workgroups per CU have one: a second round of workgroups costs more than a second partition per
+// lane.  (Five are resident up to 5 stages, with strategy 2 up to 8; deeper kernels hold four, three or two, and then
+// run further rounds.)
+uint64_t run_length(uint64_t partitions) {
+  const uint64_t lanes_balanced = 256ull * 16 * BLOCK, lanes_resident = 256ull * 5 * BLOCK;
+  uint64_t per = partitions / lanes_balanced;
+  if (per < 4) per = std::min<uint64_t>(4, (partitions + lanes_resident - 1) / lanes_resident);
+  return std::max<uint64_t>(1, std::min<uint64_t>(per, 32));
+}
+
 int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t *base_out, uint32_t *weights_out,
                   hipStream_t st) {
   FastLaunch fl;
@@ -670,18 +691,7 @@ int launch_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uin
   fl.tab = f->d_tables;
   fl.base_out = base_out;
   fl.weights_out = weights_out;
-  // Run length per lane.  Runs of at most 32 partitions (longer ones leave too few workgroups to even out the
-  // tail: 62.9 M partitions then make about 30 workgroups per compute unit, six rounds of the five that are
-  // resident); spaces below 2^25 partitions get at least 16 workgroups per compute unit and correspondingly shorter
-  // runs (measured on 10 to 15 M partitions: unranking once per 10 to 15 partitions costs less than the idle tail
-  // of fewer, longer workgroups; runs of 5 to 7 were 1 to 8 % slower).  Small spaces: runs of 4, or as short
-  // as lets every lane of five workgroups per CU have one: a second round of workgroups costs more than a second partition per
-  // lane.  (Five are resident up to 5 stages, with strategy 2 up to 8; deeper kernels hold four, three or two, and then
-  // run further rounds.)
-  const uint64_t lanes_balanced = 256ull * 16 * BLOCK, lanes_resident = 256ull * 5 * BLOCK;
-  uint64_t per = a.part_count / lanes_balanced;
-  if (per < 4) per = std::min<uint64_t>(4, (a.part_count + lanes_resident - 1) / lanes_resident);
-  per = std::max<uint64_t>(1, std::min<uint64_t>(per, 32));
+  uint64_t per = run_length(a.part_count);
   if (a.jump_at != 0xffffffffu) per = 1;               // a run must not straddle two windows
   else if (a.costs_out != nullptr) per = std::min<uint64_t>(per, 8);   // bounds the LDS tile of the cost store
   fl.per_lane = (uint32_t)per;
@@ -955,6 +965,36 @@ int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void 
   const bool list = a.ranks != nullptr || a.cuts != nullptr;
   if (list && h.fam[a.strategy].stages > PACKED_MAX_STAGES) return 1;
   return list ? launch_list(f, h, a, st) : launch_search(f, h, a, nullptr, nullptr, st);
+}
+
+int fast_search_families(FastState *f, const DevScenario &h, const SearchLaunch *a, int n, void *stream) {
+  FamiliesLaunch fl;
+  memset((void *)&fl, 0, sizeof(fl));
+  uint64_t total = 0;
+  int deep = 0, s1 = 0;
+  for (int i = 0; i < n; ++i) {
+    const int k = a[i].strategy;
+    if (k < 0 || k > 2 || !f->usable[k] || a[i].ranks || a[i].cuts || a[i].costs_out || fl.family[k].tab) return 1;
+    fl.family[k].s = a[i];
+    fl.family[k].tab = f->d_tables;
+    total += a[i].part_count;
+    (k == 1 ? s1 : deep) = h.fam[k].stages;            // (strategies 0 and 2 have the stages of the grid)
+  }
+  if (deep == 0 || total > FAMILIES_UP_TO) return 1;
+  if (s1 == 0) s1 = deep - 1;
+  const uint64_t per = run_length(total);
+  uint32_t blocks = 0;
+  for (int k = 0; k < 3; ++k) {
+    if (!fl.family[k].tab) continue;
+    fl.family[k].per_lane = fl.family[k].s.jump_at != 0xffffffffu ? 1 : (uint32_t)per;       // (a run must not straddle two windows)
+    fl.blocks[k] = (uint32_t)((fl.family[k].s.part_count + BLOCK * fl.family[k].per_lane - 1) / (BLOCK * fl.family[k].per_lane));
+    blocks += fl.blocks[k];
+  }
+  if (blocks == 0) return 0;
+  const int rc = deep <= 8 ? chmk_families_8(deep, s1, fl, blocks, stream) : deep <= 12 ? chmk_families_12(deep, s1, fl, blocks, stream)
+                 : deep <= 16 ? chmk_families_16(deep, s1, fl, blocks, stream) : chmk_families_24(deep, s1, fl, blocks, stream);
+  if (rc) return rc;
+  return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int fast_score_reroute(FastState *f, const DevScenario &h, const DevScenario *d_scn, uint64_t local_first,

@@ -548,27 +548,37 @@ constexpr int FLOW_FROM = 16;
 // MODE 0: every lane evaluates its own partitions; 1: QUEUED; 2: QUEUED with the bounds of a bounded search (a
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
 // spilled bytes per lane at 8 stages and 4 % of its time).
-template <int SP, int STRAT, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 16 ? 3 : SP <= 24 ? 4 : 3)))
-k_fast_search(FastLaunch a) {
+template <int SP, int MODE>
+struct SearchShared {
+  static constexpr bool QUEUED = MODE >= 1;
+  uint4 q_cuts[QUEUED ? (BLOCK / 64) * QCAP : 1];
+  uint64_t BN[(SP > 1 ? SP - 1 : 1) * DEV_MAX_L];       // BN[(i-1)*128 + x] = C(x, i), i = 1..K
+  // prefix sums: forward and forward + backward; static memory; activation memory
+  int2 TC[DEV_MAX_L + 1];
+  uint64_t wave_keys[BLOCK / 64];
+  uint32_t q_pos[QUEUED ? (BLOCK / 64) * QCAP : 1];
+  int PW[DEV_MAX_L + 1], PA[DEV_MAX_L + 1];
+  uint32_t wave_fit[BLOCK / 64], wave_eval[BLOCK / 64];
+};
+
+// One workgroup (`block` of the family's) of a search.  cost_tile: BLOCK * per_lane costs when a cost store with per_lane > 1 is
+// asked for.
+template <int SP, int STRAT, int MODE>
+__device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t block, SearchShared<SP, MODE> &sh, int64_t *cost_tile) {
   constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
-  __shared__ uint4 q_cuts[QUEUED ? (BLOCK / 64) * QCAP : 1];
-  __shared__ uint32_t q_pos[QUEUED ? (BLOCK / 64) * QCAP : 1];
-  // prefix sums: forward and forward + backward; static memory; activation memory
-  __shared__ int2 TC[DEV_MAX_L + 1];
-  __shared__ int PW[DEV_MAX_L + 1], PA[DEV_MAX_L + 1];
-  __shared__ uint64_t BN[(K > 0 ? K : 1) * DEV_MAX_L];   // BN[(i-1)*128 + x] = C(x, i), i = 1..K
-  __shared__ uint64_t wave_keys[BLOCK / 64];
-  __shared__ uint32_t wave_fit[BLOCK / 64];
-  __shared__ uint32_t wave_eval[BLOCK / 64];
-  extern __shared__ int64_t cost_tile[];       // BLOCK * per_lane costs when a cost store with per_lane > 1 is asked for
+  uint4 *const q_cuts = sh.q_cuts;
+  uint32_t *const q_pos = sh.q_pos;
+  int2 *const TC = sh.TC;
+  int *const PW = sh.PW, *const PA = sh.PA;
+  uint64_t *const BN = sh.BN, *const wave_keys = sh.wave_keys;
+  uint32_t *const wave_fit = sh.wave_fit, *const wave_eval = sh.wave_eval;
   const ScnPtr scn = as_const(a.s.scn);
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
   const int L = scn->L;
   const bool compact = !QUEUED && a.cut_list != nullptr;
-  const uint32_t n_slots = compact ? a.cut_count[blockIdx.x] : 0u;       // filled slots of this workgroup's region
+  const uint32_t n_slots = compact ? a.cut_count[block] : 0u;       // filled slots of this workgroup's region
   if (compact && n_slots == 0) return;
   for (int i = threadIdx.x; i <= L; i += BLOCK) {
     TC[i] = make_int2((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]));
@@ -579,11 +589,11 @@ k_fast_search(FastLaunch a) {
     for (int i = threadIdx.x; i < K * DEV_MAX_L; i += BLOCK) BN[i] = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
   __syncthreads();
 
-  const uint32_t lane_id = blockIdx.x * BLOCK + threadIdx.x;
+  const uint32_t lane_id = block * BLOCK + threadIdx.x;
   const uint32_t run_first = lane_id * a.per_lane;                       // chunk-local (a chunk holds at most 2^30 partitions)
   const uint32_t run_len = (LIST || compact || run_first >= a.s.part_count) ? 0u
                            : (uint32_t)(a.s.part_count - run_first < a.per_lane ? a.s.part_count - run_first : a.per_lane);
-  const uint32_t region = blockIdx.x * a.per_lane * BLOCK;               // compact mode: first slot of this workgroup
+  const uint32_t region = block * a.per_lane * BLOCK;               // compact mode: first slot of this workgroup
 
   // cut positions c[1..K]; c[0] = 0 and c[SP] = L are constants
   int c[SP + 1];
@@ -658,7 +668,7 @@ k_fast_search(FastLaunch a) {
   // A list's next entry is on its way while this one is worked on (a tile waits for memory otherwise, and three wavefronts per
   // SIMD do not hide that at 16 stages: 3 x 2^24 rows 692 us without, 658 with it).
   auto entry_of_list = [&](uint32_t it) -> uint4 {
-    const uint32_t entry = (blockIdx.x * a.per_lane + it) * BLOCK + threadIdx.x;
+    const uint32_t entry = (block * a.per_lane + it) * BLOCK + threadIdx.x;
     const bool there = entry < a.s.part_count;
     uint32_t w[4] = {0, 0, 0, 0};
     if (a.s.cuts != nullptr) {
@@ -690,7 +700,7 @@ k_fast_search(FastLaunch a) {
         bool valid = true;
         if (LIST) {
           // tile `it` of this workgroup's part of the list: neighbouring lanes read neighbouring entries
-          const uint32_t entry = (blockIdx.x * a.per_lane + it) * BLOCK + threadIdx.x;
+          const uint32_t entry = (block * a.per_lane + it) * BLOCK + threadIdx.x;
           live = entry < a.s.part_count;
           pos = a.pos_base + entry;
           const uint4 now = ahead;
@@ -930,7 +940,7 @@ k_fast_search(FastLaunch a) {
 
   if (!QUEUED && a.s.costs_out != nullptr && a.per_lane > 1 && !compact) {
     __syncthreads();
-    const uint64_t block_first = (uint64_t)blockIdx.x * BLOCK * a.per_lane;
+    const uint64_t block_first = (uint64_t)block * BLOCK * a.per_lane;
     const uint32_t n_tile = BLOCK * a.per_lane;
     for (uint32_t i = threadIdx.x; i < n_tile; i += BLOCK)
       if (block_first + i < a.s.part_count) a.s.costs_out[block_first + i] = cost_tile[i];
@@ -943,7 +953,7 @@ k_fast_search(FastLaunch a) {
   __syncthreads();
   if (threadIdx.x == 0) {
     // one atomic of each kind per workgroup, spread over several words (see SearchLaunch)
-    const uint32_t slot = (blockIdx.x & a.s.slot_mask) * a.s.slot_stride;
+    const uint32_t slot = (block & a.s.slot_mask) * a.s.slot_stride;
     uint64_t k = wave_keys[0];
     uint32_t fit = wave_fit[0], evaluated = wave_eval[0];
 #pragma unroll
@@ -955,6 +965,28 @@ k_fast_search(FastLaunch a) {
       atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)(k >> a.s.idx_bits));
     if (k != CHM_KEY_NONE) atomicMin((unsigned long long *)a.s.result + slot, (unsigned long long)k);
   }
+}
+
+#define CHM_WAVES(SP, STRAT) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : SP <= 24 ? 4 : 3)))
+template <int SP, int STRAT, int MODE = 0>
+__global__ void __launch_bounds__(BLOCK) CHM_WAVES(SP, STRAT) k_fast_search(FastLaunch a) {
+  __shared__ SearchShared<SP, MODE> sh;
+  extern __shared__ int64_t cost_tile[];
+  search_partitions<SP, STRAT, MODE>(a, blockIdx.x, sh, cost_tile);
+}
+
+// The families of a call in one launch: strategies 2 and 0 of SP stages, 1 of S1.  Small families take microseconds, as long as
+// it takes to launch the next: side by side they take as long as the
+// longest (9,455 partitions of 4 stages: kernels of 5, 5.5 and 7 us, a search 39 us one after the other, 31 together).
+template <int SP, int S1>
+__global__ void __launch_bounds__(BLOCK) CHM_WAVES(SP, 2) k_search_families(FamiliesLaunch a) {
+  typedef SearchShared<SP, 0> Shared;                  // (S1 < SP: room for both)
+  static_assert(S1 < SP && sizeof(SearchShared<S1, 0>) <= sizeof(Shared), "one shared block for all families");
+  __shared__ Shared sh;
+  const uint32_t b = blockIdx.x;
+  if (b < a.blocks[2]) search_partitions<SP, 2, 0>(a.family[2], b, sh, nullptr);
+  else if (b < a.blocks[2] + a.blocks[0]) search_partitions<SP, 0, 0>(a.family[0], b - a.blocks[2], sh, nullptr);
+  else search_partitions<S1, 1, 0>(a.family[1], b - a.blocks[2] - a.blocks[0], *(SearchShared<S1, 0> *)&sh, nullptr);
 }
 
 // Which variant of the search kernel: every lane its own partitions; the partitions that fit (and, in a bounded search, may
