@@ -9,6 +9,7 @@
 
 #include "chm_fast.h"
 #include "chm_pool.h"
+#include "chm_window.h"
 
 // typed front ends of the caching allocator (chm_pool.h)
 template <typename T>
@@ -155,49 +156,8 @@ __global__ void __launch_bounds__(BLOCK) k_expand(ExpandArgs a) {
   __builtin_nontemporal_store((int64_t)(base == ~0ull ? CHM_INF_COST : (int64_t)(base + a.K * pen)), &a.costs[gid]);
 }
 
-// The same with 32-bit index arithmetic, for reroute spaces below 2^31 vectors per partition and launches
-// of at most 2^31 plan indices: the host passes the partition (relative to the pass) and the reroute rank of
-// the launch's first plan index, so a lane divides first_rr + gid, which fits 32 bits.
-// Division of a 32-bit number by a divisor fixed at launch: one multiply-high, two shifts, an add and a subtract
-// (round-up method of Granlund and Montgomery), exact for every dividend; the compiler's generic 32-bit
-// division costs about five times as much.
-struct FastDiv {
-  uint32_t d, m, sh1, sh2;
-};
-static FastDiv make_fast_div(uint32_t d) {
-  FastDiv f;
-  f.d = d;
-  uint32_t l = 0;
-  while ((1ull << l) < d) ++l;                               // ceil(log2 d)
-  f.m = (uint32_t)(((1ull << 32) * ((1ull << l) - d)) / d) + 1u;
-  f.sh1 = l < 1 ? l : 1;
-  f.sh2 = l > 0 ? l - 1 : 0;
-  return f;
-}
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) {
-  const uint32_t t = __umulhi(f.m, n);
-  return (t + ((n - t) >> f.sh1)) >> f.sh2;
-}
-
-struct ExpandArgs32 {
-  const uint64_t *base;
-  const uint32_t *weights;
-  const uint32_t *rows[DEV_MAX_AFF];
-  FastDiv R[DEV_MAX_AFF];
-  int32_t stride[DEV_MAX_AFF], peers[DEV_MAX_AFF];
-  int32_t n_aff;
-  FastDiv R_joint;
-  uint32_t first_part, first_rr, count;
-  uint64_t K;
-  int64_t *costs;
-};
-
-// Plan indices per workgroup: EXPAND_PER consecutive tiles of BLOCK.  A lane computes its EXPAND_PER costs
-// first and stores them back to back at the end: memory operations of a wave complete in order, so a load
-// issued after a store would wait for that store to be acknowledged (microseconds when HBM is saturated
-// with writes), and with one 512-byte store in flight per wave the kernel stayed below 1.5 TB/s.
-constexpr int EXPAND_PER = 8;
-
+// The same with 32-bit index arithmetic (ExpandArgs32), for reroute spaces below 2^31 vectors per partition and launches of at
+// most 2^31 plan indices.
 __device__ __forceinline__ int64_t expand_one(const ExpandArgs32 &a, uint32_t gid) {
   const uint32_t idx = a.first_rr + gid;
   const uint32_t q = fast_div(idx, a.R_joint);
@@ -246,74 +206,6 @@ __global__ void __launch_bounds__(BLOCK) k_expand32(ExpandArgs32 a) {
   for (int rep = 0; rep < EXPAND_PER; rep += 2) {
     const uint32_t gid = first + (rep >> 1) * (2 * BLOCK);
     // streamed out, never read back here
-    if (aligned && gid + 1 < a.count) {
-      typedef long long pair_t __attribute__((ext_vector_type(2)));
-      pair_t v;
-      v.x = cost[rep];
-      v.y = cost[rep + 1];
-      __builtin_nontemporal_store(v, (pair_t *)(a.costs + gid));
-    } else {
-      if (gid < a.count) __builtin_nontemporal_store(cost[rep], &a.costs[gid]);
-      if (gid + 1 < a.count) __builtin_nontemporal_store(cost[rep + 1], &a.costs[gid + 1]);
-    }
-  }
-}
-
-// One stage lost nodes and its vector table is small: the table and the data of the partitions a workgroup's
-// plan indices belong to (cost without penalty, peer stage times) are staged in LDS first, so that the vector
-// memory path carries the stores and little else (with all three reads per plan index going through it the
-// kernel was bound by the address and data path of the CU's texture unit at about 350 G plan indices/s).
-constexpr int EXPAND_REC = 3;         // uint4 words per partition record: cost, 8 peer stage times
-
-__global__ void __launch_bounds__(BLOCK) k_expand32_lds(ExpandArgs32 a, uint32_t max_parts) {
-  extern __shared__ uint4 staged[];   // [R * stride / 4] rows, then [max_parts][EXPAND_REC] partition records
-  const uint32_t R = a.R_joint.d;
-  const uint32_t row_words = R * ((uint32_t)a.stride[0] / 4u);
-  uint4 *rec = staged + row_words;
-  const uint32_t tile_first = blockIdx.x * (EXPAND_PER * BLOCK);
-  const uint32_t tile_last = min(tile_first + EXPAND_PER * BLOCK, a.count) - 1;   // tile_first < count by the grid size
-  const uint32_t p_first = fast_div(a.first_rr + tile_first, a.R_joint);
-  const uint32_t n_parts = min(fast_div(a.first_rr + tile_last, a.R_joint) - p_first + 1, max_parts);
-  const uint4 *rows4 = (const uint4 *)a.rows[0];
-  for (uint32_t i = threadIdx.x; i < row_words; i += BLOCK) staged[i] = rows4[i];
-  for (uint32_t i = threadIdx.x; i < n_parts; i += BLOCK) {
-    const uint32_t pl = a.first_part + p_first + i;
-    const uint64_t b = a.base[pl];
-    const uint4 *w4 = (const uint4 *)(a.weights + (size_t)pl * (a.n_aff * ROWS_MAX_P));
-    rec[i * EXPAND_REC] = make_uint4((uint32_t)b, (uint32_t)(b >> 32), 0u, 0u);
-    rec[i * EXPAND_REC + 1] = w4[0];
-    rec[i * EXPAND_REC + 2] = w4[1];
-  }
-  __syncthreads();
-  const uint32_t first = tile_first + 2 * threadIdx.x;
-  int64_t cost[EXPAND_PER];
-#pragma unroll
-  for (int rep = 0; rep < EXPAND_PER; ++rep) {
-    uint32_t gid = first + (rep >> 1) * (2 * BLOCK) + (rep & 1);
-    gid = gid < a.count ? gid : a.count - 1;                        // lanes past the end redo the last index
-    const uint32_t idx = a.first_rr + gid;
-    const uint32_t q = fast_div(idx, a.R_joint);
-    const uint32_t rr = idx - q * R;
-    uint32_t lp = q - p_first;
-    lp = lp < n_parts ? lp : n_parts - 1;
-    const uint4 head = rec[lp * EXPAND_REC], w_lo = rec[lp * EXPAND_REC + 1];
-    const uint64_t base = (uint64_t)head.x | ((uint64_t)head.y << 32);
-    uint32_t m;
-    if (a.stride[0] == 4) {
-      const uint4 row = staged[rr];
-      m = max(max(__umul24(row.x, w_lo.x), __umul24(row.y, w_lo.y)), max(__umul24(row.z, w_lo.z), __umul24(row.w, w_lo.w)));
-    } else {
-      const uint4 w_hi = rec[lp * EXPAND_REC + 2];
-      const uint4 row = staged[2 * rr], row2 = staged[2 * rr + 1];
-      m = max(max(__umul24(row.x, w_lo.x), __umul24(row.y, w_lo.y)), max(__umul24(row.z, w_lo.z), __umul24(row.w, w_lo.w)));
-      m = max(m, max(max(__umul24(row2.x, w_hi.x), __umul24(row2.y, w_hi.y)), max(__umul24(row2.z, w_hi.z), __umul24(row2.w, w_hi.w))));
-    }
-    cost[rep] = base == ~0ull ? CHM_INF_COST : (int64_t)(base + a.K * m);
-  }
-  const bool aligned = (((uintptr_t)a.costs) & 15u) == 0;            // uniform
-#pragma unroll
-  for (int rep = 0; rep < EXPAND_PER; rep += 2) {
-    const uint32_t gid = first + (rep >> 1) * (2 * BLOCK);
     if (aligned && gid + 1 < a.count) {
       typedef long long pair_t __attribute__((ext_vector_type(2)));
       pair_t v;
@@ -1010,6 +902,37 @@ int fast_score_reroute(FastState *f, const DevScenario &h, const DevScenario *d_
   }
   const FastTables &t = f->h_tables;
   const uint64_t R = h.fam[2].n_reroute;
+  // one stage lost nodes, a table of at most 32 KB: costs straight from the partitions, a tile of plan indices at a time
+  const uint64_t row_bytes = R * (h.aff_peers[0] <= 4 ? 16u : 32u);
+  if (h.n_aff == 1 && R >= WINDOW_LEAST_R && row_bytes <= (32u << 10)) {
+    for (uint64_t done = 0; done < count;) {
+      const uint64_t first = local_first + done;
+      WindowArgs w;
+      memset((void *)&w, 0, sizeof(w));
+      w.search.s = SearchLaunch();
+      w.search.s.scn = d_scn;
+      w.search.s.strategy = 2;
+      w.search.s.idx_bits = 1;
+      w.search.tab = f->d_tables;
+      w.search.per_lane = 1;
+      w.part_first = first / R;
+      w.first_rr = (uint32_t)(first % R);
+      w.R = make_fast_div((uint32_t)R);
+      w.step_parts = 2 * BLOCK / (uint32_t)R;
+      w.step_rr = 2 * BLOCK % (uint32_t)R;
+      w.rows = f->d_vecs + t.vec_off[0];
+      w.stride = h.aff_peers[0] <= 4 ? 4 : 8;
+      w.K = (uint64_t)h.K;
+      w.count = (uint32_t)std::min<uint64_t>(count - done, (1ull << 31) - (1ull << 20));
+      w.costs = d_costs + done;
+      w.tile = window_tile((uint32_t)R, w.count);
+      const int rc = chmk_window_plans(h.fam[2].stages, w, (uint32_t)row_bytes, stream);
+      if (rc) return rc;
+      if (hipGetLastError() != hipSuccess) return -1;
+      done += w.count;
+    }
+    return 0;
+  }
   if (!ensure_scratch(f, (local_first + count - 1) / R - local_first / R + 1)) return -1;
   ExpandArgs e;
   memset(&e, 0, sizeof(e));
@@ -1058,14 +981,7 @@ int fast_score_reroute(FastState *f, const DevScenario &h, const DevScenario *d_
         x.first_rr = (uint32_t)(first % R);
         x.count = (uint32_t)std::min<uint64_t>(e.count - done, (1ull << 31) - (1ull << 20));
         x.costs = e.costs + done;
-        // one affected stage with a table of at most 32 KB: rows and partition data through LDS
-        const uint32_t row_bytes = (uint32_t)R * (uint32_t)x.stride[0] * 4u;
-        const uint32_t max_parts = (uint32_t)((uint64_t)BLOCK * EXPAND_PER / R) + 2;
-        if (h.n_aff == 1 && R >= 16 && row_bytes <= (32u << 10))
-          hipLaunchKernelGGL(k_expand32_lds, dim3((x.count + BLOCK * EXPAND_PER - 1) / (BLOCK * EXPAND_PER)), dim3(BLOCK),
-                             row_bytes + max_parts * EXPAND_REC * sizeof(uint4), st, x, max_parts);
-        else
-          hipLaunchKernelGGL(k_expand32, dim3((x.count + BLOCK * EXPAND_PER - 1) / (BLOCK * EXPAND_PER)), dim3(BLOCK), 0, st, x);
+        hipLaunchKernelGGL(k_expand32, dim3((x.count + BLOCK * EXPAND_PER - 1) / (BLOCK * EXPAND_PER)), dim3(BLOCK), 0, st, x);
         done += x.count;
       }
       if (hipGetLastError() != hipSuccess) return -1;

@@ -599,7 +599,9 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   int c[SP + 1];
   c[0] = 0;
   c[SP] = L;
-  if (!compact && !LIST) {
+  // (a wavefront without partitions has nothing to unrank: most of a window's tile)
+  const bool idle = !compact && !LIST && !QUEUED && __builtin_amdgcn_ballot_w64(run_len != 0) == 0;
+  if (!compact && !LIST && !idle) {
     uint64_t rem = run_len ? a.s.part_first + run_first + (run_first >= a.s.jump_at ? a.s.jump_by : 0) : 0;   // idle lanes walk from rank 0: always valid cuts
     // combinadic digits from the LDS copy of the binomial table
     unrank_digits<K, uint64_t>(rem, L, unrank_steps(L - K), BN, c);
@@ -690,7 +692,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   uint4 ahead = make_uint4(0, 0, 0, 0);
   if (LIST) ahead = entry_of_list(0);
 
-  for (uint32_t it = 0; it < (wave_dead ? 0u : a.per_lane + (QUEUED ? 1u : 0u)); ++it) {
+  for (uint32_t it = 0; it < (wave_dead || idle ? 0u : a.per_lane + (QUEUED ? 1u : 0u)); ++it) {
     bool live = it < run_len;             // this lane has a partition in this round
     uint32_t pos = run_first + it;        // where its result is reported
     if (QUEUED) {
@@ -958,7 +960,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
     uint32_t fit = wave_fit[0], evaluated = wave_eval[0];
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; evaluated += wave_eval[i]; }
-    if (fit) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
+    if (fit && a.s.feasible != nullptr) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
     if (MODE == 2 && bounded && evaluated) atomicAdd((unsigned long long *)a.s.evaluated + slot, (unsigned long long)evaluated);
     // a search over a list of candidates of a bounded search makes its best cost known to what follows
     if (!QUEUED && a.s.incumbent != nullptr && k != CHM_KEY_NONE)
