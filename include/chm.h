@@ -172,14 +172,14 @@ int chm_search_cuts(chm_scenario *s, int32_t strategy, const uint8_t *d_cuts, ui
  * step time of every partition of every selected family are worked out on the device; for data
  * rerouting with the least penalty over every reroute vector of every stage that lost nodes (an order
  * statistic: the orphans-th smallest multiple of the peers' stage times; the penalty is a sum of
- * independent per-stage terms).  In large families (2^21 partitions and more, searched by halves) the transition time
- * is worked out where horizon x step time alone does not already exceed the lowest cost met so far.  Ties go to the
+ * independent per-stage terms).  The time of other pipeline classes than the one with the most work, penalties and the transition time
+ * are worked out where the terms before them do not already exceed the lowest cost met so far.  Ties go to the
  * lowest plan index.  Synchronises hip_stream before returning.  Errors:
  * CHM_ERR_UNRECOVERABLE (mask selects no existing family), CHM_ERR_NO_FEASIBLE (out is
  * filled with index UINT64_MAX, cost CHM_INFEASIBLE), CHM_ERR_OVERFLOW (the selected families hold more
  * than 2^16 chunks of 2^idx_bits partitions, idx_bits <= 30: beyond exhaustive reach; search windows with
  * chm_search_range or lists instead), CHM_ERR_ARG, CHM_ERR_HIP.  The first search of a large family lays out a table
- * of at most 8 MB of device memory per strategy, which the handle keeps (where there is none to be had, the search
+ * of under 0.7 MB of device memory per strategy, which the handle keeps (where there is none to be had, the search
  * runs on the kernels that need no table). */
 int chm_search_best(chm_scenario *s, uint32_t strategy_mask, chm_best *out, void *hip_stream);
 
@@ -206,8 +206,8 @@ int chm_search_best_batch(chm_scenario *const *handles, int32_t n, uint32_t stra
  * beyond; with the usual idx_bits of 30 that is every space chm_search_best accepts short of 2^43 partitions),
  * and no rerouting family with a large reroute space (more than 4,096 vectors over its stages, at most 8 peers
  * and 2^23 vectors each: CHM_ERR_LIMIT, use chm_search_best).  Families that chm_search_best searches by halves
- * run so here only on a handle that it has searched before: the tables are laid out then (at most 8 MB a strategy,
- * kept until the handle is freed); otherwise the kernels that need none take them, two to four times as long.  On CHM_ERR_LIMIT out is filled as for
+ * run so here only on a handle that it has searched before: the tables are laid out then (under 0.7 MB a strategy,
+ * kept until the handle is freed); otherwise the kernels that need none take them, three to seven times as long.  On CHM_ERR_LIMIT out is filled as for
  * CHM_ERR_NO_FEASIBLE.  All calls on one GPU share the array, which keeps the last call's contents (the
  * call resets what it reads): two calls that overlap in time on one GPU, from any handles or threads, race.
  * Otherwise as chm_search_best (synchronises hip_stream; same errors). */
@@ -240,12 +240,14 @@ int chm_decode_plan(const chm_scenario *s, uint64_t index, chm_best *out);
  * above the lowest cost evaluated so far in the same call.  The plan returned is the same, ties included:
  * only plans that can neither win nor tie are skipped, one by one or a run of consecutive ranks at a time
  * (the stages above the cuts that change within the run are common to all of its partitions, and so is their
- * share of the bound), or never enumerated at all: for a family searched as a whole the library counts on
+ * share of the bound), or never enumerated at all: up to 2^30 partitions at nominal speeds (searched by halves) the
+ * loops over the cuts leave out what the cuts placed so far already make too slow; for other families searched as a whole the library counts on
  * the host, stage by stage, the partitions whose bound stays within the best cost known, and the device
  * enumerates and evaluates only those (this also reaches families of more than 2^46 partitions, which
  * chm_search_best otherwise refuses with CHM_ERR_OVERFLOW, whenever at most 2^26 candidates remain).  The search
  * starts with the ranks around the time-balanced and the memory-balanced partition of each range, so that a
- * good cost is known early.  chm_timing.evaluated (chm_measure.h) tells how many
+ * good cost is known early.  (Families of 2^22 partitions together and fewer are searched exhaustively in one launch, which takes less
+ * time.)  chm_timing.evaluated (chm_measure.h) tells how many
  * partitions were evaluated in full; chm_timing.feasible then counts only those partitions that were looked
  * at one by one and fit.  Covers
  * the range and list searches of the specialised kernels without cost store (other paths evaluate everything;

@@ -161,6 +161,7 @@ struct HalvesLaunch {
   HalvesItems *items;
   uint32_t n_pairs, n_items;
   uint32_t chunk;               // upper halves per item
+  uint32_t bounded;             // 1: what the cuts placed so far make too slow is left out
   uint32_t chunk_words;         // words from one chunk's argmin words to the next chunk's
 };
 
@@ -234,7 +235,7 @@ int chmk_halves_s2(int sp, int up, const HalvesLaunch &a, bool build, void *stre
 // fast_halves_covers: whether it takes the family at all.
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
-                       bool may_allocate, void *stream);
+                       bool may_allocate, bool bounded, void *stream);
 // The stream of the last search has been waited for: the tables its launches filled are there.
 void fast_halves_settled(FastState *f);
 // Sampled share of partitions of a strategy that pass the memory filter (1.0 where no sample applies).

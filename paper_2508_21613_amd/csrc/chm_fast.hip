@@ -814,7 +814,7 @@ bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_
 }
 
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
-                       bool may_allocate, void *stream) {
+                       bool may_allocate, bool bounded, void *stream) {
   const int k = a.strategy;
   if (!fast_halves_covers(f, h, k, partitions)) return 1;
   const HalvesShape &hs = f->halves[k];
@@ -829,6 +829,7 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.s = a;
   hl.tab = f->d_tables;
   hl.chunk_words = chunk_words;
+  hl.bounded = bounded ? 1 : 0;
   hl.chunk = hs.chunk;
   hl.n_items = hs.n_items;
   hl.n_pairs = n_pairs;

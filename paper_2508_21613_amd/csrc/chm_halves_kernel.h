@@ -161,7 +161,8 @@ __device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint
 
 // One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.  The upper halves
 // that go with v are numbered by falling digits x (position = sum of C(x_i, i) over UP of them), cut = L-1-x.
-template <int N, int STRAT, int UP>
+// PRUNE: a bounded search (compiled apart: its tests in the loops over the outer cuts cost the exhaustive search 5 % as a flag).
+template <int N, int STRAT, int UP, bool PRUNE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRAT == 0 ? (N <= 10 ? 5 : 4) : N <= 8 ? 7 : N <= 11 ? 6 : 5))) k_search_halves(HalvesLaunch a) {
   constexpr int K = N - 1, H = K - UP;
   constexpr int LOW = STRAT == 0 ? H - 1 : H;         // nodes of the lower half alone
@@ -459,6 +460,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
         y -= 2;
       }
     };
+    // A bounded search: whether some lane may still win, given what the cuts placed so far are worth at least.  su, sv: lower bounds of
+    // the suffix maxima that reach the terms of node H (strategy 0: of node H-1) and below.
+    auto hopeless = [&](int su, int sv, int least) -> bool {
+      const int t = imax32(imax32(least, su + sv + gmax), imax32(imax32(only_u + sv, only_v + su), both_lim));
+      return __builtin_amdgcn_ballot_w64(t <= lim) == 0;
+    };
+    if (PRUNE && STRAT != 0 && __builtin_amdgcn_ballot_w64(both <= __builtin_elementwise_sub_sat(lim, pen_low)) == 0) left = 0;
     while (left != 0) {
       bool fits = true;
       int pen_g = 0, c_h = 0, f_h = 0;
@@ -477,6 +485,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
           gmax = imax32(none, scalar_own(H, c_h, tg.y));
           if (STRAT == 2) pen_g = (int)share_h * c_h;
           layers_up = imax32(layers_low, g - v);
+          if (PRUNE) {
+            if (STRAT == 2) lim = ok ? __builtin_elementwise_sub_sat(limit, comm + pen_low + pen_g) : (int)0x80000000;
+            fits = fits && !hopeless(imax32(u_h, tl.y), imax32(v_h, tl.y), 0);
+          }
         }
       }
       do {
@@ -516,6 +528,15 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
             off = comm + pen_low + pen_up;
             lim = ok ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
           }
+          if (PRUNE) {
+            int su = tl.y, sv = tl.y, least = 0;
+            if (UP == 3) {
+              su = imax32(su, u_m);
+              sv = imax32(sv, v_m);
+              least = su + sv + own_m;
+            }
+            if (hopeless(imax32(su, u_h), imax32(sv, v_h), least)) continue;
+          }
           walk(m, m, y, n, 0, 0);
         } else {
           // node H-1 = [cut H-1, cut H+1); UP = 3: node H = [v, m); node N-2 = [m, L)
@@ -554,6 +575,16 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
           lim = ok_g ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
           room = ok_g ? room_z : (int)0x80000000;
           const int k_z = cl->steady[N - 1];
+          if (PRUNE) {
+            // (the ends of the records' nodes lie behind `base`)
+            int su = base + imax32(u_m, xb2), sv = base + imax32(v_m, xf2), least = 0;
+            if (UP == 3) {
+              su = imax32(su, u_h);
+              sv = imax32(sv, v_h);
+              least = su + sv + own_h;
+            }
+            if (hopeless(imax32(su, u_g), imax32(sv, v_g), least)) continue;
+          }
           walk(UP == 3 ? g : v, m, y, n, c2, k_z < 0 ? 0 : k_z);
         }
       } while (left != 0 && UP == 3 && x[2] < x[UP]);
@@ -592,7 +623,8 @@ template <int STRAT, int N, int UP>
 void launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
   if (build) hipLaunchKernelGGL((k_pair_records<N, STRAT, UP>), dim3((a.n_pairs + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, st, a);
   const uint32_t blocks = (a.n_items + BLOCK / 64 - 1) / (BLOCK / 64);
-  hipLaunchKernelGGL((k_search_halves<N, STRAT, UP>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  if (a.bounded) hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  else hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
 }
 
 // build: the table of pairs is filled first.  1 = no instance for this shape (5 and 6 stages: three upper cuts would leave

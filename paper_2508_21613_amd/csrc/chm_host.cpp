@@ -549,6 +549,20 @@ bool side_join(chm_scenario *s, SideStreams *side, hipStream_t st) {
   return ok;
 }
 
+// Bounded search of a whole family by halves: its loops leave out what the cuts placed so far already make too slow.  us a search of the
+// 32-card shape (62.9, 62.9 and 10.7 M partitions): 111, exhaustive 180, with candidates counted on the host 183.  Up to this many partitions, for the wavefronts still set up all lower
+// halves; larger families are enumerated.
+constexpr uint64_t BOUNDED_HALVES = 1ull << 30;
+bool whole_family(const chm_scenario *s, const Job &j) {
+  return !j.ranks && !j.cuts && !j.costs && !j.cand && !j.seed && j.first == 0 && j.count == s->h.fam[j.strategy].n_part;
+}
+bool bounded_by_halves(const chm_scenario *s, const Job &j) {
+  return s->bounded == 1 && j.count <= BOUNDED_HALVES && whole_family(s, j) && fast_halves_covers(&s->fast, s->h, j.strategy, j.count);
+}
+// Partitions of all families up to which one launch searches them exhaustively in less time than seeds and bounds take, us exhaustive /
+// bounded: 1.2 M of 6 stages 49 / 78, 3.6 M of 8 stages at uneven speeds 104 / 110 and, few of which fit, 78 / 105; 9.7 M 239 / 187.
+constexpr uint64_t BOUNDED_FROM = 1ull << 22;
+
 // One search call in flight on a handle: what launch_jobs set up and collect_jobs needs.
 struct SearchCtx {
   std::vector<Job> jobs;                 // (copies: a batch keeps them across the launches of other handles)
@@ -689,7 +703,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
     const Job &j = jobs[ji];
     bool by_halves = together[ji] != 0;                // launched already
     if (by_halves) si += (size_t)((j.count + chunk - 1) / chunk);
-    if (!by_halves && want_result && !bounded && !j.seed && !j.cand && !j.ranks && !j.cuts && !j.costs && j.first == 0 && j.jump_at == 0xffffffffu) {
+    if (!by_halves && want_result && (!bounded || bounded_by_halves(s, j)) && !j.seed && !j.cand && !j.ranks && !j.cuts && !j.costs && j.first == 0 && j.jump_at == 0xffffffffu) {
       // a whole family, all its chunks in one launch
       SearchLaunch a;
       a.scn = s->d_scn; a.comp = s->d_comp; a.strategy = j.strategy;
@@ -699,7 +713,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
       a.slot_mask = c.ways - 1;
       a.slot_stride = c.stride;
       a.incumbent = d_incumbent;
-      const int rc = fast_halves_search(&s->fast, s->h, a, j.count, c.chunk_words, !s->no_alloc, st);
+      const int rc = fast_halves_search(&s->fast, s->h, a, j.count, c.chunk_words, !s->no_alloc, bounded, st);
       if (rc < 0) return CHM_ERR_HIP;
       by_halves = rc == 0;
       if (by_halves) si += (size_t)((j.count + chunk - 1) / chunk);
@@ -955,6 +969,7 @@ std::vector<Job> in_launch_order(const chm_scenario *s, const std::vector<Job> &
     if (j.ranks || j.cuts || j.costs || j.first != 0 || j.count != s->h.fam[j.strategy].n_part) return all;
   std::stable_sort(all.begin(), all.end(), [](const Job &a, const Job &b) { return a.count < b.count; });
   for (const Job &j : all) {
+    if (s->bounded && !bounded_by_halves(s, j)) continue;
     if (!fast_halves_covers(&s->fast, s->h, j.strategy, j.count)) continue;
     // seeds of the first such family, or, where one launch takes them (fast_search_families), of all families
     const uint64_t chunk = 1ull << s->idx_bits;
@@ -980,20 +995,40 @@ bool any_enumerable(const chm_scenario *s, const std::vector<Job> &given) {
   const uint64_t enumerate_from = s->bounded == 2 ? 1 : ENUMERATE_FROM;
   bool any = false;
   for (const Job &j : given)
-    any = any || (!j.ranks && !j.cuts && !j.costs && j.first == 0 && j.count == s->h.fam[j.strategy].n_part &&
-                  j.count >= enumerate_from && s->idx_bits >= 23);
+    any = any || (whole_family(s, j) && j.count >= enumerate_from && s->idx_bits >= 23 && !bounded_by_halves(s, j));
   return any;
+}
+
+// Jobs of a search that needs the host only at its end, in the order they are launched, and whether they are searched with bounds.
+std::vector<Job> single_pass(const chm_scenario *s, const std::vector<Job> &given, bool *bounded) {
+  *bounded = s->bounded != 0;
+  if (s->bounded == 0) return in_launch_order(s, given);
+  bool halves = false, whole = true;
+  uint64_t total = 0;
+  int least = DEV_MAX_S, most = 0;
+  for (const Job &j : given) {
+    halves = halves || bounded_by_halves(s, j);
+    whole = whole && whole_family(s, j);
+    total += j.count;
+    least = std::min(least, s->h.fam[j.strategy].stages);
+    most = std::max(most, s->h.fam[j.strategy].stages);
+  }
+  if (s->bounded == 1 && whole && given.size() > 1 && !s->timing && total <= BOUNDED_FROM && most - least <= 2 && most <= 24) *bounded = false;
+  if (halves || !*bounded) return in_launch_order(s, given);
+  std::vector<Job> all = make_seeds(s, given);
+  all.insert(all.end(), given.begin(), given.end());
+  return all;
 }
 
 int run_search(chm_scenario *s, const std::vector<Job> &given, chm_best *out, uint64_t *position, hipStream_t st) {
   if (!(s->bounded && out != nullptr)) return run_jobs(s, out ? in_launch_order(s, given) : given, out, position, st, ~0ull, false);
   const uint64_t enumerate_from = s->bounded == 2 ? 1 : ENUMERATE_FROM;
-  const std::vector<Job> seeds = make_seeds(s, given);
   if (!any_enumerable(s, given)) {
-    std::vector<Job> all(seeds);
-    all.insert(all.end(), given.begin(), given.end());
-    return run_jobs(s, all, out, position, st, ~0ull, true);
+    bool bounded = true;
+    const std::vector<Job> all = single_pass(s, given, &bounded);
+    return run_jobs(s, all, out, position, st, ~0ull, bounded);
   }
+  const std::vector<Job> seeds = make_seeds(s, given);
   chm_best seed_best;
   int seed_rc = CHM_ERR_NO_FEASIBLE;
   if (!seeds.empty()) {
@@ -1346,14 +1381,9 @@ extern "C" int chm_search_best_batch(chm_scenario *const *handles, int32_t n, ui
     // searches that need the host between two of their passes (a bounded search that enumerates candidates) run
     // on their own; all others are launched now and collected after one wait for the whole batch
     if (s->bounded && any_enumerable(s, jobs)) { codes[i] = run_search(s, jobs, &outs[i], nullptr, stream_of(i)); continue; }
-    if (s->bounded) {
-      std::vector<Job> all = make_seeds(s, jobs);
-      all.insert(all.end(), jobs.begin(), jobs.end());
-      jobs.swap(all);
-    } else {
-      jobs = in_launch_order(s, jobs);
-    }
-    codes[i] = launch_jobs(s, jobs, true, stream_of(i), ~0ull, s->bounded != 0, false);
+    bool bounded = false;
+    jobs = single_pass(s, jobs, &bounded);
+    codes[i] = launch_jobs(s, jobs, true, stream_of(i), ~0ull, bounded, false);
     if (codes[i] != CHM_OK) { nothing_found(&outs[i]); continue; }
     if (s->search->ctx.device_finish || s->search->ctx.empty) { pending[i] = 1; codes[i] = CHM_ERR_HIP; }
     else codes[i] = collect_jobs(s, &outs[i], nullptr, stream_of(i), false);
