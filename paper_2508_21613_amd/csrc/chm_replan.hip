@@ -26,11 +26,11 @@ struct AssignArgs {
   int32_t n;                                   // nodes = positions
   int32_t L;
   const int32_t *held;                         // [2n] device: layers [lo, hi) every node holds
-  const int32_t *pos;                          // [2n] device: layers [lo, hi) of every position
+  const int32_t *pos;                          // [layouts][2n] device: layers [lo, hi) of every position
   const int64_t *pw;                           // [L+1] device: prefix sums of per-layer memory
-  int64_t *total;                              // device: least total MiB
-  int32_t *position_of_node;                   // [n] device: one optimal assignment
-  int32_t *rounds;                             // device: layers of the largest position = rounds of gradient communication
+  int64_t *total;                              // [layouts][2] device: least total MiB; layers of the largest position (int32) =
+                                               // rounds of gradient communication
+  int32_t *position_of_node;                   // [layouts][n] device: one optimal assignment
 };
 
 // Minimum-cost one-to-one assignment (Kuhn-Munkres with potentials), one wavefront.  Rows (nodes)
@@ -39,7 +39,8 @@ struct AssignArgs {
 // 64 apart), the column with the least slack joins (wave minimum of slack << 10 | column, so ties
 // take the lowest column), potentials move by that slack, until a free column is reached; then the
 // matching is flipped along the path.  Cost[i][j] is never stored: it is the memory of position
-// j's layers minus what node i already holds of them, two prefix-sum reads.
+// j's layers minus what node i already holds of them, two prefix-sum reads.  A chain of dependent steps (31 nodes: 105 us), so
+// the layouts of a call go side by side, one workgroup each.
 __global__ void __launch_bounds__(64) k_min_assignment(AssignArgs a) {
   __shared__ int64_t pw[RP_MAX_L + 1];
   __shared__ int64_t u[RP_MAX_NODES + 1], v[RP_MAX_NODES + 1], slack[RP_MAX_NODES + 1];
@@ -48,11 +49,12 @@ __global__ void __launch_bounds__(64) k_min_assignment(AssignArgs a) {
   __shared__ uint8_t in_tree[RP_MAX_NODES + 1];
   __shared__ uint64_t pick;
   const int n = a.n, lane = threadIdx.x;
+  const int32_t *const pos = a.pos + (size_t)blockIdx.x * 2 * n;
   const int64_t BIG = INT64_MAX / 4;
   for (int i = lane; i <= a.L; i += 64) pw[i] = a.pw[i];
   for (int i = lane; i < n; i += 64) {
     h_lo[i] = a.held[2 * i]; h_hi[i] = a.held[2 * i + 1];
-    p_lo[i] = a.pos[2 * i]; p_hi[i] = a.pos[2 * i + 1];
+    p_lo[i] = pos[2 * i]; p_hi[i] = pos[2 * i + 1];
     u[i] = 0;
   }
   for (int c = lane; c <= n; c += 64) { v[c] = 0; row_of_col[c] = -1; }
@@ -108,7 +110,7 @@ __global__ void __launch_bounds__(64) k_min_assignment(AssignArgs a) {
     const int i = row_of_col[c];
     const int lo = p_lo[c] > h_lo[i] ? p_lo[c] : h_lo[i], hi = p_hi[c] < h_hi[i] ? p_hi[c] : h_hi[i];
     part += pw[p_hi[c]] - pw[p_lo[c]] - (hi > lo ? pw[hi] - pw[lo] : 0);
-    a.position_of_node[i] = c;
+    a.position_of_node[(size_t)blockIdx.x * n + i] = c;
   }
   // every position holds one contiguous range of layers, so the greedy colouring of the layer graph
   // (Restorer, "Asymmetric Communication") needs exactly as many rounds as the largest position has layers
@@ -119,13 +121,13 @@ __global__ void __launch_bounds__(64) k_min_assignment(AssignArgs a) {
     const int other = __shfl_xor(most, off, 64);
     most = other > most ? other : most;
   }
-  if (lane == 0) { *a.total = part; *a.rounds = most; }
+  if (lane == 0) { a.total[2 * blockIdx.x] = part; a.total[2 * blockIdx.x + 1] = most; }
 }
 
 struct Scratch {
   int32_t *d_held = nullptr, *d_pos = nullptr, *d_assign = nullptr;
-  int64_t *d_pw = nullptr, *d_total = nullptr; // d_total: [0] least total MiB, [1] rounds (int32 in its low half)
-  int64_t *h_total = nullptr;                  // pinned, two words
+  int64_t *d_pw = nullptr, *d_total = nullptr; // d_total: least total MiB and rounds per candidate
+  int64_t *h_total = nullptr;                  // pinned, the same
   hipStream_t stream = nullptr;                // the stream every kernel and copy that touches these blocks runs on
   ~Scratch() {
     (void)hipStreamSynchronize(stream);        // (an early return may leave work in flight)
@@ -228,11 +230,11 @@ int replan_core(const chm_replan_desc *d, chm_replan_plan *out, void *hip_stream
   sc.stream = st;
   if (N > 0) {
     bool ok = pool_take(sc.d_held, held.size() * sizeof(int32_t));
-    ok = ok && pool_take(sc.d_pos, held.size() * sizeof(int32_t));
-    ok = ok && pool_take(sc.d_assign, (size_t)N * sizeof(int32_t));
+    ok = ok && pool_take(sc.d_pos, CHM_MAX_DP * held.size() * sizeof(int32_t));          // (one candidate per number of pipelines)
+    ok = ok && pool_take(sc.d_assign, CHM_MAX_DP * (size_t)N * sizeof(int32_t));
     ok = ok && pool_take(sc.d_pw, pw.size() * sizeof(int64_t));
-    ok = ok && pool_take(sc.d_total, 2 * sizeof(int64_t));
-    ok = ok && pool_take_pinned(sc.h_total, 2 * sizeof(int64_t));
+    ok = ok && pool_take(sc.d_total, CHM_MAX_DP * 2 * sizeof(int64_t));
+    ok = ok && pool_take_pinned(sc.h_total, CHM_MAX_DP * 2 * sizeof(int64_t));
     ok = ok && hipMemcpyAsync(sc.d_held, held.data(), held.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) == hipSuccess;
     ok = ok && hipMemcpyAsync(sc.d_pw, pw.data(), pw.size() * sizeof(int64_t), hipMemcpyHostToDevice, st) == hipSuccess;
     ok = ok && hipStreamSynchronize(st) == hipSuccess;
@@ -247,6 +249,8 @@ int replan_core(const chm_replan_desc *d, chm_replan_plan *out, void *hip_stream
   bool have = false;
   __int128 best_gain = 0;
   int64_t best_step = 1;
+  std::vector<chm_replan_plan> cands;                                   // those that fit, in ascending dp
+  std::vector<int32_t> pos;                                             // their positions, one after the other
   for (int dp = d->dp_min; dp <= d->dp_max; ++dp) {
     if (dp > N) break;
     int len[CHM_MAX_DP], mb[CHM_MAX_DP];
@@ -304,30 +308,31 @@ int replan_core(const chm_replan_desc *d, chm_replan_plan *out, void *hip_stream
     }
     if (!fits) continue;
     // positions of the new layout, pipeline by pipeline, stage by stage
-    std::vector<int32_t> pos;
     for (int p = 0; p < dp; ++p)
       for (int j = 0; j < len[p]; ++j) {
         pos.push_back(j == 0 ? 0 : cand.cuts[p][j - 1]);
         pos.push_back(j == len[p] - 1 ? L : cand.cuts[p][j]);
       }
+    cands.push_back(cand);
+  }
+  if (!cands.empty()) {
+    // the transfer of every candidate, in one launch
     if (hipMemcpyAsync(sc.d_pos, pos.data(), pos.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess) return CHM_ERR_HIP;
     AssignArgs a;
     a.n = N; a.L = L; a.held = sc.d_held; a.pos = sc.d_pos; a.pw = sc.d_pw; a.total = sc.d_total; a.position_of_node = sc.d_assign;
-    a.rounds = (int32_t *)(sc.d_total + 1);
     if (hipEventRecord(ev.a, st) != hipSuccess) return CHM_ERR_HIP;
-    hipLaunchKernelGGL(k_min_assignment, dim3(1), dim3(64), 0, st, a);
+    hipLaunchKernelGGL(k_min_assignment, dim3((uint32_t)cands.size()), dim3(64), 0, st, a);
     if (hipGetLastError() != hipSuccess || hipEventRecord(ev.b, st) != hipSuccess) return CHM_ERR_HIP;
-    if (hipMemcpyAsync(sc.h_total, sc.d_total, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st) != hipSuccess) return CHM_ERR_HIP;
+    if (hipMemcpyAsync(sc.h_total, sc.d_total, cands.size() * 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st) != hipSuccess) return CHM_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) return CHM_ERR_HIP;     // also keeps `pos` alive until the copy is done
-    float ms = 0;
-    if (hipEventElapsedTime(&ms, ev.a, ev.b) != hipSuccess) return CHM_ERR_HIP;
-    assign_ms += ms;
-    cand.fetch_mib = sc.h_total[0];
+    if (hipEventElapsedTime(&assign_ms, ev.a, ev.b) != hipSuccess) return CHM_ERR_HIP;
+  }
+  for (size_t i = 0; i < cands.size(); ++i) {
+    chm_replan_plan &cand = cands[i];
+    cand.fetch_mib = sc.h_total[2 * i];
     if (d->allreduce_us > 0) {
-      int32_t rounds;
-      memcpy(&rounds, &sc.h_total[1], sizeof(rounds));
-      cand.comm_rounds = rounds;
-      cand.t_step_us += (int64_t)d->allreduce_us * rounds;
+      cand.comm_rounds = (int32_t)sc.h_total[2 * i + 1];
+      cand.t_step_us += (int64_t)d->allreduce_us * cand.comm_rounds;
     }
     cand.t_trans_us = (int64_t)d->restart_us + (int64_t)d->xfer_us_per_mib * cand.fetch_mib;
     // (H - t_trans) / t_step, larger is better; exact comparison by cross-multiplication
