@@ -317,9 +317,10 @@ HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
     if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return hs;
     steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
   }
-  // upper halves per wavefront: about 12,000 wavefronts (one and a half rounds of the resident ones), but enough steps to carry the
-  // lower half's set-up (62.9 M partitions of 8 stages, both cuts: 32, 64 or 128 steps within 3 %; 3 M of 7 stages 15, 21 us at 32, 64)
-  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 12288));
+  // upper halves per wavefront: so many that every resident wavefront gets about one item, but at least 32, which carry the lower
+  // half's set-up (steps / 12,288, 8,192, 6,144, 4,096: 32 cards 169, 167, 163, 167 us, plan cache of 64 sets 4,081, 4,043, 3,808, 3,825;
+  // 3 M partitions of 7 stages 15 and 21 us with 32 and 64)
+  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 6144));
   for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hs.chunk - 1) / hs.chunk);
   if (items >= (1ull << 31)) return hs;
   hs.up = up;
