@@ -969,9 +969,10 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   }
 }
 
-#define CHM_WAVES(SP, STRAT) __attribute__((amdgpu_waves_per_eu(SP <= (STRAT == 2 ? 8 : 5) ? 5 : SP <= 10 ? 4 : SP <= 16 ? 3 : SP <= 24 ? 4 : 3)))
+#define CHM_WAVES(SP, STRAT) __attribute__((amdgpu_waves_per_eu((SP) <= (STRAT == 2 ? 8 : 5) ? 5 : (SP) <= 10 ? 4 : (SP) <= 16 ? 3 : (SP) <= 24 ? 4 : 3)))
 template <int SP, int STRAT, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) CHM_WAVES(SP, STRAT) k_fast_search(FastLaunch a) {
+// (lists of 11 to 15 stages, strategy 1: 133 registers with the next entry ahead are asked into 128, four wavefronts per SIMD)
+__global__ void __launch_bounds__(BLOCK) CHM_WAVES((MODE == 3 && STRAT == 1 && SP > 10 && SP <= 15 ? 10 : SP), STRAT) k_fast_search(FastLaunch a) {
   __shared__ SearchShared<SP, MODE> sh;
   extern __shared__ int64_t cost_tile[];
   search_partitions<SP, STRAT, MODE>(a, blockIdx.x, sh, cost_tile);
