@@ -413,8 +413,8 @@ void fast_select(FastState *f, const DevScenario &h, bool int32_ok) {
     std::vector<int> order;
     for (int ci = 0; ci < fam.n_cls; ++ci) order.push_back(ci);
     ff.n_time = fam.n_cls;
-    // The class with the most work (micro-batches x factors of its nodes) goes first: a search times the others only where
-    // that one does not decide already.
+    // The class with the most work (micro-batches x factors of its nodes) goes first: a search by halves and a list of strategy 0
+    // time the others only where that one does not decide already.
     auto work = [&fam](int c) {
       uint64_t w = 0;
       for (int j = 0; j < fam.cls[c].n; ++j) w += fam.cls[c].q[j];

@@ -548,6 +548,20 @@ constexpr int FLOW_FROM = 16;
 // MODE 0: every lane evaluates its own partitions; 1: QUEUED; 2: QUEUED with the bounds of a bounded search (a
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
 // spilled bytes per lane at 8 stages and 4 % of its time).
+// Lists of more stages than this have their next entry on its way while one is worked on: a tile waits for memory otherwise,
+// which three or four wavefronts per SIMD do not hide (2^22 rows of 16 stages, strategy 2: 105 us without, 102 with it; strategy 0
+// 87 and 85).  With fewer stages more of them are resident, and the load, which waits for the cost stores ahead of it, costs more than
+// it saves (with a cost store: 7 stages, strategy 1, 65 us without, 69 with it; 5 stages, strategy 0, 67 and 69).
+constexpr int LIST_AHEAD_FROM = 10;
+// Lists of redundant computation, which has a class of pipelines for every node that is short: the rows come in no order, so that after
+// a few rounds next to none of 64 can win.  The class with the most work decides first, and the others and the weights to fetch are
+// worked out only where it leaves a cost not above the wavefront's lowest (2^22 rows: 8 stages 72 us without, 70 with it, 12 stages
+// 79 and 74, 16 stages 90 and 85).  From this many rounds of a workgroup on: with fewer there is nothing to compare with yet.  Nowhere
+// else: neighbouring ranks have neighbouring costs, so that some of 64 may nearly always win, and what is left out with one
+// class of pipelines costs less than the comparison (10 M ranks of 7 stages, strategy 1, 104 us with it, 90 without; of 8
+// stages, strategy 2, 134 and 120; lists of 2^22 rows of 4 stages 54 and 51).
+constexpr uint32_t NARROW_ROUNDS = 8;
+
 template <int SP, int MODE>
 struct SearchShared {
   static constexpr bool QUEUED = MODE >= 1;
@@ -567,6 +581,7 @@ template <int SP, int STRAT, int MODE>
 __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t block, SearchShared<SP, MODE> &sh, int64_t *cost_tile) {
   constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
+  constexpr bool AHEAD = LIST && SP > LIST_AHEAD_FROM, NARROWS = LIST && STRAT == 0;
   uint4 *const q_cuts = sh.q_cuts;
   uint32_t *const q_pos = sh.q_pos;
   int2 *const TC = sh.TC;
@@ -667,30 +682,30 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   ce[0] = 0;
   ce[SP] = L;
 
-  // A list's next entry is on its way while this one is worked on (a tile waits for memory otherwise, and three wavefronts per
-  // SIMD do not hide that at 16 stages: 3 x 2^24 rows 692 us without, 658 with it).
-  auto entry_of_list = [&](uint32_t it) -> uint4 {
+  auto row_of_list = [&](uint32_t entry, uint32_t (&w)[4]) {
+    const uint64_t at = (uint64_t)entry * K;
+    if (at + 16 <= (uint64_t)a.s.part_count * K) {
+      __builtin_memcpy(w, a.s.cuts + at, 16);                  // (unaligned; bytes behind the row are not looked at)
+    } else {
+      for (int i = 0; i < K; ++i) {
+        const uint32_t b = (uint32_t)a.s.cuts[at + i] << (8 * (i & 3));
+        w[0] |= i < 4 ? b : 0; w[1] |= (i >> 2) == 1 ? b : 0; w[2] |= (i >> 2) == 2 ? b : 0; w[3] |= (i >> 2) == 3 ? b : 0;
+      }
+    }
+  };
+  uint32_t ahead[4] = {0, 0, 0, 0};                // AHEAD: the next entry, its cuts or its rank
+  auto look_ahead = [&](uint32_t it) {
     const uint32_t entry = (block * a.per_lane + it) * BLOCK + threadIdx.x;
     const bool there = entry < a.s.part_count;
-    uint32_t w[4] = {0, 0, 0, 0};
+    ahead[0] = ahead[1] = ahead[2] = ahead[3] = 0;
     if (a.s.cuts != nullptr) {
-      const uint64_t at = (uint64_t)(there ? entry : 0) * K;
-      if (at + 16 <= (uint64_t)a.s.part_count * K) {
-        __builtin_memcpy(w, a.s.cuts + at, 16);                // (unaligned; bytes behind the row are not looked at)
-      } else {
-        for (int i = 0; i < K; ++i) {
-          const uint32_t b = (uint32_t)a.s.cuts[at + i] << (8 * (i & 3));
-          w[0] |= i < 4 ? b : 0; w[1] |= (i >> 2) == 1 ? b : 0; w[2] |= (i >> 2) == 2 ? b : 0; w[3] |= (i >> 2) == 3 ? b : 0;
-        }
-      }
+      row_of_list(there ? entry : 0, ahead);
     } else {
       const uint64_t r = there ? a.s.ranks[entry] : 0;
-      w[0] = (uint32_t)r; w[1] = (uint32_t)(r >> 32);
+      ahead[0] = (uint32_t)r; ahead[1] = (uint32_t)(r >> 32);
     }
-    return make_uint4(w[0], w[1], w[2], w[3]);
   };
-  uint4 ahead = make_uint4(0, 0, 0, 0);
-  if (LIST) ahead = entry_of_list(0);
+  if (AHEAD) look_ahead(0);
 
   for (uint32_t it = 0; it < (wave_dead || idle ? 0u : a.per_lane + (QUEUED ? 1u : 0u)); ++it) {
     bool live = it < run_len;             // this lane has a partition in this round
@@ -705,10 +720,13 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
           const uint32_t entry = (block * a.per_lane + it) * BLOCK + threadIdx.x;
           live = entry < a.s.part_count;
           pos = a.pos_base + entry;
-          const uint4 now = ahead;
-          if (it + 1 < a.per_lane) ahead = entry_of_list(it + 1);
+          const uint64_t ahead_rank = (uint64_t)ahead[0] | ((uint64_t)ahead[1] << 32);
+          if (AHEAD) {
+            for (int w = 0; w < 4; ++w) words[w] = ahead[w];
+            if (it + 1 < a.per_lane) look_ahead(it + 1);
+          }
           if (a.s.cuts != nullptr) {
-            words[0] = now.x; words[1] = now.y; words[2] = now.z; words[3] = now.w;
+            if (!AHEAD) row_of_list(live ? entry : 0, words);
             // a row that does not increase strictly within 1..L-1 does not fit; 1..K stands in for it
             int prev = 0;
 #pragma unroll
@@ -724,7 +742,8 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
 #pragma unroll
             for (int i = 1; i <= K; ++i) c[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
           } else {
-            uint64_t rem = live ? (uint64_t)now.x | ((uint64_t)now.y << 32) : 0;
+            for (int w = 0; w < 4 && AHEAD; ++w) words[w] = 0;
+            uint64_t rem = live ? (AHEAD ? ahead_rank : a.s.ranks[entry]) : 0;
             valid = rem < scn->fam[STRAT].n_part;
             if (!valid) rem = 0;
             unrank_digits<K, uint64_t>(rem, L, unrank_steps(L - K), BN, c);
@@ -806,17 +825,25 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
     if (!QUEUED) n_fit += (uint32_t)__popcll(ok_mask);
     if (ok_mask != 0) {
       int t_step = ff->fixed_step;
-      // A search looks no further at partitions whose time already exceeds the wave's lowest cost: their other classes,
-      // penalties and weights to fetch only add to it.  (A cost store needs every term.)
-      const bool every = a.s.costs_out != nullptr || (!QUEUED && STRAT == 2 && a.base_out != nullptr);
+      auto weights_to_fetch = [&]() -> int {
+        int wp[SP + 1];                     // memory prefix at the cuts
+        wp[0] = 0;
+#pragma unroll
+        for (int j = 1; j <= SP; ++j) wp[j] = PW[ce[j]];
+        return missing_weights<SP, STRAT>(ff, wp);
+      };
+      int missing = 0;
+      if (!NARROWS) missing = weights_to_fetch();
+      // (NARROWS) whether some partition of the wavefront may still win: what is not worked out yet only adds to its cost
+      const bool every = a.s.costs_out != nullptr || a.per_lane < NARROW_ROUNDS;
       auto may_win = [&]() -> bool {
         const uint64_t least = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT];
         return every || __builtin_amdgcn_ballot_w64(ok && least <= wave_low) != 0;
       };
+      bool open = true;
       // Times per pipeline class.  The stage sums are read from the LDS table again for every class: at 16 stages keeping them
       // for the next class costs a wave per SIMD (two pipelines of 16 stages alike or not, 168 registers and spills).
-      bool open = true;
-      for (int ci = 0; ci < ff->n_time && open; ++ci) {
+      for (int ci = 0; ci < ff->n_time && (!NARROWS || open); ++ci) {
         const ClsPtr cl = &ff->cls[ci];
         // (the compiler is not to know that these reads are the same for every class)
 #pragma unroll
@@ -856,9 +883,9 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
           time = pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24);
         }
         t_step = imax32(t_step, time);
-        open = may_win();
+        if (NARROWS) open = may_win();
       }
-      if (open) {
+      if (!NARROWS || open) {
         if (ff->allreduce > 0) {
           // rounds of gradient communication: largest stage on any device, or the ring colouring when nodes hold two stages
           int rounds;
@@ -893,29 +920,24 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
             }
           }
         }
-        if ((STRAT != 2 && ff->allreduce <= 0) || may_win()) {
-          int wp[SP + 1];                     // memory prefix at the cuts
-          wp[0] = 0;
-#pragma unroll
-          for (int j = 1; j <= SP; ++j) wp[j] = PW[ce[j]];
-          cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] +
-                 (uint64_t)scn->xfer * (uint32_t)missing_weights<SP, STRAT>(ff, wp);
-          // a lane meets the entries of a compacted list or of a ring in no particular order of position:
-          // there the lower position wins among equal costs; a run is walked in ascending order
-          const bool lower = (QUEUED || compact) ? (cost < best_cost || (cost == best_cost && pos < best_pos)) : cost < best_cost;
-          if (ok && lower) { best_cost = cost; best_pos = pos; }
-          if (!every) wave_low = umin64(wave_low, uniform64(wave_min(ok ? cost : ~0ull)));
-        }
+        if (NARROWS) missing = weights_to_fetch();
+        cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] + (uint64_t)scn->xfer * (uint32_t)missing;
+        // a lane meets the entries of a compacted list or of a ring in no particular order of position:
+        // there the lower position wins among equal costs; a run is walked in ascending order
+        const bool lower = (QUEUED || compact) ? (cost < best_cost || (cost == best_cost && pos < best_pos)) : cost < best_cost;
+        if (ok && lower) { best_cost = cost; best_pos = pos; }
+        if (NARROWS && !every && __builtin_amdgcn_ballot_w64(ok && cost < wave_low) != 0) wave_low = uniform64(wave_min(ok ? cost : ~0ull));
       }
       if (bounded) {
         // the round's lowest cost becomes known to every wave; what the others found is picked up in turn
         n_eval += (uint32_t)__popcll(ok_mask);
-        if (wave_low < incumbent) {
-          incumbent = wave_low;
-          if (lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)wave_low);
+        const uint64_t round_best = wave_min(ok ? cost : ~0ull);
+        if (round_best < incumbent) {
+          incumbent = round_best;
+          if (lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)round_best);
         }
         incumbent = umin64(incumbent, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        wave_low = umin64(wave_low, uniform64(incumbent));
+        if (NARROWS) wave_low = umin64(wave_low, uniform64(incumbent));
       }
       if (!QUEUED && STRAT == 2 && a.base_out != nullptr && ok) a.base_out[run_first + it] = cost;
     }
