@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
   uint64_t best_cost = ~0ull, best_rank = ~0ull;
   uint32_t n_fit = 0;
-  const uint64_t inc0 = __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t inc0 = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   if (item < a.n_items) {
     // the item's v: items are numbered v by v
     const uint64_t below_lo = __builtin_amdgcn_ballot_w64(a.items->first[lane] <= item);

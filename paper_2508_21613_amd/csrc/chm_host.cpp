@@ -713,6 +713,7 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
       a.slot_mask = c.ways - 1;
       a.slot_stride = c.stride;
       a.incumbent = d_incumbent;
+      a.incumbent0 = incumbent0;
       const int rc = fast_halves_search(&s->fast, s->h, a, j.count, c.chunk_words, !s->no_alloc, bounded, st);
       if (rc < 0) return CHM_ERR_HIP;
       by_halves = rc == 0;
