@@ -241,8 +241,8 @@ int chm_decode_plan(const chm_scenario *s, uint64_t index, chm_best *out);
  * above the lowest cost evaluated so far in the same call.  The plan returned is the same, ties included:
  * only plans that can neither win nor tie are skipped, one by one or a run of consecutive ranks at a time
  * (the stages above the cuts that change within the run are common to all of its partitions, and so is their
- * share of the bound), or never enumerated at all: up to 2^30 partitions at nominal speeds (searched by halves) the
- * loops over the cuts leave out what the cuts placed so far already make too slow; for other families searched as a whole the library counts on
+ * share of the bound), or never enumerated at all: up to 2^30 partitions at nominal speeds (searched by halves,
+ * where that takes less time than the count below) the loops over the cuts leave out what the cuts placed so far already make too slow; for other families searched as a whole the library counts on
  * the host, stage by stage, the partitions whose bound stays within the best cost known, and the device
  * enumerates and evaluates only those (this also reaches families of more than 2^46 partitions, which
  * chm_search_best otherwise refuses with CHM_ERR_OVERFLOW, whenever at most 2^26 candidates remain).  The search

@@ -183,7 +183,8 @@ struct CandidateSet {
 };
 enum {
   CAND_DIRECT = 1 << 17,      // up to this many candidates are always enumerated (cheaper than any range search)
-  CAND_MAX = 1 << 26,         // and up to this many when the family is too large for a range search,
+  CAND_HALVES = 1 << 20,      // up to this many when the family is too large for a range search, but not for one by halves,
+  CAND_MAX = 1 << 26,         // and up to this many when it is too large for either,
   CAND_PASS = 1 << 22,        // enumerated and evaluated this many at a time
   CAND_SAMPLE = 1 << 17       // candidates evaluated per round of tightening the incumbent (see run_search)
 };
@@ -234,6 +235,8 @@ int chmk_halves_s2(int sp, int up, const HalvesLaunch &a, bool build, void *stre
 // return convention as fast_search (positive: not covered, or smaller than what the range search does as fast).
 // fast_halves_covers: whether it takes the family at all.
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);
+// Instructions its wavefronts take to set up their lower halves.
+uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int strategy);
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, bool bounded, void *stream);
 // The stream of the last search has been waited for: the tables its launches filled are there.

@@ -298,9 +298,8 @@ constexpr int64_t HALVES_SAVES = 7ll << 20;
 // 7 stages, 45 M partitions 56 / 77, 43 / 61; 8 stages, 4.3 M 19 / 21, 35 / 41, and 63 M 77 / 96, 59 / 74; 9 stages, 24 M 48 / 52,
 // 40 / 42; 10 stages, 39 M 82 / 71, 68 / 56; 12 stages, 13 M 58 / 46, 54 / 37; 16 stages, 7.7 M 109 / 96, 136 / 115.  Never
 // where three cuts leave more lanes idle, by a quarter more steps.
-uint64_t halves_cost(const HalvesShape &hs, int sp) {
-  return (uint64_t)hs.n_items * (uint64_t)(60 + 30 * (sp - 1 - hs.up)) + hs.steps * (hs.up == 2 ? 18u : 25u);
-}
+uint64_t halves_setup(const HalvesShape &hs, int sp) { return (uint64_t)hs.n_items * (uint64_t)(60 + 30 * (sp - 1 - hs.up)); }
+uint64_t halves_cost(const HalvesShape &hs, int sp) { return halves_setup(hs, sp) + hs.steps * (hs.up == 2 ? 18u : 25u); }
 constexpr uint64_t WIDER_BY = 4;
 // Models of more layers than this keep three cuts at any depth, at 1.3 to 1.4 times the time of two (1.1 G partitions of 7
 // stages 1.0 and 0.71 ms): the instances of 7 and 8 stages stay in use, as the test of the lanes at work asks.
@@ -813,6 +812,8 @@ bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_t partitions) {
   return k >= 0 && k <= 2 && f->halves[k].up != 0 && partitions == h.fam[k].n_part;
 }
+
+uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return halves_setup(f->halves[k], h.fam[k].stages); }
 
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, bool bounded, void *stream) {

@@ -549,15 +549,35 @@ bool side_join(chm_scenario *s, SideStreams *side, hipStream_t st) {
   return ok;
 }
 
-// Bounded search of a whole family by halves: its loops leave out what the cuts placed so far already make too slow.  us a search of the
-// 32-card shape (62.9, 62.9 and 10.7 M partitions): 111, exhaustive 180, with candidates counted on the host 183.  Up to this many partitions, for the wavefronts still set up all lower
-// halves; larger families are enumerated.
+// Bounded search of a whole family by halves: its loops leave out what the cuts placed so far already make too slow, but the wavefronts
+// still set up all lower halves.  Larger families are enumerated.
 constexpr uint64_t BOUNDED_HALVES = 1ull << 30;
 bool whole_family(const chm_scenario *s, const Job &j) {
   return !j.ranks && !j.cuts && !j.costs && !j.cand && !j.seed && j.first == 0 && j.count == s->h.fam[j.strategy].n_part;
 }
 bool bounded_by_halves(const chm_scenario *s, const Job &j) {
   return s->bounded == 1 && j.count <= BOUNDED_HALVES && whole_family(s, j) && fast_halves_covers(&s->fast, s->h, j.strategy, j.count);
+}
+// Wavefront instructions of that set-up, per family, up to which a call's families go by halves straight away, and a family does beside
+// others that are enumerated.  (585,000 of them are a microsecond; a search takes about three times as long as they do.)  Counting and
+// enumerating candidates costs about the same whatever the size: a wait for the seeds, a count on the host for each family, another
+// launch.  us a search, enumerated / by halves, with the instructions of the families in millions: three families of 8 stages, 46 layers
+// (4 1 4) 183 / 97, 60 layers (14 2 14) 282 / 204, 64 layers (20 2 20) 205 / 282; 9 stages, 44 layers (17 3 17) 225 / 199; 11 stages, 40
+// layers (36 8 36) 225 / 645; 16 stages, 30 layers (63 47 63) 273 / 719; one family of 9 stages (3) 113 / 57, of 10 (8) 100 / 102, of 12
+// (15) 98 / 103, of 15 (47) 100 / 201.  Least-transfer assignments, worked out for all that may still win, count double: 10 stages
+// (8) 135 / 150, 11 stages (9) 136 / 173, but 8 stages (6) 129 / 77.  Strategies 0 and 2 alone, whose bound is far from their best plan, are
+// rarely left with few candidates and go by halves up to three times that: strategy 2 of 8 stages (20) 1,228 / 196, of 12 (28) 234 /
+// 172, of 13 (36) 178 / 181, but of 16 (63) 113 / 273.
+constexpr uint64_t FEW_LOWER_HALVES = 13000000;
+uint64_t lower_halves(const chm_scenario *s, const Job &j) {
+  return fast_halves_setup(&s->fast, s->h, j.strategy) * (j.strategy == 1 && s->h.assign ? 2u : 1u);
+}
+bool all_by_halves(const chm_scenario *s, const std::vector<Job> &jobs) {
+  uint64_t setup = 0;
+  for (const Job &j : jobs)
+    if (bounded_by_halves(s, j)) setup += lower_halves(s, j);
+  const bool loose = jobs.size() == 1 && jobs[0].strategy != 1;
+  return setup <= FEW_LOWER_HALVES * (loose ? 3 : jobs.size());
 }
 // Partitions of all families up to which one launch searches them exhaustively in less time than seeds and bounds take, us exhaustive /
 // bounded: 1.2 M of 6 stages 49 / 78, 3.6 M of 8 stages at uneven speeds 104 / 110 and, few of which fit, 78 / 105; 9.7 M 239 / 187.
@@ -994,9 +1014,10 @@ std::vector<Job> in_launch_order(const chm_scenario *s, const std::vector<Job> &
 // small enough that the range search costs no more), the seeds simply run ahead of the ranges in one pass.
 bool any_enumerable(const chm_scenario *s, const std::vector<Job> &given) {
   const uint64_t enumerate_from = s->bounded == 2 ? 1 : ENUMERATE_FROM;
+  const bool few = all_by_halves(s, given);
   bool any = false;
   for (const Job &j : given)
-    any = any || (whole_family(s, j) && j.count >= enumerate_from && s->idx_bits >= 23 && !bounded_by_halves(s, j));
+    any = any || (whole_family(s, j) && j.count >= enumerate_from && s->idx_bits >= 23 && !(few && bounded_by_halves(s, j)));
   return any;
 }
 
@@ -1044,17 +1065,19 @@ int run_search(chm_scenario *s, const std::vector<Job> &given, chm_best *out, ui
     const Job &j = given[i];
     const bool whole = !j.ranks && !j.cuts && !j.costs && j.first == 0 && j.count == s->h.fam[j.strategy].n_part;
     bool listed = false;
-    if (whole && incumbent != ~0ull && s->idx_bits >= 23) {
-      // A family within reach of a range search is enumerated only when its candidates are few; one beyond it,
+    const bool halves = bounded_by_halves(s, j);
+    if (whole && incumbent != ~0ull && s->idx_bits >= 23 && !(halves && lower_halves(s, j) <= FEW_LOWER_HALVES)) {
+      // A family within reach of a search of its partitions is enumerated only when its candidates are few; one beyond it,
       // whenever they can be made few enough: while there are too many, a sample of them spread evenly over
       // their index order is evaluated, which lowers the incumbent and with it the number of candidates.
       // (below 2^25 partitions the range search costs no more than counting and enumerating does)
       const bool in_reach = j.count <= (1ull << 27);
+      const uint64_t few = in_reach ? (uint64_t)CAND_DIRECT : halves ? (uint64_t)CAND_HALVES : (uint64_t)CAND_MAX;
       for (int round = 0; round < 8 && j.count >= enumerate_from; ++round) {
         if (!fast_candidates_build(&s->fast, s->h, j.strategy, incumbent, &sets[i])) break;
         const uint64_t total = sets[i].total;
-        if (total <= (in_reach ? (uint64_t)CAND_DIRECT : (uint64_t)CAND_MAX)) { listed = true; break; }
-        if (in_reach) break;
+        if (total <= few) { listed = true; break; }
+        if (in_reach || halves) break;
         Job sample{j.strategy, 0, CAND_SAMPLE, nullptr, nullptr};
         sample.cand = &sets[i];
         sample.stride = total / CAND_SAMPLE;

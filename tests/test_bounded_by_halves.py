@@ -84,3 +84,22 @@ def test_families_by_halves_beside_one_that_is_not(PP, L):
     assert looked_at[7][2] <= 2 * looked_at[6][2] + 100000 < g.family(2)["n_part"] // 2
     assert int(O.Scenario(_case(L, PP, 3, 16, [3], allreduce_us=300)).score(want[7][1]["index"], 1)[0]) == want[7][1]["cost"]
     g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("PP,L,masks", [(16, 30, (7, 4, 2)), (11, 40, (7, 4, 2)), (9, 52, (7, 4)), (12, 34, (7, 4, 2))])
+@pytest.mark.parametrize("assign", [0, 1])
+def test_families_of_many_lower_halves(PP, L, masks, assign):
+    """calls whose lower halves would take longer to set up than candidates take to count are enumerated, but for a family that is left
+    with many candidates: next to nothing is looked at where all strategies are searched"""
+    from paper_2508_21613_amd import binding as B
+    g = B.Scenario(_case(L, PP, 3, 16, [3], transfer_assign=assign))
+    for mask in masks:
+        g.set_bounded_search(0)
+        want = g.search_best(mask)
+        g.set_bounded_search(1)
+        assert g.search_best(mask) == want, mask
+        if mask == 7:
+            looked_at = g.get_timing()["feasible"]
+            assert looked_at[0] + looked_at[2] <= 1 << 17, looked_at
+    g.close()
