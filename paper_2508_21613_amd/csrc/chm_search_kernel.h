@@ -577,11 +577,15 @@ struct SearchShared {
 
 // One workgroup (`block` of the family's) of a search.  cost_tile: BLOCK * per_lane costs when a cost store with per_lane > 1 is
 // asked for.
-template <int SP, int STRAT, int MODE>
+// FLOW: times by class_time.
+template <int SP, int STRAT, int MODE, bool FLOW = (SP > FLOW_FROM)>
 __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t block, SearchShared<SP, MODE> &sh, int64_t *cost_tile) {
   constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
   constexpr int K = SP - 1;
   constexpr bool AHEAD = LIST && SP > LIST_AHEAD_FROM, NARROWS = LIST && STRAT == 0;
+  constexpr bool FETCH_LATE = NARROWS || AHEAD || FLOW;   // weights to fetch after the times, which need the registers first
+  // cost store of plan indices: costs without penalties and the peers' stage times, for the kernel that expands them
+  const bool expands = (!QUEUED && STRAT == 2 && a.base_out != nullptr);
   uint4 *const q_cuts = sh.q_cuts;
   uint32_t *const q_pos = sh.q_pos;
   int2 *const TC = sh.TC;
@@ -833,7 +837,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
         return missing_weights<SP, STRAT>(ff, wp);
       };
       int missing = 0;
-      if (!NARROWS) missing = weights_to_fetch();
+      if (!FETCH_LATE) missing = weights_to_fetch();
       // (NARROWS) whether some partition of the wavefront may still win: what is not worked out yet only adds to its cost
       const bool every = a.s.costs_out != nullptr || a.per_lane < NARROW_ROUNDS;
       auto may_win = [&]() -> bool {
@@ -849,7 +853,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
 #pragma unroll
         for (int j = 1; j <= K; ++j) asm volatile("" : "+v"(ce[j]));
         int time;
-        if constexpr (SP > FLOW_FROM) {
+        if constexpr (FLOW) {
           auto at = [&](int i) -> int2 { return i == 0 ? make_int2(0, 0) : TC[ce[i]]; };
           time = ff->time24 ? class_time<SP, STRAT, true>(cl, at) : class_time<SP, STRAT, false>(cl, at);
         } else {
@@ -898,15 +902,14 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
           }
           t_step += ff->allreduce * rounds;
         }
-        if (STRAT == 2 && (QUEUED || a.base_out == nullptr)) {
+        if (STRAT == 2 && !expands) {
           // least penalty over the reroute vectors of every stage that lost nodes
           for (int st = 0; st < scn->n_aff; ++st) {
             const int2 t = stage_times<SP>(TC, ce, scn->aff_stage[st]);
             t_step += (int)stage_penalty<SP>(scn, tab, st, t.x, t.y - t.x);
           }
         }
-        if (!QUEUED && STRAT == 2 && a.base_out != nullptr) {
-          // cost store of plan indices: hand the peer stage times of this partition to the expanding kernel
+        if (expands) {
           if (ok) {
             uint4 *wout = (uint4 *)(a.weights_out + (size_t)(run_first + it) * (scn->n_aff * ROWS_MAX_P));
             for (int st = 0; st < scn->n_aff; ++st) {
@@ -920,7 +923,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
             }
           }
         }
-        if (NARROWS) missing = weights_to_fetch();
+        if (FETCH_LATE) missing = weights_to_fetch();
         cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] + (uint64_t)scn->xfer * (uint32_t)missing;
         // a lane meets the entries of a compacted list or of a ring in no particular order of position:
         // there the lower position wins among equal costs; a run is walked in ascending order
@@ -939,9 +942,9 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
         incumbent = umin64(incumbent, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         if (NARROWS) wave_low = umin64(wave_low, uniform64(incumbent));
       }
-      if (!QUEUED && STRAT == 2 && a.base_out != nullptr && ok) a.base_out[run_first + it] = cost;
+      if (expands && ok) a.base_out[run_first + it] = cost;
     }
-    if (!QUEUED && STRAT == 2 && a.base_out != nullptr && !ok && it < run_len) a.base_out[run_first + it] = ~0ull;
+    if (expands && !ok && it < run_len) a.base_out[run_first + it] = ~0ull;
     if (LIST && a.s.costs_out != nullptr && live) a.s.costs_out[pos] = (int64_t)cost;
     if (!QUEUED && a.s.costs_out != nullptr) {
       // per_lane == 1: the store is coalesced as it is; longer runs go through an LDS tile
@@ -971,7 +974,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   }
   uint64_t key = best_cost == ~0ull ? CHM_KEY_NONE
                                     : ((best_cost << a.s.idx_bits) | (uint64_t)best_pos);
-  if (!QUEUED && STRAT == 2 && a.base_out != nullptr) key = CHM_KEY_NONE;   // the combine kernel takes the argmin
+  if (expands) key = CHM_KEY_NONE;   // the combine kernel takes the argmin
   key = wave_min(key);
   if (lane == 0) { wave_keys[wave] = key; wave_fit[wave] = n_fit; wave_eval[wave] = n_eval; }
   __syncthreads();
@@ -991,10 +994,12 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   }
 }
 
+// Lists ask for four wavefronts per SIMD as deep as that needs no spills (2^22 rows of 15 stages, strategy 1: 80 us with 133 registers and
+// three, 75 with 128; of 14 stages, strategy 0: 85 and 77).
+constexpr int list_four_waves(int strategy) { return strategy == 0 ? 14 : 15; }
 #define CHM_WAVES(SP, STRAT) __attribute__((amdgpu_waves_per_eu((SP) <= (STRAT == 2 ? 8 : 5) ? 5 : (SP) <= 10 ? 4 : (SP) <= 16 ? 3 : (SP) <= 24 ? 4 : 3)))
 template <int SP, int STRAT, int MODE = 0>
-// (lists of 11 to 15 stages, strategy 1: 133 registers with the next entry ahead are asked into 128, four wavefronts per SIMD)
-__global__ void __launch_bounds__(BLOCK) CHM_WAVES((MODE == 3 && STRAT == 1 && SP > 10 && SP <= 15 ? 10 : SP), STRAT) k_fast_search(FastLaunch a) {
+__global__ void __launch_bounds__(BLOCK) CHM_WAVES((MODE == 3 && SP > 10 && SP <= list_four_waves(STRAT) ? 10 : SP), STRAT) k_fast_search(FastLaunch a) {
   __shared__ SearchShared<SP, MODE> sh;
   extern __shared__ int64_t cost_tile[];
   search_partitions<SP, STRAT, MODE>(a, blockIdx.x, sh, cost_tile);
@@ -1011,7 +1016,7 @@ __global__ void __launch_bounds__(BLOCK) CHM_WAVES(SP, 2) k_search_families(Fami
   const uint32_t b = blockIdx.x;
   if (b < a.blocks[2]) search_partitions<SP, 2, 0>(a.family[2], b, sh, nullptr);
   else if (b < a.blocks[2] + a.blocks[0]) search_partitions<SP, 0, 0>(a.family[0], b - a.blocks[2], sh, nullptr);
-  else search_partitions<S1, 1, 0>(a.family[1], b - a.blocks[2] - a.blocks[0], *(SearchShared<S1, 0> *)&sh, nullptr);
+  else search_partitions<S1, 1, 0, (SP > FLOW_FROM)>(a.family[1], b - a.blocks[2] - a.blocks[0], *(SearchShared<S1, 0> *)&sh, nullptr);
 }
 
 // Which variant of the search kernel: every lane its own partitions; the partitions that fit (and, in a bounded search, may
