@@ -929,6 +929,7 @@ int fast_score_reroute(FastState *f, const DevScenario &h, const DevScenario *d_
       w.count = (uint32_t)std::min<uint64_t>(count - done, (1ull << 31) - (1ull << 20));
       w.costs = d_costs + done;
       w.tile = window_tile((uint32_t)R, w.count);
+      w.in_place = row_bytes > WINDOW_BEHIND ? 1 : 0;
       const int rc = chmk_window_plans(h.fam[2].stages, w, (uint32_t)row_bytes, stream);
       if (rc) return rc;
       if (hipGetLastError() != hipSuccess) return -1;

@@ -547,7 +547,8 @@ constexpr int FLOW_FROM = 16;
 // written and read by one wave only, whose LDS operations complete in order: no barrier is needed.
 // MODE 0: every lane evaluates its own partitions; 1: QUEUED; 2: QUEUED with the bounds of a bounded search (a
 // variant of its own: the bounds cost the plain queued kernel registers it does not have, 36 instead of 16
-// spilled bytes per lane at 8 stages and 4 % of its time).
+// spilled bytes per lane at 8 stages and 4 % of its time); 3: QUEUED, fed from a list; 4: the partitions of a window of plan indices, for
+// the workgroup that calls it (k_window_plans), without an argmin.
 // Lists of more stages than this have their next entry on its way while one is worked on: a tile waits for memory otherwise,
 // which three or four wavefronts per SIMD do not hide (2^22 rows of 16 stages, strategy 2: 105 us without, 102 with it; strategy 0
 // 87 and 85).  With fewer stages more of them are resident, and the load, which waits for the cost stores ahead of it, costs more than
@@ -564,7 +565,7 @@ constexpr uint32_t NARROW_ROUNDS = 8;
 
 template <int SP, int MODE>
 struct SearchShared {
-  static constexpr bool QUEUED = MODE >= 1;
+  static constexpr bool QUEUED = MODE >= 1 && MODE <= 3;
   uint4 q_cuts[QUEUED ? (BLOCK / 64) * QCAP : 1];
   uint64_t BN[(SP > 1 ? SP - 1 : 1) * DEV_MAX_L];       // BN[(i-1)*128 + x] = C(x, i), i = 1..K
   // prefix sums: forward and forward + backward; static memory; activation memory
@@ -580,12 +581,12 @@ struct SearchShared {
 // FLOW: times by class_time.
 template <int SP, int STRAT, int MODE, bool FLOW = (SP > FLOW_FROM)>
 __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t block, SearchShared<SP, MODE> &sh, int64_t *cost_tile) {
-  constexpr bool QUEUED = MODE >= 1, LIST = MODE == 3;
+  constexpr bool QUEUED = MODE >= 1 && MODE <= 3, LIST = MODE == 3, WINDOW = MODE == 4;
   constexpr int K = SP - 1;
   constexpr bool AHEAD = LIST && SP > LIST_AHEAD_FROM, NARROWS = LIST && STRAT == 0;
   constexpr bool FETCH_LATE = NARROWS || AHEAD || FLOW;   // weights to fetch after the times, which need the registers first
   // cost store of plan indices: costs without penalties and the peers' stage times, for the kernel that expands them
-  const bool expands = (!QUEUED && STRAT == 2 && a.base_out != nullptr);
+  const bool expands = WINDOW || (!QUEUED && STRAT == 2 && a.base_out != nullptr);
   uint4 *const q_cuts = sh.q_cuts;
   uint32_t *const q_pos = sh.q_pos;
   int2 *const TC = sh.TC;
@@ -596,7 +597,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
   const int L = scn->L;
-  const bool compact = !QUEUED && a.cut_list != nullptr;
+  const bool compact = !QUEUED && !WINDOW && a.cut_list != nullptr;
   const uint32_t n_slots = compact ? a.cut_count[block] : 0u;       // filled slots of this workgroup's region
   if (compact && n_slots == 0) return;
   for (int i = threadIdx.x; i <= L; i += BLOCK) {
@@ -619,7 +620,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
   c[0] = 0;
   c[SP] = L;
   // (a wavefront without partitions has nothing to unrank: most of a window's tile)
-  const bool idle = !compact && !LIST && !QUEUED && __builtin_amdgcn_ballot_w64(run_len != 0) == 0;
+  const bool idle = WINDOW && __builtin_amdgcn_ballot_w64(run_len != 0) == 0;
   if (!compact && !LIST && !idle) {
     uint64_t rem = run_len ? a.s.part_first + run_first + (run_first >= a.s.jump_at ? a.s.jump_by : 0) : 0;   // idle lanes walk from rank 0: always valid cuts
     // combinadic digits from the LDS copy of the binomial table
@@ -946,7 +947,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
     }
     if (expands && !ok && it < run_len) a.base_out[run_first + it] = ~0ull;
     if (LIST && a.s.costs_out != nullptr && live) a.s.costs_out[pos] = (int64_t)cost;
-    if (!QUEUED && a.s.costs_out != nullptr) {
+    if (!QUEUED && !WINDOW && a.s.costs_out != nullptr) {
       // per_lane == 1: the store is coalesced as it is; longer runs go through an LDS tile
       // (laid out in output order) and are written out together after the loop
       const int64_t v = ok ? (int64_t)cost : CHM_INF_COST;
@@ -965,13 +966,14 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
     }
   }
 
-  if (!QUEUED && a.s.costs_out != nullptr && a.per_lane > 1 && !compact) {
+  if (!QUEUED && !WINDOW && a.s.costs_out != nullptr && a.per_lane > 1 && !compact) {
     __syncthreads();
     const uint64_t block_first = (uint64_t)block * BLOCK * a.per_lane;
     const uint32_t n_tile = BLOCK * a.per_lane;
     for (uint32_t i = threadIdx.x; i < n_tile; i += BLOCK)
       if (block_first + i < a.s.part_count) a.s.costs_out[block_first + i] = cost_tile[i];
   }
+  if (WINDOW) return;
   uint64_t key = best_cost == ~0ull ? CHM_KEY_NONE
                                     : ((best_cost << a.s.idx_bits) | (uint64_t)best_pos);
   if (expands) key = CHM_KEY_NONE;   // the combine kernel takes the argmin
@@ -985,7 +987,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
     uint32_t fit = wave_fit[0], evaluated = wave_eval[0];
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; evaluated += wave_eval[i]; }
-    if (fit && a.s.feasible != nullptr) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
+    if (fit) atomicAdd((unsigned long long *)a.s.feasible + slot, (unsigned long long)fit);
     if (MODE == 2 && bounded && evaluated) atomicAdd((unsigned long long *)a.s.evaluated + slot, (unsigned long long)evaluated);
     // a search over a list of candidates of a bounded search makes its best cost known to what follows
     if (!QUEUED && a.s.incumbent != nullptr && k != CHM_KEY_NONE)

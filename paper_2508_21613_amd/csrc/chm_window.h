@@ -4,6 +4,8 @@
 #define CHM_WINDOW_H
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "chm_fast.h"
 
 namespace {
@@ -59,18 +61,31 @@ struct WindowArgs {
   const uint32_t *rows;         // rank-ordered vectors, `stride` (4 or 8) entries each
   uint64_t part_first;          // partition and reroute rank of the first plan index
   uint32_t first_rr, count, tile, stride;
+  uint32_t in_place;            // 1: the vectors take the room of what the partitions took
   FastDiv R;                    // vectors
   uint32_t step_parts, step_rr; // 2 * BLOCK plan indices on: whole partitions, and vectors
   uint64_t K;
   int64_t *costs;
 };
-// Plan indices per workgroup, a multiple of BLOCK * EXPAND_PER.  Partitions that a tile begins or ends in are worked out twice, and
-// their lanes are one per partition: four times the least where 64 vectors and more leave a wavefront and a half of partitions
-// (153 vectors, 2^26 plans: 212 us with the least, 137 with twice, 111 with four times that, 116 with 16 times), the least where a launch would have fewer workgroups than compute units.
-enum { WINDOW_LEAST_R = 16 };
+// WINDOW_LEAST_R: fewer vectors have more partitions in the smallest tile than lanes.  WINDOW_BEHIND: larger tables, bytes, take the room of
+// what the partitions took (and are staged after them): three or four workgroups fit a compute unit then instead of two, and at most
+// 53 KB are asked for.
+enum { WINDOW_LEAST_R = 16, WINDOW_BEHIND = 8 << 10 };
+// Plan indices per workgroup, a multiple of 2 * BLOCK.  The partitions a tile touches are worked out ahead of its stores, one per lane,
+// those it begins or ends in twice; the least, 2,048, only where a launch would have fewer workgroups than compute units otherwise.
+// - Fewer than 64 vectors: as many plan indices as have a lane for every partition, up to four times the least (us with the least / so:
+//   36 vectors, 16 M plans of 8 stages 73 / 49, of 24 stages 145 / 67; 16 vectors, of 28 stages 166 / 114).
+// - From 64 on four times the least (153 vectors, 2^26 plans of 8 stages: 212 with the least, 137 with twice, 111 with four times that,
+//   116 with 16 times), and where a launch has more than three workgroups a compute unit then, as many as fill one wavefront with
+//   partitions: it works out 64 of them in the time of five (1,891 vectors, 16 M plans of 24 stages 98 / 57, of 8 stages 57 / 50).
 static inline uint32_t window_tile(uint32_t R, uint32_t count) {
   const uint32_t least = BLOCK * EXPAND_PER;
-  return R >= 64 && count >= 256u * 4 * least ? 4 * least : least;
+  if (R < 64) {
+    const uint32_t tile = std::min(4 * least, (BLOCK - 1) * R / (2 * BLOCK) * (2 * BLOCK));
+    return count >= 256u * tile ? tile : least;
+  }
+  const uint32_t times = count >= 256u * 4 * least ? 4 : 1;
+  return std::max(times, std::min(64u * R / least, (count + 768u * least - 1) / (768u * least))) * least;
 }
 static_assert((BLOCK * EXPAND_PER + WINDOW_LEAST_R - 1) / WINDOW_LEAST_R + 1 <= BLOCK && (4 * BLOCK * EXPAND_PER + 63) / 64 + 1 <= BLOCK,
               "a lane for every partition of a tile");
