@@ -63,6 +63,8 @@ struct FastTables {
   uint32_t lb_mult[DEV_MAX_AFF], lb_q[DEV_MAX_AFF];
 };
 
+// Widths of the upper half that some model length takes (halves_cost, chm_fast.hip): two cuts up to 11 stages, three from 9 on.
+enum { HALVES_TWO_UP_TO = 11, HALVES_THREE_FROM = 9 };
 // How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
 struct HalvesShape {
   int up = 0;                   // cuts of an upper half

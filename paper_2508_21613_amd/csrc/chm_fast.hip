@@ -296,14 +296,11 @@ constexpr int64_t HALVES_SAVES = 7ll << 20;
 // theirs costs more (25 instead of 18) and their lower halves, a cut shorter, may be few: the 64 lanes of a wavefront share the
 // last lower cut.  Deep pipelines, whose upper halves are few for every v, take three.  us, two cuts / three, strategies 0 and 2:
 // 7 stages, 45 M partitions 56 / 77, 43 / 61; 8 stages, 4.3 M 19 / 21, 35 / 41, and 63 M 77 / 96, 59 / 74; 9 stages, 24 M 48 / 52,
-// 40 / 42; 10 stages, 39 M 82 / 71, 68 / 56; 12 stages, 13 M 58 / 46, 54 / 37; 16 stages, 7.7 M 109 / 96, 136 / 115.  Never
-// where three cuts leave more lanes idle, by a quarter more steps.
+// 40 / 42; 10 stages, 39 M 82 / 71, 68 / 56; 12 stages, 13 M 58 / 46, 54 / 37; 16 stages, 7.7 M 109 / 96, 136 / 115; 7 stages, 3.6 G
+// 2,165 / 2,821, 1,693 / 2,164.  Never where three cuts leave more lanes idle, by a quarter more steps.
 uint64_t halves_setup(const HalvesShape &hs, int sp) { return (uint64_t)hs.n_items * (uint64_t)(60 + 30 * (sp - 1 - hs.up)); }
 uint64_t halves_cost(const HalvesShape &hs, int sp) { return halves_setup(hs, sp) + hs.steps * (hs.up == 2 ? 18u : 25u); }
 constexpr uint64_t WIDER_BY = 4;
-// Models of more layers than this keep three cuts at any depth, at 1.3 to 1.4 times the time of two (1.1 G partitions of 7
-// stages 1.0 and 0.71 ms): the instances of 7 and 8 stages stay in use, as the test of the lanes at work asks.
-constexpr int WIDE_LAYERS = 120;
 
 // wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts; steps = 0: not
 // within the kernel's 32-bit ranks of lower halves
@@ -339,13 +336,10 @@ HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
   if (k != 0 && ff.n_time > 1) return none;
   for (int s = 0; k == 2 && s < h.n_aff; ++s)
     if (t->even_share[s] == 0) return none;
-  const HalvesShape two = halves_of_width(h, sp, 2);
-  HalvesShape taken = two;
-  if (sp >= 7) {                          // (5 and 6 stages: never worth it, and no instance)
-    const HalvesShape three = halves_of_width(h, sp, 3);
-    const bool wide = h.L > WIDE_LAYERS || halves_cost(three, sp) < halves_cost(two, sp);
-    if (three.up != 0 && (two.up == 0 || (wide && three.steps <= two.steps + two.steps / WIDER_BY))) taken = three;
-  }
+  const HalvesShape two = sp <= HALVES_TWO_UP_TO ? halves_of_width(h, sp, 2) : none;
+  const HalvesShape three = sp >= HALVES_THREE_FROM ? halves_of_width(h, sp, 3) : none;
+  const bool wide = two.up == 0 || (halves_cost(three, sp) < halves_cost(two, sp) && three.steps <= two.steps + two.steps / WIDER_BY);
+  const HalvesShape taken = three.up != 0 && wide ? three : two;
   if (taken.up == 0) return none;
   const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
   return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)std::min(ff.n_time, 2) + (unsigned)HALVES_SAVES ? taken : none;

@@ -627,14 +627,13 @@ void launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
   else hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
 }
 
-// build: the table of pairs is filled first.  1 = no instance for this shape (5 and 6 stages: three upper cuts would leave
-// lower halves of one or two cuts, too few for 64 lanes).
+// build: the table of pairs is filled first.  1 = no instance for this shape.
 template <int STRAT>
 int halves_by_stages(int sp, int up, const HalvesLaunch &a, bool build, hipStream_t st) {
-#define CHM_CASE(SPV)                                                                   \
-  case SPV:                                                                             \
-    if (up == 2) { launch_halves<STRAT, SPV, 2>(a, build, st); return 0; }              \
-    if constexpr (SPV >= 7) { if (up == 3) { launch_halves<STRAT, SPV, 3>(a, build, st); return 0; } } \
+#define CHM_CASE(SPV)                                                                                                        \
+  case SPV:                                                                                                                  \
+    if constexpr (SPV <= HALVES_TWO_UP_TO) { if (up == 2) { launch_halves<STRAT, SPV, 2>(a, build, st); return 0; } }        \
+    if constexpr (SPV >= HALVES_THREE_FROM) { if (up == 3) { launch_halves<STRAT, SPV, 3>(a, build, st); return 0; } }       \
     return 1;
   switch (sp) {
 #ifdef CHM_TUNING_SUBSET

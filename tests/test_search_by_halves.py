@@ -64,7 +64,8 @@ def test_lanes_are_at_work_in_every_family_searched_by_halves():
                 by_width = {w: sum(-(-comb(v - 1, stages - 2 - w) // 64) * comb(L - 1 - v, w) for v in range(stages - 1 - w, L - w)) for w in (2, 3)}
                 assert steps == by_width[up] and 4 * steps <= 5 * by_width[2], (L, stages, k)
                 assert n / (64 * steps) > (0.3 if stages == 5 else 0.55), (L, stages, k)
-    assert {(5, 0), (5, 2), (6, 2), (7, 2), (7, 3), (8, 3), (16, 3)} <= widths
+    assert {(5, 0), (5, 2), (6, 2), (7, 2), (8, 2), (9, 2), (9, 3), (10, 2), (10, 3), (11, 3), (12, 3), (16, 3)} <= widths
+    assert all(stages >= 9 if up == 3 else stages <= 11 for stages, up in widths if up)
     assert B.halves_selection(_large(90, 5, 3, 8, [3]), 0)[0] == B.halves_selection(_large(87, 5, 3, 8, [3]), 2)[0] == 0
     assert B.halves_selection(_large(54, 6, 3, 8, [3]), 0)[0] == B.halves_selection(_large(60, 7, 3, 8, [3]), 2)[0] == 2
     assert B.halves_selection(dict(_large(48, 8, 3, 8, [3]), speed_q16=np.full(24, 65537, np.uint32)), 2)[0] == 0
