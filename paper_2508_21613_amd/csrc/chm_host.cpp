@@ -581,6 +581,9 @@ bool all_by_halves(const chm_scenario *s, const std::vector<Job> &jobs) {
 }
 // Partitions of all families up to which one launch searches them exhaustively in less time than seeds and bounds take, us exhaustive /
 // bounded: 1.2 M of 6 stages 49 / 78, 3.6 M of 8 stages at uneven speeds 104 / 110 and, few of which fit, 78 / 105; 9.7 M 239 / 187.
+// Whatever a partition costs, since bounds and seeds grow with it: 1.5 M of 16 stages 78 / 148, with eight uneven classes 143 / 211, nine
+// peers 87 / 170, every option 144 / 191; 1.4 M of 24 stages 124 / 245, 235 / 391, 122 / 256, 303 / 449; 2.4 M of 10 stages 63 / 108, 140 /
+// 162, 72 / 121, 102 / 132 (65 shapes of 4 to 24 stages, none slower).
 constexpr uint64_t BOUNDED_FROM = 1ull << 22;
 
 // One search call in flight on a handle: what launch_jobs set up and collect_jobs needs.
