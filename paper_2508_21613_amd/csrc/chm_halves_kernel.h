@@ -25,6 +25,7 @@ namespace {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+typedef u32x16 record_pair __attribute__((aligned(32)));       // two neighbouring records: 32 bytes each, a scalar load of 64
 
 // least reroute penalty of a stage all of whose peers have one speed (stage_penalty; nothing else comes here)
 __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
@@ -369,12 +370,12 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
     auto walk = [&](int row, int m, int y, uint32_t n, int c2, int own_z) {
       // (y > m > 2: there are records ahead of (row, y))
       RowPtr at = pairs + (size_t)(uint32_t)(row * (L + 1) + y - 1) * PAIR_WORDS;
-      u32x16 next = *(const CHM_CONST u32x16 *)at;
+      u32x16 next = *(const CHM_CONST record_pair *)at;
       for (;;) {
         const u32x16 r = next;
         constexpr int A = PAIR_WORDS, B = 0;           // words of y's record and of y - 1's
         at -= 2 * PAIR_WORDS;
-        next = *(const CHM_CONST u32x16 *)at;
+        next = *(const CHM_CONST record_pair *)at;
         const bool two = n >= 2;
         // the longest class's time less what is common to the level (off)
         auto time_of = [&](int o) -> int {
