@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
         if (rounds > 0) step += imax32(rounds_low, pair_rounds);
       } else {
         for (int ci = 1; ci < ff->n_time; ++ci)
-          step = imax32(step, class_time<N, STRAT, true>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
+          step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
       }
       const bool near_best = ((mask >> lane) & 1u) && step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;

@@ -138,7 +138,8 @@ constexpr int TERM_NEVER = -(1 << 30);   // a term of a maximum that does not ex
 // i).  The maximum of pipeline_time, read the other way round: a pair of stages (s, s') at which the two ends turn goes with
 // the best own term of a stage not above either.  Four running maxima take the place of the arrays (16 instructions a stage
 // instead of 13, but no registers that grow with the stages).
-template <int N, int STRAT, bool M24, typename At>
+// EVEN: all nodes of the class have speed 1.
+template <int N, int STRAT, bool M24, bool EVEN, typename At>
 __device__ __forceinline__ int class_time(ClsPtr cl, At at) {
   const int M = cl->M;
   int none = TERM_NEVER, only_u = TERM_NEVER, only_v = TERM_NEVER, both = TERM_NEVER;
@@ -153,7 +154,7 @@ __device__ __forceinline__ int class_time(ClsPtr cl, At at) {
       f &= keep;
       c &= keep;
     }
-    if (!cl->unit) {                                   // uniform
+    if (!EVEN && !cl->unit) {                          // uniform
       const uint32_t q = cl->q_stage[s];
       const int b = scale32(c - f, q);
       f = scale32(f, q);
@@ -856,7 +857,7 @@ __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t 
         int time;
         if constexpr (FLOW) {
           auto at = [&](int i) -> int2 { return i == 0 ? make_int2(0, 0) : TC[ce[i]]; };
-          time = ff->time24 ? class_time<SP, STRAT, true>(cl, at) : class_time<SP, STRAT, false>(cl, at);
+          time = ff->time24 ? class_time<SP, STRAT, true, false>(cl, at) : class_time<SP, STRAT, false, false>(cl, at);
         } else {
           int F[SP], C[SP];
           int2 t[SP + 1];
