@@ -555,13 +555,14 @@ constexpr int FLOW_FROM = 16;
 // 87 and 85).  With fewer stages more of them are resident, and the load, which waits for the cost stores ahead of it, costs more than
 // it saves (with a cost store: 7 stages, strategy 1, 65 us without, 69 with it; 5 stages, strategy 0, 67 and 69).
 constexpr int LIST_AHEAD_FROM = 10;
-// Lists of redundant computation, which has a class of pipelines for every node that is short: the rows come in no order, so that after
-// a few rounds next to none of 64 can win.  The class with the most work decides first, and the others and the weights to fetch are
-// worked out only where it leaves a cost not above the wavefront's lowest (2^22 rows: 8 stages 72 us without, 70 with it, 12 stages
-// 79 and 74, 16 stages 90 and 85).  From this many rounds of a workgroup on: with fewer there is nothing to compare with yet.  Nowhere
-// else: neighbouring ranks have neighbouring costs, so that some of 64 may nearly always win, and what is left out with one
-// class of pipelines costs less than the comparison (10 M ranks of 7 stages, strategy 1, 104 us with it, 90 without; of 8
-// stages, strategy 2, 134 and 120; lists of 2^22 rows of 4 stages 54 and 51).
+// Lists of redundant computation, which has a class of pipelines for every node that is short, and deep ones of strategy 1, whose
+// weights to fetch are many: the rows come in no order, so that after a few rounds next to none of 64 can win.  The class with the most
+// work decides first, and the others and the weights to fetch are worked out only where it leaves a cost not above the wavefront's
+// lowest (strategy 0, 2^22 rows: 8 stages 72 us without, 67 with it, 12 stages 79 and 73, 16 stages 90 and 84; strategy 1, 15 stages,
+// 2^24 rows 199 and 191, but 2^20 rows 43.7 and 44.4 of 13).  From this many rounds of a workgroup on: with fewer there is nothing to
+// compare with yet.  Nowhere else: neighbouring ranks have neighbouring costs, so that some of 64 may nearly always win, and what is left
+// out with one class of pipelines costs less than the comparison (10 M ranks of 7 stages, strategy 1, 104 us with it, 90 without; of 8
+// stages, strategy 2, 134 and 120; lists of 2^22 rows of 4 stages 54 and 51, of 14 stages, strategy 2, 96 and 92).
 constexpr uint32_t NARROW_ROUNDS = 8;
 
 template <int SP, int MODE>
@@ -584,7 +585,7 @@ template <int SP, int STRAT, int MODE, bool FLOW = (SP > FLOW_FROM)>
 __device__ __forceinline__ void search_partitions(const FastLaunch &a, uint32_t block, SearchShared<SP, MODE> &sh, int64_t *cost_tile) {
   constexpr bool QUEUED = MODE >= 1 && MODE <= 3, LIST = MODE == 3, WINDOW = MODE == 4;
   constexpr int K = SP - 1;
-  constexpr bool AHEAD = LIST && SP > LIST_AHEAD_FROM, NARROWS = LIST && STRAT == 0;
+  constexpr bool AHEAD = LIST && SP > LIST_AHEAD_FROM, NARROWS = LIST && (STRAT == 0 || (STRAT == 1 && SP > LIST_AHEAD_FROM));
   constexpr bool FETCH_LATE = NARROWS || AHEAD || FLOW;   // weights to fetch after the times, which need the registers first
   // cost store of plan indices: costs without penalties and the peers' stage times, for the kernel that expands them
   const bool expands = WINDOW || (!QUEUED && STRAT == 2 && a.base_out != nullptr);
