@@ -242,14 +242,14 @@ int chm_decode_plan(const chm_scenario *s, uint64_t index, chm_best *out);
  * only plans that can neither win nor tie are skipped, one by one or a run of consecutive ranks at a time
  * (the stages above the cuts that change within the run are common to all of its partitions, and so is their
  * share of the bound), or never enumerated at all: up to 2^30 partitions at nominal speeds (searched by halves,
- * where that takes less time than the count below) the loops over the cuts leave out what the cuts placed so far already make too slow; for other families searched as a whole the library counts on
- * the host, stage by stage, the partitions whose bound stays within the best cost known, and the device
+ * where that takes less time than the count below) the loops over the cuts leave out what the cuts placed so far
+ * already make too slow; for other families searched as a whole the library counts on the host, stage by stage, the partitions whose bound stays within the best cost known, and the device
  * enumerates and evaluates only those (this also reaches families of more than 2^46 partitions, which
  * chm_search_best otherwise refuses with CHM_ERR_OVERFLOW, whenever at most 2^26 candidates remain).  The search
  * starts with the ranks around the time-balanced and the memory-balanced partition of each range, so that a
  * good cost is known early.  (Families of 2^22 partitions together and fewer are searched exhaustively in one launch, which takes less
  * time.)  chm_timing.evaluated (chm_measure.h) tells how many
- * partitions were evaluated in full; chm_timing.feasible then counts only those partitions that were looked
+ * partitions had their pipeline times worked out; chm_timing.feasible then counts only those partitions that were looked
  * at one by one and fit.  Covers
  * the range and list searches of the specialised kernels without cost store (other paths evaluate everything;
  * with a cost store every cost is wanted and nothing is skipped).  Errors: CHM_ERR_ARG. */

@@ -25,7 +25,9 @@ typedef struct {
   uint64_t evaluations[3];     /* (partition, reroute vector) evaluations per strategy               */
   uint64_t feasible[3];        /* partitions per strategy that passed the memory filter              */
   uint64_t evaluated[3];       /* of those, partitions whose pipeline times were worked out: all of
-                                * them, or fewer in a bounded search (chm_set_bounded_search)         */
+                                * them, or fewer in a bounded search (chm_set_bounded_search).  (By
+                                * halves, and in long lists of strategy 0: the time of the class with
+                                * the most work; the others only where it does not decide.)           */
 } chm_timing;
 
 /* Which kernels a scenario would run on, decided from the description alone (host only, no device needed; the
@@ -54,7 +56,10 @@ int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
 int chm_halves_selection(const chm_scenario_desc *desc, int32_t strategy, int32_t *upper_cuts, uint64_t *wave_steps);
 
 /* Switches event timing of chm_search_best / chm_search_range on or off for a handle,
- * and reads the timings of the last such call. */
+ * and reads the timings of the last such call.  What is timed is the families' own kernels one after the other: with timing on,
+ * small families do not share a launch, large ones start behind the seeds of the first of them alone, and a bounded
+ * search of few partitions runs with its bounds instead of exhaustively in one launch.  The plans are the same; a
+ * call without timing takes less time than total_ms by what that saves. */
 int chm_set_timing(chm_scenario *s, int32_t on);
 int chm_get_timing(const chm_scenario *s, chm_timing *out);
 

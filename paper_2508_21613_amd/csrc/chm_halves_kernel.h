@@ -11,8 +11,9 @@
 // laid out once per handle and strategy).
 // Bound by VALU issue: 14 to 17 instructions a partition in the innermost loop (26 under redundant computation), 20 to 28 in all;
 // working every lane's upper stages out on their own took 51 to 54 (104 with two classes of pipelines), one partition at a time
-// 200 and more.  62.9 M partitions of 8 stages: 57 us (120; one by one 434), under redundant computation 75 (209; 516), 5.2 G of
-// 11 stages 4.0 ms (6.4; 51).  Six waves per SIMD and more hide the scalar loads.
+// 200 and more.  62.9 M partitions of 8 stages: 54 us (120; one by one 434), under redundant computation 66 (209; 516), 5.2 G of
+// 11 stages 4.0 ms (6.4; 51).  As many waves per SIMD as the registers leave hide the scalar loads: 7 up to 8 stages, 6 up to 11, 5
+// beyond, under redundant computation 5 up to 10 and 4 beyond (strategy 1 of 11, 15 and 16 stages spills two to nine registers).
 //
 // Every partition's memory peak and the time of its longest pipeline class are worked out.  The time of other classes (strategy
 // 0: pipelines without the failed nodes) and the weights to fetch (the transition time) only where horizon x that time does not
