@@ -26,9 +26,10 @@ HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize
                  "-Xarch_host", "-g"]
 SOURCES = ["chm_host.cpp", "chm_pool.cpp", "chm_kernels.hip", "chm_fast.hip", "chm_search_s0.hip", "chm_search_s1.hip", "chm_search_s2.hip", "chm_families_8.hip",
            "chm_families_12.hip", "chm_families_16.hip", "chm_families_24.hip", "chm_window.hip", "chm_replan.hip", "chm_probe.hip"]
+# no device code meets a NaN: a maximum of floats is one instruction then, not one more for each operand that might be one;
 # packed-FP32 instruction selection is switched off for all device code; so is the vectorizer of straight-line code, which
 # finds nothing to gain in integer kernels and puts arrays it has half packed into scratch
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-slp-vectorize",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-slp-vectorize", "-Xarch_device", "-fno-honor-nans",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]
 
 

@@ -65,12 +65,22 @@ struct FastTables {
 
 // Widths of the upper half that some model length takes (halves_cost, chm_fast.hip): two cuts up to 11 stages, three from 9 on.
 enum { HALVES_TWO_UP_TO = 11, HALVES_THREE_FROM = 9 };
+// What a wavefront of the search walks (chm_halves_kernel.h): the upper half's cuts and, of the lower half's, the last ones that leave its
+// lanes enough choices of the cuts below.  One more walked cut leaves an eighth of the lanes' set-ups (300 instructions) to a family of 8
+// stages, but more lanes idle (8 stages, 48 layers, two / three / four walked: strategy 0 91 / 82 / 114 us a search, strategy 2 85 / 85 / 113;
+// 7 stages 46 / 48; 11 stages of 48 layers, three / four 2,880 / 2,650).  From 10 stages on a lane keeps two choices: half the scalar
+// instructions and record loads a partition, for four wavefronts per SIMD instead of six (11 stages 2,960 us with one, 2,650 with two; 8 stages 47
+// and 48, strategy 0 52 and 58).
+constexpr int halves_walked(int stages) { return stages <= 7 ? 2 : stages <= 10 ? 3 : 4; }
+constexpr int halves_choices(int stages) { return stages <= 9 ? 1 : 2; }
+constexpr int halves_waves(int stages) { return stages <= 7 ? 7 : stages <= 9 ? 6 : 4; }
 // How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
 struct HalvesShape {
   int up = 0;                   // cuts of an upper half
-  uint32_t n_items = 0;         // wavefronts of the search
-  uint32_t chunk = 0;           // upper halves per item
   uint64_t steps = 0;           // 64 lower halves x one upper half
+  uint64_t setup = 0;           // lower halves to set up, in instructions, were a lane to keep each
+  uint32_t n_items = 0;         // wavefronts of the search
+  uint64_t units = 0;           // work to share out among them
 };
 
 struct FastState {
@@ -153,16 +163,30 @@ struct FamiliesLaunch {
 enum { PAIR_RECORD_WORDS = 8 };
 struct HalvesItems {
   int4 prefix[DEV_MAX_L + 1];   // prefix sums: forward, forward + backward, static memory, activation memory
-  uint32_t first[DEV_MAX_L];    // per last lower cut, its first wavefront item
+  uint64_t first[DEV_MAX_L];    // per last cut of the lanes, its first unit of work
+  uint32_t share[DEV_MAX_S];    // strategy 2: reroute penalty of a stage as a multiple of its time
+  uint32_t units[4 * DEV_MAX_L];            // row i - 1: units of i walked cuts whose leading digit is below x
   uint32_t binom[DEV_MAX_S * DEV_MAX_L];    // row i - 1: C(x, i), 0 < i <= lower cuts
 };
+// Work of a block of 64 choices of the lanes' cuts (`kept` of them, the last one v): what a step of the innermost loop takes is a unit;
+// its set-up and a turn of the loop around (a row) take as long as this many.
+enum { HALVES_SETUP = 60, HALVES_ROW = 5 };
+template <typename Scenario>
+__host__ __device__ inline uint64_t halves_blocks(const Scenario &h, int kept, int choices, int v) {
+  return (h->binom[kept - 1][v - 1] + 64 * choices - 1) / (64 * choices);
+}
+template <typename Scenario>
+__host__ __device__ inline uint64_t halves_units(const Scenario &h, int kept, int walked, int v) {
+  (void)kept;
+  return HALVES_SETUP + h->binom[walked][h->L - 1 - v] + HALVES_ROW * h->binom[walked - 1][h->L - 2 - v];
+}
 struct HalvesLaunch {
   SearchLaunch s;               // result = words of the family's first chunk
   const FastTables *tab;
-  uint32_t *pairs;              // records of pairs of cuts, (L + 1)^2 of PAIR_RECORD_WORDS
+  uint32_t *pairs, *steps;      // records of pairs of cuts, (L + 1)^2 of PAIR_RECORD_WORDS each
   HalvesItems *items;
-  uint32_t n_pairs, n_items;
-  uint32_t chunk;               // upper halves per item
+  uint32_t n_rows, n_items;     // layers + 1; wavefronts
+  uint64_t n_units, per_item;   // units of work, of all and of a wavefront
   uint32_t bounded;             // 1: what the cuts placed so far make too slow is left out
   uint32_t chunk_words;         // words from one chunk's argmin words to the next chunk's
 };
@@ -228,9 +252,9 @@ int chmk_families_24(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, v
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
-int chmk_halves_s0(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
-int chmk_halves_s1(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
-int chmk_halves_s2(int sp, int up, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s0(int sp, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s1(int sp, const HalvesLaunch &a, bool build, void *stream);
+int chmk_halves_s2(int sp, const HalvesLaunch &a, bool build, void *stream);
 // Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
 // halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
 // search, only for what chm_halves_kernel.h says.  may_allocate = false, or no memory to be had: only with tables that are already there.  Same

@@ -292,37 +292,52 @@ constexpr uint64_t HALVES_FROM = 1ull << 21;
 // kernel / by halves: 5 stages, 2.1 M partitions (a third of the lanes at work) 30 / 36 and, strategy 0, 29 / 17; 3.0 M 38 / 38 and
 // 35 / 18; 5.6 M 56 / 46 and 51 / 23; 6 stages, 2.9 M (78 % at work) 37 / 34 and 38 / 17.
 constexpr int64_t HALVES_SAVES = 7ll << 20;
-// Upper halves of three cuts leave a wavefront fewer lower halves to set up (the time of 60 + 30 a lower cut instructions each), but a step of
-// theirs costs more (25 instead of 18) and their lower halves, a cut shorter, may be few: the 64 lanes of a wavefront share the
-// last lower cut.  Deep pipelines, whose upper halves are few for every v, take three.  us, two cuts / three, strategies 0 and 2:
-// 7 stages, 45 M partitions 56 / 77, 43 / 61; 8 stages, 4.3 M 19 / 21, 35 / 41, and 63 M 77 / 96, 59 / 74; 9 stages, 24 M 48 / 52,
-// 40 / 42; 10 stages, 39 M 82 / 71, 68 / 56; 12 stages, 13 M 58 / 46, 54 / 37; 16 stages, 7.7 M 109 / 96, 136 / 115; 7 stages, 3.6 G
-// 2,165 / 2,821, 1,693 / 2,164.  Never where three cuts leave more lanes idle, by a quarter more steps.
-uint64_t halves_setup(const HalvesShape &hs, int sp) { return (uint64_t)hs.n_items * (uint64_t)(60 + 30 * (sp - 1 - hs.up)); }
-uint64_t halves_cost(const HalvesShape &hs, int sp) { return halves_setup(hs, sp) + hs.steps * (hs.up == 2 ? 18u : 25u); }
+// How large an upper half is counted with: two cuts, or three where that leaves so many fewer lower halves (60 + 30 a lower cut
+// instructions each) that dearer steps (25 instead of 18) pay, and not a quarter more of them; deep pipelines, whose upper halves are few for
+// every v.  (The kernel walks more cuts than these from 8 stages on, halves_walked; the sizes from which a family goes by halves were
+// measured with a lane for every lower half.)
+uint64_t halves_cost(const HalvesShape &hs) { return hs.setup + hs.steps * (hs.up == 2 ? 18u : 25u); }
 constexpr uint64_t WIDER_BY = 4;
+// Units of work a wavefront is given at least where there is more than one round of them (8 stages, 48 layers, one round / two / three 82 / 84 / 88
+// us a search, strategy 0; 5.2 G partitions of 11 stages 3,240 / 2,880 / 2,660 us with 2 / 4 / 8 rounds).
+constexpr uint64_t HALVES_UNITS = 256;
 
-// wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts; steps = 0: not
+// wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts, `chunk` at most each; false: not
 // within the kernel's 32-bit ranks of lower halves
-HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
+bool halves_count(const DevScenario &h, int sp, int up, uint64_t chunk, uint64_t *steps, uint64_t *items) {
   const int H = sp - 1 - up, L = h.L;
+  *steps = *items = 0;
+  if (H < 2 || L - 1 - H < up) return false;
+  for (int v = H; v <= L - 1 - up; ++v) {
+    if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return false;
+    const uint64_t low = (h.binom[H - 1][v - 1] + 63) / 64, upper = h.binom[up][L - 1 - v];
+    *steps += low * upper;
+    *items += low * ((upper + chunk - 1) / chunk);
+  }
+  return true;
+}
+
+HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
   HalvesShape hs;
   uint64_t steps = 0, items = 0;
-  if (L - 1 - H < up) return hs;
-  for (int v = H; v <= L - 1 - up; ++v) {
-    if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return hs;
-    steps += (h.binom[H - 1][v - 1] + 63) / 64 * h.binom[up][L - 1 - v];
-  }
-  // upper halves per wavefront: so many that every resident wavefront gets about one item, but at least 32, which carry the lower
-  // half's set-up (steps / 12,288, 8,192, 6,144, 4,096: 32 cards 169, 167, 163, 167 us, plan cache of 64 sets 4,081, 4,043, 3,808, 3,825;
-  // 3 M partitions of 7 stages 15 and 21 us with 32 and 64)
-  hs.chunk = (uint32_t)std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 6144));
-  for (int v = H; v <= L - 1 - up; ++v) items += (h.binom[H - 1][v - 1] + 63) / 64 * ((h.binom[up][L - 1 - v] + hs.chunk - 1) / hs.chunk);
+  if (!halves_count(h, sp, up, 1, &steps, &items)) return hs;
+  halves_count(h, sp, up, std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 6144)), &steps, &items);
   if (items >= (1ull << 31)) return hs;
   hs.up = up;
   hs.steps = steps;
-  hs.n_items = (uint32_t)items;
+  hs.setup = items * (uint64_t)(60 + 30 * (sp - 1 - up));
   return hs;
+}
+
+// The work of the search and the wavefronts it is shared out among: as many as are resident at a time, or several times as many where
+// each still has a few hundred units.
+void halves_share(const DevScenario &h, int sp, HalvesShape *hs) {
+  const int walked = halves_walked(sp), kept = sp - 1 - walked;
+  hs->units = 0;
+  for (int v = kept; v <= h.L - 1 - walked; ++v) hs->units += halves_units(&h, kept, walked, v) * halves_blocks(&h, kept, halves_choices(sp), v);
+  const uint64_t resident = 1024u * (uint64_t)halves_waves(sp);
+  const uint64_t rounds = std::min<uint64_t>(8, hs->units / (HALVES_UNITS * resident));
+  hs->n_items = (uint32_t)(rounds ? rounds * resident : std::max<uint64_t>(1, std::min<uint64_t>(resident, hs->units / 64)));
 }
 
 HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
@@ -338,9 +353,10 @@ HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
     if (t->even_share[s] == 0) return none;
   const HalvesShape two = sp <= HALVES_TWO_UP_TO ? halves_of_width(h, sp, 2) : none;
   const HalvesShape three = sp >= HALVES_THREE_FROM ? halves_of_width(h, sp, 3) : none;
-  const bool wide = two.up == 0 || (halves_cost(three, sp) < halves_cost(two, sp) && three.steps <= two.steps + two.steps / WIDER_BY);
-  const HalvesShape taken = three.up != 0 && wide ? three : two;
+  const bool wide = two.up == 0 || (halves_cost(three) < halves_cost(two) && three.steps <= two.steps + two.steps / WIDER_BY);
+  HalvesShape taken = three.up != 0 && wide ? three : two;
   if (taken.up == 0) return none;
+  halves_share(h, sp, &taken);
   const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
   return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)std::min(ff.n_time, 2) + (unsigned)HALVES_SAVES ? taken : none;
 }
@@ -807,7 +823,7 @@ bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_
   return k >= 0 && k <= 2 && f->halves[k].up != 0 && partitions == h.fam[k].n_part;
 }
 
-uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return halves_setup(f->halves[k], h.fam[k].stages); }
+uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return f->halves[k].setup; }
 
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, bool bounded, void *stream) {
@@ -815,25 +831,26 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   if (!fast_halves_covers(f, h, k, partitions)) return 1;
   const HalvesShape &hs = f->halves[k];
   const int sp = h.fam[k].stages;
-  const uint32_t n_pairs = (uint32_t)((h.L + 1) * (h.L + 1));
-  const size_t words = (size_t)n_pairs * PAIR_RECORD_WORDS;
+  const size_t words = (size_t)((h.L + 1) * (h.L + 1)) * PAIR_RECORD_WORDS;
   if (!f->d_pairs[k]) {
     // (no memory for the table: the range kernel needs none)
-    if (!may_allocate || !pool_take(f->d_pairs[k], words * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
+    if (!may_allocate || !pool_take(f->d_pairs[k], 2 * words * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
   }
   HalvesLaunch hl;
   hl.s = a;
   hl.tab = f->d_tables;
   hl.chunk_words = chunk_words;
   hl.bounded = bounded ? 1 : 0;
-  hl.chunk = hs.chunk;
   hl.n_items = hs.n_items;
-  hl.n_pairs = n_pairs;
+  hl.n_units = hs.units;
+  hl.per_item = (hs.units + hs.n_items - 1) / hs.n_items;
+  hl.n_rows = (uint32_t)(h.L + 1);
   hl.pairs = f->d_pairs[k];
-  hl.items = (HalvesItems *)(f->d_pairs[k] + words);         // (records are whole 32 bytes)
+  hl.steps = f->d_pairs[k] + words;
+  hl.items = (HalvesItems *)(f->d_pairs[k] + 2 * words);     // (records are whole 32 bytes)
   const bool build = !f->pairs_ready[k];
-  const int rc = k == 0 ? chmk_halves_s0(sp, hs.up, hl, build, stream)
-                 : k == 1 ? chmk_halves_s1(sp, hs.up, hl, build, stream) : chmk_halves_s2(sp, hs.up, hl, build, stream);
+  const int rc = k == 0 ? chmk_halves_s0(sp, hl, build, stream)
+                 : k == 1 ? chmk_halves_s1(sp, hl, build, stream) : chmk_halves_s2(sp, hl, build, stream);
   if (rc) return rc;
   if (hipGetLastError() != hipSuccess) return -1;
   f->pairs_queued[k] = true;

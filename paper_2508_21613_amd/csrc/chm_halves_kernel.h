@@ -1,25 +1,27 @@
 // Exhaustive search of a whole family by halves: the kernels for large spaces.  Included by one translation unit per
 // strategy, behind chm_search_kernel.h.
 //
-// A partition is a lower half (its first H cuts) and an upper half (its last UP cuts).  Everything a plan's step time is
-// made of (pipeline_time in chm_search_kernel.h) splits at the cut between them: maxima and sums over the stages of one
-// half alone, and a few terms of the stages that cross.  A lane keeps one lower half in registers and its wavefront walks the
-// upper halves as nested loops, one cut each.  All lanes of a wavefront have the same last lower cut v, so the stage between
-// the halves, and every stage above it, is the same for all of them: its times and memory are scalars, and what a cut decides
-// is worked out where its loop stands.  Only what depends on the last cut is left to the innermost loop, and of that
-// the scalar share (a function of two cuts) is read from a table of (L + 1)^2 records (k_pair_records, 32 bytes each,
-// laid out once per handle and strategy).
-// Bound by VALU issue: 14 to 17 instructions a partition in the innermost loop (26 under redundant computation), 20 to 28 in all;
-// working every lane's upper stages out on their own took 51 to 54 (104 with two classes of pipelines), one partition at a time
-// 200 and more.  62.9 M partitions of 8 stages: 54 us (120; one by one 434), under redundant computation 66 (209; 516), 5.2 G of
-// 11 stages 4.0 ms (6.4; 51).  As many waves per SIMD as the registers leave hide the scalar loads: 7 up to 8 stages, 6 up to 11, 5
-// beyond, under redundant computation 5 up to 10 and 4 beyond (strategy 1 of 11, 15 and 16 stages spills two to nine registers).
+// A wavefront's lanes keep the first G cuts of a partition, a choice or two of them each, all with the same last one v; the W cuts
+// above are walked as nested loops, one cut each.  What a step time is made of (pipeline_time in chm_search_kernel.h, read the way
+// class_time does) is a state of six numbers that takes up one stage after the other: maxima of forward and backward times, and of the
+// terms that have met neither end's turn, one of them or both.  So a loop over a cut adds the stage that the cut ends to the lane's state
+// (Terms::add, 12 instructions), whose times are the same for all lanes, and the innermost one, over the last cut y, is left with the two
+// last stages: 13 instructions (under redundant computation 22).  What is the same for all lanes of the last two levels is a function of two
+// cuts and comes from tables of (L + 1)^2 records (k_cut_records, 32 bytes each, laid out once per handle and strategy).
 //
-// Every partition's memory peak and the time of its longest pipeline class are worked out.  The time of other classes (strategy
-// 0: pipelines without the failed nodes) and the weights to fetch (the transition time) only where horizon x that time does not
-// already exceed the lowest cost met so far in the search: elsewhere they cannot change the argmin, ties included.
+// Times are floats.  A float addition or multiply-add issues beside a maximum of another wavefront (2.6 to 3 cycles an instruction for
+// such streams, 4.2 for integers).  Up to 2^24 they are the whole numbers they stand for; above, sums are rounded, and the limit they are
+// compared with is raised by more than that (SLACK).  They only decide which partitions may have a cost not above the lowest met; the cost
+// of these is worked out anew, in integers (consider).  Times of pipeline classes but the one with the most work take part there, too.
+//
+// Bound by the issue of vector instructions (0.6 to 0.7 of the rate above while all wavefronts run) and, for searches of tens of
+// microseconds, by the 6 us until the first lanes are set up and the end, when few wavefronts are left on a SIMD.  62.9 M partitions of
+// 8 stages: 46 us (integers, a lane for every lower half: 54; one by one 434), under redundant computation 53 (66; 516), 10.7 M of 7
+// stages 13 to 18 (27), 5.2 G of 11 stages 2.65 ms (3.93; 51).
 #ifndef CHM_HALVES_KERNEL_H
 #define CHM_HALVES_KERNEL_H
+#include <type_traits>
+
 #include "chm_search_kernel.h"
 
 namespace {
@@ -27,113 +29,195 @@ namespace {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 typedef u32x16 record_pair __attribute__((aligned(32)));       // two neighbouring records: 32 bytes each, a scalar load of 64
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 
 // least reroute penalty of a stage all of whose peers have one speed (stage_penalty; nothing else comes here)
 __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st, int f, int b) {
   return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);
 }
-constexpr int HALVES_NEVER = TERM_NEVER;
-constexpr int HALVES_UNFIT = 1 << 30;      // in place of a memory peak or a time: these partitions do not fit
+constexpr float NEVER = -1e30f, HUGE_TIME = 1e30f;     // terms that do not exist, times of what does not fit
+// What a stage's node lacks of the weights it is to hold ([lo, hi) of the memory prefix, stage s), and the time of a step that fetching
+// that much costs, a whole number not above it (0 where the nodes' assignment is open).
+template <int STRAT>
+__device__ __forceinline__ int lacking(FamPtr ff, int lo, int hi, int s) {
+  const int a = STRAT == 1 ? ff->cls[0].wlo[s] : ff->w0[s], b = STRAT == 1 ? ff->cls[0].whi[s] : ff->w0[s + 1];
+  return hi - lo - imax32(0, imin32(hi, b) - imax32(lo, a));
+}
+__device__ __forceinline__ float fetch_per_mib(ScnPtr scn, FamPtr ff, int strategy) {
+  return strategy == 1 && ff->assign ? 0.0f : (float)((double)scn->xfer / (double)scn->K) * 0.99999f;
+}
+constexpr int HALVES_UNFIT = 1 << 30;                  // in place of a share of a node's memory
+// A time is a chain of at most two additions a level and four more, of numbers up to six times as large: rounded to 24 bits
+// they stay within 2^-24 x 6 x (2 x 16 + 4) < 2^-16 of it.
+constexpr double SLACK = 1.0 + 1.0 / 65536;
 
-// A record of two cuts x < y.  Strategies 1 and 2: x, y = the last two cuts; stage N-2 = [x, y) and stage N-1 = [y, L), times as
-// prefixes from the front.  Strategy 0 (node s runs stages s and s+1): x = the last cut but two, y = the last one; node N-3 =
-// [x, y), times relative to the end of node N-4 less the prefix at x.
-enum { PAIR_END = 0,        // end of stage N-2 (strategy 0: of node N-3)
-       PAIR_U, PAIR_V,      // U and V of pipeline_time of that stage alone, under 1 and 2 not below those of the last stage
-       PAIR_OWN,            // its (M - n + s) C - P
-       PAIR_LAST,           // 1, 2: the last stage's whole term; 0: its share of node N-1 (which also runs stage 0): time
-       PAIR_PENALTY,        // 2: reroute penalties of the two stages; 0: node N-1's share of memory, HALVES_UNFIT if N-3 does not fit
-       PAIR_ROUNDS,         // 1, 2: communication rounds of the larger of the two stages; 0: U of node N-2 from N-3's backward
-       PAIR_FIT,            // 1, 2: 1 = both fit; 0: V of node N-2 from N-3's forward
+__device__ __forceinline__ float fmax2(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ float fmax3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
+
+// The state of the stages (nodes) taken up so far: largest forward and backward time, and the largest sums of class_time.
+struct Terms {
+  float mf, mb, none, ou, ov, both;
+  // takes up a stage: forward and backward time, its own term less the prefix, `after` stages behind it, the prefix at its end
+  __device__ __forceinline__ void add(float f, float b, float own, float after, float end) {
+    mf = fmax2(mf, f);
+    mb = fmax2(mb, b);
+    const float u = __builtin_fmaf(mb, after, end), w = __builtin_fmaf(mf, after, end);
+    none = fmax2(none, own);
+    ou = fmax2(ou, none + u);
+    ov = fmax2(ov, none + w);
+    both = fmax3(both, ou + w, ov + u);
+  }
+  // the same with times counted from the end of the last node taken up, c = f + b further on now
+  __device__ __forceinline__ void add_from_end(float f, float b, float c, float own, float after) {
+    both -= c;
+    none += c;
+    add(f, b, own, after, 0.0f);
+  }
+};
+
+// Records of two cuts, 8 words each, (L + 1)^2 of both kinds.
+// The innermost loop's, x < y.  Strategies 1 and 2: x, y = the last two cuts; stage N-2 = [x, y) and stage N-1 = [y, L), times less
+// the whole model's.  Strategy 0 (node s runs stages s and s+1): x = the last cut but two, y = the last one; node N-3 = [x, y), times
+// from the end of node N-4.
+enum { PAIR_LAST = 0,       // 1, 2: time of stage N-1; 0: its share of node N-1 (which also runs stage 0)
+       PAIR_U, PAIR_V,      // 1, 2: what stage N-2's backward, forward exceeds that by, at least 0; 0: node N-2's terms from N-3's
+       PAIR_OWN,            // own term of stage N-2 (0: node N-3) without the prefix
+       PAIR_TERM,           // 1, 2: the last stage's whole term, HUGE_TIME where one of the two does not fit; 0: end of node N-3
+       PAIR_COST,           // 1, 2: reroute penalties of the two stages, and the time to fetch what they lack; 0: U of node N-3
+       PAIR_V3,             // 0: V of node N-3
+       PAIR_FIT,            // 0: node N-1's share of memory, HALVES_UNFIT if N-3 does not fit; 1, 2, in the record (x, L): y that fit behind x (whole numbers)
        PAIR_WORDS };
+// The loop's over the last cut but one, x < m.  Strategies 1 and 2: stage N-3 = [x, m).  Strategy 0: node N-4 = [x, m) and, whatever x,
+// node N-2 = [m, L).
+enum { STEP_F = 0, STEP_B,  // forward and backward time
+       STEP_OWN,            // own term
+       STEP_END,            // 1, 2: prefix at m less the whole model's; 0: time of node N-2
+       STEP_COST,           // 1, 2: reroute penalty of the stage, and the time to fetch what it lacks; 0: forward time of node N-2
+       STEP_LAYERS,         // 1, 2: layers of the stage; 0: backward time of node N-2
+       STEP_FETCH,          // 0: time to fetch what the two last stages lack at least, wherever the last cut is
+       STEP_FIT,            // whether what the record holds fits (whole number)
+       STEP_WORDS };
+static_assert((int)PAIR_WORDS == (int)PAIR_RECORD_WORDS && (int)STEP_WORDS == (int)PAIR_RECORD_WORDS, "a record of either kind");
 
-// One lane per pair of cuts; the first workgroup also lays out what every workgroup of the search stages in LDS.
-template <int N, int STRAT, int UP>
-__global__ void __launch_bounds__(BLOCK) k_pair_records(HalvesLaunch a) {
-  constexpr int K = N - 1, H = K - UP;
+// One wavefront per cut x, its lanes take the cuts above; the first workgroup also lays out what every workgroup of the search stages in
+// LDS.
+template <int N, int STRAT>
+__global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
+  constexpr int K = N - 1, W = halves_walked(N), G = K - W, ROWS = G > W ? G : W;
   const ScnPtr scn = as_const(a.s.scn);
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
   const ClsPtr cl = &ff->cls[0];
-  const int L = scn->L, W = L + 1;
+  const int L = scn->L;
   if (blockIdx.x == 0) {
-    __shared__ uint32_t items[DEV_MAX_L];
+    __shared__ uint64_t units[DEV_MAX_L];
     const int v = (int)threadIdx.x;
-    if (v < DEV_MAX_L) {
-      // wavefront items per last lower cut v, and where v's first one is
-      uint32_t n = 0;
-      if (v >= H && v <= L - 1 - UP) {
-        const uint32_t low = (uint32_t)scn->binom[H - 1][v - 1], up = (uint32_t)scn->binom[UP][L - 1 - v];
-        n = ((low + 63u) / 64u) * ((up + a.chunk - 1) / a.chunk);
-      }
-      items[v] = n;
-    }
+    if (v < DEV_MAX_L) units[v] = v >= G && v <= L - 1 - W ? halves_units(scn, G, W, v) * halves_blocks(scn, G, halves_choices(N), v) : 0;
     __syncthreads();
     if (v < DEV_MAX_L) {
-      uint32_t first = 0;
-      for (int i = 0; i < v; ++i) first += items[i];
+      uint64_t first = 0;
+      for (int i = 0; i < v; ++i) first += units[i];
       a.items->first[v] = first;
+    }
+    for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) {
+      const int n = i / DEV_MAX_L + 1, x = i % DEV_MAX_L;
+      const uint64_t u = scn->binom[n][x] + (x > 0 ? HALVES_ROW * scn->binom[n - 1][x - 1] : 0);
+      a.items->units[i] = u > 0xffffffffull ? 0xffffffffu : (uint32_t)u;
     }
     for (int i = threadIdx.x; i <= L; i += BLOCK)
       a.items->prefix[i] = make_int4((int)scn->pf[i], (int)(scn->pf[i] + scn->pb[i]), (int)scn->pw[i], (int)scn->pa[i]);
+    // (peers of one speed, nominal: what the loss of a stage costs is so many times its time)
+    if (STRAT == 2 && threadIdx.x < DEV_MAX_S) {
+      uint32_t share = 0;
+      for (int st = 0; st < scn->n_aff; ++st)
+        if (scn->aff_stage[st] == (int)threadIdx.x) share = tab->even_share[st];
+      a.items->share[threadIdx.x] = share;
+    }
     // (binomials up to 2^32 - 1: ranks of lower halves are below that)
-    for (int i = threadIdx.x; i < H * DEV_MAX_L; i += BLOCK) {
+    for (int i = threadIdx.x; i < ROWS * DEV_MAX_L; i += BLOCK) {
       const uint64_t b = scn->binom[1 + i / DEV_MAX_L][i % DEV_MAX_L];
       a.items->binom[i] = b > 0xffffffffull ? 0xffffffffu : (uint32_t)b;
     }
   }
-  const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
-  if (p >= (uint32_t)(W * W)) return;
-  const int x = (int)p / W, y = (int)p % W;
-  uint32_t rec[PAIR_WORDS];
-#pragma unroll
-  for (int i = 0; i < PAIR_WORDS; ++i) rec[i] = 0;
-  if (x >= 1 && x < y && y < L) {
-    auto fwd = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo]); };
-    auto both = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo] + scn->pb[hi] - scn->pb[lo]); };
-    auto peak = [&](int lo, int hi, int s) {           // (0: nobody's)
-      const int coef = ff->mem_coef[s];
-      return coef < 0 ? 0 : (int)(scn->pw[hi] - scn->pw[lo]) + (ff->has_act ? (int)__umul24((uint32_t)(scn->pa[hi] - scn->pa[lo]), (uint32_t)coef) : 0);
-    };
-    const int cap = (int)scn->cap;
-    const int end = both(0, y);
+  const int lane = threadIdx.x & 63;
+  const int x = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6));
+  if (x > L) return;
+  auto fwd = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo]); };
+  auto both = [&](int lo, int hi) { return (int)(scn->pf[hi] - scn->pf[lo] + scn->pb[hi] - scn->pb[lo]); };
+  const int cap = (int)scn->cap, M = cl->M;
+  auto memory = [&](int lo, int hi, int s) {           // (0: nobody's)
+    const int coef = ff->mem_coef[s];
+    return coef < 0 ? 0 : (int)(scn->pw[hi] - scn->pw[lo]) + (ff->has_act ? (int)__umul24((uint32_t)(scn->pa[hi] - scn->pa[lo]), (uint32_t)coef) : 0);
+  };
+  auto penalty = [&](int lo, int hi, int s) {
+    uint32_t pen = 0;
+    for (int st = 0; STRAT == 2 && st < scn->n_aff; ++st)
+      if (scn->aff_stage[st] == s) pen += even_penalty(scn, tab, st, fwd(lo, hi), both(lo, hi) - fwd(lo, hi));
+    return (float)pen;
+  };
+  auto store = [&](uint32_t *table, int y, const float (&rec)[7], uint32_t last_word) {
+    uint4 *dst = (uint4 *)(table + (size_t)(x * (L + 1) + y) * PAIR_RECORD_WORDS);
+    dst[0] = make_uint4(__float_as_uint(rec[0]), __float_as_uint(rec[1]), __float_as_uint(rec[2]), __float_as_uint(rec[3]));
+    dst[1] = make_uint4(__float_as_uint(rec[4]), __float_as_uint(rec[5]), __float_as_uint(rec[6]), last_word);
+  };
+  const float per_mib = fetch_per_mib(scn, ff, STRAT);
+  auto lacks = [&](int lo, int hi, int s) { return lacking<STRAT>(ff, (int)scn->pw[lo], (int)scn->pw[hi], s); };
+  uint32_t n_fit = 0;
+  for (int y0 = 0; y0 <= L; y0 += 64) {
+    const int y = y0 + lane;
+    const bool there = x < y && y < L;
+    const int lo = there ? x : 0, hi = there ? y : 0;
+    const int f = fwd(lo, hi), c = both(lo, hi), last = both(hi, L), total = both(0, L);
+    float pair[7] = {}, step[7] = {};
+    uint32_t pair_word, step_word;
     if (STRAT == 0) {
-      constexpr int S = N - 3;
-      const bool dead = (cl->dead >> S) & 1u, gone = (cl->dead >> (N - 1)) & 1u;
-      const int f = dead ? 0 : fwd(x, y), c = dead ? 0 : both(x, y), e = dead ? both(0, x) : end;
-      rec[PAIR_END] = (uint32_t)e;
-      rec[PAIR_U] = (uint32_t)(e + cl->after[S] * (c - f));
-      rec[PAIR_V] = (uint32_t)(e + cl->after[S] * f);
-      rec[PAIR_OWN] = (uint32_t)(cl->steady[S] < 0 ? HALVES_NEVER : cl->steady[S] * c - e);
-      rec[PAIR_LAST] = (uint32_t)(gone ? 0 : both(y, L));
-      const int coef = ff->mem_coef[N - 1];
-      const int share = coef < 0 ? 0 : (int)(scn->pw[L] - scn->pw[y]) + (ff->has_act ? (int)__umul24((uint32_t)(scn->pa[L] - scn->pa[y]), (uint32_t)coef) : 0);
-      rec[PAIR_PENALTY] = (uint32_t)(peak(x, y, S) <= cap ? share : HALVES_UNFIT);
-      rec[PAIR_ROUNDS] = (uint32_t)(e + cl->after[N - 2] * (c - f));
-      rec[PAIR_FIT] = (uint32_t)(e + cl->after[N - 2] * f);
-    } else {
-      const int f = fwd(x, y), c = both(x, y), total = both(0, L);
-      rec[PAIR_END] = (uint32_t)end;
-      rec[PAIR_U] = (uint32_t)imax32(total, end + (c - f));
-      rec[PAIR_V] = (uint32_t)imax32(total, end + f);
-      rec[PAIR_OWN] = (uint32_t)(cl->steady[N - 2] * c - end);
-      rec[PAIR_LAST] = (uint32_t)(cl->steady[N - 1] * both(y, L) + total);
-      if (STRAT == 2) {
-        uint32_t pen = 0;
-        for (int st = 0; st < scn->n_aff; ++st) {
-          const int sa = scn->aff_stage[st];
-          if (sa == N - 2) pen += even_penalty(scn, tab, st, f, c - f);
-          if (sa == N - 1) pen += even_penalty(scn, tab, st, fwd(y, L), both(y, L) - fwd(y, L));
-        }
-        rec[PAIR_PENALTY] = pen;
+      {
+        constexpr int S = N - 3;
+        const bool dead = (cl->dead >> S) & 1u, gone = (cl->dead >> (N - 1)) & 1u;
+        const float b = dead ? 0.0f : (float)(c - f), ff3 = dead ? 0.0f : (float)f, cc = dead ? 0.0f : (float)c;
+        pair[PAIR_LAST] = gone ? 0.0f : (float)last;
+        pair[PAIR_U] = b * (float)cl->after[N - 2];
+        pair[PAIR_V] = ff3 * (float)cl->after[N - 2];
+        pair[PAIR_OWN] = dead ? NEVER : (float)cl->steady[S] * cc;
+        pair[PAIR_TERM] = cc;
+        pair[PAIR_COST] = b * (float)cl->after[S];
+        pair[PAIR_V3] = ff3 * (float)cl->after[S];
+        pair_word = (uint32_t)(there && memory(lo, hi, S) <= cap ? memory(hi, L, N - 1) : HALVES_UNFIT);
       }
-      rec[PAIR_ROUNDS] = (uint32_t)(ff->allreduce * imax32(y - x, L - y));
-      rec[PAIR_FIT] = peak(x, y, N - 2) <= cap && peak(y, L, N - 1) <= cap ? 1u : 0u;
+      constexpr int S = N - 4;
+      const bool dead = (cl->dead >> S) & 1u, gone = (cl->dead >> (N - 2)) & 1u;
+      const float c2 = gone ? 0.0f : (float)last, f2 = gone ? 0.0f : (float)fwd(hi, L);
+      step[STEP_F] = dead ? 0.0f : (float)f;
+      step[STEP_B] = dead ? 0.0f : (float)(c - f);
+      step[STEP_OWN] = dead ? NEVER : (float)cl->steady[S] * (float)c;
+      step[STEP_END] = c2;
+      step[STEP_COST] = f2;
+      step[STEP_LAYERS] = c2 - f2;
+      step[STEP_FETCH] = floorf((float)imax32(0, ff->w0[N - 2] - (int)scn->pw[hi]) * per_mib);
+      // (two cuts walked: node N-4 starts with the lanes' last cut but one, its memory is not looked at here)
+      step_word = there && (W == 2 || memory(lo, hi, S) <= cap) && memory(hi, L, N - 2) <= cap ? 1u : 0u;
+    } else {
+      const bool fit = there && x >= 1 && memory(lo, hi, N - 2) <= cap && memory(hi, L, N - 1) <= cap;
+      pair[PAIR_LAST] = (float)last;
+      pair[PAIR_U] = (float)imax32(0, c - f - last);
+      pair[PAIR_V] = (float)imax32(0, f - last);
+      pair[PAIR_OWN] = (float)((M - 2) * c + last) + (float)total;
+      pair[PAIR_TERM] = fit ? (float)((M - 1) * last) + (float)total : HUGE_TIME;
+      pair[PAIR_COST] = penalty(lo, hi, N - 2) + penalty(hi, L, N - 1) + floorf((float)(lacks(lo, hi, N - 2) + lacks(hi, L, N - 1)) * per_mib);
+      n_fit += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(fit));
+      pair_word = y == L ? n_fit : 0;
+      step[STEP_F] = (float)f;
+      step[STEP_B] = (float)(c - f);
+      step[STEP_OWN] = (float)((M - 3) * c + last) + (float)total;
+      step[STEP_END] = (float)-last;
+      step[STEP_COST] = penalty(lo, hi, N - 3) + floorf((float)lacks(lo, hi, N - 3) * per_mib);
+      step[STEP_LAYERS] = (float)(hi - lo);
+      step_word = there && memory(lo, hi, N - 3) <= cap ? 1u : 0u;
     }
+    if (y > L) continue;
+    store(a.pairs, y, pair, pair_word);
+    store(a.steps, y, step, step_word);
   }
-  uint4 *dst = (uint4 *)(a.pairs + (size_t)p * PAIR_WORDS);
-  dst[0] = make_uint4(rec[0], rec[1], rec[2], rec[3]);
-  dst[1] = make_uint4(rec[4], rec[5], rec[6], rec[7]);
 }
 
 // Digits x_K > ... > x_1 of `rem` = sum of C(x_i, i), as cuts c[i] = x_i + 1, all below `end`.  table[(i-1) * DEV_MAX_L + x] = C(x, i),
@@ -161,15 +245,16 @@ __device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint
   c[1] = (int)rem + 1;                                 // C(x, 1) = x
 }
 
-// One wavefront per (v, 64 lower halves that end with cut v, `chunk` upper halves); see the head of the file.  The upper halves
-// that go with v are numbered by falling digits x (position = sum of C(x_i, i) over UP of them), cut = L-1-x.
+// A wavefront takes one stretch of units of work after the other, each of one v and 64 choices of the lanes' cuts that end with v; see
+// the head of the file.  The upper cuts that go with v are numbered by falling digits x (position = sum of C(x_i, i) over W of them), cut =
+// L-1-x; a stretch begins and ends with a row, a choice of all of them but the last.
 // PRUNE: a bounded search (compiled apart: its tests in the loops over the outer cuts cost the exhaustive search 5 % as a flag).
-template <int N, int STRAT, int UP, bool PRUNE>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRAT == 0 ? (N <= 10 ? 5 : 4) : N <= 8 ? 7 : N <= 11 ? 6 : 5))) k_search_halves(HalvesLaunch a) {
-  constexpr int K = N - 1, H = K - UP;
-  constexpr int LOW = STRAT == 0 ? H - 1 : H;         // nodes of the lower half alone
+template <int N, int STRAT, bool PRUNE>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halves_waves(N)))) k_search_halves(HalvesLaunch a) {
+  constexpr int K = N - 1, W = halves_walked(N), G = K - W, ROWS = G > W ? G : W, R = halves_choices(N);
+  constexpr int LOW = STRAT == 0 ? G - 1 : G;         // nodes the lanes' cuts alone decide
   __shared__ int4 T[DEV_MAX_L + 1];
-  __shared__ uint32_t BN[H * DEV_MAX_L];
+  __shared__ uint32_t BN[ROWS * DEV_MAX_L], UN[W * DEV_MAX_L];
   __shared__ uint64_t wave_cost[BLOCK / 64], wave_rank[BLOCK / 64];
   __shared__ uint32_t wave_fit[BLOCK / 64];
   const ScnPtr scn = as_const(a.s.scn);
@@ -179,177 +264,222 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
   const CHM_CONST i32x4 *pre = (const CHM_CONST i32x4 *)(uintptr_t)a.items->prefix;      // {forward, both, memory, activations}
   const int L = scn->L;
   for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = a.items->prefix[i];
-  for (int i = threadIdx.x; i < H * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
+  for (int i = threadIdx.x; i < ROWS * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
+  for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) UN[i] = a.items->units[i];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
   uint64_t best_cost = ~0ull, best_rank = ~0ull;
   uint32_t n_fit = 0;
-  const uint64_t inc0 = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  if (item < a.n_items) {
-    // the item's v: items are numbered v by v
-    const uint64_t below_lo = __builtin_amdgcn_ballot_w64(a.items->first[lane] <= item);
-    const uint64_t below_hi = __builtin_amdgcn_ballot_w64(a.items->first[lane + 64] <= item);
-    const int v = (int)__popcll(below_lo) + (int)__popcll(below_hi) - 1;     // first_item grows with v (equal where v has none)
-    const uint32_t local = item - as_const(a.items->first)[v];
-    const uint32_t n_up = (uint32_t)scn->binom[UP][L - 1 - v];               // upper halves that go with v
-    const uint32_t n_low = (uint32_t)scn->binom[H - 1][v - 1];               // lower halves that end with v
-    const uint32_t low_blocks = (n_low + 63u) / 64u;
-    const uint32_t part = local / low_blocks, low_block = local - part * low_blocks;
-    const uint32_t up_first = part * a.chunk;
-    uint32_t left = n_up - up_first < a.chunk ? n_up - up_first : a.chunk;   // upper halves still to walk
-    // digits of the first one: x[i], i = UP .. 1
-    int x[UP + 1];
-    {
-      uint32_t rem = up_first;
+  uint64_t low_cost = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  // The item's part of all units of work: blocks of 64 choices of the lanes' cuts, v by v, each its set-up and its upper cuts in turn.
+  uint64_t unit = (uint64_t)item * a.per_item;
+  const uint64_t unit_end = umin64(unit + a.per_item, a.n_units);
+  while (unit < unit_end) {
+    const uint64_t first_lo = a.items->first[lane], first_hi = a.items->first[lane + 64];
+    // (units are numbered v by v: first grows with v, and is the same where v has none)
+    const int v = (int)__popcll(__builtin_amdgcn_ballot_w64(first_lo <= unit)) + (int)__popcll(__builtin_amdgcn_ballot_w64(first_hi <= unit)) - 1;
+    const uint64_t behind = unit - as_const(a.items->first)[v];
+    const uint32_t n_up = (uint32_t)scn->binom[W][L - 1 - v];                // upper cuts that go with v
+    const uint32_t n_low = (uint32_t)scn->binom[G - 1][v - 1];               // choices of the lanes' cuts that end with v
+    const uint32_t units = (uint32_t)halves_units(scn, G, W, v);
+    const uint32_t low_block = (behind >> 32) == 0 ? (uint32_t)behind / units : (uint32_t)(behind / units);
+    const uint32_t from = (uint32_t)(behind - (uint64_t)low_block * units);
+    const uint32_t to = unit_end - unit < units - from ? from + (uint32_t)(unit_end - unit) : units;
+    unit += units - from;
+    // Digits x[i], i = W .. 2, of the row (all but the last cut) that a unit of upper cuts belongs to; the rows' position is returned.
+    // (C(x, i) positions have a leading digit below x, in C(x-1, i-1) rows.)
+    auto row_of = [&](uint32_t rem, uint32_t (&x)[5]) -> uint32_t {
+      uint32_t position = 0;
 #pragma unroll
-      for (int i = UP; i >= 1; --i) {
-        // largest x with C(x, i) <= rem (binomials of up to three cuts grow strictly from i - 1 on)
-        const uint64_t lo = __builtin_amdgcn_ballot_w64(BN[(i - 1) * DEV_MAX_L + lane] <= rem);
-        const uint64_t hi = __builtin_amdgcn_ballot_w64(BN[(i - 1) * DEV_MAX_L + lane + 64] <= rem);
-        x[i] = (int)__popcll(lo) + (int)__popcll(hi) - 1;
-        rem -= as_const(a.items->binom)[(i - 1) * DEV_MAX_L + x[i]];
+      for (int i = W; i >= 2; --i) {
+        // largest x with that many units or fewer
+        const uint32_t lo = UN[(i - 1) * DEV_MAX_L + lane], hi = UN[(i - 1) * DEV_MAX_L + lane + 64];
+        x[i] = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(lo <= rem)) + (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(hi <= rem)) - 1u;
+        rem -= (uint32_t)(x[i] < 64 ? __builtin_amdgcn_readlane((int)lo, (int)x[i]) : __builtin_amdgcn_readlane((int)hi, (int)x[i] - 64));
+        position += (uint32_t)__builtin_amdgcn_readfirstlane((int)BN[(i - 1) * DEV_MAX_L + x[i]]);
       }
-    }
+      return position;
+    };
+    uint32_t x[5] = {}, x_end[5];
+    const uint32_t up_end = to == units ? n_up : row_of(to < HALVES_SETUP ? 0 : to - HALVES_SETUP, x_end);
+    uint32_t left = up_end - row_of(from < HALVES_SETUP ? 0 : from - HALVES_SETUP, x);       // upper cuts still to walk
+    if (left == 0) continue;
+    uint32_t fit_up = 0;                               // strategies 1, 2: upper cuts that fit
 
-    // ---- this lane's lower half
-    const uint32_t q = low_block * 64u + (uint32_t)lane;
-    const bool active = q < n_low;
-    uint32_t low_cuts[(H + 3) / 4];                    // its cuts, a byte each
-    int c_first, c_before;                             // cut 1; cut H-1 (strategy 0)
-    int layers_low = 0;
-    int none = HALVES_NEVER, only_u = HALVES_NEVER, only_v = HALVES_NEVER, both = HALVES_NEVER;     // see class_time
-    int sum_low = 0, mf = 0, mb = 0;
-    int pen_low = 0;
-    bool ok = active;
+    // ---- this lane's cuts, R choices of them
     const int cap = (int)scn->cap;
-    {
-      int c[H + 1];
-      unrank_by_bits<H - 1>(active ? q : 0u, v, BN, c);          // cuts 1..v-1
+    const int total = pre[L].y;
+    const float shift = (float)total;
+    const float per_mib = fetch_per_mib(scn, ff, STRAT);
+    const CHM_CONST uint32_t *share = as_const(a.items)->share;       // 2: share of a stage's time that its loss costs
+    struct Choice {
+      uint32_t cuts[(G + 3) / 4];                      // a byte each
+      Terms low;
+      float off, layers;                               // what the limit is lowered by (0: the comm term and the end of the last node)
+      int mem_b, f_b, c_b;                             // 0: prefixes at cut G-1 (memory as node G-1 counts it)
+      float zl;                                        // 0: stage 0's time on node N-1, and what it leaves of its memory
+      int room_z;
+      bool ok;
+    };
+    Choice mine[R];
+    uint32_t low_fit = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      Choice &o = mine[r];
+      const uint32_t q = low_block * (64u * R) + 64u * r + (uint32_t)lane;
+      o.ok = q < n_low;
+      o.low = {0, 0, NEVER, NEVER, NEVER, NEVER};
+      if (STRAT == 1) o.low.both = (float)(ff->fixed_step - cl->comm_total);    // (untouched pipelines: whatever the cuts)
+      o.off = (float)cl->comm_total;
+      int c[G + 1];
+      unrank_by_bits<G - 1>(o.ok ? q : 0u, v, BN, c);  // cuts 1..v-1
       c[0] = 0;
-      c[H] = v;
+      c[G] = v;
 #pragma unroll
-      for (int i = 0; i < (H + 3) / 4; ++i) low_cuts[i] = 0;
+      for (int i = 0; i < (G + 3) / 4; ++i) o.cuts[i] = 0;
 #pragma unroll
-      for (int i = 1; i <= H; ++i) low_cuts[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
-      c_first = c[1];
-      c_before = c[H - 1];
-      int4 t[H + 1];
+      for (int i = 1; i <= G; ++i) o.cuts[(i - 1) >> 2] |= (uint32_t)c[i] << (8 * ((i - 1) & 3));
+      int4 t[G + 1];
       t[0] = make_int4(0, 0, 0, 0);
 #pragma unroll
-      for (int i = 1; i <= H; ++i) t[i] = T[c[i]];
+      for (int i = 1; i <= G; ++i) t[i] = T[c[i]];
+      o.layers = 0;
+      if (STRAT != 0 && ff->allreduce > 0) {
+        int layers = ff->fixed_layers;
 #pragma unroll
-      for (int s = 0; s < H; ++s) layers_low = imax32(layers_low, c[s + 1] - c[s]);
-      if (STRAT != 0) layers_low = imax32(layers_low, ff->fixed_layers);
+        for (int s = 0; s < G; ++s) layers = imax32(layers, c[s + 1] - c[s]);
+        o.layers = (float)layers;
+      }
 #pragma unroll
       for (int s = 0; s < LOW; ++s) {
         const int e = STRAT == 0 ? s + 2 : s + 1;
         int f = t[e].x - t[s].x, cc = t[e].y - t[s].y;
         const int coef = ff->mem_coef[s];
         const int m = t[e].z - t[s].z + (ff->has_act ? (int)__umul24((uint32_t)(t[e].w - t[s].w), (uint32_t)(coef < 0 ? 0 : coef)) : 0);
-        ok = ok && (coef < 0 || m <= cap);
-        if (STRAT == 2)
-          for (int st = 0; st < scn->n_aff; ++st)
-            if (scn->aff_stage[st] == s) pen_low += (int)even_penalty(scn, tab, st, f, cc - f);      // uniform
-        if (STRAT == 0 && ((cl->dead >> s) & 1u)) f = cc = 0;
-        sum_low += cc;
-        mf = imax32(mf, f);
-        mb = imax32(mb, cc - f);
-        const int u = (int)__umul24((uint32_t)mb, (uint32_t)cl->after[s]) + sum_low, w = (int)__umul24((uint32_t)mf, (uint32_t)cl->after[s]) + sum_low;
-        none = imax32(none, cl->steady[s] < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)cc, (uint32_t)cl->steady[s]) - sum_low);
-        only_u = imax32(only_u, none + u);
-        only_v = imax32(only_v, none + w);
-        both = imax32(both, imax32(only_u + w, only_v + u));
+        o.ok = o.ok && (coef < 0 || m <= cap);
+        if (STRAT == 2) o.off += (float)(int)((uint32_t)cc * share[s]);
+        if (STRAT == 0) {
+          const bool dead = (cl->dead >> s) & 1u;      // uniform
+          if (dead) f = cc = 0;
+          o.low.add_from_end((float)f, (float)(cc - f), (float)cc, dead ? NEVER : (float)cl->steady[s] * (float)cc, (float)cl->after[s]);
+          o.off += (float)cc;
+        } else {
+          // (the whole model's time is left out of both prefixes a term holds: the records' are less by as much)
+          o.low.add((float)f, (float)(cc - f), (float)((int)__umul24((uint32_t)(cl->M - N + s), (uint32_t)cc) - t[e].y + total) + shift, (float)(N - 1 - s),
+                    (float)(t[e].y - total));
+        }
       }
+      int lacks = 0;
+#pragma unroll
+      for (int s = 0; s < G; ++s) lacks += lacking<STRAT>(ff, t[s].z, t[s + 1].z, s);
+      o.off += floorf((float)lacks * per_mib);
+      if (STRAT == 0) {
+        const int coef_g = ff->mem_coef[G - 1], coef_z = ff->mem_coef[N - 1];
+        o.f_b = t[G - 1].x;
+        o.c_b = t[G - 1].y;
+        o.mem_b = coef_g < 0 ? 0 : t[G - 1].z + (ff->has_act ? (int)__umul24((uint32_t)t[G - 1].w, (uint32_t)coef_g) : 0);
+        o.zl = ((cl->dead >> (N - 1)) & 1u) ? 0.0f : (float)t[1].y;
+        o.room_z = coef_z < 0 ? HALVES_UNFIT - 1 : cap - t[1].z - (ff->has_act ? (int)__umul24((uint32_t)t[1].w, (uint32_t)coef_z) : 0);
+      }
+      low_fit += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(o.ok));
     }
-    const i32x4 tv = pre[v], tl = pre[L];
-    // strategy 0: the lane's shares of nodes H-1 = [cut H-1, g) and N-1 (stage 0 of it)
-    int4 tb = make_int4(0, 0, 0, 0);
-    int zl = 0, room_z = 0;                            // stage 0's time, and what it leaves of node N-1's memory
-    if (STRAT == 0) {
-      tb = T[c_before];
-      const int coef_g = ff->mem_coef[H - 1], coef_z = ff->mem_coef[N - 1];
-      const int4 t1 = T[c_first];
-      zl = ((cl->dead >> (N - 1)) & 1u) ? 0 : t1.y;
-      room_z = coef_z < 0 ? HALVES_UNFIT - 1 : cap - t1.z - (ff->has_act ? (int)__umul24((uint32_t)t1.w, (uint32_t)coef_z) : 0);
-      // (from here on the memory of the lower share of node H-1 in tb.z: one subtraction per g)
-      tb.z = coef_g < 0 ? 0 : tb.z + (ff->has_act ? (int)__umul24((uint32_t)tb.w, (uint32_t)coef_g) : 0);
-    }
-    const uint64_t low_mask = __builtin_amdgcn_ballot_w64(ok);
-    const uint32_t low_fit = (uint32_t)__popcll(low_mask);
-    if (low_mask == 0) left = 0;                       // uniform: none of these lower halves fits
+    if (low_fit == 0) left = 0;                        // uniform: none of these lower cuts fits
+    const i32x4 tv = pre[v];
 
-    // ---- the upper halves
+    // ---- the upper cuts
     const int rounds = STRAT != 0 ? ff->allreduce : 0;
-    const int fixed_step = ff->fixed_step, comm = cl->comm_total;
     const double per_step = 1.0 / (double)scn->K;
-    auto limit_of = [&](uint64_t cost) -> int {       // no step time above this can reach `cost` (rounded up)
+    auto limit_of = [&](uint64_t cost) -> float {      // no step time above this can reach `cost`
       const uint64_t reconf = (uint64_t)scn->reconf[STRAT];
-      if (cost == ~0ull) return 0x7fffffff;
-      if (cost < reconf) return -1;
-      const double y = (double)(cost - reconf) * per_step + 1.0;
-      return y >= 2147483647.0 ? 0x7fffffff : (int)y;
+      if (cost == ~0ull) return HUGE_TIME / 2;
+      if (cost < reconf) return NEVER;
+      return (float)(((double)(cost - reconf) * per_step + 1.0) * SLACK);
     };
-    int limit = __builtin_amdgcn_readfirstlane(limit_of(inc0));
-    // a node above the lower half, the same for all lanes: times (0 when nobody runs it), and whether it fits
-    auto scalar_peak = [&](i32x4 lo, i32x4 hi, int s) {
+    float limit = limit_of(low_cost);
+    // memory of a node above the lanes' cuts, the same for all lanes
+    auto peak = [&](i32x4 lo, i32x4 hi, int s) {
       const int coef = ff->mem_coef[s];
       return coef < 0 ? 0 : hi.z - lo.z + (hi.w - lo.w) * coef;
     };
     auto gone = [&](int s) { return STRAT == 0 && ((cl->dead >> s) & 1u) != 0; };
     const int M = cl->M;
-    auto scalar_own = [&](int s, int c, int p) {       // (strategies 1, 2: every stage has its node)
-      const int k = STRAT == 0 ? cl->steady[s] : M - N + s;
-      return STRAT == 0 && k < 0 ? HALVES_NEVER : k * c - p;
-    };
-    uint32_t share_h = 0, share_m = 0;                 // strategy 2: share of a stage's time that its loss costs, stages H and N-3
-    if (STRAT == 2) {
-      for (int st = 0; st < scn->n_aff; ++st) {
-        if (scn->aff_stage[st] == H) share_h = tab->even_share[st];
-        if (UP == 3 && scn->aff_stage[st] == N - 3) share_m = tab->even_share[st];
-      }
-    }
-    const RowPtr pairs = as_const((const uint32_t *)a.pairs);
+    const RowPtr pairs = as_const((const uint32_t *)a.pairs), steps = as_const((const uint32_t *)a.steps);
+    const float after_g = STRAT == 0 ? (float)cl->after[N - 4] : 0.0f;
+    const float after_y = STRAT == 0 ? (float)cl->after[N - 3] : 0.0f, after_m = STRAT == 0 ? (float)cl->after[N - 2] : 0.0f;
+    const float last_m = STRAT == 0 ? (float)(cl->steady[N - 2] + 1) : 0.0f;      // (0, a node that is gone: as good as no own term)
+    const float last_own = STRAT == 0 ? (float)(cl->steady[N - 1] + 1) : 0.0f;
 
-    int g = 0;                                         // cut H+1
-    i32x4 tg = tv;
-    // of the levels above the innermost loop, per lane (see the kernel's use of them)
-    int xf = 0, xb = 0, u_h = 0, v_h = 0, gmax = 0, both_lim = 0, lim = 0, off = 0;
-    int xf2 = 0, xb2 = 0, u_m = 0, v_m = 0, own_m = 0;
-    int u_g = 0, v_g = 0, own_h = 0, room = 0, layers_up = 0, rounds_low = 0, pen_up = 0;
-    int bf = 0, bb = 0, c0 = 0;
-    bool ok_g = ok;
-    if (STRAT != 0) {
-      both_lim = both;
-      off = comm;
-      lim = ok ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
-    }
-
-    auto upper_rank = [&](int m, int y) -> uint64_t {
-      uint64_t r = 0;
-      if (UP == 3) r = scn->binom[H + 1][g - 1];
-      return r + scn->binom[K - 1][m - 1] + scn->binom[K][y - 1];
+    i32x4 at[W + 1];                                   // prefixes at the cuts walked: at[0] = v, at[i] = cut G+i
+    int cut[W + 1];
+    at[0] = tv;
+    cut[0] = v;
+    // of the levels above the innermost loop: everything below stage N-2 (0: node N-3), the limit, and, strategy 0, what of the last nodes is
+    // the same for a row
+    struct Row {
+      Terms now;
+      float lim, off;
+      float um, vm, xb, xf;
+      int room;
     };
-    // the few that may win: other classes, weights to fetch, cost, ties by rank
-    auto consider = [&](uint64_t mask, int r, int m, int y, int pen, int pair_rounds) {
+    Row row[R];
+    float own_m = 0, c_m = 0;
+
+    // the few that may win: time of every class, weights to fetch, cost, ties by rank, all in integers
+    auto consider = [&](uint64_t mask, int y, int half) {
+      // (the compiler is not to know that cuts and tables are the same each time: kept across the loops, what follows from them takes the
+      // registers)
+      uint64_t tables = (uint64_t)(uintptr_t)scn, family = (uint64_t)(uintptr_t)ff;
+      asm volatile("" : "+s"(tables), "+s"(family));
+      const ScnPtr scn = (ScnPtr)(uintptr_t)tables;
+      const FamPtr ff = (FamPtr)(uintptr_t)family;
       int c[N + 1];
       c[0] = 0;
       c[N] = L;
+      uint32_t words[(G + 3) / 4];
 #pragma unroll
-      for (int i = 1; i <= H; ++i) c[i] = (int)((low_cuts[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
-      if (UP == 3) c[H + 1] = g;
-      c[K - 1] = m;
-      c[K] = y;
-      int step = r + off;                              // (off: what the limits of this level have been lowered by)
-      if (STRAT != 0) {
-        const int pens = pen_low + pen_up;
-        step = imax32(step - pens, fixed_step) + pens + pen;
-        if (rounds > 0) step += imax32(rounds_low, pair_rounds);
-      } else {
-        for (int ci = 1; ci < ff->n_time; ++ci)
-          step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[ci], [&](int i) { const int4 t = T[c[i]]; return make_int2(t.x, t.y); }));
+      for (int i = 0; i < (G + 3) / 4; ++i) {
+        words[i] = mine[0].cuts[i];
+        if (R == 2 && half != 0) words[i] = mine[R - 1].cuts[i];      // (uniform)
+        asm volatile("" : "+v"(words[i]));
       }
-      const bool near_best = ((mask >> lane) & 1u) && step <= limit;
+      asm volatile("" : "+s"(c[N]));
+#pragma unroll
+      for (int i = 1; i <= G; ++i) c[i] = (int)((words[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xffu);
+#pragma unroll
+      for (int i = 1; i < W; ++i) {
+        c[G + i] = cut[i];
+        asm volatile("" : "+s"(c[G + i]));
+      }
+      c[K] = y;
+      int step = STRAT == 1 ? ff->fixed_step : 0;
+      auto prefix_at = [&](int i) { return i == 0 ? make_int2(0, 0) : make_int2(T[c[i]].x, T[c[i]].y); };
+      if (STRAT != 0) {                                // (one class is timed)
+        step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[0], prefix_at));
+      } else {
+        for (int ci = 0; ci < ff->n_time; ++ci) {
+#pragma unroll
+          for (int i = 1; i <= G; ++i) asm volatile("" : "+v"(c[i]));
+          step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[ci], prefix_at));
+        }
+      }
+      if (STRAT == 2) {
+        for (int st = 0; st < scn->n_aff; ++st) {
+#pragma unroll
+          for (int s = 0; s < N; ++s)
+            if (scn->aff_stage[st] == s) {             // uniform
+              const int4 lo = T[c[s]], hi = T[c[s + 1]];
+              step += (int)even_penalty(scn, tab, st, hi.x - lo.x, hi.y - lo.y - (hi.x - lo.x));
+            }
+        }
+      }
+      if (rounds > 0) {
+        int layers = ff->fixed_layers;
+#pragma unroll
+        for (int s = 0; s < N; ++s) layers = imax32(layers, c[s + 1] - c[s]);
+        step += ff->allreduce * layers;
+      }
+      const bool near_best = ((mask >> lane) & 1u) && (float)step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;
       int wp[N + 1];
       wp[0] = 0;
@@ -357,243 +487,263 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
       for (int i = 1; i <= N; ++i) wp[i] = T[c[i]].z;
       const uint64_t cost = (uint64_t)scn->K * (uint32_t)step + (uint64_t)scn->reconf[STRAT] +
                             (uint64_t)scn->xfer * (uint32_t)missing_weights<N, STRAT>(ff, wp);
-      const uint64_t rank = (uint64_t)q + BN[(H - 1) * DEV_MAX_L + v - 1] + upper_rank(m, y);
+      uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + scn->binom[K][y - 1];
+#pragma unroll
+      for (int i = 1; i < W; ++i) rank += scn->binom[G + i][cut[i] - 1];
       if (near_best && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
-      const int seen = __builtin_amdgcn_readfirstlane(limit_of(wave_min(near_best ? cost : ~0ull)));
-      if (seen < limit) {
-        limit = seen;
-        lim = ok_g ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
+      // what others have found by now counts, too; they are told of what is lower than that
+      const uint64_t least = uniform64(wave_min(near_best ? cost : ~0ull));
+      const uint64_t known = uniform64(__hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (least < known && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
+      if (umin64(least, known) < low_cost) {
+        low_cost = umin64(least, known);
+        limit = limit_of(low_cost);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row[r].lim = __builtin_fminf(row[r].lim, limit - row[r].off);
       }
     };
 
-    // Innermost loop: upper halves whose last cut is y, y-1, ... (n of them), the others being fixed.  Two records a round, the
-    // next two on their way.
-    auto walk = [&](int row, int m, int y, uint32_t n, int c2, int own_z) {
-      // (y > m > 2: there are records ahead of (row, y))
-      RowPtr at = pairs + (size_t)(uint32_t)(row * (L + 1) + y - 1) * PAIR_WORDS;
-      u32x16 next = *(const CHM_CONST record_pair *)at;
+    // Innermost loop: last cuts m+n, m+n-1, ... m+1, the others being fixed; src = records of the first two.  Four records a round.
+    // (Strategies 1 and 2: a record behind the last one is HUGE_TIME.  m > 2: there are records ahead of the row.)
+    auto walk = [&](RowPtr src, int m, uint32_t n) {
       for (;;) {
-        const u32x16 r = next;
+        const u32x16 first = *(const CHM_CONST record_pair *)src, second = *(const CHM_CONST record_pair *)(src - 2 * PAIR_WORDS);
+        src -= 4 * PAIR_WORDS;
         constexpr int A = PAIR_WORDS, B = 0;           // words of y's record and of y - 1's
-        at -= 2 * PAIR_WORDS;
-        next = *(const CHM_CONST record_pair *)at;
-        const bool two = n >= 2;
-        // the longest class's time less what is common to the level (off)
-        auto time_of = [&](int o) -> int {
-          int su, sv, t;
+        auto may_win = [&](const Row &w, float zl, const u32x16 &r, int o, bool there) -> uint64_t {
+          auto word = [&](int i) { return __uint_as_float(r[i]); };
+          float t;
           if (STRAT == 0) {
-            const int end = (int)r[o + PAIR_END], cz = (int)r[o + PAIR_LAST] + zl;
-            const int last = end + (cz + c2);
-            t = (int)__umul24((uint32_t)cz, (uint32_t)own_z) + last;
-            su = imax32(imax32(last, (int)r[o + PAIR_ROUNDS] + c2), end + u_m);
-            sv = imax32(imax32(last, (int)r[o + PAIR_FIT] + c2), end + v_m);
-            t = imax32(t, su + sv + (own_m - end));
-            su = imax32(imax32(su, (int)r[o + PAIR_U]), end + xb2);
-            sv = imax32(imax32(sv, (int)r[o + PAIR_V]), end + xf2);
-            t = imax32(t, su + sv + (int)r[o + PAIR_OWN]);
-            if (UP == 3) {
-              su = imax32(su, u_h);
-              sv = imax32(sv, v_h);
-              t = imax32(t, su + sv + own_h);
-            }
-            su = imax32(su, u_g);
-            sv = imax32(sv, v_g);
-          } else {
-            su = imax32((int)r[o + PAIR_U], (int)r[o + PAIR_END] + xb2);
-            sv = imax32((int)r[o + PAIR_V], (int)r[o + PAIR_END] + xf2);
-            t = imax32((int)r[o + PAIR_LAST], su + sv + (int)r[o + PAIR_OWN]);
-            if (UP == 3) {
-              su = imax32(su, u_m);
-              sv = imax32(sv, v_m);
-              t = imax32(t, su + sv + own_m);
-            }
-            su = imax32(su, u_h);
-            sv = imax32(sv, v_h);
+            uint64_t fit = __builtin_amdgcn_ballot_w64((int)r[o + PAIR_FIT] <= w.room);
+            fit = there ? fit : 0;
+            n_fit += (uint32_t)__popcll(fit);
+            // times from the end of node N-3
+            const float end = word(o + PAIR_TERM), cz = word(o + PAIR_LAST) + zl;
+            const float su2 = fmax3(cz, w.um, word(o + PAIR_U)), sv2 = fmax3(cz, w.vm, word(o + PAIR_V));
+            const float su = fmax3(su2 + c_m, w.xb, word(o + PAIR_COST)), sv = fmax3(sv2 + c_m, w.xf, word(o + PAIR_V3));
+            t = fmax3(__builtin_fmaf(cz, last_own, c_m), su2 + sv2 + own_m, su + sv + fmax2(w.now.none + end, word(o + PAIR_OWN)));
+            t = fmax3(t, w.now.ou + sv, w.now.ov + su);
+            return __builtin_amdgcn_ballot_w64(t <= w.lim - end) & fit;
           }
-          t = imax32(t, su + sv + gmax);
-          t = imax32(imax32(t, only_u + sv), only_v + su);
-          return imax32(t, both_lim);
+          const float last = word(o + PAIR_LAST);
+          const float su = fmax2(w.now.mb - last, word(o + PAIR_U)), sv = fmax2(w.now.mf - last, word(o + PAIR_V));
+          t = fmax3(fmax2(w.now.none, word(o + PAIR_OWN)) + su + sv, w.now.ou + sv, w.now.ov + su);
+          t = fmax3(t, w.now.both, word(o + PAIR_TERM));
+          return __builtin_amdgcn_ballot_w64(t <= w.lim - word(o + PAIR_COST));
         };
-        uint64_t near_a, near_b;
-        int ta, tb2;
-        if (STRAT == 0) {
-          const uint64_t fit_a = __builtin_amdgcn_ballot_w64((int)r[A + PAIR_PENALTY] <= room);
-          uint64_t fit_b = __builtin_amdgcn_ballot_w64((int)r[B + PAIR_PENALTY] <= room);
-          fit_b = two ? fit_b : 0;
-          near_a = near_b = 0;
-          // (nothing to time where no lane fits: a cap that next to nothing fits)
-          if ((fit_a | fit_b) != 0) {
-            n_fit += (uint32_t)__popcll(fit_a) + (uint32_t)__popcll(fit_b);
-            ta = time_of(A);
-            near_a = __builtin_amdgcn_ballot_w64(ta <= lim) & fit_a;
-            if (two) {
-              tb2 = time_of(B);
-              near_b = __builtin_amdgcn_ballot_w64(tb2 <= lim) & fit_b;
-            }
-          }
-        } else {
-          auto test = [&](int o, int &t) -> uint64_t {
-            n_fit += r[o + PAIR_FIT];
-            t = time_of(o);
-            int w = t;
-            if (STRAT == 2) w += (int)r[o + PAIR_PENALTY];
-            if (rounds > 0) {                          // uniform
-              asm volatile("");                        // (kept a branch)
-              w += imax32(rounds_low, (int)r[o + PAIR_ROUNDS]);
-            }
-            return __builtin_amdgcn_ballot_w64(w <= lim);
-          };
-          near_a = test(A, ta);
-          near_b = 0;
-          if (two) near_b = test(B, tb2);
+        uint64_t near[4 * R] = {};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          near[4 * r] = may_win(row[r], mine[r].zl, first, A, true);
+          near[4 * r + 1] = may_win(row[r], mine[r].zl, first, B, n >= 2);
         }
-        if ((near_a | near_b) != 0) {
+        if (n > 2) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            near[4 * r + 2] = may_win(row[r], mine[r].zl, second, A, true);
+            near[4 * r + 3] = may_win(row[r], mine[r].zl, second, B, n >= 4);
+          }
+        }
+        uint64_t any = 0;
+#pragma unroll
+        for (int e = 0; e < 4 * R; ++e) any |= near[e];
+        if (any != 0) {
 #pragma unroll 1
-          for (int e = 0; e < 2; ++e) {
-            const bool b = e != 0;
-            const uint64_t mask = b ? near_b : near_a;
-            if (mask == 0 || (STRAT != 0 && (b ? r[B + PAIR_FIT] : r[A + PAIR_FIT]) == 0)) continue;
-            consider(mask, b ? tb2 : ta, m, b ? y - 1 : y, STRAT == 2 ? (int)(b ? r[B + PAIR_PENALTY] : r[A + PAIR_PENALTY]) : 0,
-                     (int)(b ? r[B + PAIR_ROUNDS] : r[A + PAIR_ROUNDS]));
+          for (int e = 0; e < 4 * R; ++e) {
+            uint64_t mask = near[0];
+#pragma unroll
+            for (int i = 1; i < 4 * R; ++i) mask = e == i ? near[i] : mask;
+            if (mask != 0) consider(mask, m + (int)n - (e & 3), e >> 2);
           }
         }
-        if (n <= 2) break;
-        n -= 2;
-        y -= 2;
+        if (n <= 4) break;
+        n -= 4;
       }
     };
-    // A bounded search: whether some lane may still win, given what the cuts placed so far are worth at least.  su, sv: lower bounds of
-    // the suffix maxima that reach the terms of node H (strategy 0: of node H-1) and below.
-    auto hopeless = [&](int su, int sv, int least) -> bool {
-      const int t = imax32(imax32(least, su + sv + gmax), imax32(imax32(only_u + sv, only_v + su), both_lim));
-      return __builtin_amdgcn_ballot_w64(t <= lim) == 0;
-    };
-    if (PRUNE && STRAT != 0 && __builtin_amdgcn_ballot_w64(both <= __builtin_elementwise_sub_sat(lim, pen_low)) == 0) left = 0;
-    while (left != 0) {
-      bool fits = true;
-      int pen_g = 0, c_h = 0, f_h = 0;
-      if (UP == 3) {
-        g = L - 1 - x[UP];
-        tg = pre[g];
-        if (STRAT != 0) {
-          // stage H = [v, g)
-          f_h = tg.x - tv.x;
-          c_h = tg.y - tv.y;
-          fits = scalar_peak(tv, tg, H) <= cap;
-          xf = imax32(mf, f_h);
-          xb = imax32(mb, c_h - f_h);
-          u_h = tg.y + (N - 1 - H) * xb;
-          v_h = tg.y + (N - 1 - H) * xf;
-          gmax = imax32(none, scalar_own(H, c_h, tg.y));
-          if (STRAT == 2) pen_g = (int)share_h * c_h;
-          layers_up = imax32(layers_low, g - v);
-          if (PRUNE) {
-            if (STRAT == 2) lim = ok ? __builtin_elementwise_sub_sat(limit, comm + pen_low + pen_g) : (int)0x80000000;
-            fits = fits && !hopeless(imax32(u_h, tl.y), imax32(v_h, tl.y), 0);
-          }
-        }
-      }
-      do {
-        const int m = L - 1 - x[2];
-        const i32x4 tm = pre[m];
-        uint32_t n = (uint32_t)(x[2] - x[1]);
-        n = n < left ? n : left;
-        left -= n;
-        const int y = L - 1 - x[1];
-        x[1] = 0;
-        ++x[2];
-        if (STRAT != 0) {
-          if (UP == 3) {
-            // stage N-3 = [g, m)
-            const int f = tm.x - tg.x, c = tm.y - tg.y;
-            if (!fits || scalar_peak(tg, tm, N - 3) > cap || n == 0) continue;
-            xf2 = imax32(xf, f);
-            xb2 = imax32(xb, c - f);
-            u_m = tm.y + 2 * xb2;
-            v_m = tm.y + 2 * xf2;
-            own_m = scalar_own(N - 3, c, tm.y);
-            pen_up = STRAT == 2 ? pen_g + (int)share_m * c : 0;
-            if (rounds > 0) rounds_low = rounds * imax32(layers_up, m - g);
-          } else {
-            // stage H = N-3 = [v, m)
-            const int f = tm.x - tv.x, c = tm.y - tv.y;
-            if (scalar_peak(tv, tm, H) > cap || n == 0) continue;
-            xf2 = imax32(mf, f);
-            xb2 = imax32(mb, c - f);
-            u_h = tm.y + 2 * xb2;
-            v_h = tm.y + 2 * xf2;
-            gmax = imax32(none, scalar_own(H, c, tm.y));
-            pen_up = STRAT == 2 ? (int)share_h * c : 0;
-            if (rounds > 0) rounds_low = rounds * imax32(layers_low, m - v);
-          }
-          if (STRAT == 2) {
-            off = comm + pen_low + pen_up;
-            lim = ok ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
-          }
-          if (PRUNE) {
-            int su = tl.y, sv = tl.y, least = 0;
-            if (UP == 3) {
-              su = imax32(su, u_m);
-              sv = imax32(sv, v_m);
-              least = su + sv + own_m;
-            }
-            if (hopeless(imax32(su, u_h), imax32(sv, v_h), least)) continue;
-          }
-          walk(m, m, y, n, 0, 0);
-        } else {
-          // node H-1 = [cut H-1, cut H+1); UP = 3: node H = [v, m); node N-2 = [m, L)
-          const i32x4 tu = UP == 3 ? tg : tm;
-          if (scalar_peak(tm, tl, N - 2) > cap || (UP == 3 && scalar_peak(tv, tm, H) > cap) || n == 0) continue;
-          const int coef_g = ff->mem_coef[H - 1];
-          const int need_g = coef_g < 0 ? 0 : tu.z + tu.w * coef_g;
-          ok_g = ok && need_g - tb.z <= cap;
-          const bool gone_g = gone(H - 1);
-          const int f0 = gone_g ? 0 : tu.x - tb.x;
-          c0 = gone_g ? 0 : tu.y - tb.y;
-          bf = imax32(mf, f0);
-          bb = imax32(mb, c0 - f0);
-          if (UP == 3 && !gone(H)) { f_h = tm.x - tv.x; c_h = tm.y - tv.y; } else { f_h = c_h = 0; }
-          const int base = UP == 3 ? tg.y : tv.y;      // end of node N-4 in the records' times
-          const int x1f = imax32(bf, f_h), x1b = imax32(bb, c_h - f_h);
-          const int p_g = base - c_h;
-          const int shift = sum_low + c0 - p_g;
-          u_g = p_g + (int)__umul24((uint32_t)bb, (uint32_t)cl->after[H - 1]);
-          v_g = p_g + (int)__umul24((uint32_t)bf, (uint32_t)cl->after[H - 1]);
-          const int k_g = cl->steady[H - 1];
-          gmax = imax32(none + shift, k_g < 0 ? HALVES_NEVER : (int)__umul24((uint32_t)c0, (uint32_t)k_g) - p_g);
-          if (UP == 3) {
-            u_h = base + (int)__umul24((uint32_t)x1b, (uint32_t)cl->after[H]);
-            v_h = base + (int)__umul24((uint32_t)x1f, (uint32_t)cl->after[H]);
-            own_h = scalar_own(H, c_h, base);
-          }
-          xb2 = (int)__umul24((uint32_t)x1b, (uint32_t)cl->after[N - 3]);
-          xf2 = (int)__umul24((uint32_t)x1f, (uint32_t)cl->after[N - 3]);
-          const int f2 = gone(N - 2) ? 0 : tl.x - tm.x, c2 = gone(N - 2) ? 0 : tl.y - tm.y;
-          u_m = c2 + (int)__umul24((uint32_t)imax32(x1b, c2 - f2), (uint32_t)cl->after[N - 2]);
-          v_m = c2 + (int)__umul24((uint32_t)imax32(x1f, f2), (uint32_t)cl->after[N - 2]);
-          own_m = scalar_own(N - 2, c2, c2);
-          both_lim = both - shift;
-          off = shift + comm;
-          lim = ok_g ? __builtin_elementwise_sub_sat(limit, off) : (int)0x80000000;
-          room = ok_g ? room_z : (int)0x80000000;
-          const int k_z = cl->steady[N - 1];
-          if (PRUNE) {
-            // (the ends of the records' nodes lie behind `base`)
-            int su = base + imax32(u_m, xb2), sv = base + imax32(v_m, xf2), least = 0;
-            if (UP == 3) {
-              su = imax32(su, u_h);
-              sv = imax32(sv, v_h);
-              least = su + sv + own_h;
-            }
-            if (hopeless(imax32(su, u_g), imax32(sv, v_g), least)) continue;
-          }
-          walk(UP == 3 ? g : v, m, y, n, c2, k_z < 0 ? 0 : k_z);
-        }
-      } while (left != 0 && UP == 3 && x[2] < x[UP]);
-      if (UP == 3) { ++x[UP]; x[2] = 1; }
-    }
-    if (STRAT != 0) n_fit *= low_fit;
 
+    // A loop's cut i (1 .. W-2) is placed: whether the stage it ends (0: the node it ends) fits (in any lane),
+    float off_i[R][W], layers_i[R][W];
+    Terms state[R][W];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      state[r][0] = mine[r].low;
+      off_i[r][0] = mine[r].ok ? mine[r].off : HUGE_TIME;        // (so that nothing above can win)
+      layers_i[r][0] = mine[r].layers;
+    }
+    auto fits = [&](auto level) -> bool {
+      constexpr int I = decltype(level)::value;
+      cut[I] = L - 1 - (int)x[W + 1 - I];
+      at[I] = pre[cut[I]];
+      if constexpr (STRAT == 0 && I == 1) {            // node G-1 = [cut G-1, cut G+1)
+        const int coef = ff->mem_coef[G - 1], need = coef < 0 ? 0 : at[1].z + at[1].w * coef;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const bool fit = mine[r].ok && need - mine[r].mem_b <= cap;
+          row[r].room = fit ? mine[r].room_z : (int)0x80000000;
+          off_i[r][1] = fit ? mine[r].off : HUGE_TIME;
+        }
+        return true;
+      } else if constexpr (STRAT == 0) {               // node s = [cut s, cut s+2)
+        return peak(at[I - 2], at[I], G + I - 2) <= cap;
+      } else {                                         // stage s = [cut s, cut s+1)
+        return peak(at[I - 1], at[I], G + I - 1) <= cap;
+      }
+    };
+    // it joins the state,
+    auto take_up = [&](auto level) {
+      constexpr int I = decltype(level)::value;
+      const float fetch = floorf((float)lacking<STRAT>(ff, at[I - 1].z, at[I].z, G + I - 1) * per_mib);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        Terms t = state[r][I - 1];
+        if constexpr (STRAT == 0) {
+          constexpr int s = G + I - 2;
+          const int f_0 = I == 1 ? mine[r].f_b : at[I == 1 ? 0 : I - 2].x, c_0 = I == 1 ? mine[r].c_b : at[I == 1 ? 0 : I - 2].y;
+          const float f = gone(s) ? 0.0f : (float)(at[I].x - f_0), c = gone(s) ? 0.0f : (float)(at[I].y - c_0);
+          t.add_from_end(f, c - f, c, gone(s) ? NEVER : (float)cl->steady[s] * c, (float)cl->after[s]);
+          off_i[r][I] = off_i[r][I == 1 ? 1 : I - 1] + (c + fetch);
+        } else {
+          constexpr int s = G + I - 1;
+          const int f = at[I].x - at[I - 1].x, c = at[I].y - at[I - 1].y, end = at[I].y - total;
+          t.add((float)f, (float)(c - f), (float)((M - N + s) * c - end) + shift, (float)(N - 1 - s), (float)end);
+          off_i[r][I] = off_i[r][I - 1] + fetch;
+          if (STRAT == 2) off_i[r][I] += (float)(int)(share[G + I - 1] * (uint32_t)c);
+          if (rounds > 0) layers_i[r][I] = fmax2(layers_i[r][I - 1], (float)(cut[I] - cut[I - 1]));
+        }
+        state[r][I] = t;
+      }
+    };
+    // and whether, in a bounded search, some lane may still win whatever the cuts above are (times of strategies 1 and 2 are less by the
+    // whole model's, which every term still gets).
+    auto may_win_yet = [&](auto level) -> bool {
+      constexpr int I = decltype(level)::value;
+      if (!PRUNE) return true;
+      uint64_t any = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const Terms &t = state[r][I];
+        any |= __builtin_amdgcn_ballot_w64(fmax2(fmax3(t.none, t.ou, t.ov), t.both) <= limit - off_i[r][I]);
+      }
+      return any != 0;
+    };
+    auto left_out = [&](uint32_t all) { left = left > all ? left - all : 0; };       // (the part may end sooner)
+    if (PRUNE && STRAT != 0) {
+      uint64_t any = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) any |= __builtin_amdgcn_ballot_w64(mine[r].low.both <= limit - off_i[r][0]);
+      if (any == 0) left = 0;
+    }
+    // cut K-1, and the innermost loop: the stage it ends comes from a record
+    auto over_m = [&] {
+      constexpr int P = W - 2;
+      const uint32_t width = (uint32_t)(L + 1) * PAIR_RECORD_WORDS;
+      int m = L - 1 - (int)x[2];
+      RowPtr step = steps + (uint32_t)(STRAT != 0 ? cut[P] : W == 2 ? 0 : cut[W == 2 ? 0 : P - 1]) * width + (uint32_t)m * STEP_WORDS;
+      RowPtr pair = pairs + (uint32_t)(STRAT != 0 ? m : cut[P]) * width + (uint32_t)(L - 2) * PAIR_WORDS;
+      u32x8 next = *(const CHM_CONST u32x8 *)step;
+      do {
+        const u32x8 rec = next;
+        step -= STEP_WORDS;
+        next = *(const CHM_CONST u32x8 *)step;         // (m > 1)
+        auto word = [&](int i) { return __uint_as_float(rec[i]); };
+        const uint32_t n = x[2];
+        cut[W - 1] = m;
+        bool open = rec[STEP_FIT] != 0;
+        if (open) {
+          uint64_t any = 0;
+          if constexpr (STRAT == 0) {
+            c_m = word(STEP_END);
+            own_m = c_m * last_m;
+          }
+          i32x4 tm = {};
+          if constexpr (STRAT == 0 && W == 2) tm = pre[m];
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            Row &w = row[r];
+            w.now = state[r][P];
+            if constexpr (STRAT == 0) {
+              float f = word(STEP_F), b = word(STEP_B), own = word(STEP_OWN);
+              if constexpr (W == 2) {                  // node N-4 = [cut G-1, m)
+                const int coef = ff->mem_coef[G - 1];
+                const bool fit = mine[r].ok && (coef < 0 ? 0 : tm.z + tm.w * coef) - mine[r].mem_b <= cap;
+                w.room = fit ? mine[r].room_z : (int)0x80000000;
+                f = gone(G - 1) ? 0.0f : (float)(tm.x - mine[r].f_b);
+                b = gone(G - 1) ? 0.0f : (float)(tm.y - mine[r].c_b) - f;
+                own = gone(G - 1) ? NEVER : (float)cl->steady[G - 1] * (f + b);
+              }
+              w.now.add_from_end(f, b, f + b, own, after_g);
+              w.off = off_i[r][P] + (f + b) + word(STEP_FETCH);
+              w.um = fmax2(w.now.mb, word(STEP_LAYERS)) * after_m;
+              w.vm = fmax2(w.now.mf, word(STEP_COST)) * after_m;
+              w.xb = w.now.mb * after_y;
+              w.xf = w.now.mf * after_y;
+              // (a path that turns at both ends within the nodes so far does not get longer)
+              w.lim = limit - w.off;
+              w.lim = w.now.both <= w.lim ? w.lim : NEVER;
+            } else {
+              w.now.add(word(STEP_F), word(STEP_B), word(STEP_OWN), 2.0f, word(STEP_END));
+              w.off = off_i[r][P] + word(STEP_COST);
+              // (rounds of communication: at least the layers of the largest stage so far)
+              int some = rounds;
+              asm volatile("" : "+s"(some));           // (kept a branch)
+              if (some > 0) w.off += (float)some * fmax2(layers_i[r][P], word(STEP_LAYERS));
+              w.lim = limit - w.off;
+            }
+            if (PRUNE) any |= __builtin_amdgcn_ballot_w64(fmax2(fmax3(w.now.none, w.now.ou, w.now.ov), w.now.both) <= w.lim);
+          }
+          if (PRUNE) open = any != 0;
+        }
+        if (open) {
+          if (STRAT != 0) fit_up += pair[2 * PAIR_WORDS + PAIR_FIT];
+          walk(pair, m, n);
+        }
+        if (STRAT != 0) pair -= width;
+        --m;
+        left -= n;
+        ++x[2];
+      } while (left != 0 && W >= 3 && x[2] < x[3]);
+    };
+    // the cuts before, if they are walked; one that is left out takes with it what is left of its choices of the cuts above
+    auto over_g = [&] {
+      if constexpr (W < 3) {
+        over_m();
+      } else {
+        constexpr std::integral_constant<int, W - 2> level;
+        auto leave_out = [&] { left_out(x[3] * (x[3] - 1) / 2 - x[2] * (x[2] - 1) / 2); };
+        do {
+          if (fits(level)) {
+            take_up(level);
+            if (may_win_yet(level)) over_m();
+            else leave_out();
+          } else {
+            leave_out();
+          }
+          ++x[3];
+          x[2] = 1;
+        } while (left != 0 && W >= 4 && x[3] < x[4]);
+      }
+    };
+    while (left != 0) {
+      if constexpr (W < 4) {
+        over_g();
+      } else {
+        constexpr std::integral_constant<int, W - 3> level;
+        auto leave_out = [&] {
+          left_out(x[4] * (x[4] - 1) * (x[4] - 2) / 6 - x[3] * (x[3] - 1) * (x[3] - 2) / 6 - x[2] * (x[2] - 1) / 2);
+        };
+        if (fits(level)) {
+          take_up(level);
+          if (may_win_yet(level)) over_g();
+          else leave_out();
+        } else {
+          leave_out();
+        }
+        ++x[4];
+        x[3] = 2;
+        x[2] = 1;
+      }
+    }
+    if (STRAT != 0) n_fit += fit_up * low_fit;
   }
   // ---- lowest cost of the workgroup, then lowest rank
   {
@@ -615,31 +765,27 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STRA
     if (cost != ~0ull) {
       // the chunk of 2^idx_bits ranks the plan lies in has words of its own
       const uint64_t chunk = rank >> a.s.idx_bits, local = rank & ((1ull << a.s.idx_bits) - 1ull);
-      if (cost < inc0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)cost);
       atomicMin((unsigned long long *)a.s.result + chunk * a.chunk_words + slot, (unsigned long long)((cost << a.s.idx_bits) | local));
     }
   }
 }
 
-template <int STRAT, int N, int UP>
-void launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
-  if (build) hipLaunchKernelGGL((k_pair_records<N, STRAT, UP>), dim3((a.n_pairs + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, st, a);
+template <int STRAT, int N>
+int launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
+  if (build) hipLaunchKernelGGL((k_cut_records<N, STRAT>), dim3((a.n_rows + BLOCK / 64 - 1) / (BLOCK / 64)), dim3(BLOCK), 0, st, a);
   const uint32_t blocks = (a.n_items + BLOCK / 64 - 1) / (BLOCK / 64);
-  if (a.bounded) hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
-  else hipLaunchKernelGGL((k_search_halves<N, STRAT, UP, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  if (a.bounded) hipLaunchKernelGGL((k_search_halves<N, STRAT, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  else hipLaunchKernelGGL((k_search_halves<N, STRAT, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  return 0;
 }
 
-// build: the table of pairs is filled first.  1 = no instance for this shape.
+// build: the tables are filled first.  1 = no instance for this number of stages.
 template <int STRAT>
-int halves_by_stages(int sp, int up, const HalvesLaunch &a, bool build, hipStream_t st) {
-#define CHM_CASE(SPV)                                                                                                        \
-  case SPV:                                                                                                                  \
-    if constexpr (SPV <= HALVES_TWO_UP_TO) { if (up == 2) { launch_halves<STRAT, SPV, 2>(a, build, st); return 0; } }        \
-    if constexpr (SPV >= HALVES_THREE_FROM) { if (up == 3) { launch_halves<STRAT, SPV, 3>(a, build, st); return 0; } }       \
-    return 1;
+int halves_by_stages(int sp, const HalvesLaunch &a, bool build, hipStream_t st) {
+#define CHM_CASE(SPV) case SPV: return launch_halves<STRAT, SPV>(a, build, st);
   switch (sp) {
 #ifdef CHM_TUNING_SUBSET
-    CHM_CASE(7) CHM_CASE(8)
+    CHM_CASE(7) CHM_CASE(8) CHM_CASE(10) CHM_CASE(11)
 #else
     CHM_CASE(5) CHM_CASE(6) CHM_CASE(7) CHM_CASE(8) CHM_CASE(9) CHM_CASE(10)
     CHM_CASE(11) CHM_CASE(12) CHM_CASE(13) CHM_CASE(14) CHM_CASE(15) CHM_CASE(16)

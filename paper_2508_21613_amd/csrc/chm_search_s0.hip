@@ -5,6 +5,6 @@
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant) {
   return launch_by_stages<0>(sp, a, blocks, tile_bytes, (hipStream_t)stream, variant);
 }
-int chmk_halves_s0(int sp, int up, const HalvesLaunch &a, bool build, void *stream) {
-  return halves_by_stages<0>(sp, up, a, build, (hipStream_t)stream);
+int chmk_halves_s0(int sp, const HalvesLaunch &a, bool build, void *stream) {
+  return halves_by_stages<0>(sp, a, build, (hipStream_t)stream);
 }
