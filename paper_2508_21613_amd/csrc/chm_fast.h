@@ -68,19 +68,21 @@ enum { HALVES_TWO_UP_TO = 11, HALVES_THREE_FROM = 9 };
 // What a wavefront of the search walks (chm_halves_kernel.h): the upper half's cuts and, of the lower half's, the last ones that leave its
 // lanes enough choices of the cuts below.  One more walked cut leaves an eighth of the lanes' set-ups (300 instructions) to a family of 8
 // stages, but more lanes idle (8 stages, 48 layers, two / three / four walked: strategy 0 91 / 82 / 114 us a search, strategy 2 85 / 85 / 113;
-// 7 stages 46 / 48; 11 stages of 48 layers, three / four 2,880 / 2,650).  From 10 stages on a lane keeps two choices: half the scalar
-// instructions and record loads a partition, for four wavefronts per SIMD instead of six (11 stages 2,960 us with one, 2,650 with two; 8 stages 47
-// and 48, strategy 0 52 and 58).
+// 7 stages 46 / 48; 12 stages, 31 layers, three / four 134 / 115).  A lane may keep two choices of the cuts below: half the scalar instructions and
+// record loads a partition, for four wavefronts per SIMD instead of five or six.  That pays where the search takes milliseconds and is
+// exhaustive (HALVES_TWO_CHOICES units of work; 5.2 G partitions of 11 stages 2,960 / 2,650 us; 8 stages 47 / 48, strategy 0 52 / 58; 29 M of
+// 15 stages, strategy 0 149 / 161).
 constexpr int halves_walked(int stages) { return stages <= 7 ? 2 : stages <= 10 ? 3 : 4; }
-constexpr int halves_choices(int stages) { return stages <= 9 ? 1 : 2; }
-constexpr int halves_waves(int stages) { return stages <= 7 ? 7 : stages <= 9 ? 6 : 4; }
+enum { HALVES_TWO_CHOICES_FROM = 10 };
+constexpr int halves_waves(int stages, int strategy, int choices) { return choices == 2 ? 4 : stages <= 7 ? (strategy == 0 ? 6 : 7) : stages <= 9 && strategy != 0 ? 6 : 5; }
 // How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
 struct HalvesShape {
   int up = 0;                   // cuts of an upper half
   uint64_t steps = 0;           // 64 lower halves x one upper half
   uint64_t setup = 0;           // lower halves to set up, in instructions, were a lane to keep each
-  uint32_t n_items = 0;         // wavefronts of the search
-  uint64_t units = 0;           // work to share out among them
+  // with one choice of the lower cuts a lane, with two:
+  uint32_t n_items[2] = {0, 0}; // wavefronts of the search
+  uint64_t units[2] = {0, 0};   // work to share out among them
 };
 
 struct FastState {
@@ -163,7 +165,7 @@ struct FamiliesLaunch {
 enum { PAIR_RECORD_WORDS = 8 };
 struct HalvesItems {
   int4 prefix[DEV_MAX_L + 1];   // prefix sums: forward, forward + backward, static memory, activation memory
-  uint64_t first[DEV_MAX_L];    // per last cut of the lanes, its first unit of work
+  uint64_t first[2][DEV_MAX_L]; // per last cut of the lanes, its first unit of work (lanes of one choice, of two)
   uint32_t share[DEV_MAX_S];    // strategy 2: reroute penalty of a stage as a multiple of its time
   uint32_t units[4 * DEV_MAX_L];            // row i - 1: units of i walked cuts whose leading digit is below x
   uint32_t binom[DEV_MAX_S * DEV_MAX_L];    // row i - 1: C(x, i), 0 < i <= lower cuts
@@ -176,8 +178,7 @@ __host__ __device__ inline uint64_t halves_blocks(const Scenario &h, int kept, i
   return (h->binom[kept - 1][v - 1] + 64 * choices - 1) / (64 * choices);
 }
 template <typename Scenario>
-__host__ __device__ inline uint64_t halves_units(const Scenario &h, int kept, int walked, int v) {
-  (void)kept;
+__host__ __device__ inline uint64_t halves_units(const Scenario &h, int walked, int v) {
   return HALVES_SETUP + h->binom[walked][h->L - 1 - v] + HALVES_ROW * h->binom[walked - 1][h->L - 2 - v];
 }
 struct HalvesLaunch {
@@ -187,6 +188,7 @@ struct HalvesLaunch {
   HalvesItems *items;
   uint32_t n_rows, n_items;     // layers + 1; wavefronts
   uint64_t n_units, per_item;   // units of work, of all and of a wavefront
+  uint32_t choices;             // of the lower cuts, a lane
   uint32_t bounded;             // 1: what the cuts placed so far make too slow is left out
   uint32_t chunk_words;         // words from one chunk's argmin words to the next chunk's
 };

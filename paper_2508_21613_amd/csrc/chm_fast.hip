@@ -301,6 +301,7 @@ constexpr uint64_t WIDER_BY = 4;
 // Units of work a wavefront is given at least where there is more than one round of them (8 stages, 48 layers, one round / two / three 82 / 84 / 88
 // us a search, strategy 0; 5.2 G partitions of 11 stages 3,240 / 2,880 / 2,660 us with 2 / 4 / 8 rounds).
 constexpr uint64_t HALVES_UNITS = 256;
+constexpr uint64_t HALVES_TWO_CHOICES = 1ull << 24;      // (see halves_walked)
 
 // wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts, `chunk` at most each; false: not
 // within the kernel's 32-bit ranks of lower halves
@@ -331,13 +332,15 @@ HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
 
 // The work of the search and the wavefronts it is shared out among: as many as are resident at a time, or several times as many where
 // each still has a few hundred units.
-void halves_share(const DevScenario &h, int sp, HalvesShape *hs) {
+void halves_share(const DevScenario &h, int sp, int k, HalvesShape *hs) {
   const int walked = halves_walked(sp), kept = sp - 1 - walked;
-  hs->units = 0;
-  for (int v = kept; v <= h.L - 1 - walked; ++v) hs->units += halves_units(&h, kept, walked, v) * halves_blocks(&h, kept, halves_choices(sp), v);
-  const uint64_t resident = 1024u * (uint64_t)halves_waves(sp);
-  const uint64_t rounds = std::min<uint64_t>(8, hs->units / (HALVES_UNITS * resident));
-  hs->n_items = (uint32_t)(rounds ? rounds * resident : std::max<uint64_t>(1, std::min<uint64_t>(resident, hs->units / 64)));
+  for (int c = 0; c < 2; ++c) {
+    hs->units[c] = 0;
+    for (int v = kept; v <= h.L - 1 - walked; ++v) hs->units[c] += halves_units(&h, walked, v) * halves_blocks(&h, kept, c + 1, v);
+    const uint64_t resident = 1024u * (uint64_t)halves_waves(sp, k, c + 1);
+    const uint64_t rounds = std::min<uint64_t>(8, hs->units[c] / (HALVES_UNITS * resident));
+    hs->n_items[c] = (uint32_t)(rounds ? rounds * resident : std::max<uint64_t>(1, std::min<uint64_t>(resident, hs->units[c] / 64)));
+  }
 }
 
 HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
@@ -356,7 +359,7 @@ HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
   const bool wide = two.up == 0 || (halves_cost(three) < halves_cost(two) && three.steps <= two.steps + two.steps / WIDER_BY);
   HalvesShape taken = three.up != 0 && wide ? three : two;
   if (taken.up == 0) return none;
-  halves_share(h, sp, &taken);
+  halves_share(h, sp, k, &taken);
   const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
   return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)std::min(ff.n_time, 2) + (unsigned)HALVES_SAVES ? taken : none;
 }
@@ -841,9 +844,10 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.tab = f->d_tables;
   hl.chunk_words = chunk_words;
   hl.bounded = bounded ? 1 : 0;
-  hl.n_items = hs.n_items;
-  hl.n_units = hs.units;
-  hl.per_item = (hs.units + hs.n_items - 1) / hs.n_items;
+  hl.choices = !bounded && sp >= HALVES_TWO_CHOICES_FROM && hs.units[0] >= HALVES_TWO_CHOICES ? 2 : 1;
+  hl.n_items = hs.n_items[hl.choices - 1];
+  hl.n_units = hs.units[hl.choices - 1];
+  hl.per_item = (hl.n_units + hl.n_items - 1) / hl.n_items;
   hl.n_rows = (uint32_t)(h.L + 1);
   hl.pairs = f->d_pairs[k];
   hl.steps = f->d_pairs[k] + words;

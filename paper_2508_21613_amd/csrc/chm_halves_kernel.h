@@ -36,20 +36,28 @@ __device__ __forceinline__ uint32_t even_penalty(ScnPtr scn, TabPtr tab, int st,
   return tab->even_share[st] * peer_time(f, b, scn->aff_q[st][0]);
 }
 constexpr float NEVER = -1e30f, HUGE_TIME = 1e30f;     // terms that do not exist, times of what does not fit
-// What a stage's node lacks of the weights it is to hold ([lo, hi) of the memory prefix, stage s), and the time of a step that fetching
-// that much costs, a whole number not above it (0 where the nodes' assignment is open).
-template <int STRAT>
+// What a stage's node lacks of the weights it is to hold ([lo, hi) of the memory prefix, stage s); where the nodes' assignment is open, what
+// the node lacks that holds most of them (N = 0: it is not).
+template <int N, int STRAT>
 __device__ __forceinline__ int lacking(FamPtr ff, int lo, int hi, int s) {
-  const int a = STRAT == 1 ? ff->cls[0].wlo[s] : ff->w0[s], b = STRAT == 1 ? ff->cls[0].whi[s] : ff->w0[s + 1];
-  return hi - lo - imax32(0, imin32(hi, b) - imax32(lo, a));
+  auto held = [&](int a, int b) { return imax32(0, imin32(hi, b) - imax32(lo, a)); };
+  if (STRAT != 1) return hi - lo - held(ff->w0[s], ff->w0[s + 1]);
+  const ClsPtr cl = &ff->cls[0];
+  if (N == 0 || !ff->assign) return hi - lo - held(cl->wlo[s], cl->whi[s]);
+  int most = 0;
+  for (int j = 0; j < N; ++j) most = imax32(most, held(cl->wlo[j], cl->whi[j]));
+  return hi - lo - most;
 }
-__device__ __forceinline__ float fetch_per_mib(ScnPtr scn, FamPtr ff, int strategy) {
-  return strategy == 1 && ff->assign ? 0.0f : (float)((double)scn->xfer / (double)scn->K) * 0.99999f;
+// time of a step that fetching so much costs: a whole number not above it
+__device__ __forceinline__ float fetch_time(ScnPtr scn, int mib) {
+  return floorf((float)mib * ((float)((double)scn->xfer / (double)scn->K) * 0.99999f));
 }
 constexpr int HALVES_UNFIT = 1 << 30;                  // in place of a share of a node's memory
 // A time is a chain of at most two additions a level and four more, of numbers up to six times as large: rounded to 24 bits
 // they stay within 2^-24 x 6 x (2 x 16 + 4) < 2^-16 of it.
 constexpr double SLACK = 1.0 + 1.0 / 65536;
+// Below this a time is exact: what it is the sum of, the whole model's time added twice at most, stays below 2^24.
+constexpr float EXACT_TIME = 4194304.0f;
 
 __device__ __forceinline__ float fmax2(float a, float b) { return __builtin_fmaxf(a, b); }
 __device__ __forceinline__ float fmax3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
@@ -94,7 +102,7 @@ enum { STEP_F = 0, STEP_B,  // forward and backward time
        STEP_END,            // 1, 2: prefix at m less the whole model's; 0: time of node N-2
        STEP_COST,           // 1, 2: reroute penalty of the stage, and the time to fetch what it lacks; 0: forward time of node N-2
        STEP_LAYERS,         // 1, 2: layers of the stage; 0: backward time of node N-2
-       STEP_FETCH,          // 0: time to fetch what the two last stages lack at least, wherever the last cut is
+       STEP_FETCH,          // 0: time to fetch what the two last stages lack at least, wherever the last cut is; 1: what [x, m) lacks (whole number)
        STEP_FIT,            // whether what the record holds fits (whole number)
        STEP_WORDS };
 static_assert((int)PAIR_WORDS == (int)PAIR_RECORD_WORDS && (int)STEP_WORDS == (int)PAIR_RECORD_WORDS, "a record of either kind");
@@ -110,15 +118,15 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
   const ClsPtr cl = &ff->cls[0];
   const int L = scn->L;
   if (blockIdx.x == 0) {
-    __shared__ uint64_t units[DEV_MAX_L];
-    const int v = (int)threadIdx.x;
-    if (v < DEV_MAX_L) units[v] = v >= G && v <= L - 1 - W ? halves_units(scn, G, W, v) * halves_blocks(scn, G, halves_choices(N), v) : 0;
+    // (one choice a lane, two choices a lane)
+    __shared__ uint64_t units[2 * DEV_MAX_L];
+    static_assert(BLOCK == 2 * DEV_MAX_L, "a thread for each");
+    const int v = (int)threadIdx.x % DEV_MAX_L, choices = (int)threadIdx.x / DEV_MAX_L + 1;
+    units[threadIdx.x] = v >= G && v <= L - 1 - W ? halves_units(scn, W, v) * halves_blocks(scn, G, choices, v) : 0;
     __syncthreads();
-    if (v < DEV_MAX_L) {
-      uint64_t first = 0;
-      for (int i = 0; i < v; ++i) first += units[i];
-      a.items->first[v] = first;
-    }
+    uint64_t first = 0;
+    for (int i = 0; i < v; ++i) first += units[(choices - 1) * DEV_MAX_L + i];
+    a.items->first[choices - 1][v] = first;
     for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) {
       const int n = i / DEV_MAX_L + 1, x = i % DEV_MAX_L;
       const uint64_t u = scn->binom[n][x] + (x > 0 ? HALVES_ROW * scn->binom[n - 1][x - 1] : 0);
@@ -160,8 +168,7 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
     dst[0] = make_uint4(__float_as_uint(rec[0]), __float_as_uint(rec[1]), __float_as_uint(rec[2]), __float_as_uint(rec[3]));
     dst[1] = make_uint4(__float_as_uint(rec[4]), __float_as_uint(rec[5]), __float_as_uint(rec[6]), last_word);
   };
-  const float per_mib = fetch_per_mib(scn, ff, STRAT);
-  auto lacks = [&](int lo, int hi, int s) { return lacking<STRAT>(ff, (int)scn->pw[lo], (int)scn->pw[hi], s); };
+  auto lacks = [&](int lo, int hi, int s) { return lacking<N, STRAT>(ff, (int)scn->pw[lo], (int)scn->pw[hi], s); };
   uint32_t n_fit = 0;
   for (int y0 = 0; y0 <= L; y0 += 64) {
     const int y = y0 + lane;
@@ -193,7 +200,7 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
       step[STEP_END] = c2;
       step[STEP_COST] = f2;
       step[STEP_LAYERS] = c2 - f2;
-      step[STEP_FETCH] = floorf((float)imax32(0, ff->w0[N - 2] - (int)scn->pw[hi]) * per_mib);
+      step[STEP_FETCH] = fetch_time(scn, imax32(0, ff->w0[N - 2] - (int)scn->pw[hi]));
       // (two cuts walked: node N-4 starts with the lanes' last cut but one, its memory is not looked at here)
       step_word = there && (W == 2 || memory(lo, hi, S) <= cap) && memory(hi, L, N - 2) <= cap ? 1u : 0u;
     } else {
@@ -203,14 +210,16 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
       pair[PAIR_V] = (float)imax32(0, f - last);
       pair[PAIR_OWN] = (float)((M - 2) * c + last) + (float)total;
       pair[PAIR_TERM] = fit ? (float)((M - 1) * last) + (float)total : HUGE_TIME;
-      pair[PAIR_COST] = penalty(lo, hi, N - 2) + penalty(hi, L, N - 1) + floorf((float)(lacks(lo, hi, N - 2) + lacks(hi, L, N - 1)) * per_mib);
+      pair[PAIR_COST] = penalty(lo, hi, N - 2) + penalty(hi, L, N - 1) + fetch_time(scn, lacks(lo, hi, N - 2) + lacks(hi, L, N - 1));
       n_fit += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(fit));
       pair_word = y == L ? n_fit : 0;
       step[STEP_F] = (float)f;
       step[STEP_B] = (float)(c - f);
       step[STEP_OWN] = (float)((M - 3) * c + last) + (float)total;
       step[STEP_END] = (float)-last;
-      step[STEP_COST] = penalty(lo, hi, N - 3) + floorf((float)lacks(lo, hi, N - 3) * per_mib);
+      const int lack = lacks(lo, hi, N - 3);
+      step[STEP_COST] = penalty(lo, hi, N - 3) + fetch_time(scn, lack);
+      step[STEP_FETCH] = __int_as_float(lack);         // (read where the assignment is open: of any stage)
       step[STEP_LAYERS] = (float)(hi - lo);
       step_word = there && memory(lo, hi, N - 3) <= cap ? 1u : 0u;
     }
@@ -249,9 +258,9 @@ __device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint
 // the head of the file.  The upper cuts that go with v are numbered by falling digits x (position = sum of C(x_i, i) over W of them), cut =
 // L-1-x; a stretch begins and ends with a row, a choice of all of them but the last.
 // PRUNE: a bounded search (compiled apart: its tests in the loops over the outer cuts cost the exhaustive search 5 % as a flag).
-template <int N, int STRAT, bool PRUNE>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halves_waves(N)))) k_search_halves(HalvesLaunch a) {
-  constexpr int K = N - 1, W = halves_walked(N), G = K - W, ROWS = G > W ? G : W, R = halves_choices(N);
+template <int N, int STRAT, int R, bool PRUNE>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halves_waves(N, STRAT, R)))) k_search_halves(HalvesLaunch a) {
+  constexpr int K = N - 1, W = halves_walked(N), G = K - W, ROWS = G > W ? G : W;
   constexpr int LOW = STRAT == 0 ? G - 1 : G;         // nodes the lanes' cuts alone decide
   __shared__ int4 T[DEV_MAX_L + 1];
   __shared__ uint32_t BN[ROWS * DEV_MAX_L], UN[W * DEV_MAX_L];
@@ -271,18 +280,18 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
   uint64_t best_cost = ~0ull, best_rank = ~0ull;
   uint32_t n_fit = 0;
-  uint64_t low_cost = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  uint64_t low_cost = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));     // lowest known
   // The item's part of all units of work: blocks of 64 choices of the lanes' cuts, v by v, each its set-up and its upper cuts in turn.
   uint64_t unit = (uint64_t)item * a.per_item;
   const uint64_t unit_end = umin64(unit + a.per_item, a.n_units);
   while (unit < unit_end) {
-    const uint64_t first_lo = a.items->first[lane], first_hi = a.items->first[lane + 64];
+    const uint64_t first_lo = a.items->first[R - 1][lane], first_hi = a.items->first[R - 1][lane + 64];
     // (units are numbered v by v: first grows with v, and is the same where v has none)
     const int v = (int)__popcll(__builtin_amdgcn_ballot_w64(first_lo <= unit)) + (int)__popcll(__builtin_amdgcn_ballot_w64(first_hi <= unit)) - 1;
-    const uint64_t behind = unit - as_const(a.items->first)[v];
+    const uint64_t behind = unit - as_const(a.items->first[R - 1])[v];
     const uint32_t n_up = (uint32_t)scn->binom[W][L - 1 - v];                // upper cuts that go with v
     const uint32_t n_low = (uint32_t)scn->binom[G - 1][v - 1];               // choices of the lanes' cuts that end with v
-    const uint32_t units = (uint32_t)halves_units(scn, G, W, v);
+    const uint32_t units = (uint32_t)halves_units(scn, W, v);
     const uint32_t low_block = (behind >> 32) == 0 ? (uint32_t)behind / units : (uint32_t)(behind / units);
     const uint32_t from = (uint32_t)(behind - (uint64_t)low_block * units);
     const uint32_t to = unit_end - unit < units - from ? from + (uint32_t)(unit_end - unit) : units;
@@ -311,7 +320,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     const int cap = (int)scn->cap;
     const int total = pre[L].y;
     const float shift = (float)total;
-    const float per_mib = fetch_per_mib(scn, ff, STRAT);
+    const bool open_nodes = STRAT == 1 && ff->assign != 0;
     const CHM_CONST uint32_t *share = as_const(a.items)->share;       // 2: share of a stage's time that its loss costs
     struct Choice {
       uint32_t cuts[(G + 3) / 4];                      // a byte each
@@ -371,9 +380,14 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
         }
       }
       int lacks = 0;
+      if (open_nodes) {
 #pragma unroll
-      for (int s = 0; s < G; ++s) lacks += lacking<STRAT>(ff, t[s].z, t[s + 1].z, s);
-      o.off += floorf((float)lacks * per_mib);
+        for (int s = 0; s < G; ++s) lacks += (int)a.steps[(uint32_t)(c[s] * (L + 1) + c[s + 1]) * STEP_WORDS + STEP_FETCH];
+      } else {
+#pragma unroll
+        for (int s = 0; s < G; ++s) lacks += lacking<0, STRAT>(ff, t[s].z, t[s + 1].z, s);
+      }
+      o.off += fetch_time(scn, lacks);
       if (STRAT == 0) {
         const int coef_g = ff->mem_coef[G - 1], coef_z = ff->mem_coef[N - 1];
         o.f_b = t[G - 1].x;
@@ -425,8 +439,15 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     Row row[R];
     float own_m = 0, c_m = 0;
 
+    auto lower_to = [&](uint64_t cost) {
+      low_cost = cost;
+      limit = limit_of(cost);
+#pragma unroll
+      for (int r = 0; r < R; ++r) row[r].lim = __builtin_fminf(row[r].lim, limit - row[r].off);
+    };
     // the few that may win: time of every class, weights to fetch, cost, ties by rank, all in integers
-    auto consider = [&](uint64_t mask, int y, int half) {
+    // (`here`: the lane has one; y, half and its time t, as far as that is a whole number, are its own)
+    auto consider = [&](bool here, int y, int half, float t) {
       // (the compiler is not to know that cuts and tables are the same each time: kept across the loops, what follows from them takes the
       // registers)
       uint64_t tables = (uint64_t)(uintptr_t)scn, family = (uint64_t)(uintptr_t)ff;
@@ -440,7 +461,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
 #pragma unroll
       for (int i = 0; i < (G + 3) / 4; ++i) {
         words[i] = mine[0].cuts[i];
-        if (R == 2 && half != 0) words[i] = mine[R - 1].cuts[i];      // (uniform)
+        if (R == 2) words[i] = half != 0 ? mine[R - 1].cuts[i] : words[i];
         asm volatile("" : "+v"(words[i]));
       }
       asm volatile("" : "+s"(c[N]));
@@ -455,7 +476,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       int step = STRAT == 1 ? ff->fixed_step : 0;
       auto prefix_at = [&](int i) { return i == 0 ? make_int2(0, 0) : make_int2(T[c[i]].x, T[c[i]].y); };
       if (STRAT != 0) {                                // (one class is timed)
-        step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[0], prefix_at));
+        if (__builtin_amdgcn_ballot_w64(here && t >= EXACT_TIME) == 0) step = imax32(step, (int)t + ff->cls[0].comm_total);
+        else step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[0], prefix_at));
       } else {
         for (int ci = 0; ci < ff->n_time; ++ci) {
 #pragma unroll
@@ -479,7 +501,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
         for (int s = 0; s < N; ++s) layers = imax32(layers, c[s + 1] - c[s]);
         step += ff->allreduce * layers;
       }
-      const bool near_best = ((mask >> lane) & 1u) && (float)step <= limit;
+      const bool near_best = here && (float)step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;
       int wp[N + 1];
       wp[0] = 0;
@@ -487,19 +509,16 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       for (int i = 1; i <= N; ++i) wp[i] = T[c[i]].z;
       const uint64_t cost = (uint64_t)scn->K * (uint32_t)step + (uint64_t)scn->reconf[STRAT] +
                             (uint64_t)scn->xfer * (uint32_t)missing_weights<N, STRAT>(ff, wp);
-      uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + scn->binom[K][y - 1];
+      uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + a.s.scn->binom[K][y - 1];
 #pragma unroll
       for (int i = 1; i < W; ++i) rank += scn->binom[G + i][cut[i] - 1];
       if (near_best && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
-      // what others have found by now counts, too; they are told of what is lower than that
       const uint64_t least = uniform64(wave_min(near_best ? cost : ~0ull));
-      const uint64_t known = uniform64(__hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      if (least < known && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
-      if (umin64(least, known) < low_cost) {
-        low_cost = umin64(least, known);
-        limit = limit_of(low_cost);
-#pragma unroll
-        for (int r = 0; r < R; ++r) row[r].lim = __builtin_fminf(row[r].lim, limit - row[r].off);
+      if (least < low_cost) {
+        // what others have found by now counts, too; they are told of what is lower than that
+        const uint64_t known = uniform64(__hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (least < known && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
+        lower_to(umin64(least, known));
       }
     };
 
@@ -510,50 +529,73 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
         const u32x16 first = *(const CHM_CONST record_pair *)src, second = *(const CHM_CONST record_pair *)(src - 2 * PAIR_WORDS);
         src -= 4 * PAIR_WORDS;
         constexpr int A = PAIR_WORDS, B = 0;           // words of y's record and of y - 1's
-        auto may_win = [&](const Row &w, float zl, const u32x16 &r, int o, bool there) -> uint64_t {
+        // a partition's time and what it may be at most (strategy 0: from the end of node N-3)
+        auto time_of = [&](const Row &w, float zl, const u32x16 &r, int o, float *most) -> float {
           auto word = [&](int i) { return __uint_as_float(r[i]); };
-          float t;
           if (STRAT == 0) {
-            uint64_t fit = __builtin_amdgcn_ballot_w64((int)r[o + PAIR_FIT] <= w.room);
-            fit = there ? fit : 0;
-            n_fit += (uint32_t)__popcll(fit);
-            // times from the end of node N-3
             const float end = word(o + PAIR_TERM), cz = word(o + PAIR_LAST) + zl;
             const float su2 = fmax3(cz, w.um, word(o + PAIR_U)), sv2 = fmax3(cz, w.vm, word(o + PAIR_V));
             const float su = fmax3(su2 + c_m, w.xb, word(o + PAIR_COST)), sv = fmax3(sv2 + c_m, w.xf, word(o + PAIR_V3));
-            t = fmax3(__builtin_fmaf(cz, last_own, c_m), su2 + sv2 + own_m, su + sv + fmax2(w.now.none + end, word(o + PAIR_OWN)));
-            t = fmax3(t, w.now.ou + sv, w.now.ov + su);
-            return __builtin_amdgcn_ballot_w64(t <= w.lim - end) & fit;
+            const float t = fmax3(__builtin_fmaf(cz, last_own, c_m), su2 + sv2 + own_m, su + sv + fmax2(w.now.none + end, word(o + PAIR_OWN)));
+            *most = w.lim - end;
+            return fmax3(t, w.now.ou + sv, w.now.ov + su);
           }
           const float last = word(o + PAIR_LAST);
           const float su = fmax2(w.now.mb - last, word(o + PAIR_U)), sv = fmax2(w.now.mf - last, word(o + PAIR_V));
-          t = fmax3(fmax2(w.now.none, word(o + PAIR_OWN)) + su + sv, w.now.ou + sv, w.now.ov + su);
-          t = fmax3(t, w.now.both, word(o + PAIR_TERM));
-          return __builtin_amdgcn_ballot_w64(t <= w.lim - word(o + PAIR_COST));
+          const float t = fmax3(fmax2(w.now.none, word(o + PAIR_OWN)) + su + sv, w.now.ou + sv, w.now.ov + su);
+          *most = w.lim - word(o + PAIR_COST);
+          return fmax3(t, w.now.both, word(o + PAIR_TERM));
         };
-        uint64_t near[4 * R] = {};
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          near[4 * r] = may_win(row[r], mine[r].zl, first, A, true);
-          near[4 * r + 1] = may_win(row[r], mine[r].zl, first, B, n >= 2);
-        }
-        if (n > 2) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            near[4 * r + 2] = may_win(row[r], mine[r].zl, second, A, true);
-            near[4 * r + 3] = may_win(row[r], mine[r].zl, second, B, n >= 4);
+        auto may_win = [&](int i, const u32x16 &r, int o, bool there) -> uint64_t {
+          float most;
+          const float t = time_of(row[i], mine[i].zl, r, o, &most);
+          uint64_t near = __builtin_amdgcn_ballot_w64(t <= most);
+          if (STRAT == 0) {
+            uint64_t fit = __builtin_amdgcn_ballot_w64((int)r[o + PAIR_FIT] <= row[i].room);
+            fit = there ? fit : 0;
+            n_fit += (uint32_t)__popcll(fit);
+            near &= fit;
           }
-        }
+          return near;
+        };
         uint64_t any = 0;
 #pragma unroll
-        for (int e = 0; e < 4 * R; ++e) any |= near[e];
-        if (any != 0) {
-#pragma unroll 1
-          for (int e = 0; e < 4 * R; ++e) {
-            uint64_t mask = near[0];
+        for (int i = 0; i < R; ++i) any |= may_win(i, first, A, true) | may_win(i, first, B, n >= 2);
+        if (n > 2) {
 #pragma unroll
-            for (int i = 1; i < 4 * R; ++i) mask = e == i ? near[i] : mask;
-            if (mask != 0) consider(mask, m + (int)n - (e & 3), e >> 2);
+          for (int i = 0; i < R; ++i) any |= may_win(i, second, A, true) | may_win(i, second, B, n >= 4);
+        }
+        if (__builtin_expect(any != 0, 0)) {
+          // the lanes' best ones together, then the next best, until none is left within the limit
+          float over[4 * R], time[4 * R];
+#pragma unroll
+          for (int e = 0; e < 4 * R; ++e) {
+            const int o = (e & 1) ? B : A;
+            const u32x16 &r = (e & 2) ? second : first;
+            float most;
+            time[e] = time_of(row[e >> 2], mine[e >> 2].zl, r, o, &most);
+            over[e] = time[e] - most;
+            const bool fit = (uint32_t)(e & 3) < n && (STRAT != 0 || (int)r[o + PAIR_FIT] <= row[e >> 2].room);
+            over[e] = fit ? over[e] : HUGE_TIME;
+          }
+#pragma unroll 1
+          for (;;) {
+            float least = over[0], t = time[0];
+            int which = 0;
+#pragma unroll
+            for (int e = 1; e < 4 * R; ++e) {
+              const bool less = over[e] < least;
+              least = less ? over[e] : least;
+              t = less ? time[e] : t;
+              which = less ? e : which;
+            }
+            const bool here = least <= 0.0f;
+            if (__builtin_amdgcn_ballot_w64(here) == 0) break;
+            const float before = limit;
+            consider(here, m + (int)n - (which & 3), which >> 2, t);
+            const float lowered = before - limit;
+#pragma unroll
+            for (int e = 0; e < 4 * R; ++e) over[e] = here && which == e ? HUGE_TIME : over[e] + lowered;
           }
         }
         if (n <= 4) break;
@@ -592,7 +634,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     // it joins the state,
     auto take_up = [&](auto level) {
       constexpr int I = decltype(level)::value;
-      const float fetch = floorf((float)lacking<STRAT>(ff, at[I - 1].z, at[I].z, G + I - 1) * per_mib);
+      int lack;
+      if (open_nodes) lack = (int)steps[(uint32_t)(cut[I - 1] * (L + 1) + cut[I]) * STEP_WORDS + STEP_FETCH];
+      else lack = lacking<0, STRAT>(ff, at[I - 1].z, at[I].z, G + I - 1);
+      const float fetch = fetch_time(scn, lack);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         Terms t = state[r][I - 1];
@@ -774,8 +819,10 @@ template <int STRAT, int N>
 int launch_halves(const HalvesLaunch &a, bool build, hipStream_t st) {
   if (build) hipLaunchKernelGGL((k_cut_records<N, STRAT>), dim3((a.n_rows + BLOCK / 64 - 1) / (BLOCK / 64)), dim3(BLOCK), 0, st, a);
   const uint32_t blocks = (a.n_items + BLOCK / 64 - 1) / (BLOCK / 64);
-  if (a.bounded) hipLaunchKernelGGL((k_search_halves<N, STRAT, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
-  else hipLaunchKernelGGL((k_search_halves<N, STRAT, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  if (a.bounded) hipLaunchKernelGGL((k_search_halves<N, STRAT, 1, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  else if (a.choices == 1) hipLaunchKernelGGL((k_search_halves<N, STRAT, 1, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  else if constexpr (N >= HALVES_TWO_CHOICES_FROM) hipLaunchKernelGGL((k_search_halves<N, STRAT, 2, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
+  else return 1;
   return 0;
 }
 

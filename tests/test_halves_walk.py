@@ -28,6 +28,8 @@ CASES = {
     "12 stages, little above the lanes' cuts": _case(25, 12, 2, 12, [11], cap_x=6.0),
     "16 stages, few layers more than stages": _case(26, 16, 2, 16, [15], cap_x=6.0, act=True),
 }
+CASES["13 stages, assignment open"] = _case(27, 14, 3, 15, [0], cap_x=5.0, transfer_assign=1, allreduce_us=300)
+CASES["7 stages, assignment open, two pipelines hit"] = _case(40, 8, 3, 10, [3, 14], transfer_assign=1, xfer_us_per_mib=3000)
 CASES.update({"8 stages, stages %d and %d lost" % (s, (s + 3) % 8): _case(35, 8, 4, 9, [s, 8 + (s + 3) % 8]) for s in range(8)})
 CASES.update({"11 stages, stage %d lost" % s: _case(27, 11, 3, 12, [s], cap_x=5.0) for s in (5, 6, 7, 8, 9, 10)})
 
