@@ -25,7 +25,7 @@ LIB = os.path.join(HERE, "libchm_san.so" if SANITIZE else "libchm.so")
 HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-omit-frame-pointer",
                  "-Xarch_host", "-g"]
 SOURCES = ["chm_host.cpp", "chm_pool.cpp", "chm_kernels.hip", "chm_fast.hip", "chm_search_s0.hip", "chm_search_s1.hip", "chm_search_s2.hip", "chm_families_8.hip",
-           "chm_families_12.hip", "chm_families_16.hip", "chm_families_24.hip", "chm_window.hip", "chm_replan.hip", "chm_probe.hip"]
+           "chm_families_12.hip", "chm_families_16.hip", "chm_families_24.hip", "chm_window.hip", "chm_list.hip", "chm_replan.hip", "chm_probe.hip"]
 # no device code meets a NaN: a maximum of floats is one instruction then, not one more for each operand that might be one;
 # packed-FP32 instruction selection is switched off for all device code; so is the vectorizer of straight-line code, which
 # finds nothing to gain in integer kernels and puts arrays it has half packed into scratch

@@ -251,6 +251,7 @@ int chmk_families_12(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, v
 int chmk_families_16(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);
 int chmk_families_24(int sp, int s1, const FamiliesLaunch &a, uint32_t blocks, void *stream);
 // Kernel launchers by strategy (chm_search_s0/1/2.hip): 1 = no instance for this number of stages, else 0.
+int chmk_list_best(int strategy, int sp, const FastLaunch &a, void *stream);       // 1 = no instance for these stages
 int chmk_fast_search_s0(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s1(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);
 int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t tile_bytes, void *stream, SearchVariant variant);

@@ -228,6 +228,9 @@ int launch_by_strategy(int strategy, int sp, const FastLaunch &a, uint32_t block
 // most stages the kernels are instantiated for: any search, and one that packs its cuts (bounded, cut lists)
 constexpr int PACKED_MAX_STAGES = 16;
 constexpr uint32_t LIST_TILES = 16;
+// Rows of cuts without stored costs: from this many on, what cannot win is left out (k_list_best).  2^20 rows: 8 stages with every option,
+// strategy 0 57 us one by one, 60 so, strategy 2 62 and 65, 16 stages 53 and 46; 1.5 * 2^20 rows: 66 and 63, 76 and 72, 61 and 51.
+constexpr uint32_t LIST_BEST_FROM = 3 << 19;
 bool stages_covered(int sp) { return sp >= 2 && sp <= DEV_MAX_S; }
 
 // Share of uniformly drawn partitions into `sp` stages whose largest per-node peak memory stays within the cap
@@ -538,6 +541,15 @@ bool ensure_scratch(FastState *f, uint64_t parts) {
   return ok;
 }
 
+// Whether the lower bound of a list's rows leaves anything out: it knows the step time alone, which over the horizon has to outweigh what
+// fetching the weights may cost (8 stages, 2^23 rows, a horizon of one step and dear weights: 115 us one by one, 130 with the bound; a horizon of
+// 2,048 steps 99 and 68).  24-bit multiplies have to do, too.
+bool times_decide(const DevScenario &h, const FastFamily &ff, int sp) {
+  if (ff.lb_prefix == 0 || ff.n_cls == 0) return false;
+  const double step = (double)ff.cls[0].M * (double)(h.pf[h.L] + h.pb[h.L]) / sp;
+  return (double)h.K * step >= (double)h.xfer * (double)h.pw[h.L];
+}
+
 // Explicit list of partition ranks or cut positions.
 int launch_list(FastState *f, const DevScenario &h, const SearchLaunch &a, hipStream_t st) {
   const int sp = h.fam[a.strategy].stages;
@@ -563,7 +575,9 @@ int launch_list(FastState *f, const DevScenario &h, const SearchLaunch &a, hipSt
     fl.cut_pos = nullptr;
     fl.cut_count = nullptr;
     const uint32_t blocks = (n + BLOCK * fl.per_lane - 1) / (BLOCK * fl.per_lane);
-    const int rc = launch_by_strategy(a.strategy, sp, fl, blocks, 0, st, SEARCH_LIST);
+    const FastFamily &ff = f->h_tables.fam[a.strategy];
+    const bool best_only = !bounded && a.cuts != nullptr && a.costs_out == nullptr && n >= LIST_BEST_FROM && times_decide(h, ff, sp);
+    const int rc = best_only ? chmk_list_best(a.strategy, sp, fl, st) : launch_by_strategy(a.strategy, sp, fl, blocks, 0, st, SEARCH_LIST);
     if (rc) return rc;
     if (hipGetLastError() != hipSuccess) return -1;
     done += n;

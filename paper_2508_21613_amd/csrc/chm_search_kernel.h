@@ -361,13 +361,10 @@ __device__ __forceinline__ void unrank_digits(Rank rem, int L, int steps, const 
 
 // largest peak memory over the nodes of a plan: static + (pipeline length - position) * activations of the
 // most demanding node of every stage (strategy 0: a node holds its stage and its ring successor's)
+// (at[] = memory prefix at the cuts)
 template <int SP, int STRAT>
-__device__ __forceinline__ int largest_peak(FamPtr ff, const int (&c)[SP + 1], const int *pw, const int *pa) {
+__device__ __forceinline__ int peak_from(FamPtr ff, const int (&c)[SP + 1], const int (&at)[SP + 1], const int *pa) {
   int mmax = 0;
-  int at[SP + 1];
-  at[0] = 0;
-#pragma unroll
-  for (int j = 1; j <= SP; ++j) at[j] = pw[c[j]];
   // strategy 0: [c[j], c[j+2]) is two stages; the last node's second one is stage 0
   if (ff->has_act) {
     int ac[SP + 1];
@@ -391,6 +388,15 @@ __device__ __forceinline__ int largest_peak(FamPtr ff, const int (&c)[SP + 1], c
     }
   }
   return mmax;
+}
+
+template <int SP, int STRAT>
+__device__ __forceinline__ int largest_peak(FamPtr ff, const int (&c)[SP + 1], const int *pw, const int *pa) {
+  int at[SP + 1];
+  at[0] = 0;
+#pragma unroll
+  for (int j = 1; j <= SP; ++j) at[j] = pw[c[j]];
+  return peak_from<SP, STRAT>(ff, c, at, pa);
 }
 
 // Weights a plan's nodes must fetch (MiB), from the memory prefix at its cuts: stage sizes minus what their nodes already

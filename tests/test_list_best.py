@@ -1,0 +1,69 @@
+"""Long lists of cut positions without stored costs (chm_list.hip), where a row is worked out only if a lower bound of its time may still win:
+the shortest list that goes there and the one before it, lists whose last workgroup is nearly empty, rows that are no partition (equal,
+falling, zero, 128 and more, behind the last layer), 128 layers, every option of the bound, times too long for it, a list of one and
+the same row, one in falling order of cost.  Winner, position and the number of rows that fit against the costs the same list stores; whole
+numbers, compared exactly."""
+import pytest
+
+from paper_2508_21613_amd import synth
+
+
+def _case(L, PP, DP, M, failed, cap_x=4.0, hetero=False, act=False, slowest=1, **kw):
+    fwd, bwd, mem = synth.layer_tables(23 * L + PP, L)
+    fwd[L // 2] *= slowest
+    bwd[L // 2] *= slowest
+    sc = synth.scenario(L, PP, DP, M, fwd, bwd, mem, failed, 150, int(cap_x * mem.sum() / PP),
+                        speed=synth.speed_factors(L, DP, PP) if hetero else None, **kw)
+    return synth.with_activations(sc, 5, cap_scale=1.1) if act else sc
+
+
+CASES = {
+    "2 stages, 128 layers": _case(128, 2, 3, 5, [1]),
+    "3 stages, the first lost": _case(128, 3, 2, 9, [0]),
+    "5 stages, every pipeline hit": _case(40, 5, 2, 12, [1, 8], cap_x=3.0),
+    "5 stages, the last lost": _case(60, 5, 3, 7, [4], allreduce_us=400),
+    "9 stages, every option": _case(33, 9, 3, 9, [3, 13], hetero=True, act=True, transfer_assign=1, allreduce_us=300),
+    "13 stages, uneven": _case(64, 13, 2, 40, [8], cap_x=5.0, hetero=True, reroute_cap=40),
+    "16 stages, one hit in each word of cuts": _case(48, 16, 5, 2, [3, 20, 40, 75], cap_x=5.0),
+    "16 stages, nothing fits": dict(_case(40, 16, 2, 20, [3]), mem_cap_mib=1),
+    "7 stages, times too long for the bound": _case(40, 7, 2, 24, [4], slowest=900),
+}
+SHORTEST = 3 << 19
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CASES)
+def test_the_winner_is_the_least_of_the_stored_costs(name):
+    import torch
+    from paper_2508_21613_amd import binding as B
+    sc = CASES[name]
+    g = B.Scenario(sc)
+    n = SHORTEST + 2049
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    for f in g.families:
+        k, width = f["strategy"], f["stages"] - 1
+        if width == 0:
+            continue
+        keys = (torch.rand((min(1 << 19, n - i), sc["L"] - 1), generator=gen, device="cuda") for i in range(0, n, 1 << 19))
+        rows = torch.cat([(x.topk(width, dim=1, sorted=False).indices + 1).sort(dim=1).values.to(torch.uint8) for x in keys])
+        for i, bad in enumerate((0, 128, 255, sc["L"])):                # one byte of a row of its own each, at every place
+            for j in range(width):
+                rows[100 * i + j, j] = bad
+        rows[1000] = rows[1001, 0]                                       # equal cuts
+        costs = torch.empty(n, dtype=torch.int64, device="cuda")
+        g.search_cuts(k, rows, costs=costs)
+        assert all(int(costs[100 * i + j]) == B.INFEASIBLE for i in range(4) for j in range(width))
+        falling = rows[torch.argsort(costs, descending=True, stable=True)].contiguous()
+        alike = rows[int(costs.argmin())].repeat(SHORTEST, 1)
+        for what in (rows[:SHORTEST - 1], rows[:SHORTEST], rows[:SHORTEST + 1], rows, falling, alike):
+            rc, best, pos = g.search_cuts(k, what.contiguous(), costs=costs[:len(what)])
+            fit = g.get_timing()["feasible"][k]
+            stored = costs[:len(what)]
+            assert fit == int((stored < B.INFEASIBLE).sum())
+            if fit:
+                least = int(stored.min())
+                assert (rc, best["cost"], pos) == (0, least, int((stored == least).nonzero()[0]))
+            assert g.search_cuts(k, what.contiguous()) == (rc, best, pos), len(what)
+            assert g.get_timing()["feasible"][k] == fit
+    g.close()
