@@ -31,7 +31,7 @@ ALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 # HBM bytes per launch = FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 KiB (factors from the 1 GiB calibration copy of the same runs)
 CONFIG2_TRAFFIC_BYTES = {0: (258.0 * 2.0 + 171.0) * 1024, 1: (289.0 * 2.0 + 55.0) * 1024, 2: (274.0 * 2.0 + 196.0) * 1024}
 # executed VALU lane-instructions per partition = SQ_INSTS_VALU x 64 / partitions of the family
-CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 33.3, 1: 33.8, 2: 29.6}
+CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 26.7, 1: 35.1, 2: 23.0}
 
 
 def note(msg):

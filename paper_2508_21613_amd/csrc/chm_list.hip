@@ -133,7 +133,7 @@ struct ListBound {
 constexpr int list_best_waves(int stages, int strategy) { return stages <= 8 && strategy != 2 ? 6 : 5; }
 
 // One workgroup to a share of the rows; a wavefront filters 64 rows a round and works out those in its ring that may win, 64 at a time.
-// Rows of a list come in no order, so that after the first 64 next to none can win: a row takes about 150 instructions (16 stages) instead of
+// Rows of a list come in no order, so that after the first 64 next to none can win: a row takes 160 to 215 instructions (16 stages) instead of
 // 190 to 330, and as the costs are few they are worked out stage after stage (class_time), in at most 96 registers: five or six wavefronts
 // per SIMD instead of three.  Bound by VALU issue and the prefixes' LDS reads.  2^23 rows of 16 stages: strategy 0 100 us -> 85, strategy 1
 // 111 -> 72, strategy 2 155 -> 91, of 8 stages 112 -> 76 (strategy 2).
