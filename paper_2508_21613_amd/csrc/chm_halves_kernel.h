@@ -56,6 +56,9 @@ constexpr int HALVES_UNFIT = 1 << 30;                  // in place of a share of
 // A time is a chain of at most two additions a level and four more, of numbers up to six times as large: rounded to 24 bits
 // they stay within 2^-24 x 6 x (2 x 16 + 4) < 2^-16 of it.
 constexpr double SLACK = 1.0 + 1.0 / 65536;
+// What a time less its limit, with that limit lowered later on, is rounded by at most, as a part of the limit before: six roundings of
+// 2^-24 (the limit less what all its partitions have, that less the record's share, the time less it, what the limit falls by less this, their sum).
+constexpr float LIMIT_ROUNDING = 1.0f / 2097152;
 // Below this a time is exact: what it is the sum of, the whole model's time added twice at most, stays below 2^24.
 constexpr float EXACT_TIME = 4194304.0f;
 
@@ -593,7 +596,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
             if (__builtin_amdgcn_ballot_w64(here) == 0) break;
             const float before = limit;
             consider(here, m + (int)n - (which & 3), which >> 2, t);
-            const float lowered = before - limit;
+            // (the new limit may be thousandths of the one before: a plan that fetches nothing behind one that fetches gigabytes)
+            const float lowered = before - limit - before * LIMIT_ROUNDING;
 #pragma unroll
             for (int e = 0; e < 4 * R; ++e) over[e] = here && which == e ? HUGE_TIME : over[e] + lowered;
           }
