@@ -74,7 +74,13 @@ enum { HALVES_TWO_UP_TO = 11, HALVES_THREE_FROM = 9 };
 // 15 stages, strategy 0 149 / 161).
 constexpr int halves_walked(int stages) { return stages <= 7 ? 2 : stages <= 10 ? 3 : 4; }
 enum { HALVES_TWO_CHOICES_FROM = 10 };
-constexpr int halves_waves(int stages, int strategy, int choices) { return choices == 2 ? 4 : stages <= 7 ? (strategy == 0 ? 6 : 7) : stages <= 9 && strategy != 0 ? 6 : 5; }
+// Wavefronts per SIMD: 5 from 8 stages on and 4 from 11 on, so that the set-up and the outer loops keep their vector registers (with six and
+// five up to 61 of them were spilled, which small families and strategy 1 paid for: us a search of all strategies, 14 stages, 25 layers
+// 114 / 90, 16 stages, 26 layers 149 / 119, 29 layers 510 / 446).  Strategy 0 of up to 13 stages, exhaustive, is better off with 5 (11 stages, 30
+// layers 71, 82 with 4; 37 layers 268 and 278).
+constexpr int halves_waves(int stages, int strategy, int choices, bool pruned) {
+  return choices == 2 ? 4 : stages <= 7 ? (strategy == 0 ? 6 : 7) : stages <= 10 || (strategy == 0 && stages <= 13 && !pruned) ? 5 : 4;
+}
 // How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
 struct HalvesShape {
   int up = 0;                   // cuts of an upper half

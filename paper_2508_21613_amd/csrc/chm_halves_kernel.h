@@ -262,11 +262,12 @@ __device__ __forceinline__ void unrank_by_bits(uint32_t rem, int end, const uint
 // L-1-x; a stretch begins and ends with a row, a choice of all of them but the last.
 // PRUNE: a bounded search (compiled apart: its tests in the loops over the outer cuts cost the exhaustive search 5 % as a flag).
 template <int N, int STRAT, int R, bool PRUNE>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halves_waves(N, STRAT, R)))) k_search_halves(HalvesLaunch a) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halves_waves(N, STRAT, R, PRUNE)))) k_search_halves(HalvesLaunch a) {
   constexpr int K = N - 1, W = halves_walked(N), G = K - W, ROWS = G > W ? G : W;
   constexpr int LOW = STRAT == 0 ? G - 1 : G;         // nodes the lanes' cuts alone decide
   __shared__ int4 T[DEV_MAX_L + 1];
   __shared__ uint32_t BN[ROWS * DEV_MAX_L], UN[W * DEV_MAX_L];
+  __shared__ uint64_t first_unit[DEV_MAX_L];
   __shared__ uint64_t wave_cost[BLOCK / 64], wave_rank[BLOCK / 64];
   __shared__ uint32_t wave_fit[BLOCK / 64];
   const ScnPtr scn = as_const(a.s.scn);
@@ -278,6 +279,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   for (int i = threadIdx.x; i <= L; i += BLOCK) T[i] = a.items->prefix[i];
   for (int i = threadIdx.x; i < ROWS * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
   for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) UN[i] = a.items->units[i];
+  if (threadIdx.x < DEV_MAX_L) first_unit[threadIdx.x] = a.items->first[R - 1][threadIdx.x];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
@@ -288,13 +290,14 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   uint64_t unit = (uint64_t)item * a.per_item;
   const uint64_t unit_end = umin64(unit + a.per_item, a.n_units);
   while (unit < unit_end) {
-    const uint64_t first_lo = a.items->first[R - 1][lane], first_hi = a.items->first[R - 1][lane + 64];
+    const uint64_t first_lo = first_unit[lane], first_hi = first_unit[lane + 64];
     // (units are numbered v by v: first grows with v, and is the same where v has none)
     const int v = (int)__popcll(__builtin_amdgcn_ballot_w64(first_lo <= unit)) + (int)__popcll(__builtin_amdgcn_ballot_w64(first_hi <= unit)) - 1;
-    const uint64_t behind = unit - as_const(a.items->first[R - 1])[v];
-    const uint32_t n_up = (uint32_t)scn->binom[W][L - 1 - v];                // upper cuts that go with v
-    const uint32_t n_low = (uint32_t)scn->binom[G - 1][v - 1];               // choices of the lanes' cuts that end with v
-    const uint32_t units = (uint32_t)halves_units(scn, W, v);
+    const uint64_t behind = unit - uniform64(first_unit[v]);
+    auto choose = [&](int x, int i) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)BN[(i - 1) * DEV_MAX_L + x]); };      // C(x, i)
+    const uint32_t n_up = choose(L - 1 - v, W);                // upper cuts that go with v
+    const uint32_t n_low = choose(v - 1, G - 1);               // choices of the lanes' cuts that end with v
+    const uint32_t units = HALVES_SETUP + n_up + HALVES_ROW * choose(L - 2 - v, W - 1);      // (halves_units)
     const uint32_t low_block = (behind >> 32) == 0 ? (uint32_t)behind / units : (uint32_t)(behind / units);
     const uint32_t from = (uint32_t)(behind - (uint64_t)low_block * units);
     const uint32_t to = unit_end - unit < units - from ? from + (uint32_t)(unit_end - unit) : units;
@@ -506,6 +509,11 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       }
       const bool near_best = here && (float)step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;
+      // What others have found by now counts, too; they are told of what is lower than that.  (Where the assignment is open, the weights take
+      // longer than to ask, and one wavefront may have to work out those of a whole cluster of partitions, one after the other.)
+      auto lowest_of_all = [&]() { return __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      uint64_t known = ~0ull;
+      if (open_nodes) known = lowest_of_all();
       int wp[N + 1];
       wp[0] = 0;
 #pragma unroll
@@ -517,12 +525,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       for (int i = 1; i < W; ++i) rank += scn->binom[G + i][cut[i] - 1];
       if (near_best && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
       const uint64_t least = uniform64(wave_min(near_best ? cost : ~0ull));
-      if (least < low_cost) {
-        // what others have found by now counts, too; they are told of what is lower than that
-        const uint64_t known = uniform64(__hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (least < known && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
-        lower_to(umin64(least, known));
-      }
+      if (!open_nodes && least < low_cost) known = lowest_of_all();
+      known = uniform64(known);
+      if (least < umin64(known, low_cost) && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
+      if (umin64(least, known) < low_cost) lower_to(umin64(least, known));
     };
 
     // Innermost loop: last cuts m+n, m+n-1, ... m+1, the others being fixed; src = records of the first two.  Four records a round.
@@ -738,7 +744,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
               if (some > 0) w.off += (float)some * fmax2(layers_i[r][P], word(STEP_LAYERS));
               w.lim = limit - w.off;
             }
-            if (PRUNE) any |= __builtin_amdgcn_ballot_w64(fmax2(fmax3(w.now.none, w.now.ou, w.now.ov), w.now.both) <= w.lim);
+            // (strategy 0: with the least that the last two nodes' turns add, and the own term of node N-2, whole by now)
+            const float none = STRAT == 0 ? w.now.none + (w.xb + w.xf) : w.now.none, ou = STRAT == 0 ? w.now.ou + w.xf : w.now.ou;
+            const float ov = STRAT == 0 ? w.now.ov + w.xb : w.now.ov, least = STRAT == 0 ? fmax2(w.now.both, w.um + w.vm + own_m) : w.now.both;
+            if (PRUNE) any |= __builtin_amdgcn_ballot_w64(fmax2(fmax3(none, ou, ov), least) <= w.lim);
           }
           if (PRUNE) open = any != 0;
         }
