@@ -20,6 +20,10 @@ __device__ __forceinline__ bool strictly_rising(const uint32_t (&w)[4]) {
 
 // With no more rows of 64 that fit than this, working them out costs less than the bound of all 64.
 constexpr int FEW_ROWS = 16;
+// Where more than so many eighths of the rows that fit pass the bound (a list of neighbours of one plan, or uneven speeds, which weaken the
+// bound), it is not looked at for a round, then three, seven, ...
+constexpr int USELESS_SHARE = 5;
+constexpr uint32_t LONGEST_STRETCH = 31;
 
 // cuts c[0..SP] from words of a byte each
 template <int SP>
@@ -63,10 +67,10 @@ struct ListBound {
     const double most = cost < reconf ? -1.0 : (double)(cost - reconf) * per_step + 1.0;
     limit = __builtin_amdgcn_readfirstlane(most < 2147483647.0 ? (int)most : 2147483647);
   }
-  // words = the cuts a byte each; cw = prefixes {forward + backward, memory}; in_memory: the lanes whose row fits
-  // (few rows that fit cost less than the bound)
+  // words = the cuts a byte each; cw = prefixes {forward + backward, memory}; in_memory: the lanes whose row fits; *look: whether the bound is
+  // to be looked at (false behind the call: it was not, for few rows that fit cost less than the bound)
   __device__ __forceinline__ bool passes(FamPtr ff, const uint32_t (&words)[4], int L, const int2 *cw, const int *pa, int cap, bool valid,
-                                         uint64_t *in_memory) const {
+                                         bool *look, uint64_t *in_memory) const {
     int t[SP + 1], at[SP + 1];
     t[0] = at[0] = 0;
 #pragma unroll
@@ -91,7 +95,8 @@ struct ListBound {
     }
     const bool fits = valid && peak <= cap;
     *in_memory = __builtin_amdgcn_ballot_w64(fits);
-    if (limit == 2147483647 || __popcll(*in_memory) <= FEW_ROWS) return fits;
+    *look = *look && limit != 2147483647 && __popcll(*in_memory) > FEW_ROWS;
+    if (!*look) return fits;                             // uniform
     int v = 0;
     if (STRAT == 0) {
       int before = 0;
@@ -129,16 +134,19 @@ struct ListBound {
   }
 };
 
-// Wavefronts per SIMD, and workgroups (of four) per compute unit: registers allow as many without spills.
-constexpr int list_best_waves(int stages, int strategy) { return stages <= 8 && strategy != 2 ? 6 : 5; }
+// Wavefronts per SIMD, and workgroups (of four) per compute unit: as many as the closed form's arrays leave without spilled vector registers
+// (strategy 2 spills about 50 scalars at any depth).
+constexpr int list_best_waves(int stages) { return stages <= 8 ? 5 : stages <= 12 ? 4 : 3; }
 
 // One workgroup to a share of the rows; a wavefront filters 64 rows a round and works out those in its ring that may win, 64 at a time.
 // Rows of a list come in no order, so that after the first 64 next to none can win: a row takes 160 to 215 instructions (16 stages) instead of
-// 190 to 330, and as the costs are few they are worked out stage after stage (class_time), in at most 96 registers: five or six wavefronts
-// per SIMD instead of three.  Bound by VALU issue and the prefixes' LDS reads.  2^23 rows of 16 stages: strategy 0 100 us -> 85, strategy 1
-// 111 -> 72, strategy 2 155 -> 91, of 8 stages 112 -> 76 (strategy 2).
+// 190 to 330.  Bound by VALU issue and the prefixes' LDS reads.  2^23 rows, us, one by one / so: 16 stages 119 / 84, 116 / 71 and 159 / 90
+// (strategies 0, 1, 2), 8 stages 98 / 64, 87 / 54 and 109 / 72, at uneven speeds 148 / 112, 95 / 60 and 242 / 116.  Lists of which nearly all
+// may win (neighbours of one plan, one row over and over) take what they take one by one, within 5 %: the bound is looked at ever more seldom
+// and times come from the closed form as there.  (Stage after stage, class_time, leaves room for a fifth or sixth wavefront per SIMD, but such lists
+// took 15 to 37 % longer and random ones no less.)
 template <int SP, int STRAT>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list_best_waves(SP, STRAT)))) k_list_best(FastLaunch a) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list_best_waves(SP)))) k_list_best(FastLaunch a) {
   constexpr int K = SP - 1;
   __shared__ uint4 q_cuts[(BLOCK / 64) * QCAP];
   __shared__ uint32_t q_pos[(BLOCK / 64) * QCAP];
@@ -193,13 +201,39 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
     unpack_cuts<SP>(words, L, c);
     int t_step = ff->fixed_step;
     // (what is not worked out yet only adds to the cost)
-    auto may_win = [&]() { return __builtin_amdgcn_ballot_w64(live && (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] <= low_cost) != 0; };
+    auto may_win = [&]() { return __builtin_amdgcn_ballot_w64(live && t_step <= bound.limit) != 0; };
     for (int ci = 0; ci < ff->n_time; ++ci) {
       const ClsPtr cl = &ff->cls[ci];
 #pragma unroll
       for (int j = 1; j <= K; ++j) asm volatile("" : "+v"(c[j]));
-      auto at = [&](int i) -> int2 { return i == 0 ? make_int2(0, 0) : TC[c[i]]; };
-      t_step = imax32(t_step, ff->time24 ? class_time<SP, STRAT, true, false>(cl, at) : class_time<SP, STRAT, false, false>(cl, at));
+      int F[SP], C[SP];
+      int2 t[SP + 1];
+      t[0] = make_int2(0, 0);
+#pragma unroll
+      for (int j = 1; j <= SP; ++j) t[j] = TC[c[j]];
+      const uint32_t dead = STRAT == 0 ? cl->dead : 0u;
+#pragma unroll
+      for (int j = 0; j < SP; ++j) {
+        const int e = STRAT == 0 ? (j + 2 <= SP ? j + 2 : SP) : j + 1;      // (strategy 0: a node runs two stages)
+        F[j] = t[e].x - t[j].x;
+        C[j] = t[e].y - t[j].y;
+        if (STRAT == 0) {
+          if (j == SP - 1) { F[j] += t[1].x; C[j] += t[1].y; }
+          const int keep = ((dead >> j) & 1u) ? 0 : -1;            // uniform
+          F[j] &= keep;
+          C[j] &= keep;
+        }
+      }
+      if (!cl->unit) {
+#pragma unroll
+        for (int j = 0; j < SP; ++j) {
+          const uint32_t q = cl->q_stage[j];
+          const int b = scale32(C[j] - F[j], q);
+          F[j] = scale32(F[j], q);
+          C[j] = F[j] + b;
+        }
+      }
+      t_step = imax32(t_step, pipeline_time<SP, STRAT == 0>(F, C, cl, ff->time24));
       if (!may_win()) return;
     }
     if (ff->allreduce > 0) {
@@ -229,13 +263,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
     const uint64_t cost = (uint64_t)scn->K * (uint32_t)t_step + (uint64_t)scn->reconf[STRAT] + (uint64_t)scn->xfer * (uint32_t)missing_weights<SP, STRAT>(ff, wp);
     // (the lower position wins among equal costs)
     if (live && (cost < best_cost || (cost == best_cost && pos < best_pos))) { best_cost = cost; best_pos = pos; }
-    const uint64_t least = uniform64(wave_min(live ? cost : ~0ull));
-    if (least < low_cost) {
-      low_cost = least;
-      bound.lower_to(least);
+    if (__builtin_amdgcn_ballot_w64(live && cost < low_cost) != 0) {
+      low_cost = uniform64(wave_min(live ? cost : ~0ull));
+      bound.lower_to(low_cost);
     }
   };
 
+  uint32_t unlooked = 0, stretch = 0;      // rounds the bound is not looked at any more, and how many the last time
   uint32_t words[4], next[4];
   row_of(0, next);
   for (uint32_t it = 0; it < a.per_lane; ++it) {
@@ -249,9 +283,16 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
 #pragma unroll
     for (int w = 0; w < 4; ++w) words[w] = valid ? words[w] : first[w];
     uint64_t in_memory;
-    const bool stays = bound.passes(ff, words, L, CW, PA, cap, entry < a.s.part_count && valid, &in_memory);
+    bool look = unlooked == 0;
+    const bool stays = bound.passes(ff, words, L, CW, PA, cap, entry < a.s.part_count && valid, &look, &in_memory);
     n_fit += (uint32_t)__popcll(in_memory);
     const uint64_t stay_mask = __builtin_amdgcn_ballot_w64(stays);
+    if (look) {
+      stretch = 8 * __popcll(stay_mask) > USELESS_SHARE * __popcll(in_memory) ? (stretch < LONGEST_STRETCH ? 2 * stretch + 1 : stretch) : 0;
+      unlooked = stretch;
+    } else if (unlooked != 0) {
+      --unlooked;
+    }
     if (stay_mask == 0) continue;           // uniform
     if (stays) {
       const uint32_t at_slot = (uint32_t)wave * QCAP + ((q_tail + (uint32_t)__popcll(stay_mask & ((1ull << lane) - 1ull))) & (QCAP - 1));
@@ -284,7 +325,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
 template <int STRAT>
 int launch_list_best(int sp, FastLaunch a, hipStream_t st) {
   // as many workgroups as are resident together
-  const uint32_t resident = 256u * (uint32_t)list_best_waves(sp, STRAT);
+  const uint32_t resident = 256u * (uint32_t)list_best_waves(sp);
   a.per_lane = (a.s.part_count + BLOCK * resident - 1) / (BLOCK * resident);
   const uint32_t blocks = (a.s.part_count + BLOCK * a.per_lane - 1) / (BLOCK * a.per_lane);
 #define CHM_CASE(SP) case SP: hipLaunchKernelGGL((k_list_best<SP, STRAT>), dim3(blocks), dim3(BLOCK), 0, st, a); return 0;

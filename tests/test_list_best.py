@@ -67,3 +67,42 @@ def test_the_winner_is_the_least_of_the_stored_costs(name):
             assert g.search_cuts(k, what.contiguous()) == (rc, best, pos), len(what)
             assert g.get_timing()["feasible"][k] == fit
     g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,sc", [("8 stages", _case(48, 8, 4, 16, [5])), ("8 stages, uneven", _case(48, 8, 4, 16, [5], hetero=True)),
+                                     ("15 stages left, uneven", _case(60, 16, 2, 24, [9], cap_x=5.0, hetero=True))], ids=lambda v: v if isinstance(v, str) else "")
+def test_lists_whose_bound_leaves_nothing_out(name, sc):
+    """neighbours of one plan, nearly all of which may win, so that rounds go by without a look at the bound; behind them random rows, for which
+    it counts again; the best row first, last, and at both ends of a round"""
+    import torch
+    from paper_2508_21613_amd import binding as B
+    g = B.Scenario(sc)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    n = 5 << 20
+    for f in g.families:
+        k, width = f["strategy"], f["stages"] - 1
+        rc, best = g.search_range(k, f["n_part"] // 3, 1 << 18)
+        assert rc == 0
+        plan = torch.tensor(best["cuts"][:width], dtype=torch.int16, device="cuda")
+        rows = plan.repeat(n, 1)
+        rows += torch.randint(-1, 2, rows.shape, generator=gen, device="cuda", dtype=torch.int16)
+        rising = (rows[:, 1:] > rows[:, :-1]).all(1) & (rows[:, 0] > 0) & (rows[:, -1] < sc["L"])
+        rows = torch.where(rising[:, None], rows, plan[None]).to(torch.uint8)
+        keys = torch.rand((1 << 19, sc["L"] - 1), generator=gen, device="cuda")
+        rows[n // 2:n // 2 + (1 << 19)] = (keys.topk(width, dim=1, sorted=False).indices + 1).sort(dim=1).values.to(torch.uint8)
+        costs = torch.empty(n, dtype=torch.int64, device="cuda")
+        g.search_cuts(k, rows, costs=costs)
+        fit = g.get_timing()["feasible"][k]
+        assert fit == int((costs < B.INFEASIBLE).sum()) > n // 4
+        lowest = rows[int(costs.argmin())].clone()
+        least = int(costs.min())
+        rows = rows[costs > least].contiguous()                          # no other row is as good as the one put in
+        for at in (0, len(rows) - 1, 64 * 4000, 64 * 4000 + 63, len(rows) // 2 + 17):
+            kept = rows[at].clone()
+            rows[at] = lowest
+            rc, got, pos = g.search_cuts(k, rows)
+            assert (rc, got["cost"], pos) == (0, least, at), (k, at)
+            rows[at] = kept
+    g.close()
