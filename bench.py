@@ -369,7 +369,7 @@ def bench_lists(args, B, synth):
                 for st, d_cuts in lists.items():
                     rc_m, best_m, pos_m = g.search_cuts(st, d_cuts, stream=stream)
                     winners.setdefault(st, []).append((rc_m, pos_m, best_m["cost"]))
-                    evaluated[st] = g.get_timing()["feasible"][st]
+                    evaluated[st] = g.get_timing()["evaluated"][st]
             stream.synchronize()
             modes[mode] = {"ms_per_step": (time.perf_counter() - t0) * 1e3 / args.steps, "entries_evaluated": [float(x) for x in evaluated]}
         g.set_bounded_search(0)

@@ -172,9 +172,10 @@ int chm_search_cuts(chm_scenario *s, int32_t strategy, const uint8_t *d_cuts, ui
  * step time of every partition of every selected family are worked out on the device; for data
  * rerouting with the least penalty over every reroute vector of every stage that lost nodes (an order
  * statistic: the orphans-th smallest multiple of the peers' stage times; the penalty is a sum of
- * independent per-stage terms).  In large families (2^21 partitions and more, searched by halves) and in long lists of strategy 0 the time
+ * independent per-stage terms).  In large families (2^21 partitions and more, searched by halves) the time
  * of other pipeline classes than the one with the most work and the transition time are worked out where the terms before them do not
- * already exceed the lowest cost met so far.  Ties go to the
+ * already exceed the lowest cost met so far.  (Lists, chm_search_cuts and chm_search_ranks: likewise; of long ones without stored costs, more
+ * than 1.5 * 2^20 rows of cuts, pipeline times are worked out only of rows whose lower bound does not exceed it.)  Ties go to the
  * lowest plan index.  Synchronises hip_stream before returning.  Errors:
  * CHM_ERR_UNRECOVERABLE (mask selects no existing family), CHM_ERR_NO_FEASIBLE (out is
  * filled with index UINT64_MAX, cost CHM_INFEASIBLE), CHM_ERR_OVERFLOW (the selected families hold more

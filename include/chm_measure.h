@@ -25,9 +25,10 @@ typedef struct {
   uint64_t evaluations[3];     /* (partition, reroute vector) evaluations per strategy               */
   uint64_t feasible[3];        /* partitions per strategy that passed the memory filter              */
   uint64_t evaluated[3];       /* of those, partitions whose pipeline times were worked out: all of
-                                * them, or fewer in a bounded search (chm_set_bounded_search).  (By
-                                * halves, and in long lists of strategy 0: the time of the class with
-                                * the most work; the others only where it does not decide.)           */
+                                * them, or fewer in a bounded search (chm_set_bounded_search) and in a
+                                * list of 1.5 * 2^20 rows of cuts or more without stored costs.  (By
+                                * halves, and in long lists: the time of the class with the most work;
+                                * the others only where it does not decide.)                          */
 } chm_timing;
 
 /* Which kernels a scenario would run on, decided from the description alone (host only, no device needed; the

@@ -247,6 +247,9 @@ int fast_search(FastState *f, const DevScenario &h, const SearchLaunch &a, void 
 // Whether fast_search would run this launch as a bounded search if a.incumbent were set (a search of a covered
 // strategy of at most 16 stages without cost store).
 bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch &a);
+// Whether fast_search would take a list of n entries, of which this launch is a part, to the kernel that leaves out rows that cannot win
+// (k_list_best).  It does where a.evaluated is set, the counters of the rows whose times are worked out.
+bool fast_list_leaves_out(const FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t n);
 // The range searches of up to three families (one launch argument each, at most one per strategy) in one launch, exhaustive; an
 // incumbent word set in them is lowered by what they find.  Same return convention; positive: some family is not covered, their
 // stages have no common instance, or they are large enough to fill the device one after the other.

@@ -577,8 +577,7 @@ int launch_list(FastState *f, const DevScenario &h, const SearchLaunch &a, hipSt
     fl.cut_pos = nullptr;
     fl.cut_count = nullptr;
     const uint32_t blocks = (n + BLOCK * fl.per_lane - 1) / (BLOCK * fl.per_lane);
-    const FastFamily &ff = f->h_tables.fam[a.strategy];
-    const bool best_only = !bounded && a.cuts != nullptr && a.costs_out == nullptr && n >= LIST_BEST_FROM && times_decide(h, ff, sp);
+    const bool best_only = !bounded && a.evaluated != nullptr;
     const int rc = best_only ? chmk_list_best(a.strategy, sp, fl, st) : launch_by_strategy(a.strategy, sp, fl, blocks, 0, st, SEARCH_LIST);
     if (rc) return rc;
     if (hipGetLastError() != hipSuccess) return -1;
@@ -836,6 +835,11 @@ float fast_fit_share(FastState *f, const DevScenario &h, int k) {
 bool fast_can_bound(const FastState *f, const DevScenario &h, const SearchLaunch &a) {
   if (a.strategy < 0 || a.strategy > 2 || !f->usable[a.strategy]) return false;
   return a.costs_out == nullptr && h.fam[a.strategy].stages <= PACKED_MAX_STAGES;
+}
+
+bool fast_list_leaves_out(const FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t n) {
+  if (!fast_can_bound(f, h, a) || a.cuts == nullptr || a.incumbent != nullptr || n < LIST_BEST_FROM) return false;
+  return times_decide(h, f->h_tables.fam[a.strategy], h.fam[a.strategy].stages);
 }
 
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_t partitions) {

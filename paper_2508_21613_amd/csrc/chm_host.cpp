@@ -592,7 +592,7 @@ struct SearchCtx {
   std::vector<Slot> slots;
   std::vector<size_t> slot_job;          // index into jobs
   uint32_t ways = 1, stride = 1, chunk_words = 1, key_words = 0;
-  bool bounded_used[3] = {false, false, false};
+  bool counted[3] = {false, false, false};         // its kernels count what they evaluate, of what fits
   int ev_of[3] = {-1, -1, -1};
   bool device_finish = false;            // the winner was picked by k_finish_search; one record waits in h_pinned
   bool light = false;
@@ -766,7 +766,10 @@ int launch_jobs(chm_scenario *s, const std::vector<Job> &jobs, bool want_result,
       if ((bounded || j.publish) && fast_can_bound(&s->fast, s->h, a)) {
         a.incumbent = d_incumbent;
         a.evaluated = j.seed ? d_seed_count : d_evaluated + (size_t)j.strategy * c.chunk_words;
-        c.bounded_used[j.strategy] |= !j.publish && !(j.ranks || j.cuts);   // lists: what passes their filter is evaluated and counted as fitting
+        c.counted[j.strategy] |= !j.publish && !(j.ranks || j.cuts);   // lists: what passes their filter is evaluated and counted as fitting
+      } else if (fast_list_leaves_out(&s->fast, s->h, a, j.count)) {
+        a.evaluated = d_evaluated + (size_t)j.strategy * c.chunk_words;
+        c.counted[j.strategy] = true;
       }
       int rc = fast_search(&s->fast, s->h, a, st);      // > 0: shape not covered by a specialised kernel
       if (rc > 0) rc = chmk_search(a, s->smax, st);
@@ -846,7 +849,7 @@ int collect_jobs(chm_scenario *s, chm_best *out, uint64_t *position, hipStream_t
     const uint64_t *rec = s->h_pinned;
     for (int k = 0; k < 3; ++k) { s->last.feasible[k] += rec[FINISH_COUNTS + k]; s->last.evaluated[k] += rec[FINISH_COUNTS + 3 + k]; }
     for (int k = 0; k < 3; ++k)
-      if (!c.bounded_used[k]) s->last.evaluated[k] = s->last.feasible[k];
+      if (!c.counted[k]) s->last.evaluated[k] = s->last.feasible[k];
     if (const int rc = read_timing(s)) return rc;
     if (rec[FINISH_STRATEGY] == ~0ull) { nothing_found(out); return CHM_ERR_NO_FEASIBLE; }
     best_cost = (int64_t)rec[FINISH_COST];
@@ -874,7 +877,7 @@ int collect_jobs(chm_scenario *s, chm_best *out, uint64_t *position, hipStream_t
     }
   // kernels that evaluate everything that fits do not count what they evaluate
   for (int k = 0; k < 3; ++k)
-    if (!c.bounded_used[k]) s->last.evaluated[k] = s->last.feasible[k];
+    if (!c.counted[k]) s->last.evaluated[k] = s->last.feasible[k];
   if (const int rc = read_timing(s)) return rc;
   // lowest cost; among equal costs the lowest plan index (strategy, then partition)
   const Job *best_job = nullptr;

@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
   __shared__ int2 CW[DEV_MAX_L + 1], TC[DEV_MAX_L + 1];      // prefixes: {forward + backward, memory}, {forward, forward + backward}
   __shared__ int PA[DEV_MAX_L + 1];
   __shared__ uint64_t wave_keys[BLOCK / 64];
-  __shared__ uint32_t wave_fit[BLOCK / 64];
+  __shared__ uint32_t wave_fit[BLOCK / 64], wave_worked[BLOCK / 64];
   const ScnPtr scn = as_const(a.s.scn);
   const TabPtr tab = as_const(a.tab);
   const FamPtr ff = &tab->fam[STRAT];
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
 
   const int cap = (int)scn->cap;
   uint64_t best_cost = ~0ull;
-  uint32_t best_pos = 0, n_fit = 0, q_head = 0, q_tail = 0;
+  uint32_t best_pos = 0, n_fit = 0, n_worked = 0, q_head = 0, q_tail = 0;
   // Row of round `it`: neighbouring lanes read neighbouring rows, a workgroup's rounds lie across the whole list, the last one comes first: in
   // a list in order of cost, rising or falling, the lowest costs are met within two rounds.
   auto entry_of = [&](uint32_t it) { return ((it == 0 ? a.per_lane - 1 : it - 1) * gridDim.x + blockIdx.x) * BLOCK + threadIdx.x; };
@@ -192,6 +192,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
   // up to 64 rows of the ring, one a lane: their costs
   auto work_out = [&](uint32_t take) {
     const bool live = (uint32_t)lane < take;
+    n_worked += take;
     const uint32_t at_slot = (uint32_t)wave * QCAP + ((q_head + (uint32_t)lane) & (QCAP - 1));
     // (lanes past the end take the first partition, cuts 1..K: always valid)
     const uint4 packed = live ? q_cuts[at_slot] : make_uint4(0x04030201u, 0x08070605u, 0x0c0b0a09u, 0x000f0e0du);
@@ -308,16 +309,17 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
 
   uint64_t key = best_cost == ~0ull ? CHM_KEY_NONE : ((best_cost << a.s.idx_bits) | (uint64_t)best_pos);
   key = wave_min(key);
-  if (lane == 0) { wave_keys[wave] = key; wave_fit[wave] = n_fit; }
+  if (lane == 0) { wave_keys[wave] = key; wave_fit[wave] = n_fit; wave_worked[wave] = n_worked; }
   __syncthreads();
   if (threadIdx.x == 0) {
     // one atomic of each kind per workgroup, spread over several words (see SearchLaunch)
     const uint32_t word = (blockIdx.x & a.s.slot_mask) * a.s.slot_stride;
     uint64_t k = wave_keys[0];
-    uint32_t fit = wave_fit[0];
+    uint32_t fit = wave_fit[0], worked = wave_worked[0];
 #pragma unroll
-    for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; }
+    for (int i = 1; i < BLOCK / 64; ++i) { k = umin64(k, wave_keys[i]); fit += wave_fit[i]; worked += wave_worked[i]; }
     if (fit) atomicAdd((unsigned long long *)a.s.feasible + word, (unsigned long long)fit);
+    if (worked) atomicAdd((unsigned long long *)a.s.evaluated + word, (unsigned long long)worked);
     if (k != CHM_KEY_NONE) atomicMin((unsigned long long *)a.s.result + word, (unsigned long long)k);
   }
 }

@@ -66,6 +66,12 @@ def test_the_winner_is_the_least_of_the_stored_costs(name):
                 assert (rc, best["cost"], pos) == (0, least, int((stored == least).nonzero()[0]))
             assert g.search_cuts(k, what.contiguous()) == (rc, best, pos), len(what)
             assert g.get_timing()["feasible"][k] == fit
+            worked_out = g.get_timing()["evaluated"][k]
+            assert (worked_out == 0) == (fit == 0) and worked_out <= fit
+            if len(what) < SHORTEST or name.endswith("too long for the bound"):
+                assert worked_out == fit
+            elif what is rows and sc["PP"] >= 5 and sc["speed_q16"] is None and fit > n // 2:
+                assert worked_out < fit // 2, (worked_out, fit)           # next to nothing can win behind the first rounds
     g.close()
 
 
