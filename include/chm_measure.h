@@ -56,6 +56,16 @@ int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
  * CHM_ERR_OVERFLOW. */
 int chm_halves_selection(const chm_scenario_desc *desc, int32_t strategy, int32_t *upper_cuts, uint64_t *wave_steps);
 
+/* How an exhaustive search by halves of that family is laid out (all 0: it is not searched so).  Host only. */
+typedef struct {
+  int32_t walked_cuts;           /* upper cuts a wavefront walks as nested loops; its lanes keep the cuts below */
+  int32_t choices;               /* choices of those a lane keeps: 1 or 2 */
+  uint64_t wavefronts;           /* of the launch */
+  uint64_t units;                /* work shared out among them (a unit: a step of the innermost loop) */
+  uint64_t table_bytes;          /* device memory of the tables the handle's first search lays out */
+} chm_halves_work;
+int chm_halves_work_of(const chm_scenario_desc *desc, int32_t strategy, chm_halves_work *out);
+
 /* Switches event timing of chm_search_best / chm_search_range on or off for a handle,
  * and reads the timings of the last such call.  What is timed is the families' own kernels one after the other: with timing on,
  * small families do not share a launch, large ones start behind the seeds of the first of them alone, and a bounded

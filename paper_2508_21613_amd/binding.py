@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(_HERE, "libchm_san.so" if os.environ.get("CHM_SANITIZE",
 OK, ERR_ARG, ERR_RANGE, ERR_OVERFLOW, ERR_UNRECOVERABLE, ERR_NO_FEASIBLE, ERR_HIP, ERR_LIMIT = 0, -1, -2, -3, -4, -5, -6, -7
 INFEASIBLE = (1 << 63) - 1
 
-SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection", "chm_halves_selection",
+SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection", "chm_halves_selection", "chm_halves_work_of",
            "chm_search_range", "chm_search_ranks", "chm_search_cuts", "chm_rank_partitions", "chm_decode_plan", "chm_set_timing", "chm_set_filter_compaction", "chm_set_bounded_search", "chm_get_timing", "chm_family_classes",
            "chm_reroute_shape", "chm_transfer_plan", "chm_replan", "chm_replan_table", "chm_compare_objective", "chm_valu_probe", "chm_free_scenario",
            "chm_strerror"]
@@ -47,6 +47,11 @@ class Best(C.Structure):
                 ("stages", C.c_int32), ("cuts", C.c_uint8 * 32), ("n_affected", C.c_int32),
                 ("affected_stage", C.c_int32 * 4), ("reroute", (C.c_uint16 * 16) * 4),
                 ("t_step_us", C.c_int64), ("t_trans_us", C.c_int64)]
+
+
+class HalvesWork(C.Structure):
+    _fields_ = [("walked_cuts", C.c_int32), ("choices", C.c_int32), ("wavefronts", C.c_uint64), ("units", C.c_uint64),
+                ("table_bytes", C.c_uint64)]
 
 
 class ReplanDesc(C.Structure):
@@ -112,6 +117,7 @@ def lib():
         L.chm_load_scenario.argtypes = [C.POINTER(Desc), C.POINTER(vp)]
         L.chm_kernel_selection.argtypes = [C.POINTER(Desc), C.POINTER(Selection)]
         L.chm_halves_selection.argtypes = [C.POINTER(Desc), C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_uint64)]
+        L.chm_halves_work_of.argtypes = [C.POINTER(Desc), C.c_int32, C.POINTER(HalvesWork)]
         L.chm_plan_space.argtypes = [vp, C.POINTER(Space)]
         L.chm_score_plans.argtypes = [vp, C.c_uint64, C.c_uint64, vp, vp]
         L.chm_score_ranks.argtypes = [vp, C.c_int32, vp, C.c_uint64, vp, vp]
@@ -300,6 +306,14 @@ def halves_selection(sc, strategy):
     up, steps = C.c_int32(), C.c_uint64()
     _check(lib().chm_halves_selection(C.byref(d), strategy, C.byref(up), C.byref(steps)))
     return int(up.value), int(steps.value)
+
+
+def halves_work(sc, strategy):
+    """chm_halves_work_of: how an exhaustive search by halves of a strategy's family is laid out (host only)"""
+    d, keep = _desc(sc)
+    out = HalvesWork()
+    _check(lib().chm_halves_work_of(C.byref(d), strategy, C.byref(out)))
+    return {name: int(getattr(out, name)) for name, _ in HalvesWork._fields_}
 
 
 def search_best_batch(scenarios, mask=7, stream=None):

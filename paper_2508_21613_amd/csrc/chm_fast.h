@@ -124,7 +124,7 @@ struct FastState {
   size_t vec_words = 0;                     // size of the vector table
   const DevScenario *d_scn = nullptr;       // the handle's device tables (for that later build)
   const uint64_t *d_comp = nullptr;
-  // search by halves, per strategy: records of pairs of cuts and first items (under 0.7 MB), laid out by the first search
+  // search by halves, per strategy: records of pairs of cuts and shares of work (halves_table_bytes), laid out by the first search
   uint32_t *d_pairs[3] = {nullptr, nullptr, nullptr};
   bool pairs_ready[3] = {false, false, false};      // the table is there: a search that filled it has been waited for
   bool pairs_queued[3] = {false, false, false};     // a launch of the current search fills it, or found it ready
@@ -187,10 +187,13 @@ template <typename Scenario>
 __host__ __device__ inline uint64_t halves_units(const Scenario &h, int walked, int v) {
   return HALVES_SETUP + h->binom[walked][h->L - 1 - v] + HALVES_ROW * h->binom[walked - 1][h->L - 2 - v];
 }
+// Bytes of device memory for all that (128 layers: 0.56 MB).
+constexpr size_t halves_table_bytes(int L) { return (size_t)((L + 1) * (L + 1)) * PAIR_RECORD_WORDS * sizeof(uint32_t) + sizeof(HalvesItems); }
+static_assert(halves_table_bytes(DEV_MAX_L) < 700000, "what chm_search_best promises");
 struct HalvesLaunch {
   SearchLaunch s;               // result = words of the family's first chunk
   const FastTables *tab;
-  uint32_t *pairs, *steps;      // records of pairs of cuts, (L + 1)^2 of PAIR_RECORD_WORDS each
+  uint32_t *pairs;              // records of pairs of cuts, (L + 1)^2 of PAIR_RECORD_WORDS words
   HalvesItems *items;
   uint32_t n_rows, n_items;     // layers + 1; wavefronts
   uint64_t n_units, per_item;   // units of work, of all and of a wavefront
@@ -267,6 +270,8 @@ int chmk_fast_search_s2(int sp, const FastLaunch &a, uint32_t blocks, uint32_t t
 int chmk_halves_s0(int sp, const HalvesLaunch &a, bool build, void *stream);
 int chmk_halves_s1(int sp, const HalvesLaunch &a, bool build, void *stream);
 int chmk_halves_s2(int sp, const HalvesLaunch &a, bool build, void *stream);
+// Choices of the lower cuts a lane keeps when a family is searched by halves.
+int fast_halves_choices(const FastState *f, const DevScenario &h, int k, bool bounded);
 // Exhaustive search of a whole family (a.part_first = 0, `partitions` of them, which may be more than one chunk) by
 // halves.  a.result = words of its first chunk, those of the next chunk chunk_words further on; a.incumbent: as in a bounded
 // search, only for what chm_halves_kernel.h says.  may_allocate = false, or no memory to be had: only with tables that are already there.  Same

@@ -848,30 +848,32 @@ bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_
 
 uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return f->halves[k].setup; }
 
+int fast_halves_choices(const FastState *f, const DevScenario &h, int k, bool bounded) {
+  return !bounded && h.fam[k].stages >= HALVES_TWO_CHOICES_FROM && f->halves[k].units[0] >= HALVES_TWO_CHOICES ? 2 : 1;
+}
+
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, bool bounded, void *stream) {
   const int k = a.strategy;
   if (!fast_halves_covers(f, h, k, partitions)) return 1;
   const HalvesShape &hs = f->halves[k];
   const int sp = h.fam[k].stages;
-  const size_t words = (size_t)((h.L + 1) * (h.L + 1)) * PAIR_RECORD_WORDS;
   if (!f->d_pairs[k]) {
     // (no memory for the table: the range kernel needs none)
-    if (!may_allocate || !pool_take(f->d_pairs[k], 2 * words * sizeof(uint32_t) + sizeof(HalvesItems))) return 1;
+    if (!may_allocate || !pool_take(f->d_pairs[k], halves_table_bytes(h.L))) return 1;
   }
   HalvesLaunch hl;
   hl.s = a;
   hl.tab = f->d_tables;
   hl.chunk_words = chunk_words;
   hl.bounded = bounded ? 1 : 0;
-  hl.choices = !bounded && sp >= HALVES_TWO_CHOICES_FROM && hs.units[0] >= HALVES_TWO_CHOICES ? 2 : 1;
+  hl.choices = (uint32_t)fast_halves_choices(f, h, k, bounded);
   hl.n_items = hs.n_items[hl.choices - 1];
   hl.n_units = hs.units[hl.choices - 1];
   hl.per_item = (hl.n_units + hl.n_items - 1) / hl.n_items;
   hl.n_rows = (uint32_t)(h.L + 1);
   hl.pairs = f->d_pairs[k];
-  hl.steps = f->d_pairs[k] + words;
-  hl.items = (HalvesItems *)(f->d_pairs[k] + 2 * words);     // (records are whole 32 bytes)
+  hl.items = (HalvesItems *)(f->d_pairs[k] + (size_t)((h.L + 1) * (h.L + 1)) * PAIR_RECORD_WORDS);     // (records are whole 32 bytes)
   const bool build = !f->pairs_ready[k];
   const int rc = k == 0 ? chmk_halves_s0(sp, hl, build, stream)
                  : k == 1 ? chmk_halves_s1(sp, hl, build, stream) : chmk_halves_s2(sp, hl, build, stream);

@@ -86,7 +86,9 @@ struct Terms {
   }
 };
 
-// Records of two cuts, 8 words each, (L + 1)^2 of both kinds.
+// Records of two cuts, 8 words each, in one table of (L + 1)^2: those of the innermost loop, x <= y, in row x and column y; those of the
+// loop ahead of it, x < m < L, in what these leave free, row L - x and columns 0 on (step_index).
+__device__ __forceinline__ uint32_t step_index(int L, int x, int m) { return (uint32_t)((L - x) * (L + 1) + (m - x - 1)); }
 // The innermost loop's, x < y.  Strategies 1 and 2: x, y = the last two cuts; stage N-2 = [x, y) and stage N-1 = [y, L), times less
 // the whole model's.  Strategy 0 (node s runs stages s and s+1): x = the last cut but two, y = the last one; node N-3 = [x, y), times
 // from the end of node N-4.
@@ -166,8 +168,8 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
       if (scn->aff_stage[st] == s) pen += even_penalty(scn, tab, st, fwd(lo, hi), both(lo, hi) - fwd(lo, hi));
     return (float)pen;
   };
-  auto store = [&](uint32_t *table, int y, const float (&rec)[7], uint32_t last_word) {
-    uint4 *dst = (uint4 *)(table + (size_t)(x * (L + 1) + y) * PAIR_RECORD_WORDS);
+  auto store = [&](uint32_t index, const float (&rec)[7], uint32_t last_word) {
+    uint4 *dst = (uint4 *)(a.pairs + (size_t)index * PAIR_RECORD_WORDS);
     dst[0] = make_uint4(__float_as_uint(rec[0]), __float_as_uint(rec[1]), __float_as_uint(rec[2]), __float_as_uint(rec[3]));
     dst[1] = make_uint4(__float_as_uint(rec[4]), __float_as_uint(rec[5]), __float_as_uint(rec[6]), last_word);
   };
@@ -226,9 +228,8 @@ __global__ void __launch_bounds__(BLOCK) k_cut_records(HalvesLaunch a) {
       step[STEP_LAYERS] = (float)(hi - lo);
       step_word = there && memory(lo, hi, N - 3) <= cap ? 1u : 0u;
     }
-    if (y > L) continue;
-    store(a.pairs, y, pair, pair_word);
-    store(a.steps, y, step, step_word);
+    if (y >= x && y <= L) store((uint32_t)(x * (L + 1) + y), pair, pair_word);
+    if (there) store(step_index(L, x, y), step, step_word);
   }
 }
 
@@ -388,7 +389,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       int lacks = 0;
       if (open_nodes) {
 #pragma unroll
-        for (int s = 0; s < G; ++s) lacks += (int)a.steps[(uint32_t)(c[s] * (L + 1) + c[s + 1]) * STEP_WORDS + STEP_FETCH];
+        for (int s = 0; s < G; ++s) lacks += (int)a.pairs[step_index(L, c[s], c[s + 1]) * STEP_WORDS + STEP_FETCH];
       } else {
 #pragma unroll
         for (int s = 0; s < G; ++s) lacks += lacking<0, STRAT>(ff, t[s].z, t[s + 1].z, s);
@@ -424,7 +425,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     };
     auto gone = [&](int s) { return STRAT == 0 && ((cl->dead >> s) & 1u) != 0; };
     const int M = cl->M;
-    const RowPtr pairs = as_const((const uint32_t *)a.pairs), steps = as_const((const uint32_t *)a.steps);
+    const RowPtr pairs = as_const((const uint32_t *)a.pairs);
     const float after_g = STRAT == 0 ? (float)cl->after[N - 4] : 0.0f;
     const float after_y = STRAT == 0 ? (float)cl->after[N - 3] : 0.0f, after_m = STRAT == 0 ? (float)cl->after[N - 2] : 0.0f;
     const float last_m = STRAT == 0 ? (float)(cl->steady[N - 2] + 1) : 0.0f;      // (0, a node that is gone: as good as no own term)
@@ -532,7 +533,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     };
 
     // Innermost loop: last cuts m+n, m+n-1, ... m+1, the others being fixed; src = records of the first two.  Four records a round.
-    // (Strategies 1 and 2: a record behind the last one is HUGE_TIME.  m > 2: there are records ahead of the row.)
+    // (Strategies 1 and 2: a record behind the last one, y = m, is HUGE_TIME; what lies ahead of that, in the row or before it, is read along
+    // and not looked at.  m > 2: something does.)
     auto walk = [&](RowPtr src, int m, uint32_t n) {
       for (;;) {
         const u32x16 first = *(const CHM_CONST record_pair *)src, second = *(const CHM_CONST record_pair *)(src - 2 * PAIR_WORDS);
@@ -645,7 +647,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     auto take_up = [&](auto level) {
       constexpr int I = decltype(level)::value;
       int lack;
-      if (open_nodes) lack = (int)steps[(uint32_t)(cut[I - 1] * (L + 1) + cut[I]) * STEP_WORDS + STEP_FETCH];
+      if (open_nodes) lack = (int)pairs[step_index(L, cut[I - 1], cut[I]) * STEP_WORDS + STEP_FETCH];
       else lack = lacking<0, STRAT>(ff, at[I - 1].z, at[I].z, G + I - 1);
       const float fetch = fetch_time(scn, lack);
 #pragma unroll
@@ -693,13 +695,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       constexpr int P = W - 2;
       const uint32_t width = (uint32_t)(L + 1) * PAIR_RECORD_WORDS;
       int m = L - 1 - (int)x[2];
-      RowPtr step = steps + (uint32_t)(STRAT != 0 ? cut[P] : W == 2 ? 0 : cut[W == 2 ? 0 : P - 1]) * width + (uint32_t)m * STEP_WORDS;
+      RowPtr step = pairs + step_index(L, STRAT != 0 ? cut[P] : W == 2 ? 0 : cut[W == 2 ? 0 : P - 1], m) * STEP_WORDS;
       RowPtr pair = pairs + (uint32_t)(STRAT != 0 ? m : cut[P]) * width + (uint32_t)(L - 2) * PAIR_WORDS;
       u32x8 next = *(const CHM_CONST u32x8 *)step;
       do {
         const u32x8 rec = next;
         step -= STEP_WORDS;
-        next = *(const CHM_CONST u32x8 *)step;         // (m > 1)
+        next = *(const CHM_CONST u32x8 *)step;         // (ahead of the first one lies the end of another row)
         auto word = [&](int i) { return __uint_as_float(rec[i]); };
         const uint32_t n = x[2];
         cut[W - 1] = m;

@@ -1263,6 +1263,29 @@ extern "C" int chm_halves_selection(const chm_scenario_desc *desc, int32_t strat
   return rc;
 }
 
+extern "C" int chm_halves_work_of(const chm_scenario_desc *desc, int32_t strategy, chm_halves_work *out) {
+  if (strategy < 0 || strategy > 2 || !out) return CHM_ERR_ARG;
+  memset(out, 0, sizeof(*out));
+  int rc = validate(desc);
+  if (rc) return rc;
+  chm_scenario *s = new (std::nothrow) chm_scenario();
+  if (!s || !s->search) { delete s; return CHM_ERR_HIP; }
+  rc = build_model(desc, s);
+  if (rc == CHM_OK) {
+    fast_select(&s->fast, s->h, s->int32_ok);
+    const HalvesShape &hs = s->fast.halves[strategy];
+    if (hs.up != 0) {
+      out->walked_cuts = halves_walked(s->h.fam[strategy].stages);
+      out->choices = fast_halves_choices(&s->fast, s->h, strategy, false);
+      out->wavefronts = hs.n_items[out->choices - 1];
+      out->units = hs.units[out->choices - 1];
+      out->table_bytes = halves_table_bytes(s->h.L);
+    }
+  }
+  delete s;
+  return rc;
+}
+
 extern "C" int chm_plan_space(const chm_scenario *s, chm_space *out) {
   if (!s || !out) return CHM_ERR_ARG;
   *out = s->space;

@@ -38,7 +38,7 @@ def test_struct_layouts_match_the_header(tmp_path):
     """sizes and field offsets of every structure of the binding against what a C compiler makes of include/chm.h"""
     import subprocess
     structs = {"chm_scenario_desc": B.Desc, "chm_family": B.Family, "chm_space": B.Space, "chm_best": B.Best,
-               "chm_timing": B.Timing, "chm_selection": B.Selection, "chm_replan_desc": B.ReplanDesc, "chm_replan_plan": B.ReplanPlan}
+               "chm_timing": B.Timing, "chm_selection": B.Selection, "chm_halves_work": B.HalvesWork, "chm_replan_desc": B.ReplanDesc, "chm_replan_plan": B.ReplanPlan}
     lines = ['#include <stdio.h>', '#include <stddef.h>', '#include "chm.h"', '#include "chm_measure.h"', 'int main(void) {']
     for cname, cls in structs.items():
         lines.append('  printf("%s %%zu\\n", sizeof(%s));' % (cname, cname))

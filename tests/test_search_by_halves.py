@@ -71,6 +71,19 @@ def test_lanes_are_at_work_in_every_family_searched_by_halves():
     assert B.halves_selection(dict(_large(48, 8, 3, 8, [3]), speed_q16=np.full(24, 65537, np.uint32)), 2)[0] == 0
 
 
+def test_tables_take_no_more_memory_than_promised():
+    """under 0.7 MB a strategy (chm_search_best), whatever the model"""
+    from paper_2508_21613_amd import binding as B
+    largest = 0
+    for L in range(40, 129, 8):
+        sc = _large(L, 6, 2, 9, [3])
+        for k in range(3):
+            work = B.halves_work(sc, k)
+            assert (work["table_bytes"] > 0) == (B.halves_selection(sc, k)[0] > 0)
+            largest = max(largest, work["table_bytes"])
+    assert 129 * 129 * 32 < largest < 700000
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", CASES)
 def test_search_by_halves_finds_what_the_range_kernel_finds(name):
