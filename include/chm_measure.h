@@ -66,6 +66,11 @@ typedef struct {
 } chm_halves_work;
 int chm_halves_work_of(const chm_scenario_desc *desc, int32_t strategy, chm_halves_work *out);
 
+/* Sets how searches by halves on a handle are laid out: choices of the lower cuts a lane keeps (1, or 2, which exhaustive searches of 10 stages
+ * and more can; 0, the default: by size) and wavefronts of the launch (up to 2^24; 0, the default: by size).  Results do not depend on either;
+ * tests reach every kernel and every boundary between shares with it.  Errors: CHM_ERR_ARG. */
+int chm_set_halves_shares(chm_scenario *s, int32_t choices, uint32_t wavefronts);
+
 /* Switches event timing of chm_search_best / chm_search_range on or off for a handle,
  * and reads the timings of the last such call.  What is timed is the families' own kernels one after the other: with timing on,
  * small families do not share a launch, large ones start behind the seeds of the first of them alone, and a bounded

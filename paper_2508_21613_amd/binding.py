@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(_HERE, "libchm_san.so" if os.environ.get("CHM_SANITIZE",
 OK, ERR_ARG, ERR_RANGE, ERR_OVERFLOW, ERR_UNRECOVERABLE, ERR_NO_FEASIBLE, ERR_HIP, ERR_LIMIT = 0, -1, -2, -3, -4, -5, -6, -7
 INFEASIBLE = (1 << 63) - 1
 
-SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection", "chm_halves_selection", "chm_halves_work_of",
+SYMBOLS = ["chm_load_scenario", "chm_plan_space", "chm_score_plans", "chm_score_ranks", "chm_search_best", "chm_search_best_static", "chm_search_best_batch", "chm_kernel_selection", "chm_halves_selection", "chm_halves_work_of", "chm_set_halves_shares",
            "chm_search_range", "chm_search_ranks", "chm_search_cuts", "chm_rank_partitions", "chm_decode_plan", "chm_set_timing", "chm_set_filter_compaction", "chm_set_bounded_search", "chm_get_timing", "chm_family_classes",
            "chm_reroute_shape", "chm_transfer_plan", "chm_replan", "chm_replan_table", "chm_compare_objective", "chm_valu_probe", "chm_free_scenario",
            "chm_strerror"]
@@ -118,6 +118,7 @@ def lib():
         L.chm_kernel_selection.argtypes = [C.POINTER(Desc), C.POINTER(Selection)]
         L.chm_halves_selection.argtypes = [C.POINTER(Desc), C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_uint64)]
         L.chm_halves_work_of.argtypes = [C.POINTER(Desc), C.c_int32, C.POINTER(HalvesWork)]
+        L.chm_set_halves_shares.argtypes = [vp, C.c_int32, C.c_uint32]
         L.chm_plan_space.argtypes = [vp, C.POINTER(Space)]
         L.chm_score_plans.argtypes = [vp, C.c_uint64, C.c_uint64, vp, vp]
         L.chm_score_ranks.argtypes = [vp, C.c_int32, vp, C.c_uint64, vp, vp]
@@ -468,6 +469,10 @@ class Scenario:
         share = (C.c_float * 3)()
         _check(lib().chm_set_filter_compaction(self._h, mode, share))
         return [float(x) for x in share]
+
+    def set_halves_shares(self, choices=0, wavefronts=0):
+        """chm_set_halves_shares: choices of the lower cuts a lane keeps, wavefronts of a search by halves (0: by size)"""
+        _check(lib().chm_set_halves_shares(self._h, choices, wavefronts))
 
     def set_bounded_search(self, on=True):
         """chm_set_bounded_search: skip partitions whose lower bound of the cost lies above the best cost found so far"""

@@ -129,6 +129,8 @@ struct FastState {
   bool pairs_ready[3] = {false, false, false};      // the table is there: a search that filled it has been waited for
   bool pairs_queued[3] = {false, false, false};     // a launch of the current search fills it, or found it ready
   HalvesShape halves[3];
+  int halves_choices_set = 0;               // chm_set_halves_shares: 0 = by the rules
+  uint32_t halves_items_set = 0;
   // scratch of the candidate path of the bounded search; grown to what a search needs
   void *d_cand_list = nullptr;              // [candidate] cut positions, 16 bytes each
   uint32_t *d_cand_pos = nullptr;           // [candidate] its index

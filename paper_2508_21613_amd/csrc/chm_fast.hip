@@ -849,7 +849,9 @@ bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_
 uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return f->halves[k].setup; }
 
 int fast_halves_choices(const FastState *f, const DevScenario &h, int k, bool bounded) {
-  return !bounded && h.fam[k].stages >= HALVES_TWO_CHOICES_FROM && f->halves[k].units[0] >= HALVES_TWO_CHOICES ? 2 : 1;
+  if (bounded || h.fam[k].stages < HALVES_TWO_CHOICES_FROM) return 1;
+  if (f->halves_choices_set != 0) return f->halves_choices_set;
+  return f->halves[k].units[0] >= HALVES_TWO_CHOICES ? 2 : 1;
 }
 
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
@@ -868,7 +870,7 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.chunk_words = chunk_words;
   hl.bounded = bounded ? 1 : 0;
   hl.choices = (uint32_t)fast_halves_choices(f, h, k, bounded);
-  hl.n_items = hs.n_items[hl.choices - 1];
+  hl.n_items = f->halves_items_set != 0 ? f->halves_items_set : hs.n_items[hl.choices - 1];
   hl.n_units = hs.units[hl.choices - 1];
   hl.per_item = (hl.n_units + hl.n_items - 1) / hl.n_items;
   hl.n_rows = (uint32_t)(h.L + 1);

@@ -1286,6 +1286,13 @@ extern "C" int chm_halves_work_of(const chm_scenario_desc *desc, int32_t strateg
   return rc;
 }
 
+extern "C" int chm_set_halves_shares(chm_scenario *s, int32_t choices, uint32_t wavefronts) {
+  if (!s || choices < 0 || choices > 2 || wavefronts > (1u << 24)) return CHM_ERR_ARG;
+  s->fast.halves_choices_set = choices;
+  s->fast.halves_items_set = wavefronts;
+  return CHM_OK;
+}
+
 extern "C" int chm_plan_space(const chm_scenario *s, chm_space *out) {
   if (!s || !out) return CHM_ERR_ARG;
   *out = s->space;

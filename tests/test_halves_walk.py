@@ -1,7 +1,7 @@
 """Search by halves (chm_halves_kernel.h) where its float times, its limit and its shares of work can go wrong: times beyond 2^24 (sums are
 rounded there), fetch times that outweigh the steps or cost nothing, untouched pipelines that decide the step time, stages that lost nodes at
-every place of the walk, an odd and a small number of layers above the lanes' cuts, two choices a lane with most of them idle.  Against the
-range kernel over the same space in two windows, the winner's cost against the oracle.  Whole numbers, compared exactly."""
+every place of the walk, an odd and a small number of layers above the lanes' cuts.  Against the range kernel over the same space in two
+windows, the winner's cost against the oracle.  Whole numbers, compared exactly."""
 import numpy as np
 import pytest
 
@@ -68,26 +68,3 @@ def test_walk_finds_what_the_range_kernel_finds(name):
     assert g.search_best(7) == best
     g.close()
 
-
-def test_units_of_work_cover_every_choice_once():
-    """the shares of the walked cuts begin and end with a row (all cuts but the last): decoded by units of work they cover each position once"""
-    from math import comb
-    rnd = np.random.default_rng(5)
-    row, setup = 5, 60
-    for _ in range(200):
-        W = int(rnd.integers(2, 5))
-        n = int(rnd.integers(W, 30))                    # layers above the lanes' last cut, less one
-        below = lambda x, i: comb(x, i) + (row * comb(x - 1, i - 1) if x > 0 else 0)
-        total = setup + comb(n, W) + row * comb(n - 1, W - 1)
-
-        def position(unit):
-            rem, at = max(0, unit - setup), 0
-            for i in range(W, 1, -1):
-                x = max(t for t in range(128) if below(t, i) <= rem)
-                assert i - 1 <= x < n
-                rem -= below(x, i)
-                at += comb(x, i)
-            return at
-        share = int(rnd.integers(1, total + 1))
-        ends = [position(u) for u in range(0, total, share)] + [comb(n, W)]
-        assert ends[0] == 0 and all(a <= b for a, b in zip(ends, ends[1:]))
