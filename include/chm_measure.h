@@ -50,9 +50,9 @@ typedef struct {
 int chm_kernel_selection(const chm_scenario_desc *desc, chm_selection *out);
 
 /* Whether chm_search_best takes a strategy's family by halves (a partition = a lower half that a lane keeps and an
- * upper half that its wavefront walks over; large families at nominal speed): *upper_cuts = cuts of an upper half, 0 = it
- * goes through the kernels that take partitions one by one; *wave_steps = steps of 64 lanes, one upper half each (partitions /
- * (64 x wave_steps) = share of the lanes at work).  Host only; the decision chm_load_scenario takes.  Errors: CHM_ERR_ARG,
+ * upper half that its wavefront walks over; families of 2^21 partitions and more at nominal speed): *upper_cuts = cuts of an upper half, 0 = it
+ * goes through the kernels that take partitions one by one; *wave_steps = steps of 64 lanes, one upper half each, where a lane keeps one
+ * lower half (partitions / (64 x wave_steps) = share of the lanes at work).  Host only; the decision chm_load_scenario takes.  Errors: CHM_ERR_ARG,
  * CHM_ERR_OVERFLOW. */
 int chm_halves_selection(const chm_scenario_desc *desc, int32_t strategy, int32_t *upper_cuts, uint64_t *wave_steps);
 

@@ -63,8 +63,6 @@ struct FastTables {
   uint32_t lb_mult[DEV_MAX_AFF], lb_q[DEV_MAX_AFF];
 };
 
-// Widths of the upper half that some model length takes (halves_cost, chm_fast.hip): two cuts up to 11 stages, three from 9 on.
-enum { HALVES_TWO_UP_TO = 11, HALVES_THREE_FROM = 9 };
 // What a wavefront of the search walks (chm_halves_kernel.h): the upper half's cuts and, of the lower half's, the last ones that leave its
 // lanes enough choices of the cuts below.  One more walked cut leaves an eighth of the lanes' set-ups (300 instructions) to a family of 8
 // stages, but more lanes idle (8 stages, 48 layers, two / three / four walked: strategy 0 91 / 82 / 114 us a search, strategy 2 85 / 85 / 113;
@@ -81,11 +79,11 @@ enum { HALVES_TWO_CHOICES_FROM = 10 };
 constexpr int halves_waves(int stages, int strategy, int choices, bool pruned) {
   return choices == 2 ? 4 : stages <= 7 ? (strategy == 0 ? 6 : 7) : stages <= 10 || (strategy == 0 && stages <= 13 && !pruned) ? 5 : 4;
 }
-// How a family is searched by halves (chm_halves_kernel.h); up = 0: it is not.
+// How a family is searched by halves (chm_halves_kernel.h); walked = 0: it is not.
 struct HalvesShape {
-  int up = 0;                   // cuts of an upper half
-  uint64_t steps = 0;           // 64 lower halves x one upper half
-  uint64_t setup = 0;           // lower halves to set up, in instructions, were a lane to keep each
+  int walked = 0;               // upper cuts a wavefront walks
+  uint64_t blocks = 0;          // of 64 choices of the cuts below, to be set up
+  uint64_t steps = 0;           // blocks x choices of the walked cuts
   // with one choice of the lower cuts a lane, with two:
   uint32_t n_items[2] = {0, 0}; // wavefronts of the search
   uint64_t units[2] = {0, 0};   // work to share out among them
@@ -280,8 +278,8 @@ int fast_halves_choices(const FastState *f, const DevScenario &h, int k, bool bo
 // return convention as fast_search (positive: not covered, or smaller than what the range search does as fast).
 // fast_halves_covers: whether it takes the family at all.
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int strategy, uint64_t partitions);
-// Instructions its wavefronts take to set up their lower halves.
-uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int strategy);
+// Blocks of 64 choices of the lower cuts that its wavefronts set up, with one choice a lane.
+uint64_t fast_halves_blocks(const FastState *f, int strategy);
 int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a, uint64_t partitions, uint32_t chunk_words,
                        bool may_allocate, bool bounded, void *stream);
 // The stream of the last search has been waited for: the tables its launches filled are there.

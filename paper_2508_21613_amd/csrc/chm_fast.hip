@@ -283,55 +283,21 @@ float estimate_fit_share(const DevScenario &h, const FastFamily &ff, int strat, 
 // 34 M 572 / 592 and 430 / 410: by then each family fills the device by itself.
 constexpr uint64_t FAMILIES_UP_TO = 1ull << 24;
 
-// Search by halves (chm_halves_kernel.h): which families, and how many cuts the upper half takes.
+// Search by halves (chm_halves_kernel.h): which families.
 //
-// Partitions from which a family is looked at: below, its seeds, its first search's table and the fixed cost of
-// a wavefront (its lower half, a round of 32 upper halves) weigh more than the partitions (1.6 M of 7 stages, us, range
-// kernel / by halves: 28 / 34).
+// Partitions from which a family goes by halves: below, its seeds, its table and the fixed cost of a wavefront weigh more than the
+// partitions.  The two meet at 1.1 to 2.0 M partitions, whatever the depth; us a search, range kernel / by halves, strategies 0 and 2: 5 stages,
+// 1.5 M 40 / 44 and 46 / 48, 2.1 M 47 / 44 and 51 / 49, 10.3 M 94 / 53 and 98 / 54; 6 stages, 1.1 M 40 / 40 and 43 / 46, 2.1 M 49 / 42 and
+// 53 / 47; 8 stages, 1.2 M 45 / 51 and 46 / 47, 2.6 M 63 / 46 and 63 / 48; 12 stages, 0.7 M 44 / 51 and 45 / 51, 2.5 M 76 / 58 and 73 / 56; 16
+// stages, 0.5 M 51 / 53 and 53 / 55, 3.3 M 118 / 72 and 111 / 68.
 constexpr uint64_t HALVES_FROM = 1ull << 21;
-// What halves must save: a partition costs the range kernel about `stages` units, a lane's step one unit per pipeline
-// class (two at most: the others are timed seldom), whether the lane has a lower half or not, and the fixed cost is about 7 M
-// units.  (A unit is a nanosecond over 1,000 of them.)  Decides for families whose lower halves leave most lanes idle, us, range
-// kernel / by halves: 5 stages, 2.1 M partitions (a third of the lanes at work) 30 / 36 and, strategy 0, 29 / 17; 3.0 M 38 / 38 and
-// 35 / 18; 5.6 M 56 / 46 and 51 / 23; 6 stages, 2.9 M (78 % at work) 37 / 34 and 38 / 17.
-constexpr int64_t HALVES_SAVES = 7ll << 20;
-// How large an upper half is counted with: two cuts, or three where that leaves so many fewer lower halves (60 + 30 a lower cut
-// instructions each) that dearer steps (25 instead of 18) pay, and not a quarter more of them; deep pipelines, whose upper halves are few for
-// every v.  (The kernel walks more cuts than these from 8 stages on, halves_walked; the sizes from which a family goes by halves were
-// measured with a lane for every lower half.)
-uint64_t halves_cost(const HalvesShape &hs) { return hs.setup + hs.steps * (hs.up == 2 ? 18u : 25u); }
-constexpr uint64_t WIDER_BY = 4;
 // Units of work a wavefront is given at least where there is more than one round of them (8 stages, 48 layers, one round / two / three 82 / 84 / 88
 // us a search, strategy 0; 5.2 G partitions of 11 stages 3,240 / 2,880 / 2,660 us with 2 / 4 / 8 rounds).
 constexpr uint64_t HALVES_UNITS = 256;
 constexpr uint64_t HALVES_TWO_CHOICES = 1ull << 24;      // (see halves_walked)
 
-// wavefront steps (64 lower halves that end with one cut x one upper half) and items of `up` upper cuts, `chunk` at most each; false: not
-// within the kernel's 32-bit ranks of lower halves
-bool halves_count(const DevScenario &h, int sp, int up, uint64_t chunk, uint64_t *steps, uint64_t *items) {
-  const int H = sp - 1 - up, L = h.L;
-  *steps = *items = 0;
-  if (H < 2 || L - 1 - H < up) return false;
-  for (int v = H; v <= L - 1 - up; ++v) {
-    if (h.binom[H][v - 1] >= (1ull << 32) - 64 || h.binom[H - 1][v - 1] >= (1ull << 32) - 64) return false;
-    const uint64_t low = (h.binom[H - 1][v - 1] + 63) / 64, upper = h.binom[up][L - 1 - v];
-    *steps += low * upper;
-    *items += low * ((upper + chunk - 1) / chunk);
-  }
-  return true;
-}
-
-HalvesShape halves_of_width(const DevScenario &h, int sp, int up) {
-  HalvesShape hs;
-  uint64_t steps = 0, items = 0;
-  if (!halves_count(h, sp, up, 1, &steps, &items)) return hs;
-  halves_count(h, sp, up, std::max<uint64_t>(32, std::min<uint64_t>(1024, steps / 6144)), &steps, &items);
-  if (items >= (1ull << 31)) return hs;
-  hs.up = up;
-  hs.steps = steps;
-  hs.setup = items * (uint64_t)(60 + 30 * (sp - 1 - up));
-  return hs;
-}
+// Most units of work of a wavefront: its workgroup counts the partitions that fit, up to 2 x 64 a unit, in 32 bits.
+constexpr uint64_t HALVES_MOST_UNITS = 1ull << 22;
 
 // The work of the search and the wavefronts it is shared out among: as many as are resident at a time, or several times as many where
 // each still has a few hundred units.  Small families, which leave wavefronts idle however they are shared out, in shares of 16 units: setting
@@ -351,22 +317,28 @@ void halves_share(const DevScenario &h, int sp, int k, HalvesShape *hs) {
 HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
   const FastFamily &ff = t->fam[k];
   const int sp = h.fam[k].stages;
-  const uint64_t partitions = h.fam[k].n_part;
   const HalvesShape none;
-  if (partitions < HALVES_FROM || sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return none;
+  if (h.fam[k].n_part < HALVES_FROM || sp < 5 || sp > 16 || !ff.time24 || (k == 0 && ff.allreduce > 0)) return none;
   for (int ci = 0; ci < ff.n_cls; ++ci)
     if (!ff.cls[ci].unit || ff.cls[ci].M < sp) return none;
   if (k != 0 && ff.n_time > 1) return none;
   for (int s = 0; k == 2 && s < h.n_aff; ++s)
     if (t->even_share[s] == 0) return none;
-  const HalvesShape two = sp <= HALVES_TWO_UP_TO ? halves_of_width(h, sp, 2) : none;
-  const HalvesShape three = sp >= HALVES_THREE_FROM ? halves_of_width(h, sp, 3) : none;
-  const bool wide = two.up == 0 || (halves_cost(three) < halves_cost(two) && three.steps <= two.steps + two.steps / WIDER_BY);
-  HalvesShape taken = three.up != 0 && wide ? three : two;
-  if (taken.up == 0) return none;
-  halves_share(h, sp, k, &taken);
-  const unsigned __int128 saved = (unsigned __int128)partitions * (unsigned)sp;
-  return saved >= (unsigned __int128)taken.steps * 64u * (unsigned)std::min(ff.n_time, 2) + (unsigned)HALVES_SAVES ? taken : none;
+  HalvesShape hs;
+  const int walked = halves_walked(sp), kept = sp - 1 - walked;
+  if (h.L - 1 - walked < kept) return none;
+  for (int v = kept; v <= h.L - 1 - walked; ++v) {
+    // (ranks of the lanes' cuts are 32 bits wide, of up to two blocks beyond the last one)
+    if (h.binom[kept][v - 1] >= (1ull << 32) - 128 || h.binom[kept - 1][v - 1] >= (1ull << 32) - 128) return none;
+    const uint64_t blocks = halves_blocks(&h, kept, 1, v);
+    hs.blocks += blocks;
+    hs.steps += blocks * h.binom[walked][h.L - 1 - v];
+  }
+  halves_share(h, sp, k, &hs);
+  for (int c = 0; c < 2; ++c)
+    if (hs.units[c] / hs.n_items[c] >= HALVES_MOST_UNITS) return none;
+  hs.walked = walked;
+  return hs;
 }
 
 }  // namespace
@@ -843,10 +815,10 @@ bool fast_list_leaves_out(const FastState *f, const DevScenario &h, const Search
 }
 
 bool fast_halves_covers(const FastState *f, const DevScenario &h, int k, uint64_t partitions) {
-  return k >= 0 && k <= 2 && f->halves[k].up != 0 && partitions == h.fam[k].n_part;
+  return k >= 0 && k <= 2 && f->halves[k].walked != 0 && partitions == h.fam[k].n_part;
 }
 
-uint64_t fast_halves_setup(const FastState *f, const DevScenario &h, int k) { return f->halves[k].setup; }
+uint64_t fast_halves_blocks(const FastState *f, int k) { return f->halves[k].blocks; }
 
 int fast_halves_choices(const FastState *f, const DevScenario &h, int k, bool bounded) {
   if (bounded || h.fam[k].stages < HALVES_TWO_CHOICES_FROM) return 1;
@@ -870,8 +842,8 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.chunk_words = chunk_words;
   hl.bounded = bounded ? 1 : 0;
   hl.choices = (uint32_t)fast_halves_choices(f, h, k, bounded);
-  hl.n_items = f->halves_items_set != 0 ? f->halves_items_set : hs.n_items[hl.choices - 1];
   hl.n_units = hs.units[hl.choices - 1];
+  hl.n_items = f->halves_items_set != 0 ? (uint32_t)std::max<uint64_t>(f->halves_items_set, hl.n_units / HALVES_MOST_UNITS + 1) : hs.n_items[hl.choices - 1];
   hl.per_item = (hl.n_units + hl.n_items - 1) / hl.n_items;
   hl.n_rows = (uint32_t)(h.L + 1);
   hl.pairs = f->d_pairs[k];

@@ -558,26 +558,23 @@ bool whole_family(const chm_scenario *s, const Job &j) {
 bool bounded_by_halves(const chm_scenario *s, const Job &j) {
   return s->bounded == 1 && j.count <= BOUNDED_HALVES && whole_family(s, j) && fast_halves_covers(&s->fast, s->h, j.strategy, j.count);
 }
-// Wavefront instructions of that set-up, per family, up to which a call's families go by halves straight away, and a family does beside
-// others that are enumerated.  (585,000 of them are a microsecond; a search takes about three times as long as they do.)  Counting and
-// enumerating candidates costs about the same whatever the size: a wait for the seeds, a count on the host for each family, another
-// launch.  us a search, enumerated / by halves, with the instructions of the families in millions: three families of 8 stages, 46 layers
-// (4 1 4) 183 / 97, 60 layers (14 2 14) 282 / 204, 64 layers (20 2 20) 205 / 282; 9 stages, 44 layers (17 3 17) 225 / 199; 11 stages, 40
-// layers (36 8 36) 225 / 645; 16 stages, 30 layers (63 47 63) 273 / 719; one family of 9 stages (3) 113 / 57, of 10 (8) 100 / 102, of 12
-// (15) 98 / 103, of 15 (47) 100 / 201.  Least-transfer assignments, worked out for all that may still win, count double: 10 stages
-// (8) 135 / 150, 11 stages (9) 136 / 173, but 8 stages (6) 129 / 77.  Strategies 0 and 2 alone, whose bound is far from their best plan, are
-// rarely left with few candidates and go by halves up to three times that: strategy 2 of 8 stages (20) 1,228 / 196, of 12 (28) 234 /
-// 172, of 13 (36) 178 / 181, but of 16 (63) 113 / 273.
-constexpr uint64_t FEW_LOWER_HALVES = 13000000;
-uint64_t lower_halves(const chm_scenario *s, const Job &j) {
-  return fast_halves_setup(&s->fast, s->h, j.strategy) * (j.strategy == 1 && s->h.assign ? 2u : 1u);
-}
+// Blocks of 64 lower halves to set up, per family, up to which a call's families go by halves straight away, and a family does beside others that
+// are enumerated.  Counting and enumerating candidates costs about the same whatever the size: a wait for the seeds, a count on the host
+// for each family, another launch.  us a search, enumerated / by halves, with the families' blocks in thousands, three pipelines: all strategies of
+// 8 stages, 45 layers (5) 145 / 72, 58 layers (15) 278 / 139, 11 stages, 37 layers (46) 244 / 239, 12 stages, 35 layers (73) 230 / 290, 16 stages,
+// 30 layers (190) 230 / 465; strategy 1 of 9 stages, 41 layers (7) 97 / 63, 12 stages, 31 layers (10) 98 / 78, 15 stages, 31 layers (83) 101 /
+// 212.  These two lose least of nine such rules: 728 searches of one strategy and of several, 34 M to 1.07 G partitions, take 1.7 % longer than
+// with the best of them for each (25,000 and 25,000: 2.9 %; counted for the kernel that set up a lane for every lower half: 3.6 %); open
+// assignments alike.  Strategies 0 and 2 alone, whose bound is far from their best plan, are rarely left with few candidates and go by halves up to
+// three times that (strategy 2 of 13 stages, 31 layers (24) 141 / 116; of 16 (121) 309 / 276).
+constexpr uint64_t FEW_BLOCKS = 18000;
+constexpr uint64_t FEW_BLOCKS_BESIDE = 10000;     // of strategies 0 and 2, beside others that are enumerated
 bool all_by_halves(const chm_scenario *s, const std::vector<Job> &jobs) {
-  uint64_t setup = 0;
+  uint64_t blocks = 0;
   for (const Job &j : jobs)
-    if (bounded_by_halves(s, j)) setup += lower_halves(s, j);
+    if (bounded_by_halves(s, j)) blocks += fast_halves_blocks(&s->fast, j.strategy);
   const bool loose = jobs.size() == 1 && jobs[0].strategy != 1;
-  return setup <= FEW_LOWER_HALVES * (loose ? 3 : jobs.size());
+  return blocks <= FEW_BLOCKS * (loose ? 3 : jobs.size());
 }
 // Partitions of all families up to which one launch searches them exhaustively in less time than seeds and bounds take, us exhaustive /
 // bounded: 1.2 M of 6 stages 49 / 78, 3.6 M of 8 stages at uneven speeds 104 / 110 and, few of which fit, 78 / 105; 9.7 M 239 / 187.
@@ -1072,7 +1069,7 @@ int run_search(chm_scenario *s, const std::vector<Job> &given, chm_best *out, ui
     const bool whole = !j.ranks && !j.cuts && !j.costs && j.first == 0 && j.count == s->h.fam[j.strategy].n_part;
     bool listed = false;
     const bool halves = bounded_by_halves(s, j);
-    if (whole && incumbent != ~0ull && s->idx_bits >= 23 && !(halves && lower_halves(s, j) <= FEW_LOWER_HALVES)) {
+    if (whole && incumbent != ~0ull && s->idx_bits >= 23 && !(halves && fast_halves_blocks(&s->fast, j.strategy) <= (j.strategy == 1 ? FEW_BLOCKS : FEW_BLOCKS_BESIDE))) {
       // A family within reach of a search of its partitions is enumerated only when its candidates are few; one beyond it,
       // whenever they can be made few enough: while there are too many, a sample of them spread evenly over
       // their index order is evaluated, which lowers the incumbent and with it the number of candidates.
@@ -1256,7 +1253,7 @@ extern "C" int chm_halves_selection(const chm_scenario_desc *desc, int32_t strat
   rc = build_model(desc, s);
   if (rc == CHM_OK) {
     fast_select(&s->fast, s->h, s->int32_ok);
-    *upper_cuts = s->fast.halves[strategy].up;
+    *upper_cuts = s->fast.halves[strategy].walked;
     *wave_steps = s->fast.halves[strategy].steps;
   }
   delete s;
@@ -1274,8 +1271,8 @@ extern "C" int chm_halves_work_of(const chm_scenario_desc *desc, int32_t strateg
   if (rc == CHM_OK) {
     fast_select(&s->fast, s->h, s->int32_ok);
     const HalvesShape &hs = s->fast.halves[strategy];
-    if (hs.up != 0) {
-      out->walked_cuts = halves_walked(s->h.fam[strategy].stages);
+    if (hs.walked != 0) {
+      out->walked_cuts = hs.walked;
       out->choices = fast_halves_choices(&s->fast, s->h, strategy, false);
       out->wavefronts = hs.n_items[out->choices - 1];
       out->units = hs.units[out->choices - 1];

@@ -45,7 +45,7 @@ def test_the_cases_cover_every_depth():
     depths = {k: {stages for j, stages, up in seen if j == k and up} for k in range(3)}
     assert depths[0] >= set(range(5, 17)) and depths[2] >= set(range(5, 17)) and depths[1] >= set(range(5, 16))
     for k in (0, 2):
-        assert {2, 3} <= {up for j, _, up in seen if j == k}
+        assert {2, 3, 4} <= {up for j, _, up in seen if j == k}
 
 
 @pytest.mark.gpu

@@ -1,5 +1,5 @@
 """Search by halves where a pipeline is short of nodes: the class that is timed for every partition lacks a node in every position
-it can lack it (both widths of the upper half; every pipeline hit), more than three classes, and a long model.  Against the range kernel over the same space in two windows, the winner's cost against
+it can lack it (two and four walked cuts; every pipeline hit), more than three classes, and a long model.  Against the range kernel over the same space in two windows, the winner's cost against
 the oracle.  Whole numbers, compared exactly."""
 import pytest
 
@@ -15,8 +15,8 @@ def _case(L, PP, DP, M, failed, cap_x=4.0, act=False, **kw):
 
 # (upper cuts of strategy 0, scenario)
 CASES = {"two cuts, stage %d gone" % s: (2, _case(39, 7, 2, 8, [s, 7 + (s + 3) % 7], act=s % 2 == 0)) for s in range(7)}
-CASES.update({"three cuts, stage %d gone" % s: (3, _case(27, 12, 2, 13, [s, 12 + (s + 5) % 12], cap_x=5.0)) for s in (0, 1, 7, 8, 9, 10, 11)})
-CASES["three cuts, activations, ring pair"] = (3, _case(27, 12, 2, 12, [8, 23], cap_x=5.0, act=True, transfer_assign=1))
+CASES.update({"four cuts, stage %d gone" % s: (4, _case(27, 12, 2, 13, [s, 12 + (s + 5) % 12], cap_x=5.0)) for s in (0, 1, 7, 8, 9, 10, 11)})
+CASES["four cuts, activations, ring pair"] = (4, _case(27, 12, 2, 12, [8, 23], cap_x=5.0, act=True, transfer_assign=1))
 CASES["five classes"] = (2, _case(40, 7, 5, 9, [1, 9, 17, 25], cap_x=3.5))
 CASES["7 stages, more than 120 layers"] = (2, _case(121, 7, 2, 8, [3], act=True))
 

@@ -1,6 +1,6 @@
 """Exhaustive search of large families by halves (from 2^21 partitions on) against the range kernel over the same space in
 two windows (which test_gpu_random.py and test_closed_forms.py hold against the oracle; test_gpu_full_space.py holds the
-search by halves itself against whole-space results of the oracle), the winner's cost against the oracle: both widths of the upper half, the smallest and largest number of stages, failed nodes that cross between the halves,
+search by halves itself against whole-space results of the oracle), the winner's cost against the oracle: two to four walked cuts, the smallest and largest number of stages, failed nodes that cross between the halves,
 one to three pipeline classes, every modelling option it takes, several chunks, no failure, no memory limit, ties.  Whole numbers,
 compared exactly."""
 import numpy as np
@@ -42,12 +42,12 @@ def _large(L, PP, DP, M, failed):
     return synth.scenario(L, PP, DP, M, fwd, bwd, mem, failed, 150, int(mem.sum()))
 
 
-def test_lanes_are_at_work_in_every_family_searched_by_halves():
-    """wavefronts share the last lower cut, so a family with few lower halves per cut leaves lanes idle: such a family takes
-    shorter upper halves, or the range kernel (5 stages, where even two upper cuts leave two thirds idle)"""
+def test_families_searched_by_halves_and_their_lanes():
+    """from 2^21 partitions on, whatever the depth; the steps reported are those of the cuts that are walked, with 64 choices of the others a
+    block, and the units of work those and what set-up and rows take (a few lanes idle where a last cut leaves few choices)"""
     from math import comb
     from paper_2508_21613_amd import binding as B
-    widths = set()
+    walked, choices = set(), set()
     for PP in range(5, 17):
         for L in range(PP + 6, 129, 3):
             sc = _large(L, PP, 3, PP + 4, [PP // 2])
@@ -55,19 +55,20 @@ def test_lanes_are_at_work_in_every_family_searched_by_halves():
                 continue
             for k, stages in ((0, PP), (1, PP - 1), (2, PP)):
                 n, (up, steps) = comb(L - 1, stages - 1), B.halves_selection(sc, k)
-                classes = 2 if k == 0 else 1
-                widths.add((stages, up))
+                assert (up > 0) == (n >= 1 << 21 and stages >= 5), (L, stages, k)
                 if up == 0:
-                    assert n < 1 << 21 or stages < 7, (L, stages, k)
                     continue
-                assert n >= 1 << 21 and n * stages >= 64 * steps * classes + (7 << 20), (L, stages, k)
-                by_width = {w: sum(-(-comb(v - 1, stages - 2 - w) // 64) * comb(L - 1 - v, w) for v in range(stages - 1 - w, L - w)) for w in (2, 3)}
-                assert steps == by_width[up] and 4 * steps <= 5 * by_width[2], (L, stages, k)
-                assert n / (64 * steps) > (0.3 if stages == 5 else 0.55), (L, stages, k)
-    assert {(5, 0), (5, 2), (6, 2), (7, 2), (8, 2), (9, 2), (9, 3), (10, 2), (10, 3), (11, 3), (12, 3), (16, 3)} <= widths
-    assert all(stages >= 9 if up == 3 else stages <= 11 for stages, up in widths if up)
-    assert B.halves_selection(_large(90, 5, 3, 8, [3]), 0)[0] == B.halves_selection(_large(87, 5, 3, 8, [3]), 2)[0] == 0
-    assert B.halves_selection(_large(54, 6, 3, 8, [3]), 0)[0] == B.halves_selection(_large(60, 7, 3, 8, [3]), 2)[0] == 2
+                walked.add((stages, up))
+                work, kept = B.halves_work(sc, k), stages - 1 - up
+                blocks = {c: {v: -(-comb(v - 1, kept - 1) // (64 * c)) for v in range(kept, L - up)} for c in (1, 2)}
+                assert work["walked_cuts"] == up and steps == sum(b * comb(L - 1 - v, up) for v, b in blocks[1].items()), (L, stages, k)
+                assert work["units"] > sum(b * comb(L - 1 - v, up) for v, b in blocks[work["choices"]].items())
+                share = n / (64 * steps)                     # lanes that keep a choice
+                assert share > (0.3 if stages == 5 else 0.7), (L, stages, k, share)
+                assert work["choices"] == 1 or (stages >= 10 and n > 1 << 28), (L, stages, k)
+                choices.add((stages, work["choices"]))
+    assert walked == {(s, 2 if s <= 7 else 3 if s <= 10 else 4) for s in range(5, 17)}
+    assert choices == {(s, 1) for s in range(5, 17)} | {(s, 2) for s in range(10, 17)}
     assert B.halves_selection(dict(_large(48, 8, 3, 8, [3]), speed_q16=np.full(24, 65537, np.uint32)), 2)[0] == 0
 
 
