@@ -21,9 +21,9 @@ __device__ __forceinline__ bool strictly_rising(const uint32_t (&w)[4]) {
 // With no more rows of 64 that fit than this, working them out costs less than the bound of all 64.
 constexpr int FEW_ROWS = 16;
 // Where more than so many eighths of the rows that fit pass the bound (a list of neighbours of one plan, or uneven speeds, which weaken the
-// bound), it is not looked at for a round, then three, seven, ...
+// bound), it is not looked at for half as many rounds as there have been.
 constexpr int USELESS_SHARE = 5;
-constexpr uint32_t LONGEST_STRETCH = 31;
+constexpr uint32_t FIRST_LOOKS = 4;       // (the first rounds lower the cost: random rows pass them, too)
 
 // cuts c[0..SP] from words of a byte each
 template <int SP>
@@ -67,10 +67,10 @@ struct ListBound {
     const double most = cost < reconf ? -1.0 : (double)(cost - reconf) * per_step + 1.0;
     limit = __builtin_amdgcn_readfirstlane(most < 2147483647.0 ? (int)most : 2147483647);
   }
-  // words = the cuts a byte each; cw = prefixes {forward + backward, memory}; in_memory: the lanes whose row fits; *look: whether the bound is
-  // to be looked at (false behind the call: it was not, for few rows that fit cost less than the bound)
+  // words = the cuts a byte each; cw = prefixes {forward + backward, memory}; in_memory: the lanes whose row fits; look: whether the bound is
+  // looked at (few rows that fit cost less than the bound)
   __device__ __forceinline__ bool passes(FamPtr ff, const uint32_t (&words)[4], int L, const int2 *cw, const int *pa, int cap, bool valid,
-                                         bool *look, uint64_t *in_memory) const {
+                                         bool look, uint64_t *in_memory) const {
     int t[SP + 1], at[SP + 1];
     t[0] = at[0] = 0;
 #pragma unroll
@@ -95,8 +95,7 @@ struct ListBound {
     }
     const bool fits = valid && peak <= cap;
     *in_memory = __builtin_amdgcn_ballot_w64(fits);
-    *look = *look && limit != 2147483647 && __popcll(*in_memory) > FEW_ROWS;
-    if (!*look) return fits;                             // uniform
+    if (!look || limit == 2147483647 || __popcll(*in_memory) <= FEW_ROWS) return fits;         // uniform
     int v = 0;
     if (STRAT == 0) {
       int before = 0;
@@ -142,8 +141,8 @@ constexpr int list_best_waves(int stages) { return stages <= 8 ? 5 : stages <= 1
 // Rows of a list come in no order, so that after the first 64 next to none can win: a row takes 160 to 215 instructions (16 stages) instead of
 // 190 to 330.  Bound by VALU issue and the prefixes' LDS reads.  2^23 rows, us, one by one / so: 16 stages 119 / 84, 116 / 71 and 159 / 90
 // (strategies 0, 1, 2), 8 stages 98 / 64, 87 / 54 and 109 / 72, at uneven speeds 148 / 112, 95 / 60 and 242 / 116.  Lists of which nearly all
-// may win (neighbours of one plan, one row over and over) take what they take one by one, within 5 %: the bound is looked at ever more seldom
-// and times come from the closed form as there.  (Stage after stage, class_time, leaves room for a fifth or sixth wavefront per SIMD, but such lists
+// may win (neighbours of one plan, one row over and over) take what they take one by one, within 8 % (the shortest, of six rounds a wavefront,
+// within 18 %): the bound is looked at ever more seldom and times come from the closed form as there.  (Stage after stage, class_time, leaves room for a fifth or sixth wavefront per SIMD, but such lists
 // took 15 to 37 % longer and random ones no less.)
 template <int SP, int STRAT>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list_best_waves(SP)))) k_list_best(FastLaunch a) {
@@ -270,7 +269,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
     }
   };
 
-  uint32_t unlooked = 0, stretch = 0;      // rounds the bound is not looked at any more, and how many the last time
+  uint32_t next_look = 0;                  // round from which on the bound is looked at
   uint32_t words[4], next[4];
   row_of(0, next);
   for (uint32_t it = 0; it < a.per_lane; ++it) {
@@ -284,16 +283,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
 #pragma unroll
     for (int w = 0; w < 4; ++w) words[w] = valid ? words[w] : first[w];
     uint64_t in_memory;
-    bool look = unlooked == 0;
-    const bool stays = bound.passes(ff, words, L, CW, PA, cap, entry < a.s.part_count && valid, &look, &in_memory);
+    const bool stays = bound.passes(ff, words, L, CW, PA, cap, entry < a.s.part_count && valid, it >= next_look, &in_memory);
     n_fit += (uint32_t)__popcll(in_memory);
     const uint64_t stay_mask = __builtin_amdgcn_ballot_w64(stays);
-    if (look) {
-      stretch = 8 * __popcll(stay_mask) > USELESS_SHARE * __popcll(in_memory) ? (stretch < LONGEST_STRETCH ? 2 * stretch + 1 : stretch) : 0;
-      unlooked = stretch;
-    } else if (unlooked != 0) {
-      --unlooked;
-    }
     if (stay_mask == 0) continue;           // uniform
     if (stays) {
       const uint32_t at_slot = (uint32_t)wave * QCAP + ((q_tail + (uint32_t)__popcll(stay_mask & ((1ull << lane) - 1ull))) & (QCAP - 1));
@@ -302,6 +294,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(list
     }
     q_tail += (uint32_t)__popcll(stay_mask);
     if (q_tail - q_head < 64) continue;
+    // (told where the ring is full: elsewhere too little stays for it to matter, and a scalar instruction a round costs half a percent)
+    if (it >= next_look && it >= FIRST_LOOKS && 8 * __popcll(stay_mask) > USELESS_SHARE * __popcll(in_memory)) next_look = it + it / 2 + 2;
     work_out(64u);
     q_head += 64;
   }
