@@ -7,15 +7,18 @@
 // terms that have met neither end's turn, one of them or both.  So a loop over a cut adds the stage that the cut ends to the lane's state
 // (Terms::add, 12 instructions), whose times are the same for all lanes, and the innermost one, over the last cut y, is left with the two
 // last stages: 13 instructions (under redundant computation 22).  What is the same for all lanes of the last two levels is a function of two
-// cuts and comes from tables of (L + 1)^2 records (k_cut_records, 32 bytes each, laid out once per handle and strategy).
+// cuts and comes from a table of (L + 1)^2 records (k_cut_records, 32 bytes each, laid out once per handle and strategy).
 //
 // Times are floats.  A float addition or multiply-add issues beside a maximum of another wavefront (2.6 to 3 cycles an instruction for
 // such streams, 4.2 for integers).  Up to 2^24 they are the whole numbers they stand for; above, sums are rounded, and the limit they are
-// compared with is raised by more than that (SLACK).  They only decide which partitions may have a cost not above the lowest met; the cost
+// compared with is raised by more than that (TIME_SLACK).  They only decide which partitions may have a cost not above the lowest met; the cost
 // of these is worked out anew, in integers (consider).  Times of pipeline classes but the one with the most work take part there, too.
 //
 // Bound by the issue of vector instructions (0.6 to 0.7 of the rate above while all wavefronts run) and, for searches of tens of
-// microseconds, by the 6 us until the first lanes are set up and the end, when few wavefronts are left on a SIMD.  62.9 M partitions of
+// microseconds, by the 6 us until the first lanes are set up and the end, when few wavefronts are left on a SIMD.  With one choice a lane
+// no vector registers are spilled, or few (strategy 1 of 9, 10 and 13 to 16 stages, 1 to 13); with two, 8 at 10 stages of strategy 1 and 22 to
+// 67 beyond, in the set-up and the outer loops (11 stages, strategy 1: 1.0 GB of scratch written in 2.6 ms; with three wavefronts per SIMD,
+// which need none, a re-plan takes 4.44 ms instead of 4.30).  62.9 M partitions of
 // 8 stages: 46 us (integers, a lane for every lower half: 54; one by one 434), under redundant computation 53 (66; 516), 10.7 M of 7
 // stages 13 to 18 (27), 5.2 G of 11 stages 2.65 ms (3.93; 51).
 #ifndef CHM_HALVES_KERNEL_H
@@ -48,14 +51,16 @@ __device__ __forceinline__ int lacking(FamPtr ff, int lo, int hi, int s) {
   for (int j = 0; j < N; ++j) most = imax32(most, held(cl->wlo[j], cl->whi[j]));
   return hi - lo - most;
 }
-// time of a step that fetching so much costs: a whole number not above it
+// time of a step that fetching so much costs: a whole number not above it (four roundings of 2^-24: the size, the price, less 2^-21, their product)
 __device__ __forceinline__ float fetch_time(ScnPtr scn, int mib) {
-  return floorf((float)mib * ((float)((double)scn->xfer / (double)scn->K) * 0.99999f));
+  return floorf((float)mib * ((float)((double)scn->xfer / (double)scn->K) * (1.0f - 1.0f / 2097152)));
 }
 constexpr int HALVES_UNFIT = 1 << 30;                  // in place of a share of a node's memory
-// A time is a chain of at most two additions a level and four more, of numbers up to six times as large: rounded to 24 bits
-// they stay within 2^-24 x 6 x (2 x 16 + 4) < 2^-16 of it.
-constexpr double SLACK = 1.0 + 1.0 / 65536;
+// A time is a chain of at most two additions a level and four more, of numbers up to six times as large, rounded to 24 bits: 6 x (2 x 16 + 4) =
+// 216 units of 2^-24 of it, and the limit is raised by 256 units of the longest time there may be (or of itself, if that is less).  What the limit
+// is lowered by (communication, penalties, fetch times, which may be many times as long) adds 20 roundings, the limit itself, its
+// difference from that, the record's share and the comparison's other side one each: 24 units of the limit, raised by 32.
+constexpr double TIME_SLACK = 1.0 / 65536, LIMIT_SLACK = 1.0 / 524288;
 // What a time less its limit, with that limit lowered later on, is rounded by at most, as a part of the limit before: six roundings of
 // 2^-24 (the limit less what all its partitions have, that less the record's share, the time less it, what the limit falls by less this, their sum).
 constexpr float LIMIT_ROUNDING = 1.0f / 2097152;
@@ -268,7 +273,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   constexpr int LOW = STRAT == 0 ? G - 1 : G;         // nodes the lanes' cuts alone decide
   __shared__ int4 T[DEV_MAX_L + 1];
   __shared__ uint32_t BN[ROWS * DEV_MAX_L], UN[W * DEV_MAX_L];
-  __shared__ uint64_t first_unit[DEV_MAX_L];
+  __shared__ uint64_t first_unit[DEV_MAX_L], RK[W * DEV_MAX_L];       // RK: row i - 1 = C(x, G + i), ranks of the walked cuts
   __shared__ uint64_t wave_cost[BLOCK / 64], wave_rank[BLOCK / 64];
   __shared__ uint32_t wave_fit[BLOCK / 64];
   const ScnPtr scn = as_const(a.s.scn);
@@ -281,6 +286,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   for (int i = threadIdx.x; i < ROWS * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
   for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) UN[i] = a.items->units[i];
   if (threadIdx.x < DEV_MAX_L) first_unit[threadIdx.x] = a.items->first[R - 1][threadIdx.x];
+  for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) RK[i] = scn->binom[G + 1 + i / DEV_MAX_L][i % DEV_MAX_L];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
@@ -411,11 +417,14 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
     // ---- the upper cuts
     const int rounds = STRAT != 0 ? ff->allreduce : 0;
     const double per_step = 1.0 / (double)scn->K;
+    // (the closed form's two ends and its own term, of sums up to twice the model's time)
+    const double longest = (double)(cl->M + N + 4) * (double)total * 2.0;
     auto limit_of = [&](uint64_t cost) -> float {      // no step time above this can reach `cost`
       const uint64_t reconf = (uint64_t)scn->reconf[STRAT];
       if (cost == ~0ull) return HUGE_TIME / 2;
       if (cost < reconf) return NEVER;
-      return (float)(((double)(cost - reconf) * per_step + 1.0) * SLACK);
+      const double most = (double)(cost - reconf) * per_step + 1.0;
+      return (float)(most + __builtin_fmin(most, longest) * TIME_SLACK + most * LIMIT_SLACK);
     };
     float limit = limit_of(low_cost);
     // memory of a node above the lanes' cuts, the same for all lanes
@@ -461,6 +470,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       asm volatile("" : "+s"(tables), "+s"(family));
       const ScnPtr scn = (ScnPtr)(uintptr_t)tables;
       const FamPtr ff = (FamPtr)(uintptr_t)family;
+      // what others have found by now counts, too
+      auto lowest_of_all = [&]() { return __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      uint64_t known = ~0ull;
+      if (STRAT != 2) known = lowest_of_all();
       int c[N + 1];
       c[0] = 0;
       c[N] = L;
@@ -490,6 +503,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
 #pragma unroll
           for (int i = 1; i <= G; ++i) asm volatile("" : "+v"(c[i]));
           step = imax32(step, class_time<N, STRAT, true, true>(&ff->cls[ci], prefix_at));
+          if (__builtin_amdgcn_ballot_w64(here && (float)step <= limit) == 0) return;
         }
       }
       if (STRAT == 2) {
@@ -508,26 +522,30 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
         for (int s = 0; s < N; ++s) layers = imax32(layers, c[s + 1] - c[s]);
         step += ff->allreduce * layers;
       }
+      if (__builtin_amdgcn_ballot_w64(here && (float)step <= limit) == 0) return;
+      // (One wavefront may have to work out a whole cluster of partitions, one after the other, most of which others have beaten by then: it
+      // asks while it works out the times, which under strategy 2 takes less time than to ask.)
+      if (STRAT != 2) {
+        known = uniform64(known);
+        if (known < low_cost) lower_to(known);
+      }
       const bool near_best = here && (float)step <= limit;
       if (__builtin_amdgcn_ballot_w64(near_best) == 0) return;
-      // What others have found by now counts, too; they are told of what is lower than that.  (Where the assignment is open, the weights take
-      // longer than to ask, and one wavefront may have to work out those of a whole cluster of partitions, one after the other.)
-      auto lowest_of_all = [&]() { return __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-      uint64_t known = ~0ull;
-      if (open_nodes) known = lowest_of_all();
       int wp[N + 1];
       wp[0] = 0;
 #pragma unroll
       for (int i = 1; i <= N; ++i) wp[i] = T[c[i]].z;
       const uint64_t cost = (uint64_t)scn->K * (uint32_t)step + (uint64_t)scn->reconf[STRAT] +
                             (uint64_t)scn->xfer * (uint32_t)missing_weights<N, STRAT>(ff, wp);
-      uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + a.s.scn->binom[K][y - 1];
+      const bool lowest = near_best && cost <= low_cost;
+      if (__builtin_amdgcn_ballot_w64(lowest) == 0) return;
+      if (STRAT == 2) known = lowest_of_all();
+      uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + RK[(W - 1) * DEV_MAX_L + y - 1];
 #pragma unroll
-      for (int i = 1; i < W; ++i) rank += scn->binom[G + i][cut[i] - 1];
-      if (near_best && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
-      const uint64_t least = uniform64(wave_min(near_best ? cost : ~0ull));
-      if (!open_nodes && least < low_cost) known = lowest_of_all();
-      known = uniform64(known);
+      for (int i = 1; i < W; ++i) rank += RK[(i - 1) * DEV_MAX_L + cut[i] - 1];
+      if (lowest && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
+      const uint64_t least = uniform64(wave_min(lowest ? cost : ~0ull));
+      if (STRAT == 2) known = uniform64(known);
       if (least < umin64(known, low_cost) && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
       if (umin64(least, known) < low_cost) lower_to(umin64(least, known));
     };
