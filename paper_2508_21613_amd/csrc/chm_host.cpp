@@ -558,23 +558,25 @@ bool whole_family(const chm_scenario *s, const Job &j) {
 bool bounded_by_halves(const chm_scenario *s, const Job &j) {
   return s->bounded == 1 && j.count <= BOUNDED_HALVES && whole_family(s, j) && fast_halves_covers(&s->fast, s->h, j.strategy, j.count);
 }
-// Blocks of 64 lower halves to set up, per family, up to which a call's families go by halves straight away, and a family does beside others that
-// are enumerated.  Counting and enumerating candidates costs about the same whatever the size: a wait for the seeds, a count on the host
+// Stages of the blocks of 64 lower halves to set up, up to which a call's families go by halves straight away, and a family does beside others
+// that are enumerated.  Counting and enumerating candidates costs about the same whatever the size: a wait for the seeds, a count on the host
 // for each family, another launch.  us a search, enumerated / by halves, with the families' blocks in thousands, three pipelines: all strategies of
-// 8 stages, 45 layers (5) 145 / 72, 58 layers (15) 278 / 139, 11 stages, 37 layers (46) 244 / 239, 12 stages, 35 layers (73) 230 / 290, 16 stages,
-// 30 layers (190) 230 / 465; strategy 1 of 9 stages, 41 layers (7) 97 / 63, 12 stages, 31 layers (10) 98 / 78, 15 stages, 31 layers (83) 101 /
-// 212.  These two lose least of nine such rules: 728 searches of one strategy and of several, 34 M to 1.07 G partitions, take 1.7 % longer than
-// with the best of them for each (25,000 and 25,000: 2.9 %; counted for the kernel that set up a lane for every lower half: 3.6 %); open
-// assignments alike.  Strategies 0 and 2 alone, whose bound is far from their best plan, are rarely left with few candidates and go by halves up to
-// three times that (strategy 2 of 13 stages, 31 layers (24) 141 / 116; of 16 (121) 309 / 276).
-constexpr uint64_t FEW_BLOCKS = 18000;
-constexpr uint64_t FEW_BLOCKS_BESIDE = 10000;     // of strategies 0 and 2, beside others that are enumerated
+// 8 stages, 45 layers (5) 145 / 72, 58 layers (15) 278 / 139, 7 stages, 79 layers (41) 216 / 158, 11 stages, 37 layers (46) 244 / 239, 9 stages, 51
+// layers (51) 177 / 234, 12 stages, 35 layers (73) 230 / 290, 16 stages, 30 layers (190) 230 / 465; strategy 1 of 9 stages, 41 layers (7) 97 / 63,
+// 12 stages, 31 layers (10) 98 / 78, 15 stages, 31 layers (83) 101 / 212; strategy 2 of 13 stages, 31 layers (24) 141 / 116, of 16 (121)
+// 309 / 276.  Strategies 0 and 2 alone, whose bound is far from their best plan, are rarely left with few candidates.  (Open assignments alike.  How
+// many candidates are left depends on the times and not on the size: with any such rule some calls take up to 1.4 times as long as
+// with the other choice.)
+constexpr uint64_t SETUP_OF_ONE = 180000, SETUP_OF_ONE_LOOSE = 540000, SETUP_OF_SEVERAL = 450000;
+constexpr uint64_t SETUP_BESIDE = 175000, SETUP_BESIDE_LOOSE = 100000;          // (loose: strategies 0 and 2)
+uint64_t setup_of(const chm_scenario *s, const Job &j) {
+  return fast_halves_blocks(&s->fast, j.strategy) * (uint64_t)s->h.fam[j.strategy].stages;
+}
 bool all_by_halves(const chm_scenario *s, const std::vector<Job> &jobs) {
-  uint64_t blocks = 0;
+  uint64_t setup = 0;
   for (const Job &j : jobs)
-    if (bounded_by_halves(s, j)) blocks += fast_halves_blocks(&s->fast, j.strategy);
-  const bool loose = jobs.size() == 1 && jobs[0].strategy != 1;
-  return blocks <= FEW_BLOCKS * (loose ? 3 : jobs.size());
+    if (bounded_by_halves(s, j)) setup += setup_of(s, j);
+  return setup <= (jobs.size() != 1 ? SETUP_OF_SEVERAL : jobs[0].strategy != 1 ? SETUP_OF_ONE_LOOSE : SETUP_OF_ONE);
 }
 // Partitions of all families up to which one launch searches them exhaustively in less time than seeds and bounds take, us exhaustive /
 // bounded: 1.2 M of 6 stages 49 / 78, 3.6 M of 8 stages at uneven speeds 104 / 110 and, few of which fit, 78 / 105; 9.7 M 239 / 187.
@@ -1069,7 +1071,7 @@ int run_search(chm_scenario *s, const std::vector<Job> &given, chm_best *out, ui
     const bool whole = !j.ranks && !j.cuts && !j.costs && j.first == 0 && j.count == s->h.fam[j.strategy].n_part;
     bool listed = false;
     const bool halves = bounded_by_halves(s, j);
-    if (whole && incumbent != ~0ull && s->idx_bits >= 23 && !(halves && fast_halves_blocks(&s->fast, j.strategy) <= (j.strategy == 1 ? FEW_BLOCKS : FEW_BLOCKS_BESIDE))) {
+    if (whole && incumbent != ~0ull && s->idx_bits >= 23 && !(halves && setup_of(s, j) <= (j.strategy == 1 ? SETUP_BESIDE : SETUP_BESIDE_LOOSE))) {
       // A family within reach of a search of its partitions is enumerated only when its candidates are few; one beyond it,
       // whenever they can be made few enough: while there are too many, a sample of them spread evenly over
       // their index order is evaluated, which lowers the incumbent and with it the number of candidates.
