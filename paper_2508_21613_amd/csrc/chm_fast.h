@@ -75,9 +75,13 @@ enum { HALVES_TWO_CHOICES_FROM = 10 };
 // Wavefronts per SIMD: 5 from 8 stages on and 4 from 11 on, so that the set-up and the outer loops keep their vector registers (with six and
 // five up to 61 of them were spilled, which small families and strategy 1 paid for: us a search of all strategies, 14 stages, 25 layers
 // 114 / 90, 16 stages, 26 layers 149 / 119, 29 layers 510 / 446).  Strategy 0 of up to 13 stages, exhaustive, is better off with 5 (11 stages, 30
-// layers 71, 82 with 4; 37 layers 268 and 278).
+// layers 71, 82 with 4; 37 layers 268 and 278); bounded searches of 8 and 9 stages, most of which is set-ups, with 6 (strategy 2 of 8 stages, 48
+// layers 27, 30 with 5).
 constexpr int halves_waves(int stages, int strategy, int choices, bool pruned) {
-  return choices == 2 ? 4 : stages <= 7 ? (strategy == 0 ? 6 : 7) : stages <= 10 || (strategy == 0 && stages <= 13 && !pruned) ? 5 : 4;
+  if (choices == 2) return 4;
+  if (stages <= 7) return strategy == 0 ? 6 : 7;
+  if (pruned && strategy != 0 && stages <= 9) return 6;
+  return stages <= 10 || (strategy == 0 && stages <= 13 && !pruned) ? 5 : 4;
 }
 // How a family is searched by halves (chm_halves_kernel.h); walked = 0: it is not.
 struct HalvesShape {
@@ -86,6 +90,7 @@ struct HalvesShape {
   uint64_t steps = 0;           // blocks x choices of the walked cuts
   // with one choice of the lower cuts a lane, with two:
   uint32_t n_items[2] = {0, 0}; // wavefronts of the search
+  uint32_t n_items_pruned = 0;  // of a bounded one (one choice)
   uint64_t units[2] = {0, 0};   // work to share out among them
 };
 

@@ -308,9 +308,13 @@ void halves_share(const DevScenario &h, int sp, int k, HalvesShape *hs) {
   for (int c = 0; c < 2; ++c) {
     hs->units[c] = 0;
     for (int v = kept; v <= h.L - 1 - walked; ++v) hs->units[c] += halves_units(&h, walked, v) * halves_blocks(&h, kept, c + 1, v);
-    const uint64_t resident = 1024u * (uint64_t)halves_waves(sp, k, c + 1, false);
-    const uint64_t rounds = std::min<uint64_t>(8, hs->units[c] / (HALVES_UNITS * resident));
-    hs->n_items[c] = (uint32_t)(rounds ? rounds * resident : std::max<uint64_t>(1, std::min<uint64_t>(resident, hs->units[c] / 16)));
+    auto items = [&](bool pruned) -> uint32_t {
+      const uint64_t resident = 1024u * (uint64_t)halves_waves(sp, k, c + 1, pruned);
+      const uint64_t rounds = std::min<uint64_t>(8, hs->units[c] / (HALVES_UNITS * resident));
+      return (uint32_t)(rounds ? rounds * resident : std::max<uint64_t>(1, std::min<uint64_t>(resident, hs->units[c] / 16)));
+    };
+    hs->n_items[c] = items(false);
+    if (c == 0) hs->n_items_pruned = items(true);
   }
 }
 
@@ -336,7 +340,7 @@ HalvesShape halves_shape(const FastTables *t, const DevScenario &h, int k) {
   }
   halves_share(h, sp, k, &hs);
   for (int c = 0; c < 2; ++c)
-    if (hs.units[c] / hs.n_items[c] >= HALVES_MOST_UNITS) return none;
+    if (hs.units[c] / (c == 0 ? std::min(hs.n_items[0], hs.n_items_pruned) : hs.n_items[c]) >= HALVES_MOST_UNITS) return none;
   hs.walked = walked;
   return hs;
 }
@@ -843,7 +847,7 @@ int fast_halves_search(FastState *f, const DevScenario &h, const SearchLaunch &a
   hl.bounded = bounded ? 1 : 0;
   hl.choices = (uint32_t)fast_halves_choices(f, h, k, bounded);
   hl.n_units = hs.units[hl.choices - 1];
-  hl.n_items = f->halves_items_set != 0 ? (uint32_t)std::max<uint64_t>(f->halves_items_set, hl.n_units / HALVES_MOST_UNITS + 1) : hs.n_items[hl.choices - 1];
+  hl.n_items = f->halves_items_set != 0 ? (uint32_t)std::max<uint64_t>(f->halves_items_set, hl.n_units / HALVES_MOST_UNITS + 1) : bounded ? hs.n_items_pruned : hs.n_items[hl.choices - 1];
   hl.per_item = (hl.n_units + hl.n_items - 1) / hl.n_items;
   hl.n_rows = (uint32_t)(h.L + 1);
   hl.pairs = f->d_pairs[k];

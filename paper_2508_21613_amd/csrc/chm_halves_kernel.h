@@ -61,6 +61,7 @@ constexpr int HALVES_UNFIT = 1 << 30;                  // in place of a share of
 // is lowered by (communication, penalties, fetch times, which may be many times as long) adds 20 roundings, the limit itself, its
 // difference from that, the record's share and the comparison's other side one each: 24 units of the limit, raised by 32.
 constexpr double TIME_SLACK = 1.0 / 65536, LIMIT_SLACK = 1.0 / 524288;
+constexpr uint32_t CLUSTER = 4;
 // What a time less its limit, with that limit lowered later on, is rounded by at most, as a part of the limit before: six roundings of
 // 2^-24 (the limit less what all its partitions have, that less the record's share, the time less it, what the limit falls by less this, their sum).
 constexpr float LIMIT_ROUNDING = 1.0f / 2097152;
@@ -286,12 +287,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
   for (int i = threadIdx.x; i < ROWS * DEV_MAX_L; i += BLOCK) BN[i] = a.items->binom[i];
   for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) UN[i] = a.items->units[i];
   if (threadIdx.x < DEV_MAX_L) first_unit[threadIdx.x] = a.items->first[R - 1][threadIdx.x];
-  for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) RK[i] = scn->binom[G + 1 + i / DEV_MAX_L][i % DEV_MAX_L];
+  if ((int)threadIdx.x % DEV_MAX_L < L)
+    for (int i = threadIdx.x; i < W * DEV_MAX_L; i += BLOCK) RK[i] = scn->binom[G + 1 + i / DEV_MAX_L][i % DEV_MAX_L];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / 64) + wave);
   uint64_t best_cost = ~0ull, best_rank = ~0ull;
-  uint32_t n_fit = 0;
+  uint32_t n_fit = 0, considered = 0;
   uint64_t low_cost = umin64(a.s.incumbent0, __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));     // lowest known
   // The item's part of all units of work: blocks of 64 choices of the lanes' cuts, v by v, each its set-up and its upper cuts in turn.
   uint64_t unit = (uint64_t)item * a.per_item;
@@ -473,7 +475,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       // what others have found by now counts, too
       auto lowest_of_all = [&]() { return __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       uint64_t known = ~0ull;
-      if (STRAT != 2) known = lowest_of_all();
+      const bool asks = STRAT != 2 && considered >= CLUSTER;
+      ++considered;
+      if (asks) known = lowest_of_all();
       int c[N + 1];
       c[0] = 0;
       c[N] = L;
@@ -524,8 +528,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       }
       if (__builtin_amdgcn_ballot_w64(here && (float)step <= limit) == 0) return;
       // (One wavefront may have to work out a whole cluster of partitions, one after the other, most of which others have beaten by then: it
-      // asks while it works out the times, which under strategy 2 takes less time than to ask.)
-      if (STRAT != 2) {
+      // asks from the CLUSTER-th on, while it works out the times, which under strategy 2 takes less time than to ask.)
+      if (asks) {
         known = uniform64(known);
         if (known < low_cost) lower_to(known);
       }
@@ -539,13 +543,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
                             (uint64_t)scn->xfer * (uint32_t)missing_weights<N, STRAT>(ff, wp);
       const bool lowest = near_best && cost <= low_cost;
       if (__builtin_amdgcn_ballot_w64(lowest) == 0) return;
-      if (STRAT == 2) known = lowest_of_all();
+      if (!asks) known = lowest_of_all();
       uint64_t rank = (uint64_t)(low_block * (64u * R) + 64u * (uint32_t)half + (uint32_t)lane) + BN[(G - 1) * DEV_MAX_L + v - 1] + RK[(W - 1) * DEV_MAX_L + y - 1];
 #pragma unroll
       for (int i = 1; i < W; ++i) rank += RK[(i - 1) * DEV_MAX_L + cut[i] - 1];
       if (lowest && (cost < best_cost || (cost == best_cost && rank < best_rank))) { best_cost = cost; best_rank = rank; }
       const uint64_t least = uniform64(wave_min(lowest ? cost : ~0ull));
-      if (STRAT == 2) known = uniform64(known);
+      known = uniform64(known);
       if (least < umin64(known, low_cost) && lane == 0) atomicMin((unsigned long long *)a.s.incumbent, (unsigned long long)least);
       if (umin64(least, known) < low_cost) lower_to(umin64(least, known));
     };
