@@ -29,9 +29,9 @@ ALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 # From the rocprofv3 --pmc runs summarised in profiles/measured_cases.md (counters cannot be read from
 # inside this process), per strategy kernel of config 2:
 # HBM bytes per launch = FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 KiB (factors from the 1 GiB calibration copy of the same runs)
-CONFIG2_TRAFFIC_BYTES = {0: (258.0 * 2.0 + 171.0) * 1024, 1: (289.0 * 2.0 + 55.0) * 1024, 2: (274.0 * 2.0 + 196.0) * 1024}
+CONFIG2_TRAFFIC_BYTES = {0: (477.0 * 2.0 + 39.0) * 1024, 1: (466.0 * 2.0 + 55.0) * 1024, 2: (506.0 * 2.0 + 40.0) * 1024}
 # executed VALU lane-instructions per partition = SQ_INSTS_VALU x 64 / partitions of the family
-CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 26.7, 1: 35.1, 2: 23.0}
+CONFIG2_EXECUTED_LANE_INSTR_PER_PARTITION = {0: 26.8, 1: 36.4, 2: 22.2}
 
 
 def note(msg):
@@ -659,8 +659,9 @@ def bench_search(args, B, synth, name):
         roofline["executed_valu_rate_tops"] = executed
         roofline["executed_valu_rate_over_measured_v_max_rate"] = executed / probes["v_max_i32"]
         roofline["executed_valu_rate_is"] = ("SQ_INSTS_VALU x 64 / partitions of the committed rocprofv3 profile x partitions / kernel time "
-                                             "of this run, against the measured issue rate of v_max_i32 (the slower of the two "
-                                             "instruction classes the kernel mixes)")
+                                             "of this run, against the measured issue rate of v_max_i32.  (The innermost loops mix maxima, which "
+                                             "issue at that rate whether of integers or of floats, with float additions and multiply-adds, which "
+                                             "issue beside them: times that only decide what is worked out are float32, costs whole numbers.)")
     out = {
         "metric": METRIC,
         "value": n_plans / (ms_per_step * 1e-3),

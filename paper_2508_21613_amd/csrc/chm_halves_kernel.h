@@ -16,10 +16,11 @@
 //
 // Bound by the issue of vector instructions (0.6 to 0.7 of the rate above while all wavefronts run) and, for searches of tens of
 // microseconds, by the 6 us until the first lanes are set up and the end, when few wavefronts are left on a SIMD.  With one choice a lane
-// no vector registers are spilled, or few (strategy 1 of 9, 10 and 13 to 16 stages, 1 to 13); with two, 8 at 10 stages of strategy 1 and 22 to
-// 67 beyond, in the set-up and the outer loops (11 stages, strategy 1: 1.0 GB of scratch written in 2.6 ms; with three wavefronts per SIMD,
-// which need none, a re-plan takes 4.44 ms instead of 4.30).  62.9 M partitions of
-// 8 stages: 46 us (integers, a lane for every lower half: 54; one by one 434), under redundant computation 53 (66; 516), 10.7 M of 7
+// no vector registers are spilled up to 7 stages, and 4 to 23 in the set-up and the outer loops of bounded searches of 8 and 9 stages, of strategy 0
+// of 11 to 13 and of strategy 1 from 9 on, where one more wavefront per SIMD is worth more; with two choices, 3 to 71 from 10 stages on (11 stages,
+// strategy 1: 1.0 GB of scratch written in 2.6 ms; with three wavefronts per SIMD, which need next to none, a re-plan takes 4.44 ms instead of
+// 4.30).  62.9 M partitions of
+// 8 stages: 44 us (integers, a lane for every lower half: 54; one by one 434), under redundant computation 54 (66; 516), 10.7 M of 7
 // stages 13 to 18 (27), 5.2 G of 11 stages 2.65 ms (3.93; 51).
 #ifndef CHM_HALVES_KERNEL_H
 #define CHM_HALVES_KERNEL_H
