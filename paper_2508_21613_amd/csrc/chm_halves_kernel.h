@@ -476,8 +476,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(halv
       // what others have found by now counts, too
       auto lowest_of_all = [&]() { return __hip_atomic_load(a.s.incumbent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       uint64_t known = ~0ull;
-      const bool asks = STRAT != 2 && considered >= CLUSTER;
-      ++considered;
+      const bool asks = STRAT != 2 && (R == 2 || considered >= CLUSTER);       // (two choices a lane: the count would be one more register to spill)
+      if (R == 1) ++considered;
       if (asks) known = lowest_of_all();
       int c[N + 1];
       c[0] = 0;
